@@ -4,9 +4,11 @@
 // closed form, or read from a per-token array), plus an optional gather of the
 // kept rows.
 //
-// Three passes over the bit mask: per-tile population counts, an exclusive scan
-// of the tile counts, and a scatter in which each wavefront ranks its 64 tokens
-// with a ballot prefix so that consecutive lanes write consecutive outputs.
+// Passes over the bit mask: per-tile population counts, (for large batches) an exclusive scan
+// of the tile counts, and a scatter in which each wavefront ranks its 64 tokens with a
+// bit-prefix so that consecutive lanes write consecutive outputs.  The scatter also gathers the
+// per-token words (ids, behaviour log-probs) and writes the per-rollout offsets; the gather of
+// hidden rows is a kernel of its own.
 #include "nat_internal.h"
 
 #include <mutex>
@@ -16,53 +18,81 @@ namespace nat {
 constexpr int kTileTokens = 4096;                 // tokens per scatter block
 constexpr int kTileWords = kTileTokens / 32;      // 128 mask words
 constexpr int kScatterThreads = 256;              // 4 wavefronts x 1024 tokens
+// Up to this many tiles (4.2 million tokens) a scatter block adds up the counts of the tiles before
+// its own instead of a scan launch between the two passes (4 loads per thread at most).
+constexpr int kInlineScanTiles = 1024;
 
 __device__ __forceinline__ int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
 
-// tile_count[b] = number of kept tokens among packed positions [b*4096, (b+1)*4096)
-__global__ void __launch_bounds__(kTileWords)
-compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, int32_t* __restrict__ tile_count) {
-  __shared__ int part[kTileWords / 64];
-  const int64_t w = (int64_t)blockIdx.x * kTileWords + threadIdx.x;
-  const int c = wave_sum(w < n_words ? __popc(mask_bits[w]) : 0);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) tile_count[blockIdx.x] = part[0] + part[1];
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  const int lane = threadIdx.x & 63;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(v, off);
+    if (lane >= off) v += up;
+  }
+  return v;
 }
 
-// tile_offset[0..n_tiles] = exclusive scan of tile_count; n_kept = total.  One block.
+// tile_count[b] = number of kept tokens among packed positions [b*4096, (b+1)*4096); one wavefront per tile
+__global__ void __launch_bounds__(256)
+compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, int n_tiles,
+                     int32_t* __restrict__ tile_count) {
+  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (tile >= n_tiles) return;
+  const int64_t w = (int64_t)tile * kTileWords + 2 * lane;      // n_words is even
+  const int c = wave_sum(w < n_words ? __popc(mask_bits[w]) + __popc(mask_bits[w + 1]) : 0);
+  if (lane == 0) tile_count[tile] = c;
+}
+
+// tile_offset[0..n_tiles] = exclusive scan of tile_count.  One block, kScanPer consecutive tiles per thread.
+constexpr int kScanPer = 8;
 __global__ void __launch_bounds__(1024)
-compact_scan_kernel(const int32_t* __restrict__ tile_count, int n_tiles, int32_t* __restrict__ tile_offset,
-                    int32_t* __restrict__ n_kept) {
+compact_scan_kernel(const int32_t* __restrict__ tile_count, int n_tiles, int32_t* __restrict__ tile_offset) {
   __shared__ int wave_tot[16];
-  __shared__ int carry_s;
-  if (threadIdx.x == 0) carry_s = 0;
-  __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int base = 0; base < n_tiles; base += 1024) {
-    const int j = base + threadIdx.x;
-    const int v = j < n_tiles ? tile_count[j] : 0;
-    int incl = v;                                   // inclusive scan inside the wavefront
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off);
-      if (lane >= off) incl += up;
+  int carry = 0;
+  for (int base = 0; base < n_tiles; base += 1024 * kScanPer) {
+    const int j0 = base + (int)threadIdx.x * kScanPer;
+    int v[kScanPer], mine = 0;
+#pragma unroll
+    for (int e = 0; e < kScanPer; ++e) {
+      v[e] = j0 + e < n_tiles ? tile_count[j0 + e] : 0;
+      mine += v[e];
     }
+    const int incl = wave_inclusive_scan(mine);
     if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
-    int before = carry_s;
-    for (int w = 0; w < wave; ++w) before += wave_tot[w];
-    if (j < n_tiles) tile_offset[j] = before + incl - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry_s = before + incl;
+    int run = carry + incl - mine;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) run += wave_tot[w];
+      carry += wave_tot[w];
+    }
+#pragma unroll
+    for (int e = 0; e < kScanPer; ++e) {
+      if (j0 + e < n_tiles) tile_offset[j0 + e] = run;
+      run += v[e];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    tile_offset[n_tiles] = carry_s;
-    *n_kept = carry_s;
+}
+
+// Number of entries of the non-decreasing cu[lo .. hi) that are < n; the whole wavefront works on one n:
+// 64 probes at once, so 4096 rollouts take two dependent loads instead of twelve.
+__device__ __forceinline__ int wave_lower_bound(const int64_t* __restrict__ cu, int lo, int hi, int64_t n) {
+  const int lane = threadIdx.x & 63;
+  while (hi > lo) {
+    const int step = (hi - lo + 63) >> 6;
+    const int probe = lo + lane * step;
+    const int below = __popcll(__ballot(probe < hi && cu[probe < hi ? probe : lo] < n));
+    if (step == 1) return lo + below;
+    if (below == 0) return lo;
+    hi = lo + below * step < hi ? lo + below * step : hi;       // the first probe that is not below, or the end
+    lo += (below - 1) * step + 1;                               // the last probe that is below lies before lo
   }
+  return lo;
 }
 
 // Horvitz-Thompson weight of kept token t (1-based) of a rollout of length T.
@@ -82,90 +112,142 @@ __device__ __forceinline__ float ht_weight(int scheme, int64_t T, int64_t t, dou
   return (float)w;
 }
 
+struct ScatterArgs {
+  double n_rollouts; const double* pi;
+  const uint32_t* mask_bits; int64_t n_words; int64_t n_tokens; int64_t kept_cap;
+  const int64_t* cu; int B;
+  const int32_t* tile_count; const int32_t* tile_offset;        // offsets, or NULL: the block adds up the counts
+  int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept;
+  const int32_t* ids; int32_t* ids_k; const float* old_logp; float* old_logp_k;
+};
+
+// One block per tile of 4096 positions, 1024 per wavefront, 64 at a time, four such groups in flight:
+// the loads of a batch (ids, log-probs, probabilities) are issued before its first weight is computed.
+// Bound by the bytes it moves and, for weights that differ from token to token, by their fp64 divisions.
+// The per-token words ride along here because the token is already in hand: a row-gather block per kept
+// token for them took 8.66 ms of a 2^26-token batch (compaction as a whole 9.06 -> 0.38 ms), 190 us of a
+// 1.3-million-token one (whole selection 222 -> 28 us).
 __global__ void __launch_bounds__(kScatterThreads)
-compact_scatter_kernel(SelectArgs a, double n_rollouts, const double* __restrict__ pi,
-                       const uint32_t* __restrict__ mask_bits, int64_t n_words, int64_t n_tokens, int64_t kept_cap,
-                       const int64_t* __restrict__ cu, int B, const int32_t* __restrict__ tile_offset,
-                       int32_t* __restrict__ kept_idx, int32_t* __restrict__ kept_seq, float* __restrict__ kept_w) {
-  __shared__ int wave_cnt[4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // this wavefront's 1024 tokens = 32 mask words
-  const int64_t word0 = (int64_t)blockIdx.x * kTileWords + wave * 32;
-  const int64_t wi = word0 + lane;
-  const uint32_t my_word = (lane < 32 && wi < n_words) ? mask_bits[wi] : 0u;
-  const int cnt = wave_sum(__popc(my_word));
-  if (lane == 0) wave_cnt[wave] = cnt;
+compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
+  constexpr int kBatch = 4;
+  __shared__ uint32_t words[kTileWords + 2];
+  __shared__ int prefix[kTileWords + 1];                        // kept tokens of the tile before word w
+  __shared__ int wave_tot[4], wave_before[4], roll_range[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tile = blockIdx.x, n_tiles = gridDim.x;
+  const int64_t tile_first = (int64_t)tile * kTileTokens;
+
+  uint32_t word = 0;
+  if (tid < kTileWords) {
+    const int64_t wi = (int64_t)tile * kTileWords + tid;
+    word = wi < c.n_words ? c.mask_bits[wi] : 0u;
+    words[tid] = word;
+  }
+  const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
+  if (lane == 63) wave_tot[wave] = incl;
+  int before = 0;
+  if (!c.tile_offset)
+    for (int j = tid; j < tile; j += kScatterThreads) before += c.tile_count[j];
+  before = wave_sum(before);
+  if (lane == 0) wave_before[wave] = before;
+  // rollouts whose first position lies in this tile (offsets outside [0, n_tokens] count as its ends)
+  if (wave < 2) {
+    const int r = wave == 0 ? (tile == 0 ? 0 : wave_lower_bound(c.cu, 0, c.B + 1, tile_first))
+                            : (tile == n_tiles - 1 ? c.B + 1 : wave_lower_bound(c.cu, 0, c.B + 1, tile_first + kTileTokens));
+    if (lane == 0) roll_range[wave] = r;
+  }
   __syncthreads();
-  int base = tile_offset[blockIdx.x];
-  for (int w = 0; w < wave; ++w) base += wave_cnt[w];
-  // rollouts touched by this wavefront's 1024 tokens: two wave-uniform searches bound the per-lane ones
-  const int64_t N = cu[B];
-  const int64_t span_first = word0 * 32;
-  int i_lo = 0, i_hi = B;
-  if (span_first < N) {
-    const int64_t span_last = span_first + 1023 < N ? span_first + 1023 : N - 1;
-    i_lo = rollout_of_pos(cu, 0, B, span_first);
-    i_hi = rollout_of_pos(cu, i_lo, B, span_last) + 1;
+  if (tid < kTileWords) {
+    const int excl = incl - cnt + (wave == 1 ? wave_tot[0] : 0);
+    prefix[tid] = excl;
+    if (tid == kTileWords - 1) prefix[kTileWords] = excl + cnt;
+  }
+  const int tile_base = c.tile_offset ? c.tile_offset[tile]
+                                      : wave_before[0] + wave_before[1] + wave_before[2] + wave_before[3];
+  __syncthreads();
+  if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + prefix[kTileWords];
+  for (int i = roll_range[0] + tid; i < roll_range[1]; i += kScatterThreads) {
+    const int64_t pos = c.cu[i] < 0 ? 0 : c.cu[i] > c.n_tokens ? c.n_tokens : c.cu[i];
+    const int64_t off = pos - tile_first;
+    const int rel = off < 0 ? 0 : off > kTileTokens ? kTileTokens : (int)off, w = rel >> 5, rem = rel & 31;
+    c.cu_kept[i] = tile_base + prefix[w] + (rem ? __popc(words[w] & ((1u << rem) - 1u)) : 0);
   }
 
-  for (int it = 0; it < 16; ++it) {
-    const uint32_t lo = __shfl(my_word, 2 * it), hi = __shfl(my_word, 2 * it + 1);
-    const uint64_t group = (uint64_t)lo | ((uint64_t)hi << 32);
-    if (group == 0) continue;                                   // wave-uniform
-    const bool keep = (group >> lane) & 1ull;
-    const int rank = __popcll(group & ((1ull << lane) - 1ull));
-    const int64_t n = (word0 + 2 * it) * 32 + lane;
-    // entries beyond the outputs' capacity are counted but not written; a set bit at a position the
-    // per-token arrays do not have (a foreign mask) is ranked but reads and writes nothing
-    if (keep && base + rank < kept_cap && n < n_tokens) {
-      const int i = rollout_of_pos(cu, i_lo, i_hi, n);
-      const int64_t start = cu[i];
-      const int64_t T = cu[i + 1] - start;
-      const int scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
-      const int out = base + rank;
-      kept_idx[out] = (int32_t)n;
-      kept_seq[out] = i;
-      kept_w[out] = pi ? (float)(1.0 / ((n_rollouts * (double)T) * pi[n]))
-                       : ht_weight(scheme, T, n - start + 1, n_rollouts, a.p, a.min_cut);
+  // this wavefront's 1024 positions; rollout of its first one (the last rollout that starts at or before it)
+  const int64_t N = c.cu[c.B], span_first = tile_first + wave * 1024;
+  if (prefix[wave * 32] == prefix[wave * 32 + 32]) return;      // nothing kept
+  int i_lo = 0, i_hi = c.B;                                     // positions at or beyond N: any rollout (foreign mask)
+  if (span_first < N) {
+    const int64_t span_last = span_first + 1023 < N ? span_first + 1023 : N - 1;
+    i_lo = wave_lower_bound(c.cu, 0, c.B, span_first + 1) - 1;
+    i_lo = __builtin_amdgcn_readfirstlane(i_lo < 0 ? 0 : i_lo);
+    i_hi = __builtin_amdgcn_readfirstlane(wave_lower_bound(c.cu, i_lo, c.B, span_last + 1));
+    i_hi = i_hi <= i_lo ? i_lo + 1 : i_hi;
+  }
+  const bool one_rollout = i_hi - i_lo == 1;
+  const int64_t one_start = c.cu[i_lo], one_T = c.cu[i_lo + 1] - one_start;
+  const int one_scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
+
+  for (int g0 = 0; g0 < 16; g0 += kBatch) {
+    bool keep[kBatch];
+    int out[kBatch], id[kBatch], seq[kBatch];
+    float lp[kBatch];
+    double p[kBatch];
+    int64_t n[kBatch];
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      const int w = wave * 32 + 2 * (g0 + b);
+      const uint64_t group = (uint64_t)words[w] | ((uint64_t)words[w + 1] << 32);
+      n[b] = span_first + (g0 + b) * 64 + lane;
+      out[b] = tile_base + prefix[w] + __popcll(group & ((1ull << lane) - 1ull));
+      // entries beyond the outputs' capacity are counted but not written; a set bit at a position the
+      // per-token arrays do not have (a foreign mask) is ranked but reads and writes nothing
+      keep[b] = ((group >> lane) & 1ull) && out[b] < c.kept_cap && n[b] < c.n_tokens;
+      id[b] = keep[b] && c.ids ? c.ids[n[b]] : 0;
+      lp[b] = keep[b] && c.old_logp ? c.old_logp[n[b]] : 0.f;
+      p[b] = keep[b] && c.pi ? c.pi[n[b]] : 1.0;
+      seq[b] = i_lo;
     }
-    base += __popcll(group);
+#pragma unroll
+    for (int b = 0; b < kBatch; ++b) {
+      if (!keep[b]) continue;
+      int64_t start = one_start, T = one_T;
+      int scheme = one_scheme;
+      if (!one_rollout) {
+        seq[b] = rollout_of_pos(c.cu, i_lo, i_hi, n[b]);
+        start = c.cu[seq[b]];
+        T = c.cu[seq[b] + 1] - start;
+        if (a.scheme_per_rollout) scheme = a.scheme_per_rollout[seq[b]];
+      }
+      const int o = out[b];
+      c.kept_idx[o] = (int32_t)n[b];
+      c.kept_seq[o] = seq[b];
+      c.kept_w[o] = c.pi ? (float)(1.0 / ((c.n_rollouts * (double)T) * p[b]))
+                         : ht_weight(scheme, T, n[b] - start + 1, c.n_rollouts, a.p, a.min_cut);
+      if (c.ids) c.ids_k[o] = id[b];
+      if (c.old_logp) c.old_logp_k[o] = lp[b];
+    }
   }
 }
 
-// cu_kept[i] = number of kept tokens at packed positions < cu[i]
-__global__ void compact_cu_kept_kernel(const uint32_t* __restrict__ mask_bits, const int64_t* __restrict__ cu, int B,
-                                       int64_t n_tokens, const int32_t* __restrict__ tile_offset,
-                                       int32_t* __restrict__ cu_kept) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > B) return;
-  const int64_t pos = cu[i] < 0 ? 0 : cu[i] > n_tokens ? n_tokens : cu[i];   // the mask holds n_tokens positions
-  const int64_t tile = pos / kTileTokens;
-  int c = tile_offset[tile];
-  const int64_t w0 = tile * kTileWords, w1 = pos >> 5;
-  for (int64_t w = w0; w < w1; ++w) c += __popc(mask_bits[w]);
-  const int rem = (int)(pos & 31);
-  if (rem) c += __popc(mask_bits[w1] & ((1u << rem) - 1u));
-  cu_kept[i] = c;
+// N = 0: nothing is kept, every rollout starts at 0.
+__global__ void __launch_bounds__(256)
+compact_empty_kernel(int B, int32_t* __restrict__ cu_kept, int32_t* __restrict__ n_kept) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i <= B) cu_kept[i] = 0;
+  if (i == 0) *n_kept = 0;
 }
 
 // One block per kept row: copy row kept_idx[k] of `src` (row_bytes, multiple of 16) to row k.
 __global__ void __launch_bounds__(256)
 gather_rows_kernel(const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ n_kept, int64_t rows_cap,
-                   const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t row_vec16,
-                   const int32_t* __restrict__ ids, int32_t* __restrict__ ids_k,
-                   const float* __restrict__ old_logp, float* __restrict__ old_logp_k) {
+                   const uint4* __restrict__ src, uint4* __restrict__ dst, int64_t row_vec16) {
   const int nk = *n_kept;
   for (int64_t k = blockIdx.x; k < nk && k < rows_cap; k += gridDim.x) {
     const int64_t n = kept_idx[k];
-    if (src) {
-      const uint4* s = src + n * row_vec16;
-      uint4* d = dst + k * row_vec16;
-      for (int64_t j = threadIdx.x; j < row_vec16; j += blockDim.x) d[j] = s[j];
-    }
-    if (threadIdx.x == 0) {
-      if (ids) ids_k[k] = ids[n];
-      if (old_logp) old_logp_k[k] = old_logp[n];
-    }
+    const uint4* s = src + n * row_vec16;
+    uint4* d = dst + k * row_vec16;
+    for (int64_t j = threadIdx.x; j < row_vec16; j += blockDim.x) d[j] = s[j];
   }
 }
 
@@ -239,28 +321,30 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
   {
     ProfScope prof(PC_COMPACT, s, !c.no_timing);
     if (n_tiles > 0) {
-      compact_count_kernel<<<(unsigned)n_tiles, kTileWords, 0, s>>>(c.mask_bits, n_words, tile_count);
+      compact_count_kernel<<<(unsigned)((n_tiles + 3) / 4), 256, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count);
       NAT_LAUNCH_CHECK();
-    }
-    compact_scan_kernel<<<1, 1024, 0, s>>>(tile_count, (int)n_tiles, tile_offset, c.n_kept);
-    NAT_LAUNCH_CHECK();
-    if (n_tiles > 0) {
+      const bool scan = n_tiles > kInlineScanTiles;
+      if (scan) {
+        compact_scan_kernel<<<1, 1024, 0, s>>>(tile_count, (int)n_tiles, tile_offset);
+        NAT_LAUNCH_CHECK();
+      }
       compact_scatter_kernel<<<(unsigned)n_tiles, kScatterThreads, 0, s>>>(
-          a, (double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B, tile_offset,
-          c.kept_idx, c.kept_seq, c.kept_w);
+          a, ScatterArgs{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B, tile_count,
+                         scan ? tile_offset : nullptr, c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept,
+                         c.ids, c.ids_k, c.old_logp, c.old_logp_k});
+      NAT_LAUNCH_CHECK();
+    } else {
+      compact_empty_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.B, c.cu_kept, c.n_kept);
       NAT_LAUNCH_CHECK();
     }
-    compact_cu_kept_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.mask_bits, c.cu, c.B, c.N, tile_offset, c.cu_kept);
-    NAT_LAUNCH_CHECK();
   }
   if (c.h_n_kept) NAT_HIP_TRY(hipMemcpyAsync(c.h_n_kept, c.n_kept, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   const int64_t gather_rows = c.N < c.kept_cap ? c.N : c.kept_cap;
-  if (gather_rows > 0 && (c.hidden || c.ids || c.old_logp)) {
+  if (gather_rows > 0 && c.hidden) {
     ProfScope prof(PC_GATHER, s, !c.no_timing);
     const int64_t grid = gather_rows < 65536 * 4 ? gather_rows : 65536 * 4;
     gather_rows_kernel<<<(unsigned)grid, 256, 0, s>>>(c.kept_idx, c.n_kept, gather_rows, (const uint4*)c.hidden,
-                                                     (uint4*)c.hidden_k, row_bytes / 16, c.ids, c.ids_k,
-                                                     c.old_logp, c.old_logp_k);
+                                                     (uint4*)c.hidden_k, row_bytes / 16);
     NAT_LAUNCH_CHECK();
   }
   return NAT_OK;

@@ -124,3 +124,22 @@ def test_zero_advantage_rollouts_are_dropped(stage, scheme, kw):
     assert_select_compact_equal(h, o, lay["N"])
     full = oracle_select_compact(cu, scheme, seed=3, step=2, **kw)
     assert o["n_kept"] < full["n_kept"]
+
+
+@pytest.mark.parametrize("n_tiles,extra", [(1, -1), (1, 0), (1, 1), (2, 1023), (1024, 0), (1024, 1)])
+def test_compaction_at_tile_and_scan_boundaries(stage, n_tiles, extra):
+    # tiles of 4096 positions; up to 1024 of them a scatter block adds up the earlier tiles' counts itself, beyond
+    # that a scan runs first.  Rollouts: runs of empty and one-token ones at the edges of tiles and wavefronts (1024)
+    N = 4096 * n_tiles + extra
+    rng = np.random.default_rng(N)
+    edges = np.concatenate([[0, 0, 1, 1023, 1024, 1025, 4095, 4095, 4096, 4096, 4097], rng.integers(0, N, 70)])
+    cu = np.concatenate([[0], np.sort(np.minimum(edges, N)), np.full(3, N)]).astype(np.int64)
+    ids = rng.integers(0, 1 << 30, N).astype(np.int32)
+    old = rng.standard_normal(N).astype(np.float32)
+    for scheme, kw in ((osel.URS, dict(p=0.4)), (osel.RPC, dict(C=7)), (osel.FULL, {})):
+        o = oracle_select_compact(cu, scheme, seed=5, step=1, **kw)
+        h = hip_select_compact(stage, cu, scheme, seed=5, step=1, ids=to_dev(ids), old_logp=to_dev(old), **kw)
+        assert_select_compact_equal(h, o, N)
+        k = o["kept_idx"]
+        assert np.array_equal(h["ids_k"].cpu().numpy()[:len(k)], ids[k])
+        assert np.array_equal(h["old_logp_k"].cpu().numpy()[:len(k)], old[k])
