@@ -1,10 +1,11 @@
-// fp32 path of nat_loss_fwd_bwd (small heads: the tiny fp32 workload).  Plain
-// vector-ALU kernels, fixed summation order, one token chunk at a time:
-//   forward   one block per token: z = W h (one wavefront per vocabulary row),
-//             log-sum-exp, log-prob of the target, ratio / clipped surrogate
-//             (Eq. 1, Eq. 3), then dz = c (onehot - softmax) in the chunk scratch;
-//   dH        dH_k = sum_v dz_kv W_v       (one block per token, lanes over H);
-//   dW        dW_v += sum_k dz_kv h_k      (one thread per (v, h), tokens in order).
+// fp32 path of nat_loss_fwd_bwd and nat_logp_fwd (small heads: the tiny fp32 workload, gradient
+// checks), one token chunk at a time:
+//   logits    z = H W^T                         (f32_gemm_kernel)
+//   token     log-sum-exp with the true row maximum, log-prob of the target, ratio / clipped
+//             surrogate (Eq. 1, Eq. 3), then dz = c (onehot - softmax) over z;
+//   dH        dH = dz W                         (f32_gemm_kernel)
+//   dW        dW (+)= dz^T H, chunks in order   (f32_gemm_kernel)
+// Every sum has a fixed order.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
 
@@ -21,38 +22,173 @@ __device__ __forceinline__ float wave_max_f(float v) {
   return v;
 }
 
-__global__ void __launch_bounds__(kF32Threads)
-f32_forward_kernel(const float* __restrict__ hidden, const float* __restrict__ W, const int32_t* __restrict__ ids,
-                   const float* __restrict__ old_logp, const float* __restrict__ adv,
-                   const int32_t* __restrict__ kept_seq, const float* __restrict__ kept_w,
-                   int chunk_start, int H, int V, float eps_lo, float eps_hi, float grad_scale, KlArgs klp,
-                   float* __restrict__ dz /*[chunk, V]*/, float* __restrict__ logp_out, float* __restrict__ term,
-                   float* __restrict__ kl_out, float* __restrict__ entropy_out, int32_t* __restrict__ diag) {
-  extern __shared__ float h_s[];             // H floats
-  __shared__ float red[4];
-  __shared__ float bcast[2];
-  const int kc = blockIdx.x;                 // token within the chunk
-  const int k = chunk_start + kc;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int h = threadIdx.x; h < H; h += kF32Threads) h_s[h] = hidden[(size_t)k * H + h];
-  __syncthreads();
-  float* z = dz + (size_t)kc * V;
-  for (int v = wave; v < V; v += 4) {
-    const float* wr = W + (size_t)v * H;
-    float p = 0.f;
-    for (int h = lane; h < H; h += 64) p = fmaf(wr[h], h_s[h], p);
-    p = wave_sum_f(p);
-    if (lane == 0) z[v] = p;
+// ------------------------------------------------------------------- GEMM ----
+// C[m][n] = sum_k A(m, k) B(n, k) in fp32 on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 products and
+// sums, 157 TFLOP/s against 79 for unpacked vector FMAs).  One workgroup per 32 x 32 tile of C: the problems
+// of this path are small (a 601 x 256 dH has 152 such tiles for 256 CUs, and a contraction of 4096), so
+// the contraction axis is split over the eight wavefronts of the workgroup, whose partial tiles are added in
+// order through LDS.  Each wavefront streams its own range of k from memory (L2) 32 at a time, the loads of the
+// next 32 in flight under the products of the current ones; nothing in the loop waits for another wavefront.
+// An MFMA operand of a lane is (row l % 32, k = 8 (j / 4) + 4 (l / 32) + j % 4 for product j of a step), the same k
+// for both operands.  A k-major operand is read as that, 32 consecutive floats per half-wavefront.  A
+// k-contiguous one is read in whole 128-byte pieces of its rows and turned through the wavefront's own LDS (read
+// lane by lane from 32 rows at once it cost four times the address cycles and bound the kernel).
+// Measured at 601 tokens, V = 4096, H = 256: logits 25 us, dH 31 us, dW 30 us (44 TFLOP/s; latency of the short
+// ranges); one block per token (logits, dH) and per vocabulary row (dW) on the vector ALU took 2500 us for the three.
+// 64 x 64 tiles (half the reads) and sixteen wavefronts were slower or equal.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int kF32Waves = 8, kF32Step = 32;
+constexpr int kF32Row = 36;      // floats per LDS row of 32: 16-byte aligned, and 16 rows at one k cover all 64 banks once
+
+// operand (row, k): k-contiguous (KMajor = false) p[row * ld + k], k-major p[k * ld + row]; rows past the end
+// read the last one.  Vec: 16-byte loads (leading dimension a multiple of 4; bases are 16-byte aligned).
+template <bool KMajor, bool Vec>
+struct F32Operand {
+  const float* p;
+  int64_t ld;
+  int row0, rows, lane;
+  float* turn;                   // [32][kF32Row] of this wavefront (k-contiguous operands)
+
+  // raw values of the 32 k from k0 on; kTail: entries at or beyond k_end are zero (read from the last valid
+  // place; with Vec, k_end is a multiple of 4: the contraction's length is the leading dimension)
+  template <bool kTail>
+  __device__ __forceinline__ void fetch(float (&r)[16], int k0, int k_end) const {
+    auto row_of = [&](int i) { return (int64_t)(row0 + i < rows ? row0 + i : rows - 1); };
+    if constexpr (KMajor) {
+      const float* col = p + row_of(lane & 31);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int k = k0 + 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3);
+        const float x = col[(int64_t)(!kTail || k < k_end ? k : k_end - 1) * ld];
+        r[j] = !kTail || k < k_end ? x : 0.f;
+      }
+    } else if constexpr (Vec) {
+      const int k = k0 + 4 * (lane & 7);
+      const bool in = !kTail || k < k_end;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float4 x = *reinterpret_cast<const float4*>(p + row_of(8 * i + (lane >> 3)) * ld + (in ? k : k_end - 4));
+        r[4 * i] = in ? x.x : 0.f; r[4 * i + 1] = in ? x.y : 0.f; r[4 * i + 2] = in ? x.z : 0.f; r[4 * i + 3] = in ? x.w : 0.f;
+      }
+    } else {
+      const int k = k0 + (lane & 31);
+      const bool in = !kTail || k < k_end;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float x = p[row_of(2 * i + (lane >> 5)) * ld + (in ? k : k_end - 1)];
+        r[i] = in ? x : 0.f;
+      }
+    }
+  }
+  // LDS operations of one wavefront execute in order: no barrier between its writes and its reads
+  __device__ __forceinline__ void put(const float (&r)[16]) const {
+    if constexpr (!KMajor && Vec) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(turn + (8 * i + (lane >> 3)) * kF32Row + 4 * (lane & 7)) = make_float4(r[4 * i], r[4 * i + 1], r[4 * i + 2], r[4 * i + 3]);
+    } else if constexpr (!KMajor) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) turn[(2 * i + (lane >> 5)) * kF32Row + (lane & 31)] = r[i];
+    }
+  }
+  __device__ __forceinline__ void get(const float (&r)[16], float (&v)[16]) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if constexpr (KMajor) {
+        v[4 * q] = r[4 * q]; v[4 * q + 1] = r[4 * q + 1]; v[4 * q + 2] = r[4 * q + 2]; v[4 * q + 3] = r[4 * q + 3];
+      } else {
+        const float4 x = *reinterpret_cast<const float4*>(turn + (lane & 31) * kF32Row + 8 * q + 4 * (lane >> 5));
+        v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+      }
+    }
+  }
+};
+
+template <bool KMajorA, bool KMajorB, bool Vec>
+__global__ void __launch_bounds__(kF32Waves * 64)
+f32_gemm_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, int M, int N, int K,
+                int tiles_n, float* __restrict__ C, int64_t ldc, int accumulate) {
+  constexpr int kTurn = 32 * kF32Row, kTurns = (KMajorA ? 0 : 1) + (KMajorB ? 0 : 1), kPart = 32 * 33;
+  __shared__ __attribute__((aligned(16))) float lds[kF32Waves * (kTurns * kTurn > kPart ? kTurns * kTurn : kPart)];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
+  const int m0 = (int)(blockIdx.x / tiles_n) * 32, n0 = (int)(blockIdx.x % tiles_n) * 32;
+  float* turn = lds + wave * kTurns * kTurn;
+  const F32Operand<KMajorA, Vec> a{A, lda, m0, M, lane, turn};
+  const F32Operand<KMajorB, Vec> b{B, ldb, n0, N, lane, turn + (KMajorA ? 0 : kTurn)};
+  const int per = ((K + kF32Waves - 1) / kF32Waves + 7) / 8 * 8;          // k per wavefront, a multiple of 8
+  const int k_first = wave * per;
+  const int k_end = k_first + per < K ? k_first + per : K;
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  if (k_first < k_end) {
+    float ra[16], rb[16], va[16], vb[16];
+    auto fetch = [&](int k) {
+      if (k + kF32Step <= k_end) {                            // wave-uniform
+        a.template fetch<false>(ra, k, k_end);
+        b.template fetch<false>(rb, k, k_end);
+      } else {
+        a.template fetch<true>(ra, k, k_end);
+        b.template fetch<true>(rb, k, k_end);
+      }
+    };
+    fetch(k_first);
+    for (int k = k_first; k < k_end; k += kF32Step) {
+      a.put(ra);
+      b.put(rb);
+      __builtin_amdgcn_wave_barrier();
+      a.get(ra, va);
+      b.get(rb, vb);
+      if (k + kF32Step < k_end) fetch(k + kF32Step);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[j], vb[j], acc, 0, 0, 0);
+    }
   }
   __syncthreads();
+  // acc[r] of lane l is C[m0 + 8 (r / 4) + 4 (l / 32) + r % 4][n0 + l % 32]
+#pragma unroll
+  for (int r = 0; r < 16; ++r) lds[wave * kPart + (8 * (r >> 2) + 4 * lhi + (r & 3)) * 33 + l32] = acc[r];
+  __syncthreads();
+#pragma unroll
+  for (int e = threadIdx.x; e < 1024; e += kF32Waves * 64) {
+    const int i = e >> 5, j = e & 31;
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) s += lds[w * kPart + i * 33 + j];
+    if (m0 + i < M && n0 + j < N) {
+      float* c = C + (int64_t)(m0 + i) * ldc + n0 + j;
+      *c = accumulate ? *c + s : s;
+    }
+  }
+}
+
+template <bool KMajorA, bool KMajorB>
+static nat_status f32_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* C,
+                           int64_t ldc, int accumulate, hipStream_t s) {
+  const int tiles_n = (N + 31) / 32;
+  const unsigned grid = (unsigned)((int64_t)((M + 31) / 32) * tiles_n);
+  // 16-byte reads of a k-contiguous operand need its rows to start on 16 bytes
+  const bool vec = (KMajorA || lda % 4 == 0) && (KMajorB || ldb % 4 == 0);
+  if (vec) f32_gemm_kernel<KMajorA, KMajorB, true><<<grid, kF32Waves * 64, 0, s>>>(A, lda, B, ldb, M, N, K, tiles_n, C, ldc, accumulate);
+  else f32_gemm_kernel<KMajorA, KMajorB, false><<<grid, kF32Waves * 64, 0, s>>>(A, lda, B, ldb, M, N, K, tiles_n, C, ldc, accumulate);
+  NAT_LAUNCH_CHECK();
+  return NAT_OK;
+}
+
+// ------------------------------------------------------------- per token ----
+// log-sum-exp pieces of one token's logits, one block per token: the maximum m, sum of e^(z-m) and of
+// e^(z-m) (z-m), all threads.
+struct F32RowSums { float m, s, t; };
+__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, float (&red)[3][4]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float m = -INFINITY;
   for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
   m = wave_max_f(m);
-  if (lane == 0) red[wave] = m;
+  if (lane == 0) red[0][wave] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float s = 0.f, t = 0.f;                    // sum of e^(z-m) and of e^(z-m) (z-m)
+  m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+  float s = 0.f, t = 0.f;
   for (int v = threadIdx.x; v < V; v += kF32Threads) {
     const float zc = z[v] - m, e = expf(zc);
     s += e;
@@ -60,14 +196,27 @@ f32_forward_kernel(const float* __restrict__ hidden, const float* __restrict__ W
   }
   s = wave_sum_f(s);
   t = wave_sum_f(t);
-  __shared__ float red_t[4];
-  if (lane == 0) { red[wave] = s; red_t[wave] = t; }
+  if (lane == 0) { red[1][wave] = s; red[2][wave] = t; }
   __syncthreads();
+  return F32RowSums{m, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]), (red[2][0] + red[2][1]) + (red[2][2] + red[2][3])};
+}
+
+__global__ void __launch_bounds__(kF32Threads)
+f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_logp, const float* __restrict__ adv,
+                 const int32_t* __restrict__ kept_seq, const float* __restrict__ kept_w,
+                 int chunk_start, int V, float eps_lo, float eps_hi, float grad_scale, KlArgs klp,
+                 float* __restrict__ dz /*[chunk, V]: logits in, gradients out*/, float* __restrict__ logp_out,
+                 float* __restrict__ term, float* __restrict__ kl_out, float* __restrict__ entropy_out,
+                 int32_t* __restrict__ diag) {
+  __shared__ float red[3][4], bcast[2];
+  const int kc = blockIdx.x;                 // token within the chunk
+  const int k = chunk_start + kc;
+  float* z = dz + (size_t)kc * V;
+  const F32RowSums sums = f32_row_sums(z, V, red);
   if (threadIdx.x == 0) {
-    const float sum = (red[0] + red[1]) + (red[2] + red[3]);
-    const float lse = m + logf(sum);
+    const float lse = sums.m + logf(sums.s);
     // -sum p log p = log(sum) - (sum of e (z - m)) / sum
-    if (entropy_out) entropy_out[k] = logf(sum) - ((red_t[0] + red_t[1]) + (red_t[2] + red_t[3])) / sum;
+    if (entropy_out) entropy_out[k] = logf(sums.s) - sums.t / sums.s;
     const int yk = ids[k];
     bcast[0] = lse;
     if (yk < 0 || yk >= V) {                 // no such token: left out (no loss term, zero gradient)
@@ -101,30 +250,6 @@ f32_forward_kernel(const float* __restrict__ hidden, const float* __restrict__ W
   }
 }
 
-__global__ void __launch_bounds__(kF32Threads)
-f32_dh_kernel(const float* __restrict__ dz, const float* __restrict__ W, int chunk_start, int H, int V,
-              float* __restrict__ dH) {
-  const int kc = blockIdx.x;
-  const float* d = dz + (size_t)kc * V;
-  for (int h = threadIdx.x; h < H; h += kF32Threads) {
-    float acc = 0.f;
-    for (int v = 0; v < V; ++v) acc = fmaf(d[v], W[(size_t)v * H + h], acc);
-    dH[(size_t)(chunk_start + kc) * H + h] = acc;
-  }
-}
-
-__global__ void __launch_bounds__(kF32Threads)
-f32_dw_kernel(const float* __restrict__ dz, const float* __restrict__ hidden, int chunk_start, int chunk_n,
-              int H, int V, int accumulate, float* __restrict__ dW) {
-  const int v = blockIdx.x;
-  for (int h = blockIdx.y * kF32Threads + threadIdx.x; h < H; h += gridDim.y * kF32Threads) {
-    float acc = accumulate ? dW[(size_t)v * H + h] : 0.f;
-    for (int kc = 0; kc < chunk_n; ++kc)
-      acc = fmaf(dz[(size_t)kc * V + v], hidden[(size_t)(chunk_start + kc) * H + h], acc);
-    dW[(size_t)v * H + h] = acc;
-  }
-}
-
 static int f32_chunk_rows(int32_t N_k, int32_t V, size_t ws_bytes) {
   const size_t fixed = (size_t)N_k * sizeof(float) + 256;
   if (ws_bytes <= fixed) return 0;
@@ -142,7 +267,7 @@ size_t loss_f32_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal)
 }
 
 nat_status loss_f32_run(const LossArgs& a) {
-  if ((size_t)a.H * sizeof(float) > 60 * 1024) return NAT_BAD_SHAPE;      // h_k is staged in LDS
+  if ((size_t)a.H * sizeof(float) > 60 * 1024) return NAT_BAD_SHAPE;      // the path's bound on H (15360)
   const int rows = f32_chunk_rows(a.N_k, a.V, a.ws_bytes);
   if (rows < 1) return NAT_WORKSPACE_TOO_SMALL;
   float* term = (float*)a.ws;
@@ -152,17 +277,17 @@ nat_status loss_f32_run(const LossArgs& a) {
     ProfScope prof(PC_F32_PATH, s);
     for (int c0 = 0; c0 < a.N_k; c0 += rows) {
       const int n = a.N_k - c0 < rows ? a.N_k - c0 : rows;
-      f32_forward_kernel<<<n, kF32Threads, (size_t)a.H * sizeof(float), s>>>(
-          (const float*)a.hidden, (const float*)a.W, a.ids, a.old_logp, a.adv, a.kept_seq, a.kept_w, c0, a.H, a.V,
-          a.eps_lo, a.eps_hi, a.grad_scale, KlArgs{a.ref_logp, a.beta_kl, a.kl_kind}, dz, a.logp, term,
-          a.kl_out, a.entropy_out, a.diag);
+      const float* hid = (const float*)a.hidden + (size_t)c0 * a.H;
+      nat_status st = f32_gemm<false, false>(hid, a.H, (const float*)a.W, a.H, n, a.V, a.H, dz, a.V, 0, s);
+      if (st != NAT_OK) return st;
+      f32_token_kernel<<<n, kF32Threads, 0, s>>>(
+          a.ids, a.old_logp, a.adv, a.kept_seq, a.kept_w, c0, a.V, a.eps_lo, a.eps_hi, a.grad_scale,
+          KlArgs{a.ref_logp, a.beta_kl, a.kl_kind}, dz, a.logp, term, a.kl_out, a.entropy_out, a.diag);
       NAT_LAUNCH_CHECK();
-      f32_dh_kernel<<<n, kF32Threads, 0, s>>>(dz, (const float*)a.W, c0, a.H, a.V, (float*)a.dH);
-      NAT_LAUNCH_CHECK();
-      const int gy = (a.H + kF32Threads - 1) / kF32Threads;
-      f32_dw_kernel<<<dim3(a.V, gy > 64 ? 64 : gy), kF32Threads, 0, s>>>(
-          dz, (const float*)a.hidden, c0, n, a.H, a.V, (c0 > 0 || a.accumulate_dw) ? 1 : 0, a.dW);
-      NAT_LAUNCH_CHECK();
+      st = f32_gemm<false, true>(dz, a.V, (const float*)a.W, a.H, n, a.H, a.V, (float*)a.dH + (size_t)c0 * a.H, a.H, 0, s);
+      if (st != NAT_OK) return st;
+      st = f32_gemm<true, true>(dz, a.V, hid, a.H, a.V, a.H, n, a.dW, a.H, (c0 > 0 || a.accumulate_dw) ? 1 : 0, s);
+      if (st != NAT_OK) return st;
     }
   }
   ProfScope prof(PC_LOSS_REDUCE, s);
@@ -172,54 +297,23 @@ nat_status loss_f32_run(const LossArgs& a) {
 }
 
 
-// Forward pass alone on the fp32 path: one block per token, logits kept in LDS-sized pieces of the
-// chunk scratch, log-sum-exp with the true row maximum, entropy from the same two sums.
+// Forward pass alone: log-prob of the target and entropy of one token per block.
 __global__ void __launch_bounds__(kF32Threads)
-f32_logp_kernel(const float* __restrict__ hidden, const float* __restrict__ W, const int32_t* __restrict__ ids,
-                int chunk_start, int H, int V, float* __restrict__ z_scratch /*[chunk, V]*/,
+f32_logp_kernel(const float* __restrict__ z_scratch /*[chunk, V]*/, const int32_t* __restrict__ ids, int chunk_start, int V,
                 float* __restrict__ logp_out, float* __restrict__ entropy_out, int32_t* __restrict__ diag) {
-  extern __shared__ float h_s[];
-  __shared__ float red[4], red_t[4];
+  __shared__ float red[3][4];
   const int kc = blockIdx.x, k = chunk_start + kc;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int h = threadIdx.x; h < H; h += kF32Threads) h_s[h] = hidden[(size_t)k * H + h];
-  __syncthreads();
-  float* z = z_scratch + (size_t)kc * V;
-  for (int v = wave; v < V; v += 4) {
-    const float* wr = W + (size_t)v * H;
-    float p = 0.f;
-    for (int h = lane; h < H; h += 64) p = fmaf(wr[h], h_s[h], p);
-    p = wave_sum_f(p);
-    if (lane == 0) z[v] = p;
-  }
-  __syncthreads();
-  float m = -INFINITY;
-  for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
-  m = wave_max_f(m);
-  if (lane == 0) red[wave] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float s = 0.f, t = 0.f;
-  for (int v = threadIdx.x; v < V; v += kF32Threads) {
-    const float zc = z[v] - m, e = expf(zc);
-    s += e;
-    t = fmaf(e, zc, t);
-  }
-  s = wave_sum_f(s);
-  t = wave_sum_f(t);
-  if (lane == 0) { red[wave] = s; red_t[wave] = t; }
-  __syncthreads();
+  const float* z = z_scratch + (size_t)kc * V;
+  const F32RowSums sums = f32_row_sums(z, V, red);
   if (threadIdx.x == 0) {
-    const float sum = (red[0] + red[1]) + (red[2] + red[3]);
     const int yk = ids[k];
     if (yk < 0 || yk >= V) {
       logp_out[k] = __builtin_nanf("");
       if (diag) atomicAdd(diag + NAT_DIAG_BAD_ID, 1);
     } else {
-      logp_out[k] = z[yk] - (m + logf(sum));
+      logp_out[k] = z[yk] - (sums.m + logf(sums.s));
     }
-    if (entropy_out) entropy_out[k] = logf(sum) - ((red_t[0] + red_t[1]) + (red_t[2] + red_t[3])) / sum;
+    if (entropy_out) entropy_out[k] = logf(sums.s) - sums.t / sums.s;
   }
 }
 
@@ -240,8 +334,10 @@ nat_status logp_f32_run(const LogpArgs& a) {
   ProfScope prof(PC_F32_PATH, s);
   for (int c0 = 0; c0 < a.N_k; c0 += (int)rows) {
     const int n = a.N_k - c0 < (int)rows ? a.N_k - c0 : (int)rows;
-    f32_logp_kernel<<<n, kF32Threads, (size_t)a.H * sizeof(float), s>>>(
-        (const float*)a.hidden, (const float*)a.W, a.ids, c0, a.H, a.V, (float*)a.ws, a.logp, a.entropy, a.diag);
+    const nat_status st = f32_gemm<false, false>((const float*)a.hidden + (size_t)c0 * a.H, a.H, (const float*)a.W, a.H, n,
+                                                 a.V, a.H, (float*)a.ws, a.V, 0, s);
+    if (st != NAT_OK) return st;
+    f32_logp_kernel<<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
     NAT_LAUNCH_CHECK();
   }
   return NAT_OK;

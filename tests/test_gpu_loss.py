@@ -71,6 +71,20 @@ def test_fp32_path(stage, n_tok, H, V):
     assert n_tok < 30 or clipped.any()
 
 
+@pytest.mark.parametrize("n_tok,H,V", [
+    (33, 68, 1028),          # one past a 32-row tile on every axis, rows on 16 bytes
+    (65, 31, 129),           # odd leading dimensions: no 16-byte operand reads
+    (5, 7, 31),              # shorter than one step of one wavefront
+    (31, 260, 2052),         # several 32-long steps per wavefront and a remainder
+    (520, 64, 300),          # the dW contraction with more than one step per wavefront
+])
+def test_fp32_contraction_remainders(stage, n_tok, H, V):
+    # tolerance: the path's 1e-5 (sums of at most 2052 fp32 products split over eight wavefronts stay below 1e-6)
+    case = make_loss_case(40 + n_tok, n_tok, H, V, "f32", noise=0.15)
+    ref = oracle_loss(**case)
+    check(hip_loss(stage, case, "f32"), ref, n_tok, TOL_F32, case)
+
+
 def test_fp32_chunked_workspace_and_accumulate(stage):
     import paper_2603_06619_amd as nat
     case = make_loss_case(5, 50, 64, 512, "f32")
