@@ -75,7 +75,7 @@ constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stag
 #endif
 constexpr int kMaxChunk = 32768;                  // most token rows per chunk (see recommended_cap)
 constexpr int kNumCU = 256;                       // compute units (one workgroup of these kernels each)
-constexpr int kMinSlicesPerRange = 32;            // shortest range of a cut dW contraction axis (k-slices)
+constexpr int kMinSlicesPerRange = 32;            // shortest range of a cut contraction axis (k-slices)
 #ifndef NAT_SUBCHUNK
 #define NAT_SUBCHUNK 8192
 #endif
@@ -163,10 +163,10 @@ struct GemmArgs {
   int tiles_m, tiles_n;
   int group_m;                // tile rows walked together (see tile_of_block)
   int kb_a_src;               // k-major A only (see TileLoaderKMajor): k-slices of the source operand
-  int k_splits;               // > 1: the contraction axis is cut into this many ranges of kt_per_split k-slices, one
-  int kt_per_split;           // workgroup per (tile, range); the epilogue is told which slab its raw sums go to
-  int tail_tiles;             // with k_splits > 1: 0 = every tile is cut (slab = range); T > 0 = only the last T tiles in
-                              // launch order are (slab = position among them * k_splits + range), the others run whole
+  // k_splits > 1: the contraction axis of the last tail_tiles tiles in launch order (all of them when there are fewer
+  // than compute units) is cut into k_splits ranges of kt_per_split k-slices, one workgroup per (tile, range); the
+  // epilogue is told which slab its raw sums go to (position among the cut tiles * k_splits + range)
+  int k_splits, kt_per_split, tail_tiles;
 };
 
 // Block id -> output tile.  Blocks are dealt round-robin to the 8 XCDs, so ids
@@ -379,18 +379,12 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   int tm, tn;
   const int n_tiles = g.tiles_m * g.tiles_n;
   int pid = (int)blockIdx.x, range = -1, slab = -1;           // range of the contraction axis / slab (-1: whole axis)
-  if (g.k_splits > 1) {
-    if (g.tail_tiles == 0) {
-      range = pid / n_tiles;
-      pid -= range * n_tiles;
-      slab = range;
-    } else if (pid >= n_tiles - g.tail_tiles) {
-      const int r = pid - (n_tiles - g.tail_tiles);
-      range = r / g.tail_tiles;
-      const int pos = r - range * g.tail_tiles;
-      pid = n_tiles - g.tail_tiles + pos;
-      slab = pos * g.k_splits + range;
-    }
+  if (g.k_splits > 1 && pid >= n_tiles - g.tail_tiles) {
+    const int r = pid - (n_tiles - g.tail_tiles);
+    range = r / g.tail_tiles;
+    const int pos = r - range * g.tail_tiles;
+    pid = n_tiles - g.tail_tiles + pos;
+    slab = pos * g.k_splits + range;
   }
   tile_of_block(g, pid, tm, tn);
   const int m0 = tm * kBM, n0 = tn * kBN;
@@ -702,8 +696,7 @@ struct DHiddenEpilogue {
   int n_valid, H;
   uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
   const float* beta;               // [n_valid]
-  float* partial;                  // split contraction: [k_splits][rows_p][cols_p] fp32 partial sums (else NULL)
-  int rows_p, cols_p;              // padded token rows / hidden columns of the launch
+  float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
 
   template <int NB> struct Pre {};
   template <int NB> static constexpr int stash_words() { return 0; }
@@ -714,14 +707,15 @@ struct DHiddenEpilogue {
                                              char* lds, int slab_id) const {
     const int l32 = lane & 31, lhi = lane >> 5;
     if (slab_id >= 0) {            // this workgroup's range of the vocabulary: the raw sums go to its slab
-      float* slab = partial + (int64_t)slab_id * rows_p * cols_p;
+      float* slab = partial + (int64_t)slab_id * (kBM * kBN);
 #pragma unroll
       for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int k = k0 + mb * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
+          if (k >= n_valid) continue;                          // padding rows of a short batch are not read back
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) slab[(int64_t)k * cols_p + h0 + nb * 32 + l32] = acc[mb][nb][r];
+          for (int nb = 0; nb < NB; ++nb) slab[(k & (kBM - 1)) * kBN + (h0 & (kBN - 1)) + nb * 32 + l32] = acc[mb][nb][r];
         }
       return;
     }
@@ -815,17 +809,29 @@ struct DWeightEpilogue {
   }
 };
 
-// dH of a launch whose contraction was split: dH[k][h] = beta_k * (slab 0 + slab 1 + ...), in slab order.
+// dH tiles of a launch whose last tail_tiles tiles (in launch order) were cut into k_splits ranges of the vocabulary:
+// dH[k][h] = beta_k * (slab 0 + slab 1 + ...) of the tile, in range order.  One block per 1024 elements of a tile.
 __global__ void __launch_bounds__(256)
-dh_reduce_kernel(const float* __restrict__ partial, int k_splits, int rows_p, int cols_p, const float* __restrict__ beta,
-                 int n_valid, int H, uint16_t* __restrict__ dH) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int k = (int)(i / H), h = (int)(i % H);
-  if (k >= n_valid) return;
-  const int64_t slab = (int64_t)rows_p * cols_p;
-  float s = 0.f;
-  for (int sp = 0; sp < k_splits; ++sp) s += partial[sp * slab + (int64_t)k * cols_p + h];
-  dH[(int64_t)k * H + h] = f32_to_bf16_bits(beta[k] * s);
+dh_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, const float* __restrict__ beta, int n_valid, int H,
+                      uint16_t* __restrict__ dH) {
+  const int pos = blockIdx.y;
+  int tm, tn;
+  tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tm, tn);
+  const int e = (blockIdx.x * 256 + threadIdx.x) * 4;                  // four columns of a row
+  const int k = tm * kBM + e / kBN, h = tn * kBN + e % kBN;
+  if (k >= n_valid || h >= H) return;                                  // H is a multiple of 64
+  const float* slab = partial + (int64_t)pos * g.k_splits * (kBM * kBN) + e;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int r = 0; r < g.k_splits; ++r) {
+    const float4 x = *reinterpret_cast<const float4*>(slab + (int64_t)r * (kBM * kBN));
+    s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+  }
+  const float b = beta[k];
+  uint2 w;
+  w.x = pack_bf16x2(b * s.x, b * s.y);
+  w.y = pack_bf16x2(b * s.z, b * s.w);
+  *reinterpret_cast<uint2*>(dH + (int64_t)k * H + h) = w;
 }
 
 // dW tiles of a launch whose last tail_tiles tiles (in launch order) were cut into k_splits ranges of tokens:
@@ -1091,6 +1097,27 @@ size_t logp_bf16_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal
   return make_fwd_plan(H, V, minimal ? kBN : recommended_cap(N_k, H, false)).total;
 }
 
+// How a launch of `tiles` output tiles and `kt_all` k-slices uses the compute units.  Full rounds of one tile per
+// compute unit run whole; the tiles left over (at most half a round: with more, two ranges each would not fit one
+// round) are cut into as many ranges of the contraction axis as fill the chip once, none shorter than
+// kMinSlicesPerRange (a workgroup's load ring and epilogue cost about ten slices), starts multiples of `align`.
+// 5003 tokens at the 7B head: 280 dH tiles took a second round for 24 of them, 6.26 ms; cut into ten ranges, 3.96 ms.
+struct RangeCut { int splits, kt_per, tail, grid; };
+static RangeCut range_cut(int tiles, int kt_all, int align) {
+  RangeCut c{1, kt_all, 0, tiles};
+  const int tail = tiles % kNumCU;
+  if (tail == 0 || tail * 2 > kNumCU) return c;
+  int splits = kNumCU / tail;
+  if (splits > kt_all / kMinSlicesPerRange) splits = kt_all / kMinSlicesPerRange;
+  if (splits <= 1) return c;
+  c.kt_per = (int)round_up((kt_all + splits - 1) / splits, align);
+  c.splits = (kt_all + c.kt_per - 1) / c.kt_per;                   // every range non-empty
+  if (c.splits <= 1) return RangeCut{1, kt_all, 0, tiles};
+  c.tail = tail;
+  c.grid = tiles - tail + tail * c.splits;
+  return c;
+}
+
 template <int NW, class Epi>
 static nat_status launch_gemm(const GemmArgs& g, const Epi& epi, int prof_class, hipStream_t s) {
   ProfScope prof(prof_class, s);
@@ -1177,23 +1204,19 @@ nat_status loss_bf16_run(const LossArgs& a) {
         NAT_LAUNCH_CHECK();
       }
       {  // dH: rows = tokens, columns = hidden units, contraction over the padded vocabulary
-        // a launch with fewer tiles than compute units cuts the vocabulary into ranges (one workgroup per tile
-        // and range, raw partial sums in fp32) and adds them up in range order afterwards
+        // The tiles left over after the last full round of one tile per compute unit (all of them in a short batch)
+        // are cut into ranges of the vocabulary: see range_cut.
         const int tiles = (snp / kBM) * (Hp / kBN);
-        int splits = tiles * 2 <= kNumCU ? kNumCU / tiles : 1;
-        if (splits > 8) splits = 8;
-        while (splits > 1 && (Vp / kBK) / splits < 64) --splits;
-        const int kt_per = (Vp / kBK + splits - 1) / splits;
+        const RangeCut cut = range_cut(tiles, Vp / kBK, 1);
         uint16_t* dH_s = (uint16_t*)a.dH + (int64_t)(c0 + s0) * H;
-        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, splits, kt_per};
-        DHiddenEpilogue e{snv, H, dH_s, beta + s0, splits > 1 ? dh_part : nullptr, snp, Hp};
+        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, cut.splits, cut.kt_per, cut.tail};
+        DHiddenEpilogue e{snv, H, dH_s, beta + s0, dh_part};
         {
           ProfScope prof(PC_DHIDDEN, s);
-          gemm_nt_kernel<DHiddenEpilogue, NAT_WAVES_DHIDDEN, false><<<tiles * splits, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+          gemm_nt_kernel<DHiddenEpilogue, NAT_WAVES_DHIDDEN, false><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
           NAT_LAUNCH_CHECK();
-          if (splits > 1) {
-            const int64_t n = (int64_t)snv * H;
-            dh_reduce_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(dh_part, splits, snp, Hp, beta + s0, snv, H, dH_s);
+          if (cut.splits > 1) {
+            dh_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, beta + s0, snv, H, dH_s);
             NAT_LAUNCH_CHECK();
           }
         }
@@ -1201,28 +1224,18 @@ nat_status loss_bf16_run(const LossArgs& a) {
     }
     {  // dW: rows = vocabulary, columns = hidden units, contraction over the chunk's (padded) tokens
       // A = E from its one copy (rows = token), i.e. stored along this contraction's k axis
-      // The tiles left over after the last full round of one tile per compute unit would occupy a fraction
-      // of the chip for a whole tile time: their token axis is cut into ranges (one workgroup per tile and
-      // range, raw sums to slabs) that are added into dW in range order afterwards.
-      const int tiles = (Vp / kBM) * (Hp / kBN), kt_all = np / kBK;
-      const int tail = tiles % kNumCU;
-      int splits = (tail > 0 && tail * 2 <= kNumCU) ? kNumCU / tail : 1, kt_per = kt_all;
-      if (splits > 8) splits = 8;
-      while (splits > 1 && kt_all / splits < kMinSlicesPerRange) --splits;
-      if (splits > 1) {
-        kt_per = (int)round_up((kt_all + splits - 1) / splits, 8);
-        splits = (kt_all + kt_per - 1) / kt_per;               // every range non-empty
-      }
+      // The leftover tiles of the last round are cut into ranges of tokens (multiples of the 8 k-slices that the
+      // k-major loader starts at): see range_cut.
+      const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), np / kBK, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
-      GemmArgs g{Eb, Hktb, np, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, splits, kt_per, splits > 1 ? tail : 0};
+      GemmArgs g{Eb, Hktb, np, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, cut.splits, cut.kt_per, cut.tail};
       DWeightEpilogue e{V, H, accumulate, a.dW, dh_part};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        const int grid = splits > 1 ? tiles - tail + tail * splits : tiles;
-        gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, true><<<grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
+        gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, true><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
         NAT_LAUNCH_CHECK();
-        if (splits > 1) {
-          dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);
+        if (cut.splits > 1) {
+          dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);
           NAT_LAUNCH_CHECK();
         }
       }

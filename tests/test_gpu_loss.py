@@ -213,6 +213,17 @@ def test_bf16_hidden_size_not_a_multiple_of_the_tile(stage):
     check(out, ref, 300, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok,H,V,label", [
+    (4700, 3584, 2100, "dH: a full round of tiles and ten more in two vocabulary ranges"),
+    (100, 128, 40000, "dH: one tile in 39 vocabulary ranges"),
+    (257, 320, 9000, "dH: four tiles, two of them with one valid row, in eight ranges"),
+])
+def test_bf16_dh_leftover_tiles_cut_into_vocabulary_ranges(stage, n_tok, H, V, label):
+    case = make_loss_case(300 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.02)
+    ref = oracle_loss(**case)
+    check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case, label=label)
+
+
 def test_bf16_dw_leftover_tiles_cut_into_token_ranges(stage):
     # 8 dW tiles on 256 compute units: all of them are "left over" after the last full round, so the library
     # cuts their token axis (8173 tokens = 256 k-slices) into 8 ranges and adds the partial tiles in range
