@@ -30,7 +30,9 @@
 // operand is kept in a blocked layout in the workspace: blocks of 256 rows x 32 k-elements (16 KiB,
 // contiguous), ordered k-fastest inside a 256-row tile, so a workgroup streams one contiguous
 // region per operand instead of 256 strided rows.  W and H_chunk are repacked (plain and
-// transposed); the soft-max numerators are produced directly in that layout.
+// transposed); the soft-max numerators are produced directly in that layout.  Short batches do not
+// repack W (kDirectTokens): the logits contraction reads its rows, the dH contraction, turned round to
+// dH^T = W^T E^T, reads them as a k-major operand.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
 
@@ -163,10 +165,12 @@ struct GemmArgs {
   int tiles_m, tiles_n;
   int group_m;                // tile rows walked together (see tile_of_block)
   int kb_a_src;               // k-major A only (see TileLoaderKMajor): k-slices of the source operand
+  int kb_b;                   // k-slices of the B operand as it is stored (>= K / kBK)
   // k_splits > 1: the contraction axis of the last tail_tiles tiles in launch order (all of them when there are fewer
   // than compute units) is cut into k_splits ranges of kt_per_split k-slices, one workgroup per (tile, range); the
   // epilogue is told which slab its raw sums go to (position among the cut tiles * k_splits + range)
   int k_splits, kt_per_split, tail_tiles;
+  int src_rows, src_cols;     // A read from a row-major matrix (TileLoaderRows, TileLoaderKMajorRows): its extent
 };
 
 // Block id -> output tile.  Blocks are dealt round-robin to the 8 XCDs, so ids
@@ -261,6 +265,67 @@ struct TileLoaderKMajor {
   }
 };
 
+// The same two tiles straight from a row-major matrix (the caller's W), for batches too small to pay for repacking it:
+// one instruction reads 64 bytes of 16 rows, each lane from where its place of the LDS tile wants it (16-byte chunk
+// p of a tile row holds chunk p XOR bits 2..3 of the row).  Rows past the end read the last row: as vocabulary rows
+// of the logits tile they are masked by the epilogue, as k of the dH contraction they meet numerators that are 0.
+template <int NW>
+struct TileLoaderRows {          // [256 rows][32 k]: rows of the matrix, k its columns
+  static constexpr int kLoads = kTileBytes / 1024 / NW;
+  const uint16_t* src[kLoads];   // this lane's chunk in k-slice 0 of each load
+  __device__ __forceinline__ void init(const uint16_t* W, int tile, int rows, int ld, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int r = (wave * kLoads + i) * 16 + (lane >> 2), row = tile * kBM + r;
+      src[i] = W + (int64_t)(row < rows ? row : rows - 1) * ld + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
+    }
+  }
+  __device__ __forceinline__ void start_at(int kt0) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) src[i] += kt0 * kBK;
+  }
+  template <int kIdx>
+  __device__ __forceinline__ void issue_one(char* lds_tile, int kt, int wave) const {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[kIdx] + kt * kBK),
+                                     (__attribute__((address_space(3))) void*)(lds_tile + (wave * kLoads + kIdx) * 1024), 16, 0, 0);
+  }
+  __device__ __forceinline__ void issue(char* lds_tile, int kt, int wave) const {
+    static_assert(kLoads == 4, "written out for 4 wavefronts");
+    issue_one<0>(lds_tile, kt, wave);
+    issue_one<1>(lds_tile, kt, wave);
+    issue_one<2>(lds_tile, kt, wave);
+    issue_one<3>(lds_tile, kt, wave);
+  }
+};
+
+template <int NW>
+struct TileLoaderKMajorRows {    // [256 rows][32 k] with k the rows of the matrix: pieces of 32 k x 32 rows, as TileLoaderKMajor
+  static constexpr int kLoads = kTileBytes / 1024 / NW;
+  const uint16_t* src;           // this lane's chunk of row 0 of the wavefront's first piece
+  int piece_step;                // elements from the wavefront's first piece to its second
+  int k_rows, ld, k_lane, kt_first;
+  __device__ __forceinline__ void init(const uint16_t* W, int tile, int rows, int cols, int wave, int lane) {
+    static_assert(kLoads == 4, "two pieces per wavefront");
+    const int c0 = tile * kBM + 64 * wave, c1 = c0 + 32;         // columns past the end (a multiple of 64 is valid): any valid ones
+    const int s0 = c0 < cols ? c0 : cols - 32, s1 = c1 < cols ? c1 : cols - 32;
+    k_lane = lane >> 2;
+    src = W + s0 + (((lane & 3) ^ ((lane >> 4) & 3)) << 3);
+    piece_step = s1 - s0;
+    k_rows = rows;
+    ld = cols;
+    kt_first = 0;
+  }
+  __device__ __forceinline__ void start_at(int kt0) { kt_first = kt0; }
+  template <int kIdx>
+  __device__ __forceinline__ void issue_one(char* lds_tile, int kt, int wave) const {
+    constexpr int piece = kIdx >> 1, half = kIdx & 1;
+    const int k = (kt_first + kt) * kBK + half * 16 + k_lane;
+    __builtin_amdgcn_global_load_lds(
+        (const __attribute__((address_space(1))) void*)(src + (int64_t)(k < k_rows ? k : k_rows - 1) * ld + piece * piece_step),
+        (__attribute__((address_space(3))) void*)(lds_tile + (wave * 4 + kIdx) * 1024), 16, 0, 0);
+  }
+};
+
 // Per-lane byte offsets, inside a [k = 32][32 rows] piece, of the two transposing reads (q = 0, 1)
 // that make one A fragment of k-substep 0.  The transposing read works on groups of 16 lanes: lane
 // i of a group supplies the address of 4 consecutive 16-bit elements and receives element i % 4 of
@@ -288,11 +353,11 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // MFMAs one fragment read of k-substep ks_load from (a_s, b_s) into (al, bl); the remaining MFMAs carry
 // the direct-to-LDS loads of this wavefront's share of slice k into lds_dst, evenly spaced (mixing them
 // with the fragment reads measured slower).
-template <int NW, int NB, int M = 0>
+template <int NW, int NB, int M = 0, class Loader>
 __device__ __forceinline__ void substep_slots(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
                                               bf16x8 (&al)[4], bf16x8 (&bl)[NB], const char* a_s, const char* b_s,
                                               int a_row0, int b_row0, int l32, int lhi, int ks_load,
-                                              const TileLoader<NW>& ld, char* lds_dst, int k, int wave) {
+                                              const Loader& ld, char* lds_dst, int k, int wave) {
   constexpr int kLoadFirst = 4 + NB, kLoadEvery = (4 * NB - kLoadFirst) / TileLoader<NW>::kLoads;
   static_assert(kLoadEvery >= 1, "every load needs a slot");
   if constexpr (M < 4 * NB) {
@@ -324,10 +389,10 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int off) {
 // (au, bu); behind the first 8 MFMAs one transposing read each (halves q = m % 2 of A block m / 2, from the
 // piece bases a_rd[q]) and behind the first 4 also one 16-byte read of B; behind MFMAs 8, 10, 12, 14 one
 // direct-to-LDS load of the refill (the A tile's when kRefillA, else the B tile's).
-template <bool kRefillA, int M = 0>
+template <bool kRefillA, int M = 0, class LoaderA>
 __device__ __forceinline__ void substep_slots_kmajor4(f32x16 (&acc)[4][4], const bf16x8 (&au)[4], const bf16x8 (&bu)[4],
                                                       s16x4 (&al)[8], bf16x8 (&bl)[4], const uint32_t (&a_rd)[2], const char* b_rd,
-                                                      const TileLoaderKMajor<4>& la, const TileLoader<4>& lb, char* lds_dst,
+                                                      const LoaderA& la, const TileLoader<4>& lb, char* lds_dst,
                                                       int k, int wave) {
   if constexpr (M < 16) {
     constexpr int i = M / 4, j = M % 4;
@@ -359,11 +424,13 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 // NW wavefronts in a 2 x (NW/2) grid over the 256 x 256 tile: wavefront (wm, wn) owns rows
 // wm*128.. and columns wn*(NB*32).. with NB = 16/NW (4 wavefronts: 128 columns, 8: 64 columns).
 // acc[mb][nb] element r of lane l is C[row0 + mb*32 + 8*(r/4) + 4*(l/32) + r%4][col0 + nb*32 + l%32]
-// AT: the A operand is read from a source stored along this contraction's k axis (TileLoaderKMajor);
-// g.kb_a_src is then the number of k-slices of that source.
-template <class Epilogue, int NW, bool AT = false>
+// kA: how the A operand is stored.  k-major: along this contraction's k axis (g.kb_a_src is then the number of
+// k-slices of that source); rows: a row-major matrix of g.src_rows x g.src_cols, read as it is.
+enum class ASource { kBlocked, kKMajorBlocked, kRows, kKMajorRows };
+template <class Epilogue, int NW, ASource kA = ASource::kBlocked>
 __global__ void __launch_bounds__(NW * 64, 1)
 gemm_nt_kernel(GemmArgs g, Epilogue epi) {
+  constexpr bool AT = kA == ASource::kKMajorBlocked || kA == ASource::kKMajorRows;
   constexpr int NB = 16 / NW;                                  // 32-column blocks per wavefront
   constexpr int kLoadsPerWave = 2 * (kTileBytes / 1024) / NW;  // direct-to-LDS loads per wavefront per slice
   // one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
@@ -406,11 +473,15 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   typename Epilogue::template Pre<NB> pre;
   epi.template prefetch<NB>(pre_stash, NW * 64, n0 + b_row0, lane, wave);
 
-  typename std::conditional<AT, TileLoaderKMajor<NW>, TileLoader<NW>>::type la;
+  using Blocked = typename std::conditional<AT, TileLoaderKMajor<NW>, TileLoader<NW>>::type;
+  using Rows = typename std::conditional<AT, TileLoaderKMajorRows<NW>, TileLoaderRows<NW>>::type;
+  constexpr bool kDirect = kA == ASource::kRows || kA == ASource::kKMajorRows;
+  typename std::conditional<kDirect, Rows, Blocked>::type la;
   TileLoader<NW> lb;
   const int kt_all = g.K / kBK;
-  la.init(g.A, tm, AT ? g.kb_a_src : kt_all, wave, lane);
-  lb.init(g.B, tn, kt_all, wave, lane);
+  if constexpr (kDirect) la.init(g.A, tm, g.src_rows, g.src_cols, wave, lane);
+  else la.init(g.A, tm, AT ? g.kb_a_src : kt_all, wave, lane);
+  lb.init(g.B, tn, g.kb_b, wave, lane);
   int kt_n = kt_all;                                           // k-slices this workgroup contracts over
   if (range >= 0) {
     const int kt0 = range * g.kt_per_split;                    // a multiple of 8 (TileLoaderKMajor::start_at)
@@ -748,6 +819,63 @@ struct DHiddenEpilogue {
   }
 };
 
+// dH^T tile of the contraction that reads W as it is: rows = hidden units (A = W^T, k-major), columns = tokens (B = E).
+// A lane holds four consecutive hidden units of its token: 8-byte LDS writes, then the same 16-byte stores of whole rows.
+struct DHiddenTEpilogue {
+  int n_valid, H;
+  uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
+  const float* beta;               // [n_valid]
+  float* partial;                  // tiles whose contraction is cut into ranges: [slab][256 tokens][256 hidden] fp32 raw sums
+
+  template <int NB> struct Pre {};
+  template <int NB> static constexpr int stash_words() { return 0; }
+  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
+  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
+  template <int NB>
+  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][NB], const Pre<NB>&, int h0, int k0, int lane, int wave,
+                                             char* lds, int slab_id) const {
+    const int l32 = lane & 31, lhi = lane >> 5;
+    if (slab_id >= 0) {
+      float* slab = partial + (int64_t)slab_id * (kBM * kBN);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int k = k0 + nb * 32 + l32;
+        if (k >= n_valid) continue;
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4)
+            *(float4*)(slab + (k & (kBN - 1)) * kBM + (h0 & (kBM - 1)) + mb * 32 + 8 * r4 + 4 * lhi) =
+                make_float4(acc[mb][nb][4 * r4], acc[mb][nb][4 * r4 + 1], acc[mb][nb][4 * r4 + 2], acc[mb][nb][4 * r4 + 3]);
+      }
+      return;
+    }
+    constexpr int kStageRow = 128 * 2 + 16;                    // 128 hidden units of a token, and 16 bytes of padding
+    char* stage = lds + wave * (32 * kStageRow);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int kk = k0 + nb * 32 + l32;
+      const float b = kk < n_valid ? beta[kk] : 0.f;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          uint2 w;
+          w.x = pack_bf16x2(b * acc[mb][nb][4 * r4], b * acc[mb][nb][4 * r4 + 1]);
+          w.y = pack_bf16x2(b * acc[mb][nb][4 * r4 + 2], b * acc[mb][nb][4 * r4 + 3]);
+          *(uint2*)(stage + l32 * kStageRow + (mb * 32 + 8 * r4 + 4 * lhi) * 2) = w;
+        }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {                            // four token rows of 256 bytes per instruction
+        const int row = i * 4 + (lane >> 4), ch = lane & 15;
+        const uint4 val = *(const uint4*)(stage + row * kStageRow + ch * 16);
+        const int k = k0 + nb * 32 + row, h = h0 + ch * 8;
+        if (k < n_valid && h < H) *(uint4*)(dH + (int64_t)k * H + h) = val;
+      }
+    }
+  }
+};
+
 // dW tile: rows = vocabulary (A = E^T), columns = hidden units (B = (diag(beta) H_chunk)^T).
 struct DWeightEpilogue {
   int V, H, accumulate;
@@ -812,12 +940,13 @@ struct DWeightEpilogue {
 // dH tiles of a launch whose last tail_tiles tiles (in launch order) were cut into k_splits ranges of the vocabulary:
 // dH[k][h] = beta_k * (slab 0 + slab 1 + ...) of the tile, in range order.  One block per 1024 elements of a tile.
 __global__ void __launch_bounds__(256)
-dh_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, const float* __restrict__ beta, int n_valid, int H,
-                      uint16_t* __restrict__ dH) {
+dh_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, bool transposed, const float* __restrict__ beta,
+                      int n_valid, int H, uint16_t* __restrict__ dH) {
   const int pos = blockIdx.y;
-  int tm, tn;
-  tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tm, tn);
-  const int e = (blockIdx.x * 256 + threadIdx.x) * 4;                  // four columns of a row
+  int tm, tn;                                                          // tile of tokens, of hidden units
+  if (transposed) tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tn, tm);
+  else tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tm, tn);
+  const int e = (blockIdx.x * 256 + threadIdx.x) * 4;                  // four hidden units of a token
   const int k = tm * kBM + e / kBN, h = tn * kBN + e % kBN;
   if (k >= n_valid || h >= H) return;                                  // H is a multiple of 64
   const float* slab = partial + (int64_t)pos * g.k_splits * (kBM * kBN) + e;
@@ -1118,10 +1247,26 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
   return c;
 }
 
-template <int NW, class Epi>
-static nat_status launch_gemm(const GemmArgs& g, const Epi& epi, int prof_class, hipStream_t s) {
-  ProfScope prof(prof_class, s);
-  gemm_nt_kernel<Epi, NW, false><<<g.tiles_m * g.tiles_n, NW * 64, 0, s>>>(g, epi);
+// Up to how many tokens a call reads W as it is instead of repacking it first.  The repack moves W three times with the
+// backward pass (0.77 ms at V x H = 151936 x 4096, 0.21 ms at H = 1024), twice without (0.50 / 0.12 ms), whatever the
+// batch; reading 64 bytes of 16 rows per instruction instead of 1 KiB in one piece costs the logits and dH
+// contractions 3 to 8 % of their time, and dH the transposing reads.  Measured, repacked against direct, whole call:
+// 59 tokens 1.92 / 1.19 ms (H = 4096), 0.61 / 0.42 (H = 1024); 1237: 4.77 / 4.12; 4096: 12.08 / 11.71; 6144: 19.6 / 18.9
+// (H = 4096), 24.2 / 24.1 (H = 5120), 5.45 / 5.43 (H = 1024); 7000 at H = 3584: 19.9 / 20.0.  Forward pass alone: 301
+// tokens 0.29 / 0.19 ms (H = 1024), 4096: 4.59 / 4.24, 8192: 8.57 / 8.35, 12289: 12.74 / 12.60 in one call and equal in
+// the next (H = 4096), 16384: 4.70 / 4.72 (H = 1024).
+constexpr int kDirectTokens = 6144, kDirectTokensForward = 10240;
+
+// logits contraction: rows = vocabulary, columns = tokens (tiles_n tiles), contraction over the hidden size; W either
+// repacked (Wb) or read as it is (Wb NULL)
+template <class Epi>
+static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uint16_t* Hb, int V, int H, int Vp, int tiles_n,
+                                const Epi& epi, hipStream_t s) {
+  ProfScope prof(PC_LOGITS, s);
+  GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H};
+  const int grid = g.tiles_m * g.tiles_n;
+  if (Wb) gemm_nt_kernel<Epi, NAT_WAVES_LOGITS><<<grid, NAT_WAVES_LOGITS * 64, 0, s>>>(g, epi);
+  else gemm_nt_kernel<Epi, NAT_WAVES_LOGITS, ASource::kRows><<<grid, NAT_WAVES_LOGITS * 64, 0, s>>>(g, epi);
   NAT_LAUNCH_CHECK();
   return NAT_OK;
 }
@@ -1151,7 +1296,8 @@ nat_status loss_bf16_run(const LossArgs& a) {
   const int H = a.H, V = a.V;
   const int Vp = (int)p.Vp, Hp = (int)p.Hp;
 
-  {  // W and W^T in the blocked layout, padding zero-filled
+  const bool direct = a.N_k <= kDirectTokens;
+  if (!direct) {  // W and W^T in the blocked layout, padding zero-filled
     ProfScope prof(PC_TRANSPOSE, s);
     pack_blocked_kernel<<<dim3(Vp / 64, Hp / 64), 256, 0, s>>>(W, H, V, H, Vp, Hp, Wb, Wtb, Vp / 32, nullptr);
     NAT_LAUNCH_CHECK();
@@ -1178,14 +1324,14 @@ nat_status loss_bf16_run(const LossArgs& a) {
       uint16_t* Eb_s = Eb + (int64_t)(s0 / 256) * (Vp / 32) * kBlkElems;    // token tile s0 / 256
       const int32_t* ids_s = a.ids + c0 + s0;
       {  // logits: rows = vocabulary, columns = tokens, contraction over the hidden size
-        GemmArgs g{Wb, Hb + (int64_t)(s0 / 256) * (H / 32) * kBlkElems, H, Vp / kBM, snp / kBN, NAT_GROUP_LOGITS};
+        const uint16_t* Hb_s = Hb + (int64_t)(s0 / 256) * (H / 32) * kBlkElems;
         nat_status st;
         if (t_part) {
           LogitsEpilogue<true> e{V, snv, cap, Vp / 32, Eb_s, s_part + s0, t_part + s0, zt + s0, ids_s, ref + s0};
-          st = launch_gemm<NAT_WAVES_LOGITS>(g, e, PC_LOGITS, s);
+          st = launch_logits(W, direct ? nullptr : Wb, Hb_s, V, H, Vp, snp / kBN, e, s);
         } else {
           LogitsEpilogue<false> e{V, snv, cap, Vp / 32, Eb_s, s_part + s0, nullptr, zt + s0, ids_s, ref + s0};
-          st = launch_gemm<NAT_WAVES_LOGITS>(g, e, PC_LOGITS, s);
+          st = launch_logits(W, direct ? nullptr : Wb, Hb_s, V, H, Vp, snp / kBN, e, s);
         }
         if (st != NAT_OK) return st;
       }
@@ -1209,16 +1355,23 @@ nat_status loss_bf16_run(const LossArgs& a) {
         const int tiles = (snp / kBM) * (Hp / kBN);
         const RangeCut cut = range_cut(tiles, Vp / kBK, 1);
         uint16_t* dH_s = (uint16_t*)a.dH + (int64_t)(c0 + s0) * H;
-        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, cut.splits, cut.kt_per, cut.tail};
-        DHiddenEpilogue e{snv, H, dH_s, beta + s0, dh_part};
-        {
-          ProfScope prof(PC_DHIDDEN, s);
-          gemm_nt_kernel<DHiddenEpilogue, NAT_WAVES_DHIDDEN, false><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+        ProfScope prof(PC_DHIDDEN, s);
+        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, Vp / kBK, cut.splits, cut.kt_per, cut.tail, V, H};
+        if (direct) {            // dH^T = W^T E^T from W as it is
+          g.A = W;
+          g.B = Eb_s;
+          g.tiles_m = Hp / kBM;
+          g.tiles_n = snp / kBN;
+          DHiddenTEpilogue e{snv, H, dH_s, beta + s0, dh_part};
+          gemm_nt_kernel<DHiddenTEpilogue, NAT_WAVES_DHIDDEN, ASource::kKMajorRows><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+        } else {
+          DHiddenEpilogue e{snv, H, dH_s, beta + s0, dh_part};
+          gemm_nt_kernel<DHiddenEpilogue, NAT_WAVES_DHIDDEN><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+        }
+        NAT_LAUNCH_CHECK();
+        if (cut.splits > 1) {
+          dh_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, direct, beta + s0, snv, H, dH_s);
           NAT_LAUNCH_CHECK();
-          if (cut.splits > 1) {
-            dh_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, beta + s0, snv, H, dH_s);
-            NAT_LAUNCH_CHECK();
-          }
         }
       }
     }
@@ -1226,13 +1379,14 @@ nat_status loss_bf16_run(const LossArgs& a) {
       // A = E from its one copy (rows = token), i.e. stored along this contraction's k axis
       // The leftover tiles of the last round are cut into ranges of tokens (multiples of the 8 k-slices that the
       // k-major loader starts at): see range_cut.
-      const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), np / kBK, 8);
+      const int kt = (nv + kBK - 1) / kBK;                       // only the slices that hold tokens
+      const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), kt, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
-      GemmArgs g{Eb, Hktb, np, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, cut.splits, cut.kt_per, cut.tail};
+      GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail};
       DWeightEpilogue e{V, H, accumulate, a.dW, dh_part};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, true><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
+        gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
           dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);
@@ -1263,7 +1417,8 @@ nat_status logp_bf16_run(const LogpArgs& a) {
   const uint16_t* W = (const uint16_t*)a.W;
   const uint16_t* hidden = (const uint16_t*)a.hidden;
   const int H = a.H, V = a.V, Vp = (int)p.Vp;
-  {
+  const bool direct = a.N_k <= kDirectTokensForward;
+  if (!direct) {
     ProfScope prof(PC_TRANSPOSE, s);
     pack_blocked_kernel<<<dim3(Vp / 64, H / 64), 256, 0, s>>>(W, H, V, H, Vp, H, Wb, nullptr, 0, nullptr);
     NAT_LAUNCH_CHECK();
@@ -1280,14 +1435,13 @@ nat_status logp_bf16_run(const LogpArgs& a) {
       NAT_LAUNCH_CHECK();
     }
     {
-      GemmArgs g{Wb, Hb, H, Vp / kBM, np / kBN, NAT_GROUP_LOGITS};
       nat_status st;
       if (t_part) {
         LogitsEpilogue<true, false> e{V, nv, cap, 0, nullptr, s_part, t_part, zt, a.ids + c0, ref};
-        st = launch_gemm<NAT_WAVES_LOGITS>(g, e, PC_LOGITS, s);
+        st = launch_logits(W, direct ? nullptr : Wb, Hb, V, H, Vp, np / kBN, e, s);
       } else {
         LogitsEpilogue<false, false> e{V, nv, cap, 0, nullptr, s_part, nullptr, zt, a.ids + c0, ref};
-        st = launch_gemm<NAT_WAVES_LOGITS>(g, e, PC_LOGITS, s);
+        st = launch_logits(W, direct ? nullptr : Wb, Hb, V, H, Vp, np / kBN, e, s);
       }
       if (st != NAT_OK) return st;
     }

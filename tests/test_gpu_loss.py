@@ -213,6 +213,21 @@ def test_bf16_hidden_size_not_a_multiple_of_the_tile(stage):
     check(out, ref, 300, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("H,V", [(64, 7), (320, 700), (192, 1025)])
+def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V):
+    # up to 6144 tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
+    # order, so the log-probs of the common tokens are equal bit for bit, and each side meets the path's tolerance
+    n = 6144
+    case = make_loss_case(77, n + 1, H, V, "bf16", noise=0.15, w_std=0.1)
+    short = {k: (v[:n] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
+    packed, direct = hip_loss(stage, case, "bf16"), hip_loss(stage, short, "bf16")
+    assert torch.equal(packed["logp"][:n], direct["logp"][:n])
+    check(direct, oracle_loss(**short), n, TOL_BF16, short)
+    check(packed, oracle_loss(**case), n + 1, TOL_BF16, case)
+    fwd = stage.logp(to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"]), n + 1)
+    assert torch.equal(fwd["logp"][:n + 1], packed["logp"][:n + 1])
+
+
 @pytest.mark.parametrize("n_tok,H,V,label", [
     (4700, 3584, 2100, "dH: a full round of tiles and ten more in two vocabulary ranges"),
     (100, 128, 40000, "dH: one tile in 39 vocabulary ranges"),
