@@ -17,10 +17,12 @@ namespace nat {
 
 constexpr int kTileTokens = 4096;                 // tokens per scatter block
 constexpr int kTileWords = kTileTokens / 32;      // 128 mask words
-constexpr int kScatterThreads = 256;              // 4 wavefronts x 1024 tokens
 // Up to this many tiles (4.2 million tokens) a scatter block adds up the counts of the tiles before
-// its own instead of a scan launch between the two passes (4 loads per thread at most).
-constexpr int kInlineScanTiles = 1024;
+// its own instead of a scan launch between the two passes; up to kInlineCountTiles (half a million
+// tokens, 64 KiB of mask) it counts the mask words themselves and there is no count launch either.
+// Up to kInlineScanTiles the block also has sixteen wavefronts of 256 tokens, not four of 1024: with fewer
+// blocks than the chip holds, the chain of loads of one wavefront is the kernel's time.
+constexpr int kInlineScanTiles = 1024, kInlineCountTiles = 128;
 
 __device__ __forceinline__ int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -79,22 +81,6 @@ compact_scan_kernel(const int32_t* __restrict__ tile_count, int n_tiles, int32_t
   }
 }
 
-// Number of entries of the non-decreasing cu[lo .. hi) that are < n; the whole wavefront works on one n:
-// 64 probes at once, so 4096 rollouts take two dependent loads instead of twelve.
-__device__ __forceinline__ int wave_lower_bound(const int64_t* __restrict__ cu, int lo, int hi, int64_t n) {
-  const int lane = threadIdx.x & 63;
-  while (hi > lo) {
-    const int step = (hi - lo + 63) >> 6;
-    const int probe = lo + lane * step;
-    const int below = __popcll(__ballot(probe < hi && cu[probe < hi ? probe : lo] < n));
-    if (step == 1) return lo + below;
-    if (below == 0) return lo;
-    hi = lo + below * step < hi ? lo + below * step : hi;       // the first probe that is not below, or the end
-    lo += (below - 1) * step + 1;                               // the last probe that is below lies before lo
-  }
-  return lo;
-}
-
 // Horvitz-Thompson weight of kept token t (1-based) of a rollout of length T.
 __device__ __forceinline__ float ht_weight(int scheme, int64_t T, int64_t t, double n_rollouts, double p, int64_t C) {
   double w;
@@ -116,23 +102,26 @@ struct ScatterArgs {
   double n_rollouts; const double* pi;
   const uint32_t* mask_bits; int64_t n_words; int64_t n_tokens; int64_t kept_cap;
   const int64_t* cu; int B;
-  const int32_t* tile_count; const int32_t* tile_offset;        // offsets, or NULL: the block adds up the counts
+  const int32_t* tile_count; const int32_t* tile_offset;        // offsets; or NULL: the block adds up the counts; or both NULL:
+                                                                // it counts the mask words
   int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept;
   const int32_t* ids; int32_t* ids_k; const float* old_logp; float* old_logp_k;
 };
 
-// One block per tile of 4096 positions, 1024 per wavefront, 64 at a time, four such groups in flight:
+// One block per tile of 4096 positions, kWaves wavefronts, 64 positions at a time, four such groups in flight:
 // the loads of a batch (ids, log-probs, probabilities) are issued before its first weight is computed.
-// Bound by the bytes it moves and, for weights that differ from token to token, by their fp64 divisions.
-// The per-token words ride along here because the token is already in hand: a row-gather block per kept
-// token for them took 8.66 ms of a 2^26-token batch (compaction as a whole 9.06 -> 0.38 ms), 190 us of a
-// 1.3-million-token one (whole selection 222 -> 28 us).
-__global__ void __launch_bounds__(kScatterThreads)
+// Bound by the bytes it moves and, for weights that differ from token to token, by their fp64 divisions; by latency
+// at the size of a real batch.  The per-token words ride along here because the token is already in hand: a
+// row-gather block per kept token for them took 8.66 ms of a 2^26-token batch (compaction as a whole 9.06 ->
+// 0.39 ms), 190 us of a 1.3-million-token one (whole selection 225 -> 25 us; scatter 17 us with four wavefronts per
+// block, 14.5 with sixteen).
+template <int kWaves>
+__global__ void __launch_bounds__(kWaves * 64)
 compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
-  constexpr int kBatch = 4;
-  __shared__ uint32_t words[kTileWords + 2];
+  constexpr int kBatch = 4, kThreads = kWaves * 64, kGroups = 64 / kWaves;      // groups of 64 positions per wavefront
+  __shared__ uint32_t words[kTileWords];
   __shared__ int prefix[kTileWords + 1];                        // kept tokens of the tile before word w
-  __shared__ int wave_tot[4], wave_before[4], roll_range[2];
+  __shared__ int wave_tot[2], wave_before[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tile = blockIdx.x, n_tiles = gridDim.x;
   const int64_t tile_first = (int64_t)tile * kTileTokens;
@@ -143,52 +132,56 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
     word = wi < c.n_words ? c.mask_bits[wi] : 0u;
     words[tid] = word;
   }
-  const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
-  if (lane == 63) wave_tot[wave] = incl;
   int before = 0;
-  if (!c.tile_offset)
-    for (int j = tid; j < tile; j += kScatterThreads) before += c.tile_count[j];
+  if (!c.tile_offset) {
+    if (c.tile_count) for (int j = tid; j < tile; j += kThreads) before += c.tile_count[j];
+    else for (int j = tid; j < tile * kTileWords; j += kThreads) before += __popc(c.mask_bits[j]);
+  }
+  // rollouts of this wavefront's positions: how many start before the span, at or before its first position, before its end
+  const int64_t N = c.cu[c.B], span_first = tile_first + wave * (kGroups * 64), span_end = span_first + kGroups * 64;
+  const int64_t span_last = span_end - 1 < N ? span_end - 1 : N - 1;
+  const int64_t key[4] = {span_first, span_end, span_first + 1, span_last + 1};
+  int at[4];
+  wave_lower_bounds<4>(c.cu, c.B + 1, key, at);
+  const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
+  if (tid < kTileWords && lane == 63) wave_tot[wave] = incl;
   before = wave_sum(before);
   if (lane == 0) wave_before[wave] = before;
-  // rollouts whose first position lies in this tile (offsets outside [0, n_tokens] count as its ends)
-  if (wave < 2) {
-    const int r = wave == 0 ? (tile == 0 ? 0 : wave_lower_bound(c.cu, 0, c.B + 1, tile_first))
-                            : (tile == n_tiles - 1 ? c.B + 1 : wave_lower_bound(c.cu, 0, c.B + 1, tile_first + kTileTokens));
-    if (lane == 0) roll_range[wave] = r;
-  }
   __syncthreads();
   if (tid < kTileWords) {
     const int excl = incl - cnt + (wave == 1 ? wave_tot[0] : 0);
     prefix[tid] = excl;
     if (tid == kTileWords - 1) prefix[kTileWords] = excl + cnt;
   }
-  const int tile_base = c.tile_offset ? c.tile_offset[tile]
-                                      : wave_before[0] + wave_before[1] + wave_before[2] + wave_before[3];
+  int tile_base = 0;
+  if (c.tile_offset) tile_base = c.tile_offset[tile];
+  else
+    for (int w = 0; w < kWaves; ++w) tile_base += wave_before[w];
   __syncthreads();
   if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + prefix[kTileWords];
-  for (int i = roll_range[0] + tid; i < roll_range[1]; i += kScatterThreads) {
+  // offsets of the rollouts that start in this span (offsets outside [0, n_tokens] count as its ends)
+  const int r0 = span_first == 0 ? 0 : at[0];
+  const int r1 = tile == n_tiles - 1 && wave == kWaves - 1 ? c.B + 1 : at[1];
+  for (int i = r0 + lane; i < r1; i += 64) {
     const int64_t pos = c.cu[i] < 0 ? 0 : c.cu[i] > c.n_tokens ? c.n_tokens : c.cu[i];
     const int64_t off = pos - tile_first;
     const int rel = off < 0 ? 0 : off > kTileTokens ? kTileTokens : (int)off, w = rel >> 5, rem = rel & 31;
     c.cu_kept[i] = tile_base + prefix[w] + (rem ? __popc(words[w] & ((1u << rem) - 1u)) : 0);
   }
 
-  // this wavefront's 1024 positions; rollout of its first one (the last rollout that starts at or before it)
-  const int64_t N = c.cu[c.B], span_first = tile_first + wave * 1024;
-  if (prefix[wave * 32] == prefix[wave * 32 + 32]) return;      // nothing kept
+  constexpr int kSpanWords = kGroups * 2;
+  if (prefix[wave * kSpanWords] == prefix[(wave + 1) * kSpanWords]) return;      // nothing kept
   int i_lo = 0, i_hi = c.B;                                     // positions at or beyond N: any rollout (foreign mask)
-  if (span_first < N) {
-    const int64_t span_last = span_first + 1023 < N ? span_first + 1023 : N - 1;
-    i_lo = wave_lower_bound(c.cu, 0, c.B, span_first + 1) - 1;
-    i_lo = __builtin_amdgcn_readfirstlane(i_lo < 0 ? 0 : i_lo);
-    i_hi = __builtin_amdgcn_readfirstlane(wave_lower_bound(c.cu, i_lo, c.B, span_last + 1));
+  if (span_first < N) {                                         // the last rollout that starts at or before the first position
+    i_lo = at[2] > 0 ? at[2] - 1 : 0;
+    i_hi = at[3] < c.B ? at[3] : c.B;
     i_hi = i_hi <= i_lo ? i_lo + 1 : i_hi;
   }
   const bool one_rollout = i_hi - i_lo == 1;
   const int64_t one_start = c.cu[i_lo], one_T = c.cu[i_lo + 1] - one_start;
   const int one_scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
 
-  for (int g0 = 0; g0 < 16; g0 += kBatch) {
+  for (int g0 = 0; g0 < kGroups; g0 += kBatch) {
     bool keep[kBatch];
     int out[kBatch], id[kBatch], seq[kBatch];
     float lp[kBatch];
@@ -196,7 +189,7 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
     int64_t n[kBatch];
 #pragma unroll
     for (int b = 0; b < kBatch; ++b) {
-      const int w = wave * 32 + 2 * (g0 + b);
+      const int w = wave * kSpanWords + 2 * (g0 + b);
       const uint64_t group = (uint64_t)words[w] | ((uint64_t)words[w + 1] << 32);
       n[b] = span_first + (g0 + b) * 64 + lane;
       out[b] = tile_base + prefix[w] + __popcll(group & ((1ull << lane) - 1ull));
@@ -321,17 +314,20 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
   {
     ProfScope prof(PC_COMPACT, s, !c.no_timing);
     if (n_tiles > 0) {
-      compact_count_kernel<<<(unsigned)((n_tiles + 3) / 4), 256, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count);
-      NAT_LAUNCH_CHECK();
-      const bool scan = n_tiles > kInlineScanTiles;
+      const bool count = n_tiles > kInlineCountTiles, scan = n_tiles > kInlineScanTiles;
+      if (count) {
+        compact_count_kernel<<<(unsigned)((n_tiles + 3) / 4), 256, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count);
+        NAT_LAUNCH_CHECK();
+      }
       if (scan) {
         compact_scan_kernel<<<1, 1024, 0, s>>>(tile_count, (int)n_tiles, tile_offset);
         NAT_LAUNCH_CHECK();
       }
-      compact_scatter_kernel<<<(unsigned)n_tiles, kScatterThreads, 0, s>>>(
-          a, ScatterArgs{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B, tile_count,
-                         scan ? tile_offset : nullptr, c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept,
-                         c.ids, c.ids_k, c.old_logp, c.old_logp_k});
+      const ScatterArgs sc{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B,
+                           count ? tile_count : nullptr, scan ? tile_offset : nullptr, c.kept_idx, c.kept_seq, c.kept_w,
+                           c.cu_kept, c.n_kept, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
+      if (scan) compact_scatter_kernel<4><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
+      else compact_scatter_kernel<16><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
       NAT_LAUNCH_CHECK();
     } else {
       compact_empty_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.B, c.cu_kept, c.n_kept);

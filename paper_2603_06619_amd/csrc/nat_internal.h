@@ -45,9 +45,43 @@ __device__ __forceinline__ int rollout_of_pos(const OffsetT* __restrict__ cu, in
   return lo;
 }
 
+// out[q] = number of entries of the non-decreasing cu[0 .. n_cu) that are < n[q], wavefront-uniform.  The whole
+// wavefront searches, 64 probes per round and K values at once: 4096 rollouts take two dependent loads, not twelve.
+template <int K>
+__device__ __forceinline__ void wave_lower_bounds(const int64_t* __restrict__ cu, int n_cu, const int64_t (&n)[K], int (&out)[K]) {
+  const int lane = threadIdx.x & 63;
+  int lo[K], hi[K];
+#pragma unroll
+  for (int q = 0; q < K; ++q) { lo[q] = 0; hi[q] = n_cu; }
+  for (bool open = n_cu > 0; open;) {
+    int64_t v[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int step = (hi[q] - lo[q] + 63) >> 6, probe = lo[q] + lane * step;
+      v[q] = probe < hi[q] ? cu[probe] : INT64_MAX;
+    }
+    open = false;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int step = (hi[q] - lo[q] + 63) >> 6;
+      const int below = __popcll(__ballot(v[q] < n[q]));        // the probes that are below come first
+      if (below == 0) { hi[q] = lo[q]; continue; }
+      const int past = lo[q] + below * step;                    // the first probe that is not below
+      lo[q] += (below - 1) * step + 1;
+      hi[q] = step == 1 ? lo[q] : past < hi[q] ? past : hi[q];
+      open |= hi[q] > lo[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < K; ++q) out[q] = __builtin_amdgcn_readfirstlane(lo[q]);
+}
+
 // mask bit n = (position of n inside its rollout) < cut_len[rollout]   (select.hip)
 nat_status launch_prefix_mask(const int64_t* d_cu, int32_t B, int64_t N, const int32_t* d_cut_len,
                               uint32_t* d_mask_bits, hipStream_t s);
+// mask bit n = Bernoulli(pi[n]) with the word of NAT_SCHEME_URS   (select.hip; of `a` the key, step, ids and drop flag)
+nat_status launch_poisson_mask(const SelectArgs& a, const double* d_pi, const int64_t* d_cu, int32_t B, int64_t N,
+                               uint32_t* d_mask_bits, hipStream_t s);
 
 // nat_compact / nat_compact_pi share one implementation (compact.hip): weights come from
 // the scheme's closed form when d_pi is NULL, else from the given probabilities.

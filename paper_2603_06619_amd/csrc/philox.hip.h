@@ -14,9 +14,8 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 ctr, uint32_t k0, uint32_t 
   constexpr uint32_t kWeylA = 0x9E3779B9u, kWeylB = 0xBB67AE85u;
 #pragma unroll
   for (int round = 0; round < 10; ++round) {
-    const uint32_t hiA = __umulhi(kMulA, ctr.x), loA = kMulA * ctr.x;
-    const uint32_t hiB = __umulhi(kMulB, ctr.z), loB = kMulB * ctr.z;
-    ctr = u32x4{hiB ^ ctr.y ^ k0, loB, hiA ^ ctr.w ^ k1, loA};
+    const uint64_t a = (uint64_t)kMulA * ctr.x, b = (uint64_t)kMulB * ctr.z;   // one wide multiply each
+    ctr = u32x4{(uint32_t)(b >> 32) ^ ctr.y ^ k0, (uint32_t)b, (uint32_t)(a >> 32) ^ ctr.w ^ k1, (uint32_t)a};
     k0 += kWeylA;
     k1 += kWeylB;
   }

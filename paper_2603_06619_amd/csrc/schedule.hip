@@ -8,12 +8,16 @@
 #include "nat_internal.h"
 #include "philox.hip.h"
 
+#include <type_traits>
+
 namespace nat {
 
-constexpr int kSchedThreads = 256;
+constexpr int64_t kLongRollout = 1024;            // mean length from which schedule_cut_kernel uses 1024 threads
 
-// Inclusive scan of one 64-bit value per thread over a 256-thread block; *total = block sum.
-// `wave_tot` is 4 words of LDS; the caller separates successive calls with a barrier.
+
+// Inclusive scan of one 64-bit value per thread over the block; *total = block sum.
+// `wave_tot` is a word of LDS per wavefront; the caller separates successive calls with a barrier.
+template <int kThreads>
 __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_tot, uint64_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint64_t incl = v;
@@ -24,7 +28,7 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
   if (lane == 63) wave_tot[wave] = incl;
   __syncthreads();
   uint64_t before = 0, all = 0;
-  for (int w = 0; w < kSchedThreads / 64; ++w) {
+  for (int w = 0; w < kThreads / 64; ++w) {
     const uint64_t t = wave_tot[w];
     if (w < wave) before += t;
     all += t;
@@ -34,13 +38,15 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
 }
 
 // One block per rollout: total weight, the cut by inversion of the running sum, and the
-// survival function for every position.
-__global__ void __launch_bounds__(kSchedThreads)
+// survival function for every position.  Bound by the chain of block scans over the longest rollout: 1024 threads
+// (4096 positions per scan) where rollouts are long, 256 where many short ones have to share the compute units.
+template <int kThreads>
+__global__ void __launch_bounds__(kThreads)
 schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout_id_base,
                     const float* __restrict__ drop_zero_adv,
                     const uint32_t* __restrict__ weights, const int64_t* __restrict__ cu, int64_t N,
                     int32_t* __restrict__ cut_len, double* __restrict__ pi) {
-  __shared__ uint64_t wave_tot[kSchedThreads / 64];
+  __shared__ uint64_t wave_tot[kThreads / 64];
   const int i = blockIdx.x;
   // offsets are clamped to the N positions the caller's arrays hold
   const int64_t start = cu[i] < 0 ? 0 : cu[i] > N ? N : cu[i];
@@ -54,12 +60,12 @@ schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout
   double* p = pi + start;
 
   uint64_t part = 0;
-  for (int64_t j = threadIdx.x; j < T; j += kSchedThreads) part += a[j];
+  for (int64_t j = threadIdx.x; j < T; j += kThreads) part += a[j];
   uint64_t A;
-  block_scan_u64(part, wave_tot, &A);
+  block_scan_u64<kThreads>(part, wave_tot, &A);
   __syncthreads();
   if (A == 0) {                                   // no schedule: keep the rollout whole, p = 1
-    for (int64_t j = threadIdx.x; j < T; j += kSchedThreads) p[j] = 1.0;
+    for (int64_t j = threadIdx.x; j < T; j += kThreads) p[j] = 1.0;
     if (threadIdx.x == 0) cut_len[i] = (drop_zero_adv && drop_zero_adv[i] == 0.f) ? 0 : (int32_t)T;
     return;
   }
@@ -74,7 +80,7 @@ schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout
   const double den = (double)A;
   uint64_t carry = 0;                              // running sum of all earlier positions
   constexpr int kPer = 4;                          // consecutive positions per thread and iteration
-  for (int64_t base = 0; base < T; base += kSchedThreads * kPer) {
+  for (int64_t base = 0; base < T; base += kThreads * kPer) {
     const int64_t j0 = base + (int64_t)threadIdx.x * kPer;
     uint32_t v[kPer];
     uint64_t mine = 0;
@@ -84,7 +90,7 @@ schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout
       mine += v[e];
     }
     uint64_t chunk_total;
-    uint64_t run = carry + block_scan_u64(mine, wave_tot, &chunk_total) - mine;   // sum of positions before j0
+    uint64_t run = carry + block_scan_u64<kThreads>(mine, wave_tot, &chunk_total) - mine;   // sum of positions before j0
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
       if (j0 + e < T) {
@@ -95,60 +101,6 @@ schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout
     }
     carry += chunk_total;
     __syncthreads();
-  }
-}
-
-// Four consecutive packed positions per lane (one Philox block serves four consecutive tokens of a
-// rollout); the 16 lanes of a 64-token group OR their nibbles into the two mask words.
-__global__ void __launch_bounds__(256)
-poisson_mask_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout_id_base,
-                    const float* __restrict__ drop_zero_adv, const double* __restrict__ pi,
-                    const int64_t* __restrict__ cu, int B, int64_t N, uint32_t* __restrict__ mask_bits) {
-  const int64_t n0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  uint32_t nibble = 0;
-  const int64_t n_end = cu[B] < N ? cu[B] : N;     // positions beyond the last rollout are never kept
-  if (n0 < n_end) {
-    int i = rollout_of_pos(cu, 0, B, n0);
-    int64_t start = cu[i], end = cu[i + 1];
-    bool dropped = drop_zero_adv && drop_zero_adv[i] == 0.f;
-    u32x4 r{0u, 0u, 0u, 0u};
-    int64_t have_block = -1;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t n = n0 + j;
-      if (n >= n_end) break;
-      if (n >= end) {
-        do { ++i; } while (i < B - 1 && cu[i + 1] <= n);
-        start = cu[i];
-        end = cu[i + 1];
-        dropped = drop_zero_adv && drop_zero_adv[i] == 0.f;
-        have_block = -1;
-      }
-      const int64_t t0 = n - start;
-      if ((t0 >> 2) != have_block) {
-        have_block = t0 >> 2;
-        r = philox4x32_10(u32x4{(uint32_t)have_block, (uint32_t)(rollout_id_base + i), 0u, step}, key0, key1);
-      }
-      const double p = pi[n];
-      uint64_t thr = 0;                                           // p <= 0 or NaN: never keep
-      if (p >= 1.0) thr = 1ull << 32;
-      else if (p > 0.0) thr = (uint64_t)floor(p * 4294967296.0);
-      const uint32_t word = (t0 & 3) == 0 ? r.x : (t0 & 3) == 1 ? r.y : (t0 & 3) == 2 ? r.z : r.w;
-      if ((uint64_t)word < thr && !dropped) nibble |= 1u << j;
-    }
-  }
-  const int sub = threadIdx.x & 15;
-  uint32_t lo = sub < 8 ? nibble << (4 * sub) : 0u;
-  uint32_t hi = sub >= 8 ? nibble << (4 * (sub - 8)) : 0u;
-#pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    lo |= __shfl_xor(lo, off);
-    hi |= __shfl_xor(hi, off);
-  }
-  if (sub == 0 && n0 < N) {
-    const int64_t group = n0 >> 6;
-    mask_bits[2 * group] = lo;
-    mask_bits[2 * group + 1] = hi;
   }
 }
 
@@ -243,9 +195,14 @@ extern "C" nat_status nat_select_schedule(const nat_select_params* params, const
   if (!d_cut_len || (N > 0 && (!d_mask_bits || !d_pi))) return NAT_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   ProfScope prof(PC_SCHEDULE, s);
-  schedule_cut_kernel<<<(unsigned)B, kSchedThreads, 0, s>>>(
-      (uint32_t)(params->seed & 0xFFFFFFFFull), (uint32_t)(params->seed >> 32), params->step,
-      params->rollout_id_base, params->d_drop_zero_adv, d_weights, d_cu_seqlens, N, d_cut_len, d_pi);
+  auto go = [&](auto threads) {
+    constexpr int kThreads = decltype(threads)::value;
+    schedule_cut_kernel<kThreads><<<(unsigned)B, kThreads, 0, s>>>(
+        (uint32_t)(params->seed & 0xFFFFFFFFull), (uint32_t)(params->seed >> 32), params->step,
+        params->rollout_id_base, params->d_drop_zero_adv, d_weights, d_cu_seqlens, N, d_cut_len, d_pi);
+  };
+  if (N / B > kLongRollout) go(std::integral_constant<int, 1024>{});
+  else go(std::integral_constant<int, 256>{});
   NAT_LAUNCH_CHECK();
   return launch_prefix_mask(d_cu_seqlens, B, N, d_cut_len, d_mask_bits, s);
 }
@@ -259,11 +216,13 @@ extern "C" nat_status nat_select_poisson(const nat_select_params* params, const 
   if (N == 0) return NAT_OK;
   hipStream_t s = (hipStream_t)stream;
   ProfScope prof(PC_SCHEDULE, s);
-  poisson_mask_kernel<<<(unsigned)((N + 1023) / 1024), 256, 0, s>>>(
-      (uint32_t)(params->seed & 0xFFFFFFFFull), (uint32_t)(params->seed >> 32), params->step,
-      params->rollout_id_base, params->d_drop_zero_adv, d_pi, d_cu_seqlens, B, N, d_mask_bits);
-  NAT_LAUNCH_CHECK();
-  return NAT_OK;
+  SelectArgs a{};
+  a.key0 = (uint32_t)(params->seed & 0xFFFFFFFFull);
+  a.key1 = (uint32_t)(params->seed >> 32);
+  a.step = params->step;
+  a.rollout_id_base = params->rollout_id_base;
+  a.drop_zero_adv = params->d_drop_zero_adv;
+  return launch_poisson_mask(a, d_pi, d_cu_seqlens, B, N, d_mask_bits, s);
 }
 
 extern "C" nat_status nat_prefix_pack(const int32_t* d_prompt_len, const int64_t* d_cu_seqlens,

@@ -1,7 +1,7 @@
 // nat_advantage and nat_select: group-relative advantage (Eq. 2) and the token
 // selection mask of Sec. 3.1 (URS) and Sec. 4 (RPC, Eq. 7; deterministic
-// truncation).  Four packed token positions per lane; the 16 lanes of a 64-token
-// group combine their bits into two 32-bit mask words.
+// truncation), and the Poisson mask of schedule.hip's entry point.  Four packed token
+// positions per lane; eight lanes combine their bits into a 32-bit mask word.
 #include "nat_internal.h"
 #include "philox.hip.h"
 
@@ -25,13 +25,8 @@ __global__ void advantage_kernel(const float* __restrict__ rewards, int P, int G
   for (int j = lane; j < G; j += 64) adv[(size_t)prompt * G + j] = (R[j] - mu) / (sigma + eps_adv);
 }
 
-// cut_len[i] = L_i (RPC), K_i (DET), T_i (FULL, URS)
-__global__ void select_cut_kernel(SelectArgs a, const int64_t* __restrict__ cu, int B,
-                                  int32_t* __restrict__ cut_len) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B) return;
-  const int64_t T = cu[i + 1] - cu[i];
-  const int scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
+// L_i (RPC), K_i (DET), T_i (FULL, URS) of rollout i of length T; 0 for a dropped one
+__device__ __forceinline__ int64_t rollout_cut(const SelectArgs& a, int scheme, int i, int64_t T) {
   int64_t cut = T;
   if (T > 0 && scheme == NAT_SCHEME_RPC) {
     int64_t Ci = a.min_cut < 1 ? 1 : a.min_cut;
@@ -43,76 +38,155 @@ __global__ void select_cut_kernel(SelectArgs a, const int64_t* __restrict__ cu, 
     cut = (int64_t)floor(a.trunc_frac * (double)T);
   }
   if (a.drop_zero_adv && a.drop_zero_adv[i] == 0.f) cut = 0;
-  cut_len[i] = (int32_t)cut;
+  return cut;
 }
 
-// Four consecutive packed positions per lane: the four words of one Philox block serve four
-// consecutive tokens of a rollout, so a lane evaluates one block (a second one where its
-// positions straddle a block or rollout boundary) and one rollout search instead of four.
-// A wavefront covers 256 positions = four 64-bit mask groups; the 16 lanes of a group OR
-// their nibbles together and the group's first lane writes the two words.
-constexpr int kSelPerLane = 4;
-constexpr int kSelPerBlock = 256 * kSelPerLane;
+struct MaskArgs {
+  const int64_t* cu; int B; int64_t N;
+  const int32_t* cut_in;         // given cut lengths (a prefix mask whatever the scheme), or NULL: drawn here
+  int32_t* cut_out;              // drawn cut lengths are also written here (blocks behind the mask blocks), or NULL
+  const double* pi;              // Poisson sampling: inclusion probabilities (16-byte aligned when pi_wide)
+  int pi_wide;
+  unsigned mask_blocks;
+  uint32_t* mask_bits;
+};
 
+constexpr int kSelPerWave = 1024;                 // packed positions per wavefront: four strips of 256, four per lane
+constexpr int kSelPerBlock = 4 * kSelPerWave;
+
+// keep iff word < floor(p 2^32); p <= 0 or NaN: never, p >= 1: always
+__device__ __forceinline__ bool poisson_keep(uint32_t word, double p) {
+  return p >= 1.0 || (p > 0.0 && word < (uint32_t)(p * 4294967296.0));
+}
+
+// Selection mask of every scheme.  Bound by the Philox rounds where tokens are drawn one by one (ten rounds of
+// two quarter-rate wide multiplies per block of four tokens), by latency at the sizes of a real batch.  A wavefront
+// finds the rollouts of its 1024 positions with two 64-wide searches.  If it is one rollout, that is uniform: lane
+// l owns Philox block first + 64 j + l of strip j, and since a block's four words serve four consecutive tokens of the
+// ROLLOUT, lanes whose four positions straddle two blocks take the second one's words from the next lane (the last
+// lane: from the first lane of the next strip): 5 evaluations per 4 strips instead of 8.  Else each lane searches.
+// Poisson mask of 2^26 tokens: 289 us with a search and up to two evaluations per lane, 144 us now (reading the
+// probabilities alone is 112 us); URS mask: 0.18 ms per 2^26 tokens before, 0.076 ms now.
+template <bool kPoisson>
 __global__ void __launch_bounds__(256)
-select_mask_kernel(SelectArgs a, const int64_t* __restrict__ cu, int B, int64_t N,
-                   const int32_t* __restrict__ cut_len, uint32_t* __restrict__ mask_bits) {
-  const int64_t n0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kSelPerLane;
-  uint32_t nibble = 0;
+select_mask_kernel(SelectArgs a, MaskArgs m) {
+  if (blockIdx.x >= m.mask_blocks) {               // the cut lengths themselves
+    const int i = (int)(blockIdx.x - m.mask_blocks) * 256 + threadIdx.x;
+    if (i >= m.B) return;
+    const int scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
+    m.cut_out[i] = (int32_t)rollout_cut(a, scheme, i, m.cu[i + 1] - m.cu[i]);
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  const int64_t w0 = ((int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kSelPerWave;
+  if (w0 >= m.N) return;
   // positions at or beyond cu[B] belong to no rollout (the host-passed N may be larger): never kept
-  const int64_t n_end = cu[B] < N ? cu[B] : N;
-  if (n0 < n_end) {
-    int i = rollout_of_pos(cu, 0, B, n0);
-    int64_t start = cu[i], end = cu[i + 1];
-    int scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
-    bool dropped = a.drop_zero_adv && a.drop_zero_adv[i] == 0.f;
-    int64_t cut = cut_len[i];
-    u32x4 r{0u, 0u, 0u, 0u};
-    int64_t have_block = -1;                       // index (t0 >> 2) of the block held in r, for rollout i
+  const int64_t n_end = m.cu[m.B] < m.N ? m.cu[m.B] : m.N;
+  int i_lo = 0, i_hi = 0;                          // rollouts of the span
+  if (w0 < n_end) {
+    const int64_t last = w0 + kSelPerWave - 1 < n_end ? w0 + kSelPerWave - 1 : n_end - 1;
+    const int64_t key[2] = {w0 + 1, last + 1};
+    int at[2];
+    wave_lower_bounds<2>(m.cu, m.B, key, at);
+    i_lo = at[0] > 0 ? at[0] - 1 : 0;
+    i_hi = at[1] > i_lo ? at[1] : i_lo + 1;
+  }
+  uint32_t nibble[4] = {0u, 0u, 0u, 0u};
+  if (i_hi - i_lo == 1 && w0 + kSelPerWave <= n_end) {          // wavefront-uniform: one rollout
+    const int64_t start = m.cu[i_lo], t_first = w0 - start;
+    const int scheme = kPoisson ? NAT_SCHEME_URS : m.cut_in ? NAT_SCHEME_DET : a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
+    const bool dropped = a.drop_zero_adv && a.drop_zero_adv[i_lo] == 0.f;
+    if (dropped) {
+    } else if (scheme == NAT_SCHEME_URS) {
+      const int shift = (int)(t_first & 3);
+      const uint32_t first = (uint32_t)(t_first >> 2) + lane, id = (uint32_t)(a.rollout_id_base + i_lo);
+      u32x4 r = philox4x32_10(u32x4{first, id, 0u, a.step}, a.key0, a.key1), r_next{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int j = 0; j < kSelPerLane; ++j) {
-      const int64_t n = n0 + j;
-      if (n >= n_end) break;
-      if (n >= end) {                              // next non-empty rollout (n < cu[B]: one exists below B)
-        do { ++i; } while (i < B - 1 && cu[i + 1] <= n);
-        start = cu[i];
-        end = cu[i + 1];
-        scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
-        dropped = a.drop_zero_adv && a.drop_zero_adv[i] == 0.f;
-        cut = cut_len[i];
-        have_block = -1;
-      }
-      const int64_t t0 = n - start;
-      bool keep;
-      if (scheme == NAT_SCHEME_URS) {
-        if ((t0 >> 2) != have_block) {
-          have_block = t0 >> 2;
-          r = philox4x32_10(u32x4{(uint32_t)have_block, (uint32_t)(a.rollout_id_base + i), 0u, a.step}, a.key0, a.key1);
+      for (int j = 0; j < 4; ++j) {
+        double p[4];
+        if (kPoisson) {
+          const double* q = m.pi + w0 + 256 * j + 4 * lane;
+          if (m.pi_wide) {
+            const double2 x = *reinterpret_cast<const double2*>(q), y = *reinterpret_cast<const double2*>(q + 2);
+            p[0] = x.x; p[1] = x.y; p[2] = y.x; p[3] = y.y;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = q[e];
+          }
         }
-        const uint32_t word = (t0 & 3) == 0 ? r.x : (t0 & 3) == 1 ? r.y : (t0 & 3) == 2 ? r.z : r.w;
-        keep = (uint64_t)word < a.urs_threshold;
-      } else if (scheme == NAT_SCHEME_FULL) {
-        keep = true;
-      } else {
-        keep = t0 < cut;
+        if (j < 3 || shift) r_next = philox4x32_10(u32x4{first + 64u * (j + 1), id, 0u, a.step}, a.key0, a.key1);
+        uint32_t w[4] = {r.x, r.y, r.z, r.w};
+        if (shift) {                               // words shift.. of this block, then the first ones of the next
+          const uint32_t up[3] = {(uint32_t)__shfl_down((int)r.x, 1), (uint32_t)__shfl_down((int)r.y, 1), (uint32_t)__shfl_down((int)r.z, 1)};
+          const uint32_t f0 = __builtin_amdgcn_readfirstlane(r_next.x), f1 = __builtin_amdgcn_readfirstlane(r_next.y),
+                         f2 = __builtin_amdgcn_readfirstlane(r_next.z);
+          const uint32_t n0 = lane == 63 ? f0 : up[0], n1 = lane == 63 ? f1 : up[1], n2 = lane == 63 ? f2 : up[2];
+          if (shift == 1) { w[0] = r.y; w[1] = r.z; w[2] = r.w; w[3] = n0; }
+          else if (shift == 2) { w[0] = r.z; w[1] = r.w; w[2] = n0; w[3] = n1; }
+          else { w[0] = r.w; w[1] = n0; w[2] = n1; w[3] = n2; }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (kPoisson ? poisson_keep(w[e], p[e]) : (uint64_t)w[e] < a.urs_threshold) nibble[j] |= 1u << e;
+        r = r_next;
       }
-      if (keep && !dropped) nibble |= 1u << j;
+    } else {
+      const int64_t cut = m.cut_in ? (int64_t)m.cut_in[i_lo] : rollout_cut(a, scheme, i_lo, m.cu[i_lo + 1] - start);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t left = cut - (t_first + 256 * j + 4 * lane);    // kept positions from this lane's first one on
+        nibble[j] = left >= 4 ? 15u : left <= 0 ? 0u : (1u << left) - 1u;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t n0 = w0 + 256 * j + 4 * lane;
+      if (n0 >= n_end) continue;
+      int i = rollout_of_pos(m.cu, i_lo, i_hi, n0);
+      int64_t start = 0, end = n0, cut = 0;        // of rollout i, set below
+      int scheme = 0;
+      bool dropped = false;
+      u32x4 r{0u, 0u, 0u, 0u};
+      int64_t have_block = -1;                     // index (t0 >> 2) of the block held in r, for rollout i
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t n = n0 + e;
+        if (n >= n_end) break;
+        if (n >= end) {                            // the first, or the next non-empty rollout (n < cu[B]: one exists below B)
+          if (e > 0) do { ++i; } while (i < m.B - 1 && m.cu[i + 1] <= n);
+          start = m.cu[i];
+          end = m.cu[i + 1];
+          scheme = kPoisson ? NAT_SCHEME_URS : m.cut_in ? NAT_SCHEME_DET : a.scheme_per_rollout ? a.scheme_per_rollout[i] : a.scheme;
+          dropped = a.drop_zero_adv && a.drop_zero_adv[i] == 0.f;
+          cut = scheme == NAT_SCHEME_URS ? 0 : m.cut_in ? (int64_t)m.cut_in[i] : rollout_cut(a, scheme, i, end - start);
+          have_block = -1;
+        }
+        const int64_t t0 = n - start;
+        bool keep;
+        if (scheme == NAT_SCHEME_URS) {
+          if ((t0 >> 2) != have_block) {
+            have_block = t0 >> 2;
+            r = philox4x32_10(u32x4{(uint32_t)have_block, (uint32_t)(a.rollout_id_base + i), 0u, a.step}, a.key0, a.key1);
+          }
+          const uint32_t word = (t0 & 3) == 0 ? r.x : (t0 & 3) == 1 ? r.y : (t0 & 3) == 2 ? r.z : r.w;
+          keep = kPoisson ? poisson_keep(word, m.pi[n]) : (uint64_t)word < a.urs_threshold;
+        } else {
+          keep = t0 < cut;
+        }
+        if (keep && !dropped) nibble[j] |= 1u << e;
+      }
     }
   }
-  // lane l of a 16-lane group holds bits 4*(l%16) .. +3 of the group's 64-bit mask
-  const int sub = threadIdx.x & 15;
-  uint32_t lo = sub < 8 ? nibble << (4 * sub) : 0u;
-  uint32_t hi = sub >= 8 ? nibble << (4 * (sub - 8)) : 0u;
+  // the nibbles of eight lanes make a word; the mask has 2 ceil(N / 64) of them
 #pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    lo |= __shfl_xor(lo, off);
-    hi |= __shfl_xor(hi, off);
-  }
-  // groups past ceil(N/64) have no words in the mask
-  if (sub == 0 && n0 < N) {
-    const int64_t group = n0 >> 6;
-    mask_bits[2 * group] = lo;
-    mask_bits[2 * group + 1] = hi;
+  for (int j = 0; j < 4; ++j) {
+    uint32_t v = nibble[j] << (4 * (lane & 7));
+    v |= __shfl_xor((int)v, 1);
+    v |= __shfl_xor((int)v, 2);
+    v |= __shfl_xor((int)v, 4);
+    const int64_t word = (w0 + 256 * j) / 32 + (lane >> 3);
+    if ((lane & 7) == 0 && (word >> 1) * 64 < m.N) m.mask_bits[word] = v;
   }
 }
 
@@ -136,12 +210,22 @@ nat_status validate_select(const nat_select_params* p, SelectArgs* out) {
   return NAT_OK;
 }
 
+static unsigned mask_blocks_of(int64_t N) { return (unsigned)((N + kSelPerBlock - 1) / kSelPerBlock); }
+
 nat_status launch_prefix_mask(const int64_t* d_cu, int32_t B, int64_t N, const int32_t* d_cut_len,
                               uint32_t* d_mask_bits, hipStream_t s) {
   if (N <= 0) return NAT_OK;
-  SelectArgs a{};
-  a.scheme = NAT_SCHEME_DET;        // any prefix scheme: keep t0 < cut_len[i]
-  select_mask_kernel<<<(unsigned)((N + kSelPerBlock - 1) / kSelPerBlock), 256, 0, s>>>(a, d_cu, B, N, d_cut_len, d_mask_bits);
+  select_mask_kernel<false><<<mask_blocks_of(N), 256, 0, s>>>(
+      SelectArgs{}, MaskArgs{d_cu, B, N, d_cut_len, nullptr, nullptr, 0, mask_blocks_of(N), d_mask_bits});
+  NAT_LAUNCH_CHECK();
+  return NAT_OK;
+}
+
+nat_status launch_poisson_mask(const SelectArgs& a, const double* d_pi, const int64_t* d_cu, int32_t B, int64_t N,
+                               uint32_t* d_mask_bits, hipStream_t s) {
+  if (N <= 0) return NAT_OK;
+  select_mask_kernel<true><<<mask_blocks_of(N), 256, 0, s>>>(
+      a, MaskArgs{d_cu, B, N, nullptr, nullptr, d_pi, ((uintptr_t)d_pi & 15) == 0, mask_blocks_of(N), d_mask_bits});
   NAT_LAUNCH_CHECK();
   return NAT_OK;
 }
@@ -173,12 +257,9 @@ extern "C" nat_status nat_select(const nat_select_params* params, const int64_t*
   if (N > 0 && !d_mask_bits) return NAT_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   ProfScope prof(PC_SELECT, s);
-  select_cut_kernel<<<(B + 255) / 256, 256, 0, s>>>(a, d_cu_seqlens, B, d_cut_len);
+  const unsigned blocks = mask_blocks_of(N);        // the cut lengths are drawn by further blocks of the same launch
+  select_mask_kernel<false><<<blocks + (unsigned)((B + 255) / 256), 256, 0, s>>>(
+      a, MaskArgs{d_cu_seqlens, B, N, nullptr, d_cut_len, nullptr, 0, blocks, d_mask_bits});
   NAT_LAUNCH_CHECK();
-  if (N > 0) {
-    const int64_t blocks = (N + kSelPerBlock - 1) / kSelPerBlock;
-    select_mask_kernel<<<(unsigned)blocks, 256, 0, s>>>(a, d_cu_seqlens, B, N, d_cut_len, d_mask_bits);
-    NAT_LAUNCH_CHECK();
-  }
   return NAT_OK;
 }

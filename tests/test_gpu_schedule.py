@@ -91,6 +91,34 @@ def test_uniform_schedule_weights_equal_the_uniform_rpc_closed_form(stage):
     assert (cut >= 1).all() and (cut <= lay["lengths"]).all()
 
 
+@pytest.mark.parametrize("head", [0, 1, 2, 3])
+def test_masks_of_spans_inside_one_rollout(stage, head):
+    # spans of 1024 positions inside one rollout take the wavefront-uniform path: every position of the rollout's start
+    # relative to a block of four draws, span and strip boundaries, a rollout that ends at a span's end
+    import paper_2603_06619_amd as nat
+    lengths = [head, 3072 - head, 1024, 5000, 0, 1, 4099, 2, 2048, 1023]
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    B, N = len(lengths), int(cu[-1])
+    pi = si.draw_inclusion_probs(N + 1, seed=head)
+    pi[::97] = 0.0
+    for off in (0, 1):                                            # 16-byte aligned probabilities, and 8 bytes further
+        p = pi[off:off + N].copy()
+        dev = torch.zeros(N + 1, dtype=torch.float64, device=DEV)[off:off + N]
+        dev.copy_(torch.from_numpy(p))
+        m = osch.select_poisson(cu, p, seed=9, step=4, rollout_id_base=3)
+        mask = torch.full((nat.mask_words(N),), -1, dtype=torch.int32, device=DEV)
+        nat.nat_select_poisson(_params(9, 4, 3), dev, to_dev(cu), B, N, mask)
+        assert _mask_words(dict(mask_bits=mask), m)
+    for scheme, kw, dkw in ((nat.URS, dict(p=0.3), dict(p=0.3)), (nat.RPC, dict(C=5), dict(min_cut=5)),
+                            (nat.DET, dict(beta=0.4), dict(trunc_frac=0.4)), (nat.FULL, {}, {})):
+        o = osel.select(cu, scheme, seed=9, step=4, rollout_id_base=3, **kw)
+        cut = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+        mask = torch.full((nat.mask_words(N),), -1, dtype=torch.int32, device=DEV)
+        nat.nat_select(nat.SelectParams(scheme, seed=9, step=4, rollout_id_base=3, **dkw), to_dev(cu), B, N, cut, mask)
+        assert _mask_words(dict(mask_bits=mask), o["mask"])
+        assert np.array_equal(cut.cpu().numpy(), o["cut_len"])
+
+
 def test_poisson_bit_exact_and_weights(stage):
     rng = np.random.default_rng(4)
     for trial in range(20):

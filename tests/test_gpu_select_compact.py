@@ -126,10 +126,10 @@ def test_zero_advantage_rollouts_are_dropped(stage, scheme, kw):
     assert o["n_kept"] < full["n_kept"]
 
 
-@pytest.mark.parametrize("n_tiles,extra", [(1, -1), (1, 0), (1, 1), (2, 1023), (1024, 0), (1024, 1)])
+@pytest.mark.parametrize("n_tiles,extra", [(1, -1), (1, 0), (1, 1), (2, 1023), (128, 0), (128, 1), (1024, 0), (1024, 1)])
 def test_compaction_at_tile_and_scan_boundaries(stage, n_tiles, extra):
-    # tiles of 4096 positions; up to 1024 of them a scatter block adds up the earlier tiles' counts itself, beyond
-    # that a scan runs first.  Rollouts: runs of empty and one-token ones at the edges of tiles and wavefronts (1024)
+    # tiles of 4096 positions; up to 128 of them a scatter block counts the earlier mask words itself, up to 1024 it adds up
+    # their counts, beyond that a scan runs first.  Rollouts: runs of empty and one-token ones at edges of tiles and spans
     N = 4096 * n_tiles + extra
     rng = np.random.default_rng(N)
     edges = np.concatenate([[0, 0, 1, 1023, 1024, 1025, 4095, 4095, 4096, 4096, 4097], rng.integers(0, N, 70)])
