@@ -372,6 +372,31 @@ __device__ __forceinline__ void substep_slots(f32x16 (&acc)[4][NB], const bf16x8
   }
 }
 
+// The same for the loop that reads its A tiles from rows (TileLoaderRows), which refills two slices' A tiles at once:
+// kRefill 0: four loads of B, one every second MFMA as above; 1: eight loads of A, the two halves of each 128-byte
+// line one right after the other; 2: none.
+template <int kRefill, int M = 0>
+__device__ __forceinline__ void substep_slots_rows(f32x16 (&acc)[4][4], const bf16x8 (&au)[4], const bf16x8 (&bu)[4],
+                                                   bf16x8 (&al)[4], bf16x8 (&bl)[4], const char* a_s, const char* b_s,
+                                                   int a_row0, int b_row0, int l32, int lhi, int ks_load,
+                                                   const TileLoaderRows<4>& la, const TileLoader<4>& lb, char* lds0, char* lds1,
+                                                   int k0, int k1, int wave) {
+  if constexpr (M < 16) {
+    constexpr int i = M / 4, j = M % 4;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
+    if constexpr (M < 4) al[M] = *(const bf16x8*)(a_s + lds_chunk_off(a_row0 + M * 32 + l32, ks_load * 2 + lhi));
+    else if constexpr (M < 8) bl[M - 4] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + (M - 4) * 32 + l32, ks_load * 2 + lhi));
+    else if constexpr (kRefill == 0) {
+      if constexpr ((M & 1) == 0) lb.template issue_one<(M - 8) / 2>(lds0, k0, wave);
+    } else if constexpr (kRefill == 1) {
+      if constexpr ((M & 1) == 0) la.template issue_one<(M - 8) / 2>(lds0, k0, wave);
+      else la.template issue_one<(M - 8) / 2>(lds1, k1, wave);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    substep_slots_rows<kRefill, M + 1>(acc, au, bu, al, bl, a_s, b_s, a_row0, b_row0, l32, lhi, ks_load, la, lb, lds0, lds1, k0, k1, wave);
+  }
+}
+
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
@@ -565,6 +590,57 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
     __syncthreads();
     epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
     return;
+  } else if constexpr (kA == ASource::kRows) {
+    // A from rows: the pipeline below, two slices per turn.  A slice is 64 bytes of a row, half a cache line; fetched
+    // a slice apart, the halves cost the line twice on the way from the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 as
+    // below, 11.48 from the repacked copy).  So both A tiles of slices
+    // kt + 3 and kt + 4 are refilled under the second k-substep of an odd slice kt, half after half; B as below.  Issue order:
+    // [even kt] B(kt + 3) [odd kt] B(kt + 3) A(kt + 3) A(kt + 4).  "Slice kt + 1 has landed" is then vmcnt(16) at the barrier
+    // of an even slice (younger: B A A of slice kt - 1, B of kt), vmcnt(8) at that of an odd one (the Bs of kt - 1 and
+    // kt).  H is a multiple of 64: the number of slices is even.
+    static_assert(NW == 4, "the loop is written for 4 wavefronts");
+    auto clamp = [&](int k) { return k < kt_n ? k : kt_n - 1; };
+    auto pair = [&](int st, int k) {
+      la.template issue_one<0>(lds[st][0], clamp(k), wave);
+      la.template issue_one<0>(lds[st + 1][0], clamp(k + 1), wave);
+      la.template issue_one<1>(lds[st][0], clamp(k), wave);
+      la.template issue_one<1>(lds[st + 1][0], clamp(k + 1), wave);
+      la.template issue_one<2>(lds[st][0], clamp(k), wave);
+      la.template issue_one<2>(lds[st + 1][0], clamp(k + 1), wave);
+      la.template issue_one<3>(lds[st][0], clamp(k), wave);
+      la.template issue_one<3>(lds[st + 1][0], clamp(k + 1), wave);
+    };
+    pair(0, 0);
+    lb.issue(lds[0][1], 0, wave);
+    lb.issue(lds[1][1], clamp(1), wave);
+    pair(2, 2);
+    lb.issue(lds[2][1], clamp(2), wave);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(16));                // slice 0 has landed (younger: B1, A2, A3, B2)
+    __syncthreads();
+    bf16x8 af[2][4], bfr[2][NB];
+    load_frags<NB>(lds[0][0], lds[0][1], a_row0, b_row0, l32, lhi, 0, af[0], bfr[0]);
+    for (int kt = 0; kt < kt_n; kt += 2) {
+      const int c0 = kt % kStages, c1 = c0 + 1, c2 = (c0 + 2) % kStages, c3 = c2 + 1;    // buffers of slices kt .. kt + 3
+      __builtin_amdgcn_sched_barrier(0);
+      substep_slots_rows<0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c0][0], lds[c0][1], a_row0, b_row0, l32, lhi, 1, la, lb,
+                            lds[c3][1], nullptr, clamp(kt + 3), 0, wave);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(16) & 0xf0ff);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      substep_slots_rows<2>(acc, af[1], bfr[1], af[0], bfr[0], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 0, la, lb,
+                            nullptr, nullptr, 0, 0, wave);
+      substep_slots_rows<0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 1, la, lb,
+                            lds[c0][1], nullptr, clamp(kt + 4), 0, wave);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(8) & 0xf0ff);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      substep_slots_rows<1>(acc, af[1], bfr[1], af[0], bfr[0], lds[c2][0], lds[c2][1], a_row0, b_row0, l32, lhi, 0, la, lb,
+                            lds[c0][0], lds[c1][0], clamp(kt + 4), clamp(kt + 5), wave);
+    }
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
+    __syncthreads();
+    epi.unstash(pre, pre_stash, NW * 64);
+    epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
   } else {
   // Software pipeline over k-slices of 32.  Slice kt lives in lds[kt % 4]; three slices are
   // in flight while one is consumed, so a load has two to three iterations to land.  The barrier
@@ -1249,13 +1325,12 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 
 // Up to how many tokens a call reads W as it is instead of repacking it first.  The repack moves W three times with the
 // backward pass (0.77 ms at V x H = 151936 x 4096, 0.21 ms at H = 1024), twice without (0.50 / 0.12 ms), whatever the
-// batch; reading 64 bytes of 16 rows per instruction instead of 1 KiB in one piece costs the logits and dH
-// contractions 3 to 8 % of their time, and dH the transposing reads.  Measured, repacked against direct, whole call:
-// 59 tokens 1.92 / 1.19 ms (H = 4096), 0.61 / 0.42 (H = 1024); 1237: 4.77 / 4.12; 4096: 12.08 / 11.71; 6144: 19.6 / 18.9
-// (H = 4096), 24.2 / 24.1 (H = 5120), 5.45 / 5.43 (H = 1024); 7000 at H = 3584: 19.9 / 20.0.  Forward pass alone: 301
-// tokens 0.29 / 0.19 ms (H = 1024), 4096: 4.59 / 4.24, 8192: 8.57 / 8.35, 12289: 12.74 / 12.60 in one call and equal in
-// the next (H = 4096), 16384: 4.70 / 4.72 (H = 1024).
-constexpr int kDirectTokens = 6144, kDirectTokensForward = 10240;
+// batch; reading rows costs the logits contraction 1 to 2 % and the dH contraction, with its transposing reads, 3 to
+// 5 %.  Measured, repacked against direct, whole call in ms: 59 tokens 1.92 / 1.19 (H = 4096), 0.61 / 0.42 (H = 1024);
+// 1237: 4.69 / 4.13; 6144: 17.8 / 17.4 (H = 4096), 5.11 / 5.03 (H = 1024); 7000 at H = 3584: 18.9 / 18.75; 8192 at
+// H = 5120: 29.40 / 29.50; 24576: 68.55 / 69.1 (H = 4096).  Forward pass alone: 301 tokens 0.29 / 0.18 (H = 1024), 12289:
+// 12.07 / 11.65 (H = 4096), 32768: 30.88 / 30.64 (H = 4096), 8.48 / 8.38 (H = 1024), 65536: equal, 131072: 120.3 / 120.6.
+constexpr int kDirectTokens = 8192, kDirectTokensForward = 49152;
 
 // logits contraction: rows = vocabulary, columns = tokens (tiles_n tiles), contraction over the hidden size; W either
 // repacked (Wb) or read as it is (Wb NULL)
