@@ -237,6 +237,25 @@ struct TileLoader {
   }
 };
 
+// The first 128 rows of a [256][32] operand block: 8 KiB of each slice, two loads for each of 4 wavefronts.
+struct HalfTileLoader {
+  static constexpr int kLoads = 2;
+  const uint16_t* src;
+  __device__ __forceinline__ void init(const uint16_t* base, int tile, int kb, int wave, int lane) {
+    src = base + (int64_t)tile * kb * kBlkElems + wave * 1024 + lane * 8;
+  }
+  __device__ __forceinline__ void start_at(int kt0) { src += (int64_t)kt0 * kBlkElems; }
+  template <int kIdx>
+  __device__ __forceinline__ void issue_one(char* lds_tile, int kt, int wave) const {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)kt * kBlkElems),
+                                     (__attribute__((address_space(3))) void*)(lds_tile + wave * 2048), 16, kIdx * 1024, 0);
+  }
+  __device__ __forceinline__ void issue(char* lds_tile, int kt, int wave) const {
+    issue_one<0>(lds_tile, kt, wave);
+    issue_one<1>(lds_tile, kt, wave);
+  }
+};
+
 // The same copy for an A operand that is only stored with its rows along THIS contraction's k axis
 // (the soft-max numerators: rows = token, k = vocabulary, read by the dW contraction whose k axis is
 // the token).  A [256 rows][32 k] tile of the contraction is then eight pieces of the source, one per
@@ -373,27 +392,35 @@ __device__ __forceinline__ void substep_slots(f32x16 (&acc)[4][NB], const bf16x8
 }
 
 // The same for the loop that reads its A tiles from rows (TileLoaderRows), which refills two slices' A tiles at once:
-// kRefill 0: four loads of B, one every second MFMA as above; 1: eight loads of A, the two halves of each 128-byte
-// line one right after the other; 2: none.
-template <int kRefill, int M = 0>
-__device__ __forceinline__ void substep_slots_rows(f32x16 (&acc)[4][4], const bf16x8 (&au)[4], const bf16x8 (&bu)[4],
-                                                   bf16x8 (&al)[4], bf16x8 (&bl)[4], const char* a_s, const char* b_s,
+// kRefill 0: the loads of B, one every second MFMA as above; 1: eight loads of A, the two halves of each 128-byte
+// line one right after the other; 2: none.  NB = 2 (a tile of 128 columns): eight MFMAs, the loads behind the last two.
+template <int NB, int kRefill, int M = 0, class LoaderB>
+__device__ __forceinline__ void substep_slots_rows(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
+                                                   bf16x8 (&al)[4], bf16x8 (&bl)[NB], const char* a_s, const char* b_s,
                                                    int a_row0, int b_row0, int l32, int lhi, int ks_load,
-                                                   const TileLoaderRows<4>& la, const TileLoader<4>& lb, char* lds0, char* lds1,
+                                                   const TileLoaderRows<4>& la, const LoaderB& lb, char* lds0, char* lds1,
                                                    int k0, int k1, int wave) {
-  if constexpr (M < 16) {
-    constexpr int i = M / 4, j = M % 4;
+  constexpr int kFirst = 4 + NB, kSlots = 4 * NB - kFirst;     // slots behind the fragment reads: 8, or 2
+  if constexpr (M < 4 * NB) {
+    constexpr int i = M / NB, j = M % NB, q = M - kFirst;
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
     if constexpr (M < 4) al[M] = *(const bf16x8*)(a_s + lds_chunk_off(a_row0 + M * 32 + l32, ks_load * 2 + lhi));
-    else if constexpr (M < 8) bl[M - 4] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + (M - 4) * 32 + l32, ks_load * 2 + lhi));
+    else if constexpr (M < kFirst) bl[M - 4] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + (M - 4) * 32 + l32, ks_load * 2 + lhi));
     else if constexpr (kRefill == 0) {
-      if constexpr ((M & 1) == 0) lb.template issue_one<(M - 8) / 2>(lds0, k0, wave);
+      if constexpr (q * LoaderB::kLoads % kSlots == 0) lb.template issue_one<q * LoaderB::kLoads / kSlots>(lds0, k0, wave);
     } else if constexpr (kRefill == 1) {
-      if constexpr ((M & 1) == 0) la.template issue_one<(M - 8) / 2>(lds0, k0, wave);
-      else la.template issue_one<(M - 8) / 2>(lds1, k1, wave);
+      if constexpr (NB == 4) {
+        if constexpr ((q & 1) == 0) la.template issue_one<q / 2>(lds0, k0, wave);
+        else la.template issue_one<q / 2>(lds1, k1, wave);
+      } else {
+        la.template issue_one<2 * q>(lds0, k0, wave);
+        la.template issue_one<2 * q>(lds1, k1, wave);
+        la.template issue_one<2 * q + 1>(lds0, k0, wave);
+        la.template issue_one<2 * q + 1>(lds1, k1, wave);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
-    substep_slots_rows<kRefill, M + 1>(acc, au, bu, al, bl, a_s, b_s, a_row0, b_row0, l32, lhi, ks_load, la, lb, lds0, lds1, k0, k1, wave);
+    substep_slots_rows<NB, kRefill, M + 1>(acc, au, bu, al, bl, a_s, b_s, a_row0, b_row0, l32, lhi, ks_load, la, lb, lds0, lds1, k0, k1, wave);
   }
 }
 
@@ -413,23 +440,36 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int off) {
 // One k-substep of the k-major loop with 4 wavefronts of 128 x 128, slot by slot (see substep_slots): MFMA m on
 // (au, bu); behind the first 8 MFMAs one transposing read each (halves q = m % 2 of A block m / 2, from the
 // piece bases a_rd[q]) and behind the first 4 also one 16-byte read of B; behind MFMAs 8, 10, 12, 14 one
-// direct-to-LDS load of the refill (the A tile's when kRefillA, else the B tile's).
-template <bool kRefillA, int M = 0, class LoaderA>
-__device__ __forceinline__ void substep_slots_kmajor4(f32x16 (&acc)[4][4], const bf16x8 (&au)[4], const bf16x8 (&bu)[4],
-                                                      s16x4 (&al)[8], bf16x8 (&bl)[4], const uint32_t (&a_rd)[2], const char* b_rd,
-                                                      const LoaderA& la, const TileLoader<4>& lb, char* lds_dst,
+// direct-to-LDS load of the refill (the A tile's when kRefillA, else the B tile's).  NB = 2 (a tile of 128 columns):
+// eight MFMAs, two transposing reads behind each of the first four, the two reads of B, then the loads.
+template <int NB, bool kRefillA, int M = 0, class LoaderA, class LoaderB>
+__device__ __forceinline__ void substep_slots_kmajor4(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
+                                                      s16x4 (&al)[8], bf16x8 (&bl)[NB], const uint32_t (&a_rd)[2], const char* b_rd,
+                                                      const LoaderA& la, const LoaderB& lb, char* lds_dst,
                                                       int k, int wave) {
-  if constexpr (M < 16) {
-    constexpr int i = M / 4, j = M % 4;
+  if constexpr (M < 4 * NB) {
+    constexpr int i = M / NB, j = M % NB;
     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
-    if constexpr (M < 4) bl[M] = *(const bf16x8*)(b_rd + M * 2048);
-    if constexpr (M < 8) al[M] = lds_read_tr16_b64(a_rd[M & 1], (M / 2) * 2048);
-    if constexpr (M >= 8 && (M & 1) == 0) {
-      if constexpr (kRefillA) la.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
-      else lb.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
+    if constexpr (NB == 4) {
+      if constexpr (M < 4) bl[M] = *(const bf16x8*)(b_rd + M * 2048);
+      if constexpr (M < 8) al[M] = lds_read_tr16_b64(a_rd[M & 1], (M / 2) * 2048);
+      if constexpr (M >= 8 && (M & 1) == 0) {
+        if constexpr (kRefillA) la.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
+        else lb.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
+      }
+    } else if constexpr (M < 4) {
+      al[2 * M] = lds_read_tr16_b64(a_rd[0], M * 2048);
+      al[2 * M + 1] = lds_read_tr16_b64(a_rd[1], M * 2048);
+    } else if constexpr (M < 6) {
+      bl[M - 4] = *(const bf16x8*)(b_rd + (M - 4) * 2048);
+    } else if constexpr (kRefillA) {
+      la.template issue_one<2 * (M - 6)>(lds_dst, k, wave);
+      la.template issue_one<2 * (M - 6) + 1>(lds_dst, k, wave);
+    } else {
+      lb.template issue_one<M - 6>(lds_dst, k, wave);
     }
     __builtin_amdgcn_sched_barrier(0);
-    substep_slots_kmajor4<kRefillA, M + 1>(acc, au, bu, al, bl, a_rd, b_rd, la, lb, lds_dst, k, wave);
+    substep_slots_kmajor4<NB, kRefillA, M + 1>(acc, au, bu, al, bl, a_rd, b_rd, la, lb, lds_dst, k, wave);
   }
 }
 
@@ -452,33 +492,24 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 // kA: how the A operand is stored.  k-major: along this contraction's k axis (g.kb_a_src is then the number of
 // k-slices of that source); rows: a row-major matrix of g.src_rows x g.src_cols, read as it is.
 enum class ASource { kBlocked, kKMajorBlocked, kRows, kKMajorRows };
-template <class Epilogue, int NW, ASource kA = ASource::kBlocked>
-__global__ void __launch_bounds__(NW * 64, 1)
-gemm_nt_kernel(GemmArgs g, Epilogue epi) {
+// one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
+// direct-to-LDS loads in flight): the ring, and behind it the words the epilogue parks across the k-loop
+template <int kStashWords>
+struct GemmShared {
+  char ring[kStages][2][kTileBytes];
+  int stash[kStashWords > 0 ? kStashWords : 1];
+};
+
+// One tile.  NB: 32-column blocks per wavefront, 16 / NW; or 2 with 4 wavefronts: a tile of which only the first 128
+// columns are computed.
+template <class Epilogue, int NW, ASource kA, int NB, class Shared>
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const Epilogue& epi, Shared& sm, int tm, int tn, int range, int slab) {
   constexpr bool AT = kA == ASource::kKMajorBlocked || kA == ASource::kKMajorRows;
-  constexpr int NB = 16 / NW;                                  // 32-column blocks per wavefront
-  constexpr int kLoadsPerWave = 2 * (kTileBytes / 1024) / NW;  // direct-to-LDS loads per wavefront per slice
-  // one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
-  // direct-to-LDS loads in flight): the ring, and behind it the words the epilogue parks across the k-loop
-  constexpr int kStashWords = Epilogue::template stash_words<16 / NW>();
-  struct Shared {
-    char ring[kStages][2][kTileBytes];
-    int stash[kStashWords > 0 ? kStashWords * NW * 64 : 1];
-  };
-  __shared__ __attribute__((aligned(1024))) Shared sm;
+  constexpr bool kHalf = NB * NW < 16;
+  constexpr int kLoadsA = kTileBytes / 1024 / NW, kLoadsB = kHalf ? HalfTileLoader::kLoads : kLoadsA;   // per wavefront and slice
+  constexpr int kLoadsPerWave = kLoadsA + kLoadsB;
   auto& lds = sm.ring;
   int* pre_stash = sm.stash;
-  int tm, tn;
-  const int n_tiles = g.tiles_m * g.tiles_n;
-  int pid = (int)blockIdx.x, range = -1, slab = -1;           // range of the contraction axis / slab (-1: whole axis)
-  if (g.k_splits > 1 && pid >= n_tiles - g.tail_tiles) {
-    const int r = pid - (n_tiles - g.tail_tiles);
-    range = r / g.tail_tiles;
-    const int pos = r - range * g.tail_tiles;
-    pid = n_tiles - g.tail_tiles + pos;
-    slab = pos * g.k_splits + range;
-  }
-  tile_of_block(g, pid, tm, tn);
   const int m0 = tm * kBM, n0 = tn * kBN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -502,7 +533,7 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   using Rows = typename std::conditional<AT, TileLoaderKMajorRows<NW>, TileLoaderRows<NW>>::type;
   constexpr bool kDirect = kA == ASource::kRows || kA == ASource::kKMajorRows;
   typename std::conditional<kDirect, Rows, Blocked>::type la;
-  TileLoader<NW> lb;
+  typename std::conditional<kHalf, HalfTileLoader, TileLoader<NW>>::type lb;
   const int kt_all = g.K / kBK;
   if constexpr (kDirect) la.init(g.A, tm, g.src_rows, g.src_cols, wave, lane);
   else la.init(g.A, tm, AT ? g.kb_a_src : kt_all, wave, lane);
@@ -524,7 +555,6 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
     // waits for it itself, lgkmcnt(0) before the next substep uses what was read.  An earlier variant kept the
     // builtin read and hid the loads instead, with 8 wavefronts and compiler-scheduled reads: 3.5 % slower.)
     static_assert(NW == 4, "the k-major loop is written for 4 wavefronts");
-    constexpr int kHalfLoads = kLoadsPerWave / 2;
     KMajorFragOffsets fo;
     fo.init(lane);
     const int a_blk0 = a_row0 / 32;
@@ -537,10 +567,10 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
       la.template issue_one<3>(lds[st][0], k, wave);
       if (st < kStages - 1) lb.issue(lds[st][1], k, wave);
     }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((2 * kStages - 3) * kHalfLoads));   // slice 0 has landed
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 1) * kLoadsA + (kStages - 2) * kLoadsB));   // slice 0 has landed
     __syncthreads();
     s16x4 ah[2][8];
-    bf16x8 bfr[2][4];
+    bf16x8 bfr[2][NB];
     auto a_bases = [&](int stage, int ks, uint32_t (&out)[2]) {
       const uint32_t piece0 = lds_addr(lds[stage][0] + a_blk0 * 2048 + ks * 1024);
       out[0] = piece0 + fo.off[0];
@@ -559,7 +589,7 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
 #pragma unroll
       for (int m = 0; m < 8; ++m) ah[0][m] = lds_read_tr16_b64(ar[m & 1], (m / 2) * 2048);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bfr[0][j] = *(const bf16x8*)(lds[0][1] + lds_chunk_off(b_row0 + j * 32 + l32, lhi));
+      for (int j = 0; j < NB; ++j) bfr[0][j] = *(const bf16x8*)(lds[0][1] + lds_chunk_off(b_row0 + j * 32 + l32, lhi));
     }
     for (int kt = 0; kt < kt_n; ++kt) {
       const int cur = kt % kStages, nxt = (kt + 1) % kStages, last = (kt + kStages - 1) % kStages;
@@ -574,7 +604,7 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
       __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): the fragments read under the last substep
       join(ah[0], au);
       __builtin_amdgcn_sched_barrier(0);
-      substep_slots_kmajor4<false>(acc, au, bfr[0], ah[1], bfr[1], ar, lds[cur][1] + lds_chunk_off(b_row0 + l32, 2 + lhi),
+      substep_slots_kmajor4<NB, false>(acc, au, bfr[0], ah[1], bfr[1], ar, lds[cur][1] + lds_chunk_off(b_row0 + l32, 2 + lhi),
                                    la, lb, lds[last][1], k1, wave);
       __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kLoadsPerWave) & 0xf0ff);
       __builtin_amdgcn_s_barrier();
@@ -583,7 +613,7 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
       a_bases(nxt, 0, ar);
       join(ah[1], au);
       __builtin_amdgcn_sched_barrier(0);
-      substep_slots_kmajor4<true>(acc, au, bfr[1], ah[0], bfr[0], ar, lds[nxt][1] + lds_chunk_off(b_row0 + l32, lhi),
+      substep_slots_kmajor4<NB, true>(acc, au, bfr[1], ah[0], bfr[0], ar, lds[nxt][1] + lds_chunk_off(b_row0 + l32, lhi),
                                   la, lb, lds[cur][0], k2, wave);
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
@@ -595,9 +625,8 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
     // a slice apart, the halves cost the line twice on the way from the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 as
     // below, 11.48 from the repacked copy).  So both A tiles of slices
     // kt + 3 and kt + 4 are refilled under the second k-substep of an odd slice kt, half after half; B as below.  Issue order:
-    // [even kt] B(kt + 3) [odd kt] B(kt + 3) A(kt + 3) A(kt + 4).  "Slice kt + 1 has landed" is then vmcnt(16) at the barrier
-    // of an even slice (younger: B A A of slice kt - 1, B of kt), vmcnt(8) at that of an odd one (the Bs of kt - 1 and
-    // kt).  H is a multiple of 64: the number of slices is even.
+    // [even kt] B(kt + 3) [odd kt] B(kt + 3) A(kt + 3) A(kt + 4).  "Slice kt + 1 has landed" is then eight loads of A and two Bs
+    // at the barrier of an even slice (B A A of slice kt - 1, B of kt), two Bs at that of an odd one (of kt - 1 and kt).  H is a multiple of 64: the number of slices is even.
     static_assert(NW == 4, "the loop is written for 4 wavefronts");
     auto clamp = [&](int k) { return k < kt_n ? k : kt_n - 1; };
     auto pair = [&](int st, int k) {
@@ -615,26 +644,26 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
     lb.issue(lds[1][1], clamp(1), wave);
     pair(2, 2);
     lb.issue(lds[2][1], clamp(2), wave);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(16));                // slice 0 has landed (younger: B1, A2, A3, B2)
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsA + 2 * kLoadsB));   // slice 0 has landed (younger: B1, A2, A3, B2)
     __syncthreads();
     bf16x8 af[2][4], bfr[2][NB];
     load_frags<NB>(lds[0][0], lds[0][1], a_row0, b_row0, l32, lhi, 0, af[0], bfr[0]);
     for (int kt = 0; kt < kt_n; kt += 2) {
       const int c0 = kt % kStages, c1 = c0 + 1, c2 = (c0 + 2) % kStages, c3 = c2 + 1;    // buffers of slices kt .. kt + 3
       __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c0][0], lds[c0][1], a_row0, b_row0, l32, lhi, 1, la, lb,
+      substep_slots_rows<NB, 0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c0][0], lds[c0][1], a_row0, b_row0, l32, lhi, 1, la, lb,
                             lds[c3][1], nullptr, clamp(kt + 3), 0, wave);
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(16) & 0xf0ff);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsA + 2 * kLoadsB) & 0xf0ff);
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<2>(acc, af[1], bfr[1], af[0], bfr[0], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 0, la, lb,
+      substep_slots_rows<NB, 2>(acc, af[1], bfr[1], af[0], bfr[0], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 0, la, lb,
                             nullptr, nullptr, 0, 0, wave);
-      substep_slots_rows<0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 1, la, lb,
+      substep_slots_rows<NB, 0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 1, la, lb,
                             lds[c0][1], nullptr, clamp(kt + 4), 0, wave);
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(8) & 0xf0ff);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsB) & 0xf0ff);
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<1>(acc, af[1], bfr[1], af[0], bfr[0], lds[c2][0], lds[c2][1], a_row0, b_row0, l32, lhi, 0, la, lb,
+      substep_slots_rows<NB, 1>(acc, af[1], bfr[1], af[0], bfr[0], lds[c2][0], lds[c2][1], a_row0, b_row0, l32, lhi, 0, la, lb,
                             lds[c0][0], lds[c1][0], clamp(kt + 4), clamp(kt + 5), wave);
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
@@ -653,6 +682,7 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   // slice kt is vmcnt(2 * kLoadsPerWave): the halves of the two younger slices may be outstanding.
   // Slices past the end re-load the last one (into a buffer nobody reads again) to keep the body
   // branch-free and the count fixed.
+  static_assert(!kHalf, "half tiles are read from rows");
   constexpr int kHalfLoads = kLoadsPerWave / 2;                // loads per wavefront and operand tile
 #pragma unroll
   for (int st = 0; st < kStages; ++st) {
@@ -691,6 +721,32 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   epi.unstash(pre, pre_stash, NW * 64);
   epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
   }
+}
+
+template <class Epilogue, int NW, ASource kA = ASource::kBlocked>
+__global__ void __launch_bounds__(NW * 64, 1)
+gemm_nt_kernel(GemmArgs g, Epilogue epi) {
+  __shared__ __attribute__((aligned(1024))) GemmShared<Epilogue::template stash_words<16 / NW>() * NW * 64> sm;
+  int tm, tn;
+  const int n_tiles = g.tiles_m * g.tiles_n;
+  int pid = (int)blockIdx.x, range = -1, slab = -1;           // range of the contraction axis / slab (-1: whole axis)
+  if (g.k_splits > 1 && pid >= n_tiles - g.tail_tiles) {
+    const int r = pid - (n_tiles - g.tail_tiles);
+    range = r / g.tail_tiles;
+    const int pos = r - range * g.tail_tiles;
+    pid = n_tiles - g.tail_tiles + pos;
+    slab = pos * g.k_splits + range;
+  }
+  tile_of_block(g, pid, tm, tn);
+  // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 of them
+  // computes only those (301 log-probs at the 0.6B head: logits 153 -> 132 us; 59 tokens at the 8B head: call 1155 -> 1067 us).
+  if constexpr (kA == ASource::kRows || kA == ASource::kKMajorRows) {
+    if (epi.n_valid - tn * kBN <= kBN / 2) {
+      gemm_tile<Epilogue, NW, kA, 2>(g, epi, sm, tm, tn, range, slab);
+      return;
+    }
+  }
+  gemm_tile<Epilogue, NW, kA, 16 / NW>(g, epi, sm, tm, tn, range, slab);
 }
 
 // ------------------------------------------------------------- epilogues ----

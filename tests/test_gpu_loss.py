@@ -213,6 +213,15 @@ def test_bf16_hidden_size_not_a_multiple_of_the_tile(stage):
     check(out, ref, 300, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok", [31, 128, 129, 384, 385, 640])
+def test_bf16_last_token_tile_half_full(stage, n_tok):
+    # a last token tile with at most 128 tokens computes only its first 128 columns (logits, and dH whole and in ranges)
+    for H, V in ((192, 1000), (64, 9000)):
+        case = make_loss_case(500 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+        ref = oracle_loss(**case)
+        check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
+
+
 @pytest.mark.parametrize("H,V", [(64, 7), (320, 700), (192, 1025)])
 def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V):
     # up to 8192 tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
