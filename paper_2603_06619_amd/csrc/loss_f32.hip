@@ -13,10 +13,6 @@ namespace nat {
 
 constexpr int kF32Threads = 256;
 
-__device__ __forceinline__ float wave_sum_f(float v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
 __device__ __forceinline__ float wave_max_f(float v) {
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
   return v;
@@ -178,27 +174,35 @@ static nat_status f32_gemm(const float* A, int64_t lda, const float* B, int64_t 
 
 // ------------------------------------------------------------- per token ----
 // log-sum-exp pieces of one token's logits, one block per token: the maximum m, sum of e^(z-m) and of
-// e^(z-m) (z-m), all threads.
-struct F32RowSums { float m, s, t; };
-__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, float (&red)[3][4]) {
+// e^(z-m) (z-m), all threads.  The sums and what follows from them (log-sum-exp, log-prob, ratio, surrogate) are formed
+// in fp64: a loss whose terms cancel is left with the rounding of its log-probs, 5e-7 each in fp32.
+__device__ __forceinline__ double wave_sum_d(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+struct F32RowSums { float m; double s, t; };
+struct F32RowShared { float m[4]; double s[4], t[4]; };
+__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, F32RowShared& sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float m = -INFINITY;
+#pragma unroll 4
   for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
   m = wave_max_f(m);
-  if (lane == 0) red[0][wave] = m;
+  if (lane == 0) sh.m[wave] = m;
   __syncthreads();
-  m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-  float s = 0.f, t = 0.f;
+  m = fmaxf(fmaxf(sh.m[0], sh.m[1]), fmaxf(sh.m[2], sh.m[3]));
+  double s = 0.0, t = 0.0;
+#pragma unroll 4
   for (int v = threadIdx.x; v < V; v += kF32Threads) {
     const float zc = z[v] - m, e = expf(zc);
-    s += e;
-    t = fmaf(e, zc, t);
+    s += (double)e;
+    t = fma((double)e, (double)zc, t);
   }
-  s = wave_sum_f(s);
-  t = wave_sum_f(t);
-  if (lane == 0) { red[1][wave] = s; red[2][wave] = t; }
+  s = wave_sum_d(s);
+  t = wave_sum_d(t);
+  if (lane == 0) { sh.s[wave] = s; sh.t[wave] = t; }
   __syncthreads();
-  return F32RowSums{m, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]), (red[2][0] + red[2][1]) + (red[2][2] + red[2][3])};
+  return F32RowSums{m, (sh.s[0] + sh.s[1]) + (sh.s[2] + sh.s[3]), (sh.t[0] + sh.t[1]) + (sh.t[2] + sh.t[3])};
 }
 
 __global__ void __launch_bounds__(kF32Threads)
@@ -208,17 +212,18 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
                  float* __restrict__ dz /*[chunk, V]: logits in, gradients out*/, float* __restrict__ logp_out,
                  float* __restrict__ term, float* __restrict__ kl_out, float* __restrict__ entropy_out,
                  int32_t* __restrict__ diag) {
-  __shared__ float red[3][4], bcast[2];
+  __shared__ F32RowShared sh;
+  __shared__ float bcast[2];
   const int kc = blockIdx.x;                 // token within the chunk
   const int k = chunk_start + kc;
   float* z = dz + (size_t)kc * V;
-  const F32RowSums sums = f32_row_sums(z, V, red);
+  const F32RowSums sums = f32_row_sums(z, V, sh);
   if (threadIdx.x == 0) {
-    const float lse = sums.m + logf(sums.s);
+    const double lse = (double)sums.m + log(sums.s);
     // -sum p log p = log(sum) - (sum of e (z - m)) / sum
-    if (entropy_out) entropy_out[k] = logf(sums.s) - sums.t / sums.s;
+    if (entropy_out) entropy_out[k] = (float)(log(sums.s) - sums.t / sums.s);
     const int yk = ids[k];
-    bcast[0] = lse;
+    bcast[0] = (float)lse;
     if (yk < 0 || yk >= V) {                 // no such token: left out (no loss term, zero gradient)
       if (logp_out) logp_out[k] = __builtin_nanf("");
       if (kl_out) kl_out[k] = __builtin_nanf("");
@@ -226,12 +231,12 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
       bcast[1] = 0.f;
       if (diag) atomicAdd(diag + NAT_DIAG_BAD_ID, 1);
     } else {
-      const float logp = z[yk] - lse;
+      const double logp = (double)z[yk] - lse;
       const float w = kept_w[k];
       const float A = adv[kept_seq[k]];
       const TokenScalars ts = grpo_token_scalars(logp, old_logp[k], A, w, eps_lo, eps_hi, grad_scale,
                                                  klp.beta, klp.kind, klp.beta != 0.f ? klp.ref_logp[k] : 0.f);
-      if (logp_out) logp_out[k] = logp;
+      if (logp_out) logp_out[k] = (float)logp;
       if (kl_out) kl_out[k] = ts.kl;
       term[k] = w * ts.L;
       bcast[1] = ts.c;
@@ -301,19 +306,19 @@ nat_status loss_f32_run(const LossArgs& a) {
 __global__ void __launch_bounds__(kF32Threads)
 f32_logp_kernel(const float* __restrict__ z_scratch /*[chunk, V]*/, const int32_t* __restrict__ ids, int chunk_start, int V,
                 float* __restrict__ logp_out, float* __restrict__ entropy_out, int32_t* __restrict__ diag) {
-  __shared__ float red[3][4];
+  __shared__ F32RowShared sh;
   const int kc = blockIdx.x, k = chunk_start + kc;
   const float* z = z_scratch + (size_t)kc * V;
-  const F32RowSums sums = f32_row_sums(z, V, red);
+  const F32RowSums sums = f32_row_sums(z, V, sh);
   if (threadIdx.x == 0) {
     const int yk = ids[k];
     if (yk < 0 || yk >= V) {
       logp_out[k] = __builtin_nanf("");
       if (diag) atomicAdd(diag + NAT_DIAG_BAD_ID, 1);
     } else {
-      logp_out[k] = z[yk] - (sums.m + logf(sums.s));
+      logp_out[k] = (float)((double)z[yk] - ((double)sums.m + log(sums.s)));
     }
-    if (entropy_out) entropy_out[k] = logf(sums.s) - sums.t / sums.s;
+    if (entropy_out) entropy_out[k] = (float)(log(sums.s) - sums.t / sums.s);
   }
 }
 
