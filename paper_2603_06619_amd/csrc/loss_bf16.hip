@@ -844,6 +844,9 @@ struct LogitsEpilogue {
     char* stage = lds + wave * (32 * kStageRow);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
+      // columns past the last token: their sums and, the contraction over tokens ending with the last slice that holds
+      // one, their numerators are read by nobody (as token rows of dH they yield rows that are not stored)
+      if (k0 + nb * 32 >= n_valid) break;
       const float nshift2 = -shift_of[nb] * kLog2e;
       float s2[2] = {0.f, 0.f}, t2[2] = {0.f, 0.f};        // two independent chains per sum
 #pragma unroll
@@ -1118,10 +1121,10 @@ dw_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, int V, int 
 // ----------------------------------------------------- reference logit ----
 // ref[kk] = h_k . W[ids_k] in fp32, one wavefront per token (row-major caller arrays).
 // An id outside [0, V) reads no row of W and gets the shift 0.
-__global__ void __launch_bounds__(256)
-target_logit_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ W, const int32_t* __restrict__ ids,
-                    int n_valid, int H, int V, float* __restrict__ ref) {
-  const int kk = blockIdx.x * 4 + (threadIdx.x >> 6);
+__device__ __forceinline__ void target_logit(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ W,
+                                             const int32_t* __restrict__ ids, int n_valid, int H, int V,
+                                             float* __restrict__ ref, int block) {
+  const int kk = block * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (kk >= n_valid) return;
   const int y = ids[kk];
@@ -1145,6 +1148,27 @@ target_logit_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restr
   if (lane == 0) ref[kk] = s;
 }
 
+// H_chunk in the blocked layout (the first pack_blocks blocks, H / 64 of them to 64 rows) and the exponent shifts (the
+// others): one launch, both read the same rows.
+__global__ void __launch_bounds__(256)
+hidden_prep_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ W, const int32_t* __restrict__ ids,
+                   int n_valid, int H, int V, uint16_t* __restrict__ Hb, float* __restrict__ ref, int pack_blocks) {
+  const int block = (int)blockIdx.x;
+  if (block >= pack_blocks) {
+    target_logit(hidden, W, ids, n_valid, H, V, ref, block - pack_blocks);
+    return;
+  }
+  const int cb = H / 64, r0 = block / cb * 64, c0 = block % cb * 64, kb = H >> 5;
+  const int c = c0 + 8 * (threadIdx.x & 7);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = r0 + (threadIdx.x >> 3) + 32 * i;
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (r < n_valid) x = *reinterpret_cast<const uint4*>(hidden + (int64_t)r * H + c);
+    *reinterpret_cast<uint4*>(Hb + blk_off(r, c, kb)) = x;
+  }
+}
+
 // ------------------------------------------------- per-token statistics ----
 // A granule's partial sum at or above e^70 means some numerator reached the range in which the
 // clamp of the exponent shift acts (a clamped numerator alone makes its granule's sum that large).
@@ -1153,9 +1177,9 @@ constexpr float kShiftRangeLimit = 2.5154386709191669e30f;     // e^70
 // Per-token sums of the per-granule partials: kStatTokens tokens per workgroup; the granules of a
 // token are split over kStatParts groups of threads (granule gi goes to group gi % kStatParts), each
 // of which walks its granules in order, and the groups' sums are added in a fixed tree, so the result
-// does not depend on timing.  The walk is a chain of dependent loads: many short chains in flight hide
-// their latency.  Returns to the first kStatTokens threads only.
-constexpr int kStatTokens = 32, kStatParts = 8;
+// does not depend on timing.  Bound by the latency of the walk (149 granules per group at V = 151936): with 32
+// loads in flight instead of 8 a launch over 3000 tokens takes 14 us instead of 19.  Returns to the first kStatTokens threads only.
+constexpr int kStatTokens = 32, kStatParts = 8, kStatBatch = 32;
 struct TokenSums { float S, TZ; bool in_shift_range; };
 struct StatShared { float s[kStatParts][kStatTokens], t[kStatParts][kStatTokens], m[kStatParts][kStatTokens]; };
 
@@ -1163,17 +1187,22 @@ __device__ __forceinline__ TokenSums token_sums(const float* __restrict__ s_part
                                                 int n_granules, int64_t ld, int kk, bool valid, StatShared& sh) {
   const int t = threadIdx.x % kStatTokens, part = threadIdx.x / kStatTokens;
   float s = 0.f, tz = 0.f, mx = 0.f;
+  // kStatBatch loads in flight, added in granule order (0 past the end leaves the sums as they are)
+  auto walk = [&](const float* __restrict__ p, auto use) {
+    for (int g0 = part; g0 < n_granules; g0 += kStatParts * kStatBatch) {
+      float v[kStatBatch];
+#pragma unroll
+      for (int e = 0; e < kStatBatch; ++e) {
+        const int gi = g0 + e * kStatParts;
+        v[e] = gi < n_granules ? p[(int64_t)gi * ld + kk] : 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < kStatBatch; ++e) use(v[e]);
+    }
+  };
   if (valid) {
-#pragma unroll 8
-    for (int gi = part; gi < n_granules; gi += kStatParts) {
-      const float v = s_part[(int64_t)gi * ld + kk];
-      s += v;
-      mx = fmaxf(mx, v);
-    }
-    if (t_part) {
-#pragma unroll 8
-      for (int gi = part; gi < n_granules; gi += kStatParts) tz += t_part[(int64_t)gi * ld + kk];
-    }
+    walk(s_part, [&](float v) { s += v; mx = fmaxf(mx, v); });
+    if (t_part) walk(t_part, [&](float v) { tz += v; });
   }
   sh.s[part][t] = s;
   sh.t[part][t] = tz;
@@ -1440,9 +1469,8 @@ nat_status loss_bf16_run(const LossArgs& a) {
     const uint16_t* hid_c = hidden + (int64_t)c0 * H;
     {  // H_chunk in the blocked layout; exponent shift = target logit
       ProfScope prof(PC_TRANSPOSE, s);
-      pack_blocked_kernel<<<dim3(np / 64, H / 64), 256, 0, s>>>(hid_c, H, nv, H, np, Hp, Hb, nullptr, 0, nullptr);
-      NAT_LAUNCH_CHECK();
-      target_logit_kernel<<<(nv + 3) / 4, 256, 0, s>>>(hid_c, W, a.ids + c0, nv, H, V, ref);
+      const int pack_blocks = np / 64 * (H / 64);
+      hidden_prep_kernel<<<pack_blocks + (nv + 3) / 4, 256, 0, s>>>(hid_c, W, a.ids + c0, nv, H, V, Hb, ref, pack_blocks);
       NAT_LAUNCH_CHECK();
     }
     // The forward sweep and the dH contraction go over the chunk in sub-chunks: shorter launches of
@@ -1560,9 +1588,8 @@ nat_status logp_bf16_run(const LogpArgs& a) {
     const uint16_t* hid_c = hidden + (int64_t)c0 * H;
     {
       ProfScope prof(PC_TRANSPOSE, s);
-      pack_blocked_kernel<<<dim3(np / 64, H / 64), 256, 0, s>>>(hid_c, H, nv, H, np, H, Hb, nullptr, 0, nullptr);
-      NAT_LAUNCH_CHECK();
-      target_logit_kernel<<<(nv + 3) / 4, 256, 0, s>>>(hid_c, W, a.ids + c0, nv, H, V, ref);
+      const int pack_blocks = np / 64 * (H / 64);
+      hidden_prep_kernel<<<pack_blocks + (nv + 3) / 4, 256, 0, s>>>(hid_c, W, a.ids + c0, nv, H, V, Hb, ref, pack_blocks);
       NAT_LAUNCH_CHECK();
     }
     {
