@@ -135,7 +135,9 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    # hipStream_t of the current stream; torch.cuda.current_stream() builds a Stream object around it (2.8 us of host
+    # time a call, five calls a step)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _raise(status, where):
