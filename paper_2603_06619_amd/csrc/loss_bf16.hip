@@ -1072,6 +1072,73 @@ struct DWeightEpilogue {
   }
 };
 
+// The same tile added to dW by reading, adding and storing, for short contractions: the fp32 memory atomics above run at
+// 28 cycles an instruction, 1024 per tile, i.e. 1.9 ms for the whole of a 151936 x 4096 dW however few tokens are added to
+// it.  32 rows of the wavefront's tile at a time go through its own part of the LDS ring (free after the k-loop), so that
+// old values come and sums leave 16 bytes per lane, two whole rows of its columns per instruction; the old values are loaded
+// two blocks ahead of their use and before the stores of the block in hand (the load counter would wait for those
+// first).  One fp32 addition old + sum per element, as with the atomics.  See kReadAddSlices.
+struct DWeightAddEpilogue {
+  DWeightEpilogue whole;           // ranges of cut tiles still go to their slabs
+
+  template <int NB> struct Pre {};
+  template <int NB> static constexpr int stash_words() { return 0; }
+  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
+  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
+  template <int MA, int NB, class P>
+  __device__ __forceinline__ void operator()(f32x16 (&acc)[MA][NB], const P& pre, int v0, int h0, int lane, int wave,
+                                             char* lds, int slab_id) const {
+    if (slab_id >= 0) {
+      whole(acc, pre, v0, h0, lane, wave, lds, slab_id);
+      return;
+    }
+    constexpr int kCols = NB * 32, kLanesPerRow = kCols / 4, kRowsPer = 64 / kLanesPerRow, kN = 32 / kRowsPer;
+    constexpr int kStageRow = kCols + 8;                       // floats: the two half-wavefronts' rows fall on different banks
+    const int l32 = lane & 31, lhi = lane >> 5, H = whole.H;
+    const int row = lane / kLanesPerRow, col = (lane % kLanesPerRow) * 4;
+    float* stage = (float*)lds + wave * (32 * kStageRow);
+    const int rows = whole.V - v0;                             // valid rows from v0 on (may be <= 0)
+    const bool col_ok = h0 + col < H;                          // H is a multiple of 64: a lane's four columns are in or out
+    float* dst = whole.dW + (int64_t)(v0 + row) * H + h0 + col;
+    auto sweep = [&](auto all_valid) {
+      constexpr bool kAll = decltype(all_valid)::value;        // no row or column to leave out
+      float4 old[2][kN];
+      auto fetch = [&](int mb) {
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+          const int r = mb * 32 + i * kRowsPer;
+          if (kAll || (col_ok && r + row < rows)) old[mb & 1][i] = *(const float4*)(dst + (int64_t)r * H);
+          else old[mb & 1][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      };
+      fetch(0);
+      fetch(1);
+#pragma unroll
+      for (int mb = 0; mb < MA; ++mb) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            stage[(8 * (r >> 2) + 4 * lhi + (r & 3)) * kStageRow + nb * 32 + l32] = acc[mb][nb][r];
+        float4 out[kN];
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+          const float4 o = old[mb & 1][i], x = *(const float4*)(stage + (i * kRowsPer + row) * kStageRow + col);
+          out[i] = make_float4(o.x + x.x, o.y + x.y, o.z + x.z, o.w + x.w);
+        }
+        if (mb + 2 < MA) fetch(mb + 2);
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+          const int r = mb * 32 + i * kRowsPer;
+          if (kAll || (col_ok && r + row < rows)) *(float4*)(dst + (int64_t)r * H) = out[i];
+        }
+      }
+    };
+    if (rows >= MA * 32 && h0 + kCols <= H) sweep(std::true_type{});
+    else sweep(std::false_type{});
+  }
+};
+
 // dH tiles of a launch whose last tail_tiles tiles (in launch order) were cut into k_splits ranges of the vocabulary:
 // dH[k][h] = beta_k * (slab 0 + slab 1 + ...) of the tile, in range order.  One block per 1024 elements of a tile.
 __global__ void __launch_bounds__(256)
@@ -1417,6 +1484,11 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 // 12.07 / 11.65 (H = 4096), 32768: 30.88 / 30.64 (H = 4096), 8.48 / 8.38 (H = 1024), 65536: equal, 131072: 120.3 / 120.6.
 constexpr int kDirectTokens = 8192, kDirectTokensForward = 49152;
 
+// Up to how many k-slices (32 tokens) a chunk is added to dW by reading, adding and storing instead of by atomics.
+// Accumulating call, atomics against read-add-store, ms at V x H = 151936 x 4096: 59 tokens 2.47 / 1.66, 300: 2.88 / 2.23,
+// 1237: 4.76 / 4.58, 2500: 8.70 / 8.74, 4096: 12.04 / 12.18; at H = 1024: 59 tokens 0.68 / 0.50, 600: 1.03 / 0.90, 4096: equal.
+constexpr int kReadAddSlices = 64;
+
 // logits contraction: rows = vocabulary, columns = tokens (tiles_n tiles), contraction over the hidden size; W either
 // repacked (Wb) or read as it is (Wb NULL)
 template <class Epi>
@@ -1545,7 +1617,10 @@ nat_status loss_bf16_run(const LossArgs& a) {
       DWeightEpilogue e{V, H, accumulate, a.dW, dh_part};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
+        if (accumulate && kt <= kReadAddSlices)
+          gemm_nt_kernel<DWeightAddEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, DWeightAddEpilogue{e});
+        else
+          gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
           dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);

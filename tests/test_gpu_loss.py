@@ -222,6 +222,21 @@ def test_bf16_last_token_tile_half_full(stage, n_tok):
         check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok", [40, 2048, 2049])
+def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok):
+    # up to 2048 tokens a chunk is added to dW by reading, adding and storing, beyond that by fp32 atomics: one addition
+    # of the same sum per element either way, so accumulating equals old + the overwritten result bit for bit.  Columns
+    # and rows past the end of the last tiles (H = 320, V = 1025) keep what they held
+    H, V = 320, 1025
+    case = make_loss_case(600 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+    plain = hip_loss(stage, case, "bf16")["dW"]
+    big = torch.randn((V + 1, H), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV) * plain.abs().mean()
+    old = big.clone()
+    acc = hip_loss(stage, case, "bf16", dW=big[:V], accumulate_dw=True)["dW"]
+    assert torch.equal(acc, old[:V] + plain)
+    assert torch.equal(big[V], old[V])
+
+
 @pytest.mark.parametrize("H,V", [(64, 7), (320, 700), (192, 1025)])
 def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V):
     # up to 8192 tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
