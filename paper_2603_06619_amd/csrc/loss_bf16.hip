@@ -844,9 +844,6 @@ struct LogitsEpilogue {
     char* stage = lds + wave * (32 * kStageRow);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      // columns past the last token: their sums and, the contraction over tokens ending with the last slice that holds
-      // one, their numerators are read by nobody (as token rows of dH they yield rows that are not stored)
-      if (k0 + nb * 32 >= n_valid) break;
       const float nshift2 = -shift_of[nb] * kLog2e;
       float s2[2] = {0.f, 0.f}, t2[2] = {0.f, 0.f};        // two independent chains per sum
 #pragma unroll
