@@ -174,6 +174,7 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
   int i_lo = 0, i_hi = c.B;                                     // positions at or beyond N: any rollout (foreign mask)
   if (span_first < N) {                                         // the last rollout that starts at or before the first position
     i_lo = at[2] > 0 ? at[2] - 1 : 0;
+    i_lo = i_lo < c.B ? i_lo : c.B - 1;                         // offsets that do not ascend must not lead past the array
     i_hi = at[3] < c.B ? at[3] : c.B;
     i_hi = i_hi <= i_lo ? i_lo + 1 : i_hi;
   }
