@@ -5,6 +5,8 @@
 #include "nat_internal.h"
 #include "philox.hip.h"
 
+#include <type_traits>
+
 namespace nat {
 
 __global__ void advantage_kernel(const float* __restrict__ rewards, int P, int G, float eps_adv,
@@ -51,8 +53,7 @@ struct MaskArgs {
   uint32_t* mask_bits;
 };
 
-constexpr int kSelPerWave = 1024;                 // packed positions per wavefront: four strips of 256, four per lane
-constexpr int kSelPerBlock = 4 * kSelPerWave;
+constexpr int kStrip = 256;                       // packed positions of a wavefront's strip, four per lane
 
 // keep iff word < floor(p 2^32); p <= 0 or NaN: never, p >= 1: always
 __device__ __forceinline__ bool poisson_keep(uint32_t word, double p) {
@@ -61,15 +62,19 @@ __device__ __forceinline__ bool poisson_keep(uint32_t word, double p) {
 
 // Selection mask of every scheme.  Bound by the Philox rounds where tokens are drawn one by one (ten rounds of
 // two quarter-rate wide multiplies per block of four tokens), by latency at the sizes of a real batch.  A wavefront
-// finds the rollouts of its 1024 positions with two 64-wide searches.  If it is one rollout, that is uniform: lane
-// l owns Philox block first + 64 j + l of strip j, and since a block's four words serve four consecutive tokens of the
-// ROLLOUT, lanes whose four positions straddle two blocks take the second one's words from the next lane (the last
-// lane: from the first lane of the next strip): 5 evaluations per 4 strips instead of 8.  Else each lane searches.
+// owns kStrips strips of 256 positions (see strips_of) and finds their rollouts with two 64-wide searches.  If it is one
+// rollout, that is uniform: lane l owns Philox block first + 64 j + l of strip j, and since a block's four words serve
+// four consecutive tokens of the ROLLOUT, lanes whose four positions straddle two blocks take the second one's words from
+// the next lane (the last lane: from the first lane of the next strip): 5 evaluations per 4 strips instead of 8.  Else
+// each lane searches, strip after strip, and draws the cut of each rollout it meets anew (a Philox block, hidden by the
+// other lanes' loads: RPC masks of 2^25 tokens in rollouts of 16 take 69 us, 144 us with a launch that draws the cuts and
+// one that reads them).
 // Poisson mask of 2^26 tokens: 289 us with a search and up to two evaluations per lane, 144 us now (reading the
 // probabilities alone is 112 us); URS mask: 0.18 ms per 2^26 tokens before, 0.076 ms now.
-template <bool kPoisson>
+template <bool kPoisson, int kStrips>
 __global__ void __launch_bounds__(256)
 select_mask_kernel(SelectArgs a, MaskArgs m) {
+  constexpr int kSelPerWave = kStrips * kStrip;
   if (blockIdx.x >= m.mask_blocks) {               // the cut lengths themselves
     const int i = (int)(blockIdx.x - m.mask_blocks) * 256 + threadIdx.x;
     if (i >= m.B) return;
@@ -91,7 +96,7 @@ select_mask_kernel(SelectArgs a, MaskArgs m) {
     i_lo = at[0] > 0 ? at[0] - 1 : 0;
     i_hi = at[1] > i_lo ? at[1] : i_lo + 1;
   }
-  uint32_t nibble[4] = {0u, 0u, 0u, 0u};
+  uint32_t nibble[kStrips] = {};
   if (i_hi - i_lo == 1 && w0 + kSelPerWave <= n_end) {          // wavefront-uniform: one rollout
     const int64_t start = m.cu[i_lo], t_first = w0 - start;
     const int scheme = kPoisson ? NAT_SCHEME_URS : m.cut_in ? NAT_SCHEME_DET : a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
@@ -102,10 +107,10 @@ select_mask_kernel(SelectArgs a, MaskArgs m) {
       const uint32_t first = (uint32_t)(t_first >> 2) + lane, id = (uint32_t)(a.rollout_id_base + i_lo);
       u32x4 r = philox4x32_10(u32x4{first, id, 0u, a.step}, a.key0, a.key1), r_next{0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < kStrips; ++j) {
         double p[4];
         if (kPoisson) {
-          const double* q = m.pi + w0 + 256 * j + 4 * lane;
+          const double* q = m.pi + w0 + kStrip * j + 4 * lane;
           if (m.pi_wide) {
             const double2 x = *reinterpret_cast<const double2*>(q), y = *reinterpret_cast<const double2*>(q + 2);
             p[0] = x.x; p[1] = x.y; p[2] = y.x; p[3] = y.y;
@@ -114,7 +119,7 @@ select_mask_kernel(SelectArgs a, MaskArgs m) {
             for (int e = 0; e < 4; ++e) p[e] = q[e];
           }
         }
-        if (j < 3 || shift) r_next = philox4x32_10(u32x4{first + 64u * (j + 1), id, 0u, a.step}, a.key0, a.key1);
+        if (j + 1 < kStrips || shift) r_next = philox4x32_10(u32x4{first + 64u * (j + 1), id, 0u, a.step}, a.key0, a.key1);
         uint32_t w[4] = {r.x, r.y, r.z, r.w};
         if (shift) {                               // words shift.. of this block, then the first ones of the next
           const uint32_t up[3] = {(uint32_t)__shfl_down((int)r.x, 1), (uint32_t)__shfl_down((int)r.y, 1), (uint32_t)__shfl_down((int)r.z, 1)};
@@ -133,15 +138,15 @@ select_mask_kernel(SelectArgs a, MaskArgs m) {
     } else {
       const int64_t cut = m.cut_in ? (int64_t)m.cut_in[i_lo] : rollout_cut(a, scheme, i_lo, m.cu[i_lo + 1] - start);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t left = cut - (t_first + 256 * j + 4 * lane);    // kept positions from this lane's first one on
+      for (int j = 0; j < kStrips; ++j) {
+        const int64_t left = cut - (t_first + kStrip * j + 4 * lane);    // kept positions from this lane's first one on
         nibble[j] = left >= 4 ? 15u : left <= 0 ? 0u : (1u << left) - 1u;
       }
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t n0 = w0 + 256 * j + 4 * lane;
+    for (int j = 0; j < kStrips; ++j) {
+      const int64_t n0 = w0 + kStrip * j + 4 * lane;
       if (n0 >= n_end) continue;
       int i = rollout_of_pos(m.cu, i_lo, i_hi, n0);
       int64_t start = 0, end = n0, cut = 0;        // of rollout i, set below
@@ -180,12 +185,12 @@ select_mask_kernel(SelectArgs a, MaskArgs m) {
   }
   // the nibbles of eight lanes make a word; the mask has 2 ceil(N / 64) of them
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < kStrips; ++j) {
     uint32_t v = nibble[j] << (4 * (lane & 7));
     v |= __shfl_xor((int)v, 1);
     v |= __shfl_xor((int)v, 2);
     v |= __shfl_xor((int)v, 4);
-    const int64_t word = (w0 + 256 * j) / 32 + (lane >> 3);
+    const int64_t word = (w0 + kStrip * j) / 32 + (lane >> 3);
     if ((lane & 7) == 0 && (word >> 1) * 64 < m.N) m.mask_bits[word] = v;
   }
 }
@@ -210,24 +215,45 @@ nat_status validate_select(const nat_select_params* p, SelectArgs* out) {
   return NAT_OK;
 }
 
-static unsigned mask_blocks_of(int64_t N) { return (unsigned)((N + kSelPerBlock - 1) / kSelPerBlock); }
+// Strips per wavefront.  Where rollouts are short a wavefront's strips are a chain of searches, so a batch that does not
+// fill the chip is cut into more wavefronts; a large one shares the span's search and the straddling Philox blocks
+// over more strips.  1 / 2 / 4 strips, us: Poisson, rollouts of 16: 2^18 positions 5.0 / 6.3 / 10.5, 2^20 6.7 / 7.4 / 10.7,
+// 2^21 10.1 / 9.4 / 12.6, 2^23 37 / 30 / 36, 2^25 167 / 136 / 133; RPC, rollouts of 300: 2^20 5.0 / 5.0 / 6.8, 2^21 7.5 / 6.5 / 7.8,
+// 2^22 11.6 / 10.0 / 9.6, 2^23 21.0 / 16.5 / 15.5.  The fp64 thresholds of a Poisson mask make two strips the better
+// ones up to 2^23.
+static int strips_of(int64_t N, bool poisson) {
+  if (N <= (int64_t(1) << 20)) return 1;
+  return N <= (int64_t(1) << (poisson ? 23 : 21)) ? 2 : 4;
+}
+
+// One launch of the mask kernel; further blocks draw the cut lengths where they are asked for.
+template <bool kPoisson>
+static nat_status launch_mask(const SelectArgs& a, MaskArgs m, hipStream_t s) {
+  auto go = [&](auto strips) {
+    constexpr int kStrips = decltype(strips)::value, kPerBlock = 4 * kStrips * kStrip;
+    m.mask_blocks = (unsigned)((m.N + kPerBlock - 1) / kPerBlock);
+    const unsigned cut_blocks = m.cut_out ? (unsigned)((m.B + 255) / 256) : 0;
+    select_mask_kernel<kPoisson, kStrips><<<m.mask_blocks + cut_blocks, 256, 0, s>>>(a, m);
+  };
+  const int strips = strips_of(m.N, kPoisson);
+  if (strips == 1) go(std::integral_constant<int, 1>{});
+  else if (strips == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 4>{});
+  NAT_LAUNCH_CHECK();
+  return NAT_OK;
+}
 
 nat_status launch_prefix_mask(const int64_t* d_cu, int32_t B, int64_t N, const int32_t* d_cut_len,
                               uint32_t* d_mask_bits, hipStream_t s) {
   if (N <= 0) return NAT_OK;
-  select_mask_kernel<false><<<mask_blocks_of(N), 256, 0, s>>>(
-      SelectArgs{}, MaskArgs{d_cu, B, N, d_cut_len, nullptr, nullptr, 0, mask_blocks_of(N), d_mask_bits});
-  NAT_LAUNCH_CHECK();
-  return NAT_OK;
+  return launch_mask<false>(SelectArgs{}, MaskArgs{d_cu, B, N, d_cut_len, nullptr, nullptr, 0, 0, d_mask_bits}, s);
 }
 
 nat_status launch_poisson_mask(const SelectArgs& a, const double* d_pi, const int64_t* d_cu, int32_t B, int64_t N,
                                uint32_t* d_mask_bits, hipStream_t s) {
   if (N <= 0) return NAT_OK;
-  select_mask_kernel<true><<<mask_blocks_of(N), 256, 0, s>>>(
-      a, MaskArgs{d_cu, B, N, nullptr, nullptr, d_pi, ((uintptr_t)d_pi & 15) == 0, mask_blocks_of(N), d_mask_bits});
-  NAT_LAUNCH_CHECK();
-  return NAT_OK;
+  const int pi_wide = ((uintptr_t)d_pi & 15) == 0;
+  return launch_mask<true>(a, MaskArgs{d_cu, B, N, nullptr, nullptr, d_pi, pi_wide, 0, d_mask_bits}, s);
 }
 
 }  // namespace nat
@@ -257,9 +283,5 @@ extern "C" nat_status nat_select(const nat_select_params* params, const int64_t*
   if (N > 0 && !d_mask_bits) return NAT_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
   ProfScope prof(PC_SELECT, s);
-  const unsigned blocks = mask_blocks_of(N);        // the cut lengths are drawn by further blocks of the same launch
-  select_mask_kernel<false><<<blocks + (unsigned)((B + 255) / 256), 256, 0, s>>>(
-      a, MaskArgs{d_cu_seqlens, B, N, nullptr, d_cut_len, nullptr, 0, blocks, d_mask_bits});
-  NAT_LAUNCH_CHECK();
-  return NAT_OK;
+  return launch_mask<false>(a, MaskArgs{d_cu_seqlens, B, N, nullptr, d_cut_len, nullptr, 0, 0, d_mask_bits}, s);
 }

@@ -93,7 +93,7 @@ def test_uniform_schedule_weights_equal_the_uniform_rpc_closed_form(stage):
 
 @pytest.mark.parametrize("head", [0, 1, 2, 3])
 def test_masks_of_spans_inside_one_rollout(stage, head):
-    # spans of 1024 positions inside one rollout take the wavefront-uniform path: every position of the rollout's start
+    # a wavefront's span (256 positions at this size) inside one rollout takes the uniform path: every position of the rollout's start
     # relative to a block of four draws, span and strip boundaries, a rollout that ends at a span's end
     import paper_2603_06619_amd as nat
     lengths = [head, 3072 - head, 1024, 5000, 0, 1, 4099, 2, 2048, 1023]
@@ -114,6 +114,31 @@ def test_masks_of_spans_inside_one_rollout(stage, head):
         o = osel.select(cu, scheme, seed=9, step=4, rollout_id_base=3, **kw)
         cut = torch.full((B,), -1, dtype=torch.int32, device=DEV)
         mask = torch.full((nat.mask_words(N),), -1, dtype=torch.int32, device=DEV)
+        nat.nat_select(nat.SelectParams(scheme, seed=9, step=4, rollout_id_base=3, **dkw), to_dev(cu), B, N, cut, mask)
+        assert _mask_words(dict(mask_bits=mask), o["mask"])
+        assert np.array_equal(cut.cpu().numpy(), o["cut_len"])
+
+
+@pytest.mark.parametrize("N", [1 << 20, (1 << 20) + 1, 1 << 21, (1 << 21) + 1, (1 << 23) + 1])
+def test_masks_on_both_sides_of_the_strip_limits(stage, N):
+    # a wavefront owns 1, 2 or 4 strips of 256 positions: up to 2^20 positions, up to 2^21 (2^23 for a Poisson mask), beyond.
+    # Short and empty rollouts first, then long ones that start at every place of a block of four draws
+    import paper_2603_06619_amd as nat
+    rng = np.random.default_rng(N)
+    short = rng.integers(0, 40, 3000)
+    rest = N - int(short.sum())
+    lengths = np.concatenate([short, np.full(13, rest // 13), [rest % 13, 0]])
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    B = len(lengths)
+    assert cu[-1] == N
+    mask = torch.full((nat.mask_words(N),), -1, dtype=torch.int32, device=DEV)
+    p = rng.random(N)
+    nat.nat_select_poisson(_params(9, 4, 3), to_dev(p), to_dev(cu), B, N, mask)
+    assert _mask_words(dict(mask_bits=mask), osch.select_poisson(cu, p, seed=9, step=4, rollout_id_base=3))
+    for scheme, kw, dkw in ((nat.URS, dict(p=0.3), dict(p=0.3)), (nat.RPC, dict(C=5), dict(min_cut=5))):
+        o = osel.select(cu, scheme, seed=9, step=4, rollout_id_base=3, **kw)
+        cut = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+        mask.fill_(-1)
         nat.nat_select(nat.SelectParams(scheme, seed=9, step=4, rollout_id_base=3, **dkw), to_dev(cu), B, N, cut, mask)
         assert _mask_words(dict(mask_bits=mask), o["mask"])
         assert np.array_equal(cut.cpu().numpy(), o["cut_len"])
