@@ -12,8 +12,16 @@
 
 namespace nat {
 
-constexpr int64_t kLongRollout = 1024;            // mean length from which schedule_cut_kernel uses 1024 threads
-
+// Threads of schedule_cut_kernel's block (one block per rollout).  1024 where a rollout's chain of block scans is the
+// time: rollouts longer than 1024 on average and no more of them than compute units, or two or three times as many
+// very long ones.  With more rollouts blocks of 256 share the compute units better.  Whole call, 256 / 1024 threads, us:
+// mean length 1500: 128 rollouts 10.2 / 9.0, 512 12.2 / 14.3, 16384 148 / 319; 4000: 128 15.8 / 12.1, 512 21.9 / 23.3,
+// 2048 47 / 71; 8000: 256 30 / 21, 512 39 / 37, 768 48 / 52, 2048 81 / 112; 16000: 768 97 / 92, 1024 116 / 123; 30000: 512
+// 144 / 116, 768 176 / 169, 1024 237 / 249.
+static int schedule_threads(int64_t N, int32_t B) {
+  const int64_t mean = N / B;
+  return (mean > 1024 && B <= 256) || (mean > 6000 && B <= 512) || (mean > 12000 && B <= 768) ? 1024 : 256;
+}
 
 // Inclusive scan of one 64-bit value per thread over the block; *total = block sum.
 // `wave_tot` is a word of LDS per wavefront; the caller separates successive calls with a barrier.
@@ -38,8 +46,8 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* wave_to
 }
 
 // One block per rollout: total weight, the cut by inversion of the running sum, and the
-// survival function for every position.  Bound by the chain of block scans over the longest rollout: 1024 threads
-// (4096 positions per scan) where rollouts are long, 256 where many short ones have to share the compute units.
+// survival function for every position.  Bound by the chain of block scans over the longest rollout (4 positions per
+// thread and scan) in a small batch, by the bytes in a large one.  See schedule_threads.
 template <int kThreads>
 __global__ void __launch_bounds__(kThreads)
 schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout_id_base,
@@ -201,7 +209,7 @@ extern "C" nat_status nat_select_schedule(const nat_select_params* params, const
         (uint32_t)(params->seed & 0xFFFFFFFFull), (uint32_t)(params->seed >> 32), params->step,
         params->rollout_id_base, params->d_drop_zero_adv, d_weights, d_cu_seqlens, N, d_cut_len, d_pi);
   };
-  if (N / B > kLongRollout) go(std::integral_constant<int, 1024>{});
+  if (schedule_threads(N, B) == 1024) go(std::integral_constant<int, 1024>{});
   else go(std::integral_constant<int, 256>{});
   NAT_LAUNCH_CHECK();
   return launch_prefix_mask(d_cu_seqlens, B, N, d_cut_len, d_mask_bits, s);

@@ -78,6 +78,27 @@ def test_schedule_full_size_batch_and_gather(stage):
     assert np.array_equal(h["ids_k"].cpu().numpy()[:oc["n_kept"]], ids[oc["kept_idx"]])
 
 
+@pytest.mark.parametrize("B,mean", [(256, 1030), (257, 1030), (512, 6010), (513, 6010)])
+def test_schedule_on_both_sides_of_the_block_size_limits(stage, B, mean):
+    # blocks of 1024 threads up to 256 rollouts longer than 1024 on average, or 512 longer than 6000; else 256.  One rollout
+    # holds a large share of the tokens, some are shorter than a block, some empty
+    import paper_2603_06619_amd as nat
+    rng = np.random.default_rng(B)
+    lengths = rng.integers(0, mean, B)
+    lengths[5] += B * mean + 1 - int(lengths.sum())
+    cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    N = int(cu[-1])
+    w = si.draw_schedule_weights(lengths, "random", seed=B)
+    o = osch.select_schedule(cu, w, seed=5, step=2)
+    cut = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+    mask = torch.full((nat.mask_words(N),), -1, dtype=torch.int32, device=DEV)
+    pi = torch.full((N,), -1.0, dtype=torch.float64, device=DEV)
+    nat.nat_select_schedule(_params(5, 2), to_dev(w.view(np.int32)), to_dev(cu), B, N, cut, mask, pi)
+    assert np.array_equal(cut.cpu().numpy(), o["cut_len"])
+    assert _mask_words(dict(mask_bits=mask), o["mask"])
+    assert np.array_equal(pi.cpu().numpy().view(np.uint64), o["pi"].view(np.uint64))
+
+
 def test_uniform_schedule_weights_equal_the_uniform_rpc_closed_form(stage):
     # property at any size: all-ones weights give p_t = (T - t + 1)/T on the device as well
     lay = si.batch_layout("qwen3_8b_long_cot", 3000, P=4, G=4)
