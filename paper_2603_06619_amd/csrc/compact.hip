@@ -49,7 +49,7 @@ compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, in
   if (lane == 0) tile_count[tile] = c;
 }
 
-// tile_offset[0..n_tiles] = exclusive scan of tile_count.  One block, kScanPer consecutive tiles per thread.
+// tile_offset[0..n_tiles) = exclusive scan of tile_count.  One block, kScanPer consecutive tiles per thread.
 constexpr int kScanPer = 8;
 __global__ void __launch_bounds__(1024)
 compact_scan_kernel(const int32_t* __restrict__ tile_count, int n_tiles, int32_t* __restrict__ tile_offset) {
@@ -137,10 +137,10 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
     if (c.tile_count) for (int j = tid; j < tile; j += kThreads) before += c.tile_count[j];
     else for (int j = tid; j < tile * kTileWords; j += kThreads) before += __popc(c.mask_bits[j]);
   }
-  // rollouts of this wavefront's positions: how many start before the span, at or before its first position, before its end
+  // how many rollouts start before the tile, before its end; at or before this wavefront's first position, its last one
   const int64_t N = c.cu[c.B], span_first = tile_first + wave * (kGroups * 64), span_end = span_first + kGroups * 64;
   const int64_t span_last = span_end - 1 < N ? span_end - 1 : N - 1;
-  const int64_t key[4] = {span_first, span_end, span_first + 1, span_last + 1};
+  const int64_t key[4] = {tile_first, tile_first + kTileTokens, span_first + 1, span_last + 1};
   int at[4];
   wave_lower_bounds<4>(c.cu, c.B + 1, key, at);
   const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
@@ -159,14 +159,22 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
     for (int w = 0; w < kWaves; ++w) tile_base += wave_before[w];
   __syncthreads();
   if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + prefix[kTileWords];
-  // offsets of the rollouts that start in this span (offsets outside [0, n_tokens] count as its ends)
-  const int r0 = span_first == 0 ? 0 : at[0];
-  const int r1 = tile == n_tiles - 1 && wave == kWaves - 1 ? c.B + 1 : at[1];
-  for (int i = r0 + lane; i < r1; i += 64) {
-    const int64_t pos = c.cu[i] < 0 ? 0 : c.cu[i] > c.n_tokens ? c.n_tokens : c.cu[i];
-    const int64_t off = pos - tile_first;
-    const int rel = off < 0 ? 0 : off > kTileTokens ? kTileTokens : (int)off, w = rel >> 5, rem = rel & 31;
-    c.cu_kept[i] = tile_base + prefix[w] + (rem ? __popc(words[w] & ((1u << rem) - 1u)) : 0);
+  // Offsets of the rollouts that start in this tile (offsets outside [0, n_tokens] count as its ends), by the whole block
+  // and four loads at a time: empty rollouts can put any number of them at one position.  Compaction of 100 rollouts of 1000
+  // tokens and 4000 / 65000 / a million empty ones: 17.8 / 210 / 5300 us by the wavefront of their span, 8.7 / 22 / 311 by the block.
+  const int r0 = tile == 0 ? 0 : at[0], r1 = tile == n_tiles - 1 ? c.B + 1 : at[1];
+  for (int i0 = r0 + tid; i0 < r1; i0 += 4 * kThreads) {
+    int64_t start[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) start[e] = r1 - i0 > e * kThreads ? c.cu[i0 + e * kThreads] : 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (r1 - i0 <= e * kThreads) break;
+      const int64_t pos = start[e] < 0 ? 0 : start[e] > c.n_tokens ? c.n_tokens : start[e];
+      const int64_t off = pos - tile_first;
+      const int rel = off < 0 ? 0 : off > kTileTokens ? kTileTokens : (int)off, w = rel >> 5, rem = rel & 31;
+      c.cu_kept[i0 + e * kThreads] = tile_base + prefix[w] + (rem ? __popc(words[w] & ((1u << rem) - 1u)) : 0);
+    }
   }
 
   constexpr int kSpanWords = kGroups * 2;

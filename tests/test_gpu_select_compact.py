@@ -143,3 +143,15 @@ def test_compaction_at_tile_and_scan_boundaries(stage, n_tiles, extra):
         k = o["kept_idx"]
         assert np.array_equal(h["ids_k"].cpu().numpy()[:len(k)], ids[k])
         assert np.array_equal(h["old_logp_k"].cpu().numpy()[:len(k)], old[k])
+
+
+@pytest.mark.parametrize("N", [1, 4096, 9000, 4096 * 129 + 5, 4096 * 1025 + 3])
+def test_compaction_offsets_of_long_runs_of_empty_rollouts(stage, N):
+    # a tile's block writes the offsets of all rollouts that start in it, 1024 (256 above 1024 tiles) x 4 at a time: runs of
+    # empty rollouts around multiples of that, at the start, at a tile's edge, inside and at N
+    rng = np.random.default_rng(N)
+    inside = rng.integers(0, N + 1, 40)
+    runs = [(0, 1022), (min(4095, N), 1024), (min(4096, N), 4097), (min(4097, N), 8192), (N // 2, 30000), (N, 9000)]
+    cu = np.sort(np.concatenate([[0, N], inside] + [np.full(n, pos) for pos, n in runs])).astype(np.int64)
+    o = oracle_select_compact(cu, osel.DET, beta=0.5)
+    assert_select_compact_equal(hip_select_compact(stage, cu, osel.DET, beta=0.5), o, N)
