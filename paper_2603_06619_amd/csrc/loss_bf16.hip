@@ -31,7 +31,7 @@
 // contiguous), ordered k-fastest inside a 256-row tile, so a workgroup streams one contiguous
 // region per operand instead of 256 strided rows.  W and H_chunk are repacked (plain and
 // transposed); the soft-max numerators are produced directly in that layout.  Short batches do not
-// repack W (kDirectTokens): the logits contraction reads its rows, the dH contraction, turned round to
+// repack W (direct_tokens): the logits contraction reads its rows, the dH contraction, turned round to
 // dH^T = W^T E^T, reads them as a k-major operand.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
@@ -1475,11 +1475,16 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 // Up to how many tokens a call reads W as it is instead of repacking it first.  The repack moves W three times with the
 // backward pass (0.77 ms at V x H = 151936 x 4096, 0.21 ms at H = 1024), twice without (0.50 / 0.12 ms), whatever the
 // batch; reading rows costs the logits contraction 1 to 2 % and the dH contraction, with its transposing reads, 3 to
-// 5 %.  Measured, repacked against direct, whole call in ms: 59 tokens 1.92 / 1.19 (H = 4096), 0.61 / 0.42 (H = 1024);
-// 1237: 4.69 / 4.13; 6144: 17.8 / 17.4 (H = 4096), 5.11 / 5.03 (H = 1024); 7000 at H = 3584: 18.9 / 18.75; 8192 at
-// H = 5120: 29.40 / 29.50; 24576: 68.55 / 69.1 (H = 4096).  Forward pass alone: 301 tokens 0.29 / 0.18 (H = 1024), 12289:
-// 12.07 / 11.65 (H = 4096), 32768: 30.88 / 30.64 (H = 4096), 8.48 / 8.38 (H = 1024), 65536: equal, 131072: 120.3 / 120.6.
-constexpr int kDirectTokens = 8192, kDirectTokensForward = 49152;
+// 5 %, so the gain shrinks with the batch.  The lines are where it ends for the last of the hidden sizes; repacked against
+// direct in alternating runs, whole call, ms at V = 151936 unless stated.  H a multiple of the 256-wide dH tile: 1500 tokens
+// 5.56 / 4.99 (H = 4096), 1.55 / 1.41 (1024); 5000: 15.1 / 14.6, 4.17 / 4.07; 7168: 21.7 / 21.2 (4096), 5.75 / 5.66 (1024), 27.08 / 26.96
+// (5120); 8192: 23.5 / 23.2 (4096) but 29.4 / 29.7 (5120).  Other H, whose dH tiles are padded (the work grows with the
+// tiles, the repack with H): 1500: 1.08 / 0.97 (576), 0.80 / 0.72 (320); 5000: 2.88 / 2.87, 2.03 / 2.00; 6144: 3.46 / 3.48, 2.39 / 2.39; 7168: 3.97 / 4.01, 2.77 / 2.81;
+// 8192 at V = 50000: 1.08 / 1.10 (320).  Forward pass alone: 2000 tokens 2.42 / 1.98 (4096), 0.68 / 0.59 (1024); 12289 with the
+// entropy: 12.02 / 11.79, 3.52 / 3.38; 24576: 24.4 / 24.1, 6.42 / 6.37, 29.9 / 29.7 (5120); 49152: 45.7 / 45.7, 12.9 / 12.9, 57.0 / 57.8; with
+// contractions of a few slices 5000: 0.386 / 0.386 (H = 64, V = 160000), 16384: 1.19 / 1.20.
+static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }
+static int direct_tokens_forward(int H) { return H >= kBN ? 24576 : 8192; }
 
 // Up to how many k-slices (32 tokens) a chunk is added to dW by reading, adding and storing instead of by atomics.
 // Accumulating call, atomics against read-add-store, ms at V x H = 151936 x 4096: 59 tokens 2.47 / 1.66, 300: 2.88 / 2.23,
@@ -1525,7 +1530,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
   const int H = a.H, V = a.V;
   const int Vp = (int)p.Vp, Hp = (int)p.Hp;
 
-  const bool direct = a.N_k <= kDirectTokens;
+  const bool direct = a.N_k <= direct_tokens(H);
   if (!direct) {  // W and W^T in the blocked layout, padding zero-filled
     ProfScope prof(PC_TRANSPOSE, s);
     pack_blocked_kernel<<<dim3(Vp / 64, Hp / 64), 256, 0, s>>>(W, H, V, H, Vp, Hp, Wb, Wtb, Vp / 32, nullptr);
@@ -1648,7 +1653,7 @@ nat_status logp_bf16_run(const LogpArgs& a) {
   const uint16_t* W = (const uint16_t*)a.W;
   const uint16_t* hidden = (const uint16_t*)a.hidden;
   const int H = a.H, V = a.V, Vp = (int)p.Vp;
-  const bool direct = a.N_k <= kDirectTokensForward;
+  const bool direct = a.N_k <= direct_tokens_forward(H);
   if (!direct) {
     ProfScope prof(PC_TRANSPOSE, s);
     pack_blocked_kernel<<<dim3(Vp / 64, H / 64), 256, 0, s>>>(W, H, V, H, Vp, H, Wb, nullptr, 0, nullptr);

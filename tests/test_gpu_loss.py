@@ -237,11 +237,10 @@ def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok):
     assert torch.equal(big[V], old[V])
 
 
-@pytest.mark.parametrize("H,V", [(64, 7), (320, 700), (192, 1025)])
-def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V):
-    # up to 8192 tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
+@pytest.mark.parametrize("H,V,n", [(64, 7, 6144), (320, 700, 6144), (192, 1025, 6144), (256, 700, 7168)])
+def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V, n):
+    # up to n tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
     # order, so the log-probs of the common tokens are equal bit for bit, and each side meets the path's tolerance
-    n = 8192
     case = make_loss_case(77, n + 1, H, V, "bf16", noise=0.15, w_std=0.1)
     short = {k: (v[:n] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
     packed, direct = hip_loss(stage, case, "bf16"), hip_loss(stage, short, "bf16")
@@ -250,6 +249,17 @@ def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V):
     check(packed, oracle_loss(**case), n + 1, TOL_BF16, case)
     fwd = stage.logp(to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"]), n + 1)
     assert torch.equal(fwd["logp"][:n + 1], packed["logp"][:n + 1])
+
+
+@pytest.mark.parametrize("H,V,n", [(64, 700, 8192), (192, 1025, 8192), (256, 300, 24576)])
+def test_bf16_forward_pass_w_repacked_and_read_as_it_is_agree(stage, H, V, n):
+    # the same for the forward pass alone: the common tokens' log-probs and entropies, bit for bit
+    case = make_loss_case(78, n + 1, H, V, "bf16", noise=0.15, w_std=0.1)
+    hidden, W, ids = to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"])
+    packed = {k: v.clone() for k, v in stage.logp(hidden, W, ids, n + 1, want_entropy=True).items() if v is not None}
+    direct = stage.logp(hidden[:n], W, ids[:n], n, want_entropy=True)
+    assert torch.equal(packed["logp"][:n], direct["logp"][:n])
+    assert torch.equal(packed["entropy"][:n], direct["entropy"][:n])
 
 
 @pytest.mark.parametrize("n_tok,H,V,label", [
