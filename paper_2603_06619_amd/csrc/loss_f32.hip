@@ -9,6 +9,8 @@
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
 
+#include <type_traits>
+
 namespace nat {
 
 constexpr int kF32Threads = 256;
@@ -29,7 +31,12 @@ __device__ __forceinline__ float wave_max_f(float v) {
 // for both operands.  A k-major operand is read as that, 32 consecutive floats per half-wavefront.  A
 // k-contiguous one is read in whole 128-byte pieces of its rows and turned through the wavefront's own LDS (read
 // lane by lane from 32 rows at once it cost four times the address cycles and bound the kernel).
-// Measured at 601 tokens, V = 4096, H = 256: logits 25 us, dH 31 us, dW 30 us (44 TFLOP/s; latency of the short
+// The logits (both operands k-contiguous) are summed in groups of 8 products, a wavefront's groups in a chain of H / 64 and the
+// wavefronts in fp64: no logit is rounded more often than by 64 lanes with H / 64 products each and a tree over them
+// (in one chain of H / 8 per wavefront its error was 1.5 times that at H = 256, 2.6 times at H = 4096; the groups cost the
+// launch 1.5 of 28 us at H = 256, 5 of 65 at H = 1024).  Operands are then read four products at a time: with all
+// sixteen in registers the kernel needs 163, and only one workgroup fits a compute unit (35 us).
+// Measured at 601 tokens, V = 4096, H = 256: logits 27 us, dH 31 us, dW 30 us (44 TFLOP/s; latency of the short
 // ranges); one block per token (logits, dH) and per vocabulary row (dW) on the vector ALU took 2500 us for the three.
 // 64 x 64 tiles (half the reads) and sixteen wavefronts were slower or equal.
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -87,13 +94,17 @@ struct F32Operand {
       for (int i = 0; i < 16; ++i) turn[(2 * i + (lane >> 5)) * kF32Row + (lane & 31)] = r[i];
     }
   }
+  // operands of products 4 q .. 4 q + 3 of a step (k-contiguous)
+  __device__ __forceinline__ float4 read4(int q) const {
+    return *reinterpret_cast<const float4*>(turn + (lane & 31) * kF32Row + 8 * q + 4 * (lane >> 5));
+  }
   __device__ __forceinline__ void get(const float (&r)[16], float (&v)[16]) const {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if constexpr (KMajor) {
         v[4 * q] = r[4 * q]; v[4 * q + 1] = r[4 * q + 1]; v[4 * q + 2] = r[4 * q + 2]; v[4 * q + 3] = r[4 * q + 3];
       } else {
-        const float4 x = *reinterpret_cast<const float4*>(turn + (lane & 31) * kF32Row + 8 * q + 4 * (lane >> 5));
+        const float4 x = read4(q);
         v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
       }
     }
@@ -101,9 +112,10 @@ struct F32Operand {
 };
 
 template <bool KMajorA, bool KMajorB, bool Vec>
-__global__ void __launch_bounds__(kF32Waves * 64)
+__global__ void __launch_bounds__(kF32Waves * 64, !KMajorA && !KMajorB && Vec ? 4 : 1)   // logits: two workgroups per compute unit
 f32_gemm_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, int M, int N, int K,
                 int tiles_n, float* __restrict__ C, int64_t ldc, int accumulate) {
+  constexpr bool kGroups = !KMajorA && !KMajorB;             // the logits
   constexpr int kTurn = 32 * kF32Row, kTurns = (KMajorA ? 0 : 1) + (KMajorB ? 0 : 1), kPart = 32 * 33;
   __shared__ __attribute__((aligned(16))) float lds[kF32Waves * (kTurns * kTurn > kPart ? kTurns * kTurn : kPart)];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lhi = lane >> 5;
@@ -133,12 +145,30 @@ f32_gemm_kernel(const float* __restrict__ A, int64_t lda, const float* __restric
       a.put(ra);
       b.put(rb);
       __builtin_amdgcn_wave_barrier();
-      a.get(ra, va);
-      b.get(rb, vb);
-      if (k + kF32Step < k_end) fetch(k + kF32Step);
-      __builtin_amdgcn_wave_barrier();
+      if constexpr (kGroups) {
+        if (k + kF32Step < k_end) fetch(k + kF32Step);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[j], vb[j], acc, 0, 0, 0);
+        for (int q = 0; q < 4; ++q) {
+          const float4 x = a.read4(q), y = b.read4(q);
+          f32x16 group;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) group[r] = 0.f;
+          group = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, group, 0, 0, 0);
+          group = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, group, 0, 0, 0);
+          group = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, group, 0, 0, 0);
+          group = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, group, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[r] += group[r];
+        }
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        a.get(ra, va);
+        b.get(rb, vb);
+        if (k + kF32Step < k_end) fetch(k + kF32Step);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(va[j], vb[j], acc, 0, 0, 0);
+      }
     }
   }
   __syncthreads();
@@ -149,12 +179,12 @@ f32_gemm_kernel(const float* __restrict__ A, int64_t lda, const float* __restric
 #pragma unroll
   for (int e = threadIdx.x; e < 1024; e += kF32Waves * 64) {
     const int i = e >> 5, j = e & 31;
-    float s = 0.f;
+    typename std::conditional<kGroups, double, float>::type s = 0;
 #pragma unroll
     for (int w = 0; w < kF32Waves; ++w) s += lds[w * kPart + i * 33 + j];
     if (m0 + i < M && n0 + j < N) {
       float* c = C + (int64_t)(m0 + i) * ldc + n0 + j;
-      *c = accumulate ? *c + s : s;
+      *c = accumulate ? *c + (float)s : (float)s;
     }
   }
 }

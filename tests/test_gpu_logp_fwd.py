@@ -33,6 +33,28 @@ def test_fp32_forward(stage, n_tok, H, V):
     assert max_rel_err(out["entropy"].cpu().numpy()[:n_tok], ref["entropy"]) <= 1e-5
 
 
+@pytest.mark.parametrize("H", [1023, 1024, 4096, 15360])
+def test_fp32_forward_rounding_of_long_contractions(stage, H):
+    # Logits of standard deviation 0.5 sqrt(H): their rounding is what the log-probs carry.  Bound: products of variance 0.25 summed in
+    # groups of 8, G = H / 64 groups of each of 8 wavefronts in a chain, the wavefronts exactly, one rounding.  A rounding of x
+    # errs by at most |x| u / sqrt(3) rms (u = 2^-24, x at the lower end of its binade), and the partial sums of n products
+    # have variance 0.25 n: 4.5 per product inside the groups, 8 sum_j 8 j over the chains, H at the end.  A log-prob has
+    # two logits (the soft-max is peaked) and its own rounding.
+    n, V = 512, 96
+    rng = np.random.default_rng(H)
+    hidden = rng.standard_normal((n, H)).astype(np.float32)
+    W = (0.5 * rng.standard_normal((V, H))).astype(np.float32)
+    ids = rng.integers(0, V, n).astype(np.int32)
+    ref = ogrpo.forward_logp(hidden, W, ids)["logp"]
+    logp = stage.logp(to_dev(hidden), to_dev(W), to_dev(ids), n)["logp"].cpu().numpy().astype(np.float64)
+    G, unit = -(-H // 64), 2.0 ** -24 / np.sqrt(3.0)
+    var_logit = unit ** 2 * 0.25 * (4.5 * H + 32.0 * G * (G + 1) + H)
+    bound = np.sqrt(2.0 * var_logit + unit ** 2 * np.mean(ref ** 2))
+    rms = np.sqrt(np.mean((logp - ref) ** 2))
+    print("H %d: rms error of the log-probs %.2e, bound %.2e" % (H, rms, bound))
+    assert rms <= bound
+
+
 @pytest.mark.parametrize("n_tok,H,V", [(300, 128, 1000), (700, 256, 5000), (1, 64, 130), (300, 320, 1500)])
 def test_bf16_forward(stage, n_tok, H, V):
     case = make_loss_case(160 + n_tok, n_tok, H, V, "bf16", w_std=0.1)
