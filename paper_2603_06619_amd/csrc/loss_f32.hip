@@ -189,16 +189,27 @@ f32_gemm_kernel(const float* __restrict__ A, int64_t lda, const float* __restric
   }
 }
 
+// A launch holds fewer than 2^32 work-items, 2^23 tiles (of more, HIP runs what is left modulo 2^32 and reports nothing): larger
+// products, a chunk of 2^33 logits, take several.
 template <bool KMajorA, bool KMajorB>
 static nat_status f32_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, float* C,
                            int64_t ldc, int accumulate, hipStream_t s) {
-  const int tiles_n = (N + 31) / 32;
-  const unsigned grid = (unsigned)((int64_t)((M + 31) / 32) * tiles_n);
+  constexpr int64_t kMaxTiles = ((int64_t(1) << 32) - 1) / (kF32Waves * 64), kMaxCols = 1 << 20;
   // 16-byte reads of a k-contiguous operand need its rows to start on 16 bytes
   const bool vec = (KMajorA || lda % 4 == 0) && (KMajorB || ldb % 4 == 0);
-  if (vec) f32_gemm_kernel<KMajorA, KMajorB, true><<<grid, kF32Waves * 64, 0, s>>>(A, lda, B, ldb, M, N, K, tiles_n, C, ldc, accumulate);
-  else f32_gemm_kernel<KMajorA, KMajorB, false><<<grid, kF32Waves * 64, 0, s>>>(A, lda, B, ldb, M, N, K, tiles_n, C, ldc, accumulate);
-  NAT_LAUNCH_CHECK();
+  for (int64_t n0 = 0; n0 < N; n0 += kMaxCols) {
+    const int cols = (int)(N - n0 < kMaxCols ? N - n0 : kMaxCols), tiles_n = (cols + 31) / 32;
+    const int64_t max_rows = kMaxTiles / tiles_n * 32;
+    for (int64_t m0 = 0; m0 < M; m0 += max_rows) {
+      const int rows = (int)(M - m0 < max_rows ? M - m0 : max_rows);
+      const unsigned grid = (unsigned)((rows + 31) / 32) * (unsigned)tiles_n;
+      const float *a = A + (KMajorA ? m0 : m0 * lda), *b = B + (KMajorB ? n0 : n0 * ldb);
+      float* c = C + m0 * ldc + n0;
+      if (vec) f32_gemm_kernel<KMajorA, KMajorB, true><<<grid, kF32Waves * 64, 0, s>>>(a, lda, b, ldb, rows, cols, K, tiles_n, c, ldc, accumulate);
+      else f32_gemm_kernel<KMajorA, KMajorB, false><<<grid, kF32Waves * 64, 0, s>>>(a, lda, b, ldb, rows, cols, K, tiles_n, c, ldc, accumulate);
+      NAT_LAUNCH_CHECK();
+    }
+  }
   return NAT_OK;
 }
 

@@ -55,6 +55,26 @@ def test_fp32_forward_rounding_of_long_contractions(stage, H):
     assert rms <= bound
 
 
+def test_fp32_forward_of_more_tiles_than_one_launch_holds(stage):
+    # 257 x 32770 tiles of 32 x 32 logits in one chunk (34 GB of workspace): more than the 2^32 work-items of a launch.
+    # Every token as with chunks of 512, bit for bit, and some of them against the oracle
+    n, H, V = 8200, 4, (1 << 20) + 40
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    hidden = torch.randn((n, H), generator=gen, device=DEV)
+    W = torch.randn((V, H), generator=gen, device=DEV)
+    ids = torch.randint(0, V, (n,), generator=gen, device=DEV, dtype=torch.int32)
+    ids[-1] = V - 1
+    whole = {k: v.clone() for k, v in stage.logp(hidden, W, ids, n, want_entropy=True, ws_bytes=256 + n * V * 4).items()
+             if v is not None}
+    stage._ws.clear()
+    parts = stage.logp(hidden, W, ids, n, want_entropy=True, ws_bytes=256 + 512 * V * 4)
+    assert torch.equal(whole["logp"], parts["logp"]) and torch.equal(whole["entropy"], parts["entropy"])
+    some = torch.tensor([0, 31, 4100, 8159, 8160, 8191, 8192, n - 1], device=DEV)
+    ref = ogrpo.forward_logp(hidden[some].cpu().numpy(), W.cpu().numpy(), ids[some].cpu().numpy())
+    assert max_rel_err(whole["logp"][some].cpu().numpy(), ref["logp"]) <= 1e-5
+    assert max_rel_err(whole["entropy"][some].cpu().numpy(), ref["entropy"]) <= 1e-5
+
+
 @pytest.mark.parametrize("n_tok,H,V", [(300, 128, 1000), (700, 256, 5000), (1, 64, 130), (300, 320, 1500)])
 def test_bf16_forward(stage, n_tok, H, V):
     case = make_loss_case(160 + n_tok, n_tok, H, V, "bf16", w_std=0.1)

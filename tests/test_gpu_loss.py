@@ -85,6 +85,14 @@ def test_fp32_contraction_remainders(stage, n_tok, H, V):
     check(hip_loss(stage, case, "f32"), ref, n_tok, TOL_F32, case)
 
 
+def test_fp32_vocabulary_beyond_the_columns_of_one_launch(stage):
+    # the contractions take 2^20 columns of the logits to a launch.  (Whole tensors only: a wavefront's chain of 2^17 terms of dH
+    # rounds by up to 2^17 x 2^-24 of the sum of their magnitudes, 8e-3 of the small part that check() takes alone)
+    case = make_loss_case(9, 40, 4, (1 << 20) + 40, "f32", noise=0.15)
+    case["ids"][:3] = [(1 << 20) - 1, 1 << 20, (1 << 20) + 39]
+    check(hip_loss(stage, case, "f32"), oracle_loss(**case), 40, TOL_F32)
+
+
 def test_fp32_chunked_workspace_and_accumulate(stage):
     import paper_2603_06619_amd as nat
     case = make_loss_case(5, 50, 64, 512, "f32")
