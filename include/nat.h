@@ -335,8 +335,8 @@ size_t nat_loss_workspace_min_bytes(int32_t N_k, int32_t H, int32_t V, int32_t d
  *   and dW (nat_loss_fwd_bwd_kl counts those too).
  * N_k = 0 is valid: loss = 0, d_dW zeroed unless accumulating, d_dH_k untouched.
  *   Alignment: d_hidden_k, d_W, d_dH_k, d_dW 16 bytes; d_ws 256 bytes (else NAT_INVALID_ARG).
- * Errors: NULL pointer, N_k < 0, eps < 0 -> NAT_INVALID_ARG; H <= 0, V <= 0, or (bf16) H not
- * a multiple of 64 -> NAT_BAD_SHAPE; dtype unknown -> NAT_UNSUPPORTED_DTYPE; ws_bytes below
+ * Errors: NULL pointer, N_k < 0, eps < 0 -> NAT_INVALID_ARG; H <= 0, V <= 0, (bf16) H not
+ * a multiple of 64 or (f32) H > 15360 -> NAT_BAD_SHAPE; dtype unknown -> NAT_UNSUPPORTED_DTYPE; ws_bytes below
  * nat_loss_workspace_min_bytes -> NAT_WORKSPACE_TOO_SMALL.
  */
 nat_status nat_loss_fwd_bwd(const void* d_hidden_k, const void* d_W, const int32_t* d_ids_k,

@@ -14,6 +14,8 @@
 namespace nat {
 
 constexpr int kF32Threads = 256;
+// Larger hidden sizes have always been refused on this path, and are; its kernels have no such bound of their own.
+constexpr int kF32MaxHidden = 15360;
 
 __device__ __forceinline__ float wave_max_f(float v) {
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
@@ -205,8 +207,12 @@ static nat_status f32_gemm(const float* A, int64_t lda, const float* B, int64_t 
       const unsigned grid = (unsigned)((rows + 31) / 32) * (unsigned)tiles_n;
       const float *a = A + (KMajorA ? m0 : m0 * lda), *b = B + (KMajorB ? n0 : n0 * ldb);
       float* c = C + m0 * ldc + n0;
-      if (vec) f32_gemm_kernel<KMajorA, KMajorB, true><<<grid, kF32Waves * 64, 0, s>>>(a, lda, b, ldb, rows, cols, K, tiles_n, c, ldc, accumulate);
-      else f32_gemm_kernel<KMajorA, KMajorB, false><<<grid, kF32Waves * 64, 0, s>>>(a, lda, b, ldb, rows, cols, K, tiles_n, c, ldc, accumulate);
+      auto go = [&](auto wide) {
+        f32_gemm_kernel<KMajorA, KMajorB, decltype(wide)::value><<<grid, kF32Waves * 64, 0, s>>>(a, lda, b, ldb, rows, cols, K, tiles_n, c, ldc, accumulate);
+      };
+      if constexpr (KMajorA && KMajorB) go(std::true_type{});         // no k-contiguous operand: nothing to widen
+      else if (vec) go(std::true_type{});
+      else go(std::false_type{});
       NAT_LAUNCH_CHECK();
     }
   }
@@ -313,7 +319,7 @@ size_t loss_f32_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal)
 }
 
 nat_status loss_f32_run(const LossArgs& a) {
-  if ((size_t)a.H * sizeof(float) > 60 * 1024) return NAT_BAD_SHAPE;      // the path's bound on H (15360)
+  if (a.H > kF32MaxHidden) return NAT_BAD_SHAPE;
   const int rows = f32_chunk_rows(a.N_k, a.V, a.ws_bytes);
   if (rows < 1) return NAT_WORKSPACE_TOO_SMALL;
   float* term = (float*)a.ws;
@@ -372,7 +378,7 @@ size_t logp_f32_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal)
 }
 
 nat_status logp_f32_run(const LogpArgs& a) {
-  if ((size_t)a.H * sizeof(float) > 60 * 1024) return NAT_BAD_SHAPE;
+  if (a.H > kF32MaxHidden) return NAT_BAD_SHAPE;
   if (a.ws_bytes < 256 + (size_t)a.V * sizeof(float)) return NAT_WORKSPACE_TOO_SMALL;
   size_t rows = (a.ws_bytes - 256) / ((size_t)a.V * sizeof(float));
   if (rows > (size_t)a.N_k) rows = a.N_k;

@@ -150,6 +150,7 @@ def test_loss_argument_errors(lib):
     assert call(eps=-0.1) == 1
     assert call(H=0) == 2 and call(V=0) == 2
     assert call(H=100) == 2                      # bf16 kernels need H % 64 == 0
+    assert call(H=15361, dtype=0) == 2           # beyond the range of the fp32 path
     assert call(W=None) == 1
     assert call(hidden=None) == 1
     assert call(ws_bytes=1024) == 3
@@ -180,7 +181,7 @@ def test_logp_fwd_argument_errors(lib):
         return lib.nat_logp_fwd(hidden, W, fake, N_k, H, V, dtype, logp, None, None, ws, ws_bytes, None)
     assert call(dtype=3) == 4
     assert call(N_k=-1) == 1
-    assert call(H=100) == 2 and call(V=0) == 2
+    assert call(H=100) == 2 and call(V=0) == 2 and call(H=15361, dtype=0) == 2
     assert call(hidden=None) == 1 and call(logp=None) == 1
     assert call(ws_bytes=100) == 3 and call(ws=None) == 3
     assert call(W=ctypes.c_void_p(264)) == 1
