@@ -230,12 +230,15 @@ def test_bf16_last_token_tile_half_full(stage, n_tok):
         check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("V", [1025, 17153])
 @pytest.mark.parametrize("n_tok", [40, 2048, 2049])
-def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok):
-    # up to 2048 tokens a chunk is added to dW by reading, adding and storing, beyond that by fp32 atomics: one addition
-    # of the same sum per element either way, so accumulating equals old + the overwritten result bit for bit.  Columns
-    # and rows past the end of the last tiles (H = 320, V = 1025) keep what they held
-    H, V = 320, 1025
+def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):
+    # up to 2048 tokens a chunk is added to dW by reading, adding and storing, beyond that by fp32 atomics; tiles whose token
+    # axis is cut are added by the kernel that sums their ranges.  V = 17153: 136 tiles, more than half a round of compute units,
+    # so none is cut; V = 1025: 10 tiles, all cut from 2048 tokens on.  One addition of the same sum per element either way, so
+    # accumulating equals old + the overwritten result bit for bit.  Columns and rows past the end of the last tiles (H = 320, one
+    # row in the last tile) keep what they held
+    H = 320
     case = make_loss_case(600 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
     plain = hip_loss(stage, case, "bf16")["dW"]
     big = torch.randn((V + 1, H), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV) * plain.abs().mean()
@@ -273,7 +276,7 @@ def test_bf16_forward_pass_w_repacked_and_read_as_it_is_agree(stage, H, V, n):
 @pytest.mark.parametrize("n_tok,H,V,label", [
     (4700, 3584, 2100, "dH: a full round of tiles and ten more in two vocabulary ranges"),
     (100, 128, 40000, "dH: one tile in 39 vocabulary ranges"),
-    (257, 320, 9000, "dH: four tiles, two of them with one valid row, in eight ranges"),
+    (257, 320, 9000, "dH: four tiles, two of them with one valid row, in nine ranges"),
 ])
 def test_bf16_dh_leftover_tiles_cut_into_vocabulary_ranges(stage, n_tok, H, V, label):
     case = make_loss_case(300 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.02)
