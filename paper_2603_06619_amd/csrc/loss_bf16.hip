@@ -77,7 +77,7 @@ constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stag
 #endif
 constexpr int kMaxChunk = 32768;                  // most token rows per chunk (see recommended_cap)
 constexpr int kNumCU = 256;                       // compute units (one workgroup of these kernels each)
-constexpr int kMinSlicesPerRange = 32;            // shortest range of a cut contraction axis (k-slices)
+constexpr int kMinSlicesPerRange = 32;            // least k-slices per range of a cut contraction axis, on average
 #ifndef NAT_SUBCHUNK
 #define NAT_SUBCHUNK 8192
 #endif
@@ -540,7 +540,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const Epilogue& epi
   lb.init(g.B, tn, g.kb_b, wave, lane);
   int kt_n = kt_all;                                           // k-slices this workgroup contracts over
   if (range >= 0) {
-    const int kt0 = range * g.kt_per_split;                    // a multiple of 8 (TileLoaderKMajor::start_at)
+    const int kt0 = range * g.kt_per_split;                    // with a blocked k-major A a multiple of 8 (TileLoaderKMajor::start_at)
     kt_n = kt_all - kt0 < g.kt_per_split ? kt_all - kt0 : g.kt_per_split;
     la.start_at(kt0);
     lb.start_at(kt0);
@@ -953,6 +953,7 @@ struct DHiddenEpilogue {
 
 // dH^T tile of the contraction that reads W as it is: rows = hidden units (A = W^T, k-major), columns = tokens (B = E).
 // A lane holds four consecutive hidden units of its token: 8-byte LDS writes, then the same 16-byte stores of whole rows.
+// (11 registers go to scratch, 9 in the epilogue of the repacked path: the accumulators fill the file.)
 struct DHiddenTEpilogue {
   int n_valid, H;
   uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
@@ -1074,7 +1075,8 @@ struct DWeightEpilogue {
 // it.  32 rows of the wavefront's tile at a time go through its own part of the LDS ring (free after the k-loop), so that
 // old values come and sums leave 16 bytes per lane, two whole rows of its columns per instruction; the old values are loaded
 // two blocks ahead of their use and before the stores of the block in hand (the load counter would wait for those
-// first).  One fp32 addition old + sum per element, as with the atomics.  See kReadAddSlices.
+// first).  One fp32 addition old + sum per element, as with the atomics.  See kReadAddSlices.  Two blocks of old values
+// (128 registers), the results and the accumulators do not fit: 65 registers go to scratch in this epilogue, none in the k-loop.
 struct DWeightAddEpilogue {
   DWeightEpilogue whole;           // ranges of cut tiles still go to their slabs
 
@@ -1453,8 +1455,9 @@ size_t logp_bf16_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal
 
 // How a launch of `tiles` output tiles and `kt_all` k-slices uses the compute units.  Full rounds of one tile per
 // compute unit run whole; the tiles left over (at most half a round: with more, two ranges each would not fit one
-// round) are cut into as many ranges of the contraction axis as fill the chip once, none shorter than
-// kMinSlicesPerRange (a workgroup's load ring and epilogue cost about ten slices), starts multiples of `align`.
+// round) are cut into as many ranges of the contraction axis as fill the chip once, of at least kMinSlicesPerRange
+// on average (a workgroup's load ring and epilogue cost about ten slices), starts multiples of `align`; the last range takes
+// what that rounding leaves (1256 slices in 39 ranges: 38 of 33 and one of 2).
 // 5003 tokens at the 7B head: 280 dH tiles took a second round for 24 of them, 6.26 ms; cut into ten ranges, 3.96 ms.
 struct RangeCut { int splits, kt_per, tail, grid; };
 static RangeCut range_cut(int tiles, int kt_all, int align) {
