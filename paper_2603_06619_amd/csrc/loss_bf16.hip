@@ -7,7 +7,7 @@
 // Tokens are processed in chunks of at most `cap` rows (16384 or 32768 with the recommended workspace); the
 // forward sweep and the dH contraction of a chunk run in sub-chunks of 8192 rows.  Per chunk:
 //   reference     ref_k = h_k . W[ids_k]: the target logit, used only as the exponent shift;
-//   logits GEMM   Z^T tile = W_tile . H^T on bf16 MFMA with fp32 accumulators; the epilogue never
+//   logits GEMM   Z^T = W . H_chunk^T on bf16 MFMA with fp32 accumulators; the epilogue never
 //                 stores Z: it stores E = exp(z - ref_k) as bf16, ONCE, rows = token (soft-max
 //                 numerators: bf16 keeps their relative precision), per (token, 128-row vocabulary
 //                 granule) partial sums of E, and the exact target logit;
@@ -17,7 +17,7 @@
 //                 patched into E as -S_k (1 - p_target), computed in fp32 before rounding;
 //   dH GEMM       dH = diag(beta) (E . W)            (contraction over the vocabulary);
 //   dW GEMM       dW (+)= E^T . (diag(beta) H_chunk) (contraction over the chunk's tokens, fp32,
-//                 one owner per output tile, chunks in order: deterministic).  Its A operand is
+//                 one owner per output tile, chunks in order: deterministic).  Its operand E^T is
 //                 the same copy of E, which is stored along this contraction's k axis: the tile
 //                 is gathered in 2 KiB pieces and fragments are formed by the transposing LDS
 //                 read (ds_read_b64_tr_b16).
@@ -26,13 +26,13 @@
 // policy gives less than e^-70 of its mode's probability does not occur for rollouts drawn from a
 // behaviour policy inside the clip range.
 // All three contractions run through one "NT" kernel (both operands contiguous along the
-// contraction axis; the k-major A operand of dW is the one exception described above).  Every
+// contraction axis; the k-major operand of dW is the one exception described above).  Every
 // operand is kept in a blocked layout in the workspace: blocks of 256 rows x 32 k-elements (16 KiB,
 // contiguous), ordered k-fastest inside a 256-row tile, so a workgroup streams one contiguous
 // region per operand instead of 256 strided rows.  W and H_chunk are repacked (plain and
 // transposed); the soft-max numerators are produced directly in that layout.  Short batches do not
-// repack W (direct_tokens): the logits contraction reads its rows, the dH contraction, turned round to
-// dH^T = W^T E^T, reads them as a k-major operand.
+// repack W (direct_tokens): the logits contraction reads its rows, the dH contraction reads them as a
+// k-major operand.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
 
@@ -41,20 +41,16 @@
 namespace nat {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 // The soft-max numerators are written once and read back only by the two backward contractions,
 // long after they have left the L2: non-temporal stores (1 % on the logits kernel).
 #define NAT_E_STORE(ptr, val) __builtin_nontemporal_store((val), (ptr))
 
-constexpr int kBM = 256, kBN = 256, kBK = 32;     // block tile: 4 wavefronts of 128 x 128 or 8 of 128 x 64
+constexpr int kBM = 256, kBN = 256, kBK = 32;     // block tile: 4 wavefronts of 128 x 128, one per SIMD
 constexpr int kStages = 4;                        // LDS ring of k-slices (4 x 32 KiB)
 constexpr int kGranule = 128;                     // vocabulary rows per soft-max partial
 constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stage
-// Wavefronts per workgroup of each contraction (4: one per SIMD, 128 x 128 each, 256 accumulator
-// registers; 8: two per SIMD, 128 x 64 each: row-major operands only).  Measured on the Qwen3-8B
-// head with the row-major kernel: dH 2 % slower with 8, the logits contraction unchanged; the k-major
-// dW loop is written for 4.
 // Tile rows per group of the block -> tile map, per contraction (measured: 4 is 1-2 % faster than 8
 // for the two backward contractions, 2 and 6 are slower, 16 is 8 % slower).
 #ifndef NAT_GROUP_LOGITS
@@ -65,15 +61,6 @@ constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stag
 #endif
 #ifndef NAT_GROUP_DWEIGHT
 #define NAT_GROUP_DWEIGHT 4
-#endif
-#ifndef NAT_WAVES_LOGITS
-#define NAT_WAVES_LOGITS 4
-#endif
-#ifndef NAT_WAVES_DHIDDEN
-#define NAT_WAVES_DHIDDEN 4
-#endif
-#ifndef NAT_WAVES_DWEIGHT
-#define NAT_WAVES_DWEIGHT 4
 #endif
 constexpr int kMaxChunk = 32768;                  // most token rows per chunk (see recommended_cap)
 constexpr int kNumCU = 256;                       // compute units (one workgroup of these kernels each)
@@ -99,13 +86,26 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float x) {
 // ------------------------------------------------------------ blocked layout ----
 constexpr int kBlkElems = 256 * 32;               // one block: 256 rows x 32 k-elements
 
-// element (row, k) of an operand with kb = K/32 k-slices.  Inside a row of a block the four
-// 16-byte chunks are stored permuted (chunk index XOR bits 2..3 of the row): a block is then a
-// byte-for-byte image of the bank-conflict-free LDS tile, and the direct-to-LDS copy reads it
+// The 16-byte chunks of a 64-byte row (32 k) are stored permuted: chunk c at position c ^ chunk_xor(row / 4).  A wavefront
+// reads a fragment of 16 rows with ds_read_b128, lane l chunk l / 16 of row l % 16; the LDS serves 16 lanes at a time over
+// its 64 banks, lanes 0-3, 12-15, 20-27 together, then 4-11, 16-19, 28-31, and the same of the upper half.  Four rows
+// apart the bank is the same, so the chunks of lanes 0-3, 12-15 (c ^ f(0), c ^ f(3)) and 20-23, 24-27 ((c + 1) ^ f(1), (c + 1)
+// ^ f(2)) have to differ: f = 0, 2, 3, 1 does it (f = row / 4 itself: half of the LDS cycles were conflicts).
+__host__ __device__ __forceinline__ constexpr int chunk_xor(int row4) { return (((row4 ^ (row4 >> 1)) & 1) << 1) | ((row4 >> 1) & 1); }
+
+// element (row, k) of an operand with kb = K/32 k-slices.  With the chunks of a row permuted a block is
+// a byte-for-byte image of the bank-conflict-free LDS tile, and the direct-to-LDS copy reads it
 // linearly, 16 bytes per lane.
 __host__ __device__ __forceinline__ int64_t blk_off(int row, int k, int kb) {
   return ((int64_t)(row >> 8) * kb + (k >> 5)) * kBlkElems + ((row & 255) << 5) +
-         (((((k & 31) >> 3) ^ ((row >> 2) & 3))) << 3) + (k & 7);
+         ((((k & 31) >> 3) ^ chunk_xor(row >> 2)) << 3) + (k & 7);
+}
+
+// element (row, k) of an operand in the blocked layout whose rows are read interleaved (16 lanes read rows 8 a + 4 p + b,
+// a, b = 0..3): as blk_off, with the permutation by row / 8
+__host__ __device__ __forceinline__ int64_t blk_off_interleaved(int row, int k, int kb) {
+  return ((int64_t)(row >> 8) * kb + (k >> 5)) * kBlkElems + ((row & 255) << 5) +
+         ((((k & 31) >> 3) ^ chunk_xor(row >> 3)) << 3) + (k & 7);
 }
 
 // Repack a row-major matrix in [R, C] (leading dimension ld_in) into the blocked layout,
@@ -122,7 +122,7 @@ __host__ __device__ __forceinline__ int64_t blk_off(int row, int k, int kb) {
 __global__ void __launch_bounds__(256)
 pack_blocked_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int R, int C, int Rp, int Cp,
                     uint16_t* __restrict__ out_rk, uint16_t* __restrict__ out_cr, int kb_cr,
-                    const float* __restrict__ row_scale) {
+                    const float* __restrict__ row_scale) {     // row_scale: the chunk's rows, in order; none: W, interleaved
   union Chunk { uint4 q; uint16_t e[8]; };
   __shared__ __attribute__((aligned(16))) uint16_t tile[64][72];     // 144-byte rows: 16-byte aligned chunks
   const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
@@ -134,7 +134,7 @@ pack_blocked_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int R, int C
     Chunk x;
     x.q = make_uint4(0u, 0u, 0u, 0u);
     if (r < R && c < C) x.q = *reinterpret_cast<const uint4*>(in + (int64_t)r * ld_in + c);
-    if (out_rk && c < C) *reinterpret_cast<uint4*>(out_rk + blk_off(r, c, C >> 5)) = x.q;
+    if (out_rk && c < C) *reinterpret_cast<uint4*>(out_rk + blk_off_interleaved(r, c, C >> 5)) = x.q;
     if (row_scale && r < R) {
       const float f = row_scale[r];
 #pragma unroll
@@ -153,15 +153,16 @@ pack_blocked_kernel(const uint16_t* __restrict__ in, int64_t ld_in, int R, int C
     Chunk y;
 #pragma unroll
     for (int e = 0; e < 8; ++e) y.e[e] = tile[rbase + e][cj];
-    *reinterpret_cast<uint4*>(out_cr + blk_off(c0 + cj, r0 + rbase, kb_cr)) = y.q;
+    const int64_t at = row_scale ? blk_off(c0 + cj, r0 + rbase, kb_cr) : blk_off_interleaved(c0 + cj, r0 + rbase, kb_cr);
+    *reinterpret_cast<uint4*>(out_cr + at) = y.q;
   }
 }
 
 // ------------------------------------------------------------------- GEMM ----
 struct GemmArgs {
-  const uint16_t* A;          // [tiles_m * 256, K] in the blocked layout
+  const uint16_t* A;          // [tiles_m * 256, K], stored as the kernel's Src says
   const uint16_t* B;          // [tiles_n * 256, K] in the blocked layout
-  int K;                      // multiple of kBK
+  int K;                      // multiple of 2 * kBK
   int tiles_m, tiles_n;
   int group_m;                // tile rows walked together (see tile_of_block)
   int kb_a_src;               // k-major A only (see TileLoaderKMajor): k-slices of the source operand
@@ -191,19 +192,13 @@ __device__ __forceinline__ void tile_of_block(const GemmArgs& g, int pid, int& t
   tn = in_group / rows;
 }
 
-// Byte offset of 16-byte chunk c (0..3) of row r in a [256][32] bf16 LDS tile (64-byte rows).
-// A ds_read_b128 is served 16 lanes at a time over 64 banks; 16 consecutive rows at one
-// chunk index would fall on 4 bank groups, so the chunk is XOR-ed with bits 2..3 of the row.
-__device__ __forceinline__ int lds_chunk_off(int r, int c) { return r * (kBK * 2) + ((c ^ ((r >> 2) & 3)) << 4); }
-
 // Global -> LDS copy of one [256][32] bf16 operand block (16 KiB, contiguous in memory)
-// without staging registers: the NW wavefronts issue 16 direct-to-LDS loads of 16 bytes per
+// without staging registers: the 4 wavefronts issue 16 direct-to-LDS loads of 16 bytes per
 // lane between them.  One instruction copies 1 KiB (16 tile rows) linearly: the hardware
 // places lane l at byte 16*l of that KiB, and the block in memory already has the LDS tile's
 // chunk order.
-template <int NW>
 struct TileLoader {
-  static constexpr int kLoads = kTileBytes / 1024 / NW;     // per wavefront
+  static constexpr int kLoads = kTileBytes / 1024 / 4;      // per wavefront
   const uint16_t* src;           // this lane's chunk in k-slice 0 of load 0
 
   // A wavefront copies kLoads consecutive KiB of the block (16 * kLoads rows): the loads of one
@@ -220,21 +215,6 @@ struct TileLoader {
                                      (__attribute__((address_space(3))) void*)(lds_tile + wave * (kLoads * 1024)), 16,
                                      kIdx * 1024, 0);
   }
-  __device__ __forceinline__ void issue(char* lds_tile, int kt, int wave) const {
-    const uint16_t* p = src + (int64_t)kt * kBlkElems;
-    char* dst = lds_tile + wave * (kLoads * 1024);
-    static_assert(kLoads == 4 || kLoads == 2, "immediate offsets below are written out");
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
-                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
-                                     (__attribute__((address_space(3))) void*)dst, 16, 1024, 0);
-    if (kLoads == 4) {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
-                                       (__attribute__((address_space(3))) void*)dst, 16, 2048, 0);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
-                                       (__attribute__((address_space(3))) void*)dst, 16, 3072, 0);
-    }
-  }
 };
 
 // The first 128 rows of a [256][32] operand block: 8 KiB of each slice, two loads for each of 4 wavefronts.
@@ -250,21 +230,16 @@ struct HalfTileLoader {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)kt * kBlkElems),
                                      (__attribute__((address_space(3))) void*)(lds_tile + wave * 2048), 16, kIdx * 1024, 0);
   }
-  __device__ __forceinline__ void issue(char* lds_tile, int kt, int wave) const {
-    issue_one<0>(lds_tile, kt, wave);
-    issue_one<1>(lds_tile, kt, wave);
-  }
 };
 
-// The same copy for an A operand that is only stored with its rows along THIS contraction's k axis
+// The same copy for an operand that is only stored with its rows along THIS contraction's k axis
 // (the soft-max numerators: rows = token, k = vocabulary, read by the dW contraction whose k axis is
 // the token).  A [256 rows][32 k] tile of the contraction is then eight pieces of the source, one per
 // 32-row block of the tile: rows (kt % 8) * 32 .. + 31 of the source block (token tile kt / 8, k-slice
 // 8 * tile + piece), 2 KiB contiguous each.  The LDS tile holds the pieces one after another, i.e.
 // [row block][k][row within block], and fragments come out of it through the transposing LDS read.
-template <int NW>
 struct TileLoaderKMajor {
-  static constexpr int kLoads = kTileBytes / 1024 / NW;     // per wavefront (4 with 4 wavefronts)
+  static constexpr int kLoads = kTileBytes / 1024 / 4;      // per wavefront
   static constexpr int kPieces = kLoads / 2;                // 2 KiB pieces per wavefront
   const uint16_t* src;           // this lane's 16 bytes of the wavefront's first piece, token tile 0, rows 0..15
   int64_t tile_stride;           // elements between consecutive token tiles of the source
@@ -286,17 +261,16 @@ struct TileLoaderKMajor {
 
 // The same two tiles straight from a row-major matrix (the caller's W), for batches too small to pay for repacking it:
 // one instruction reads 64 bytes of 16 rows, each lane from where its place of the LDS tile wants it (16-byte chunk
-// p of a tile row holds chunk p XOR bits 2..3 of the row).  Rows past the end read the last row: as vocabulary rows
+// p of a tile row holds chunk p ^ chunk_xor).  Rows past the end read the last row: as vocabulary rows
 // of the logits tile they are masked by the epilogue, as k of the dH contraction they meet numerators that are 0.
-template <int NW>
 struct TileLoaderRows {          // [256 rows][32 k]: rows of the matrix, k its columns
-  static constexpr int kLoads = kTileBytes / 1024 / NW;
+  static constexpr int kLoads = kTileBytes / 1024 / 4;
   const uint16_t* src[kLoads];   // this lane's chunk in k-slice 0 of each load
   __device__ __forceinline__ void init(const uint16_t* W, int tile, int rows, int ld, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int r = (wave * kLoads + i) * 16 + (lane >> 2), row = tile * kBM + r;
-      src[i] = W + (int64_t)(row < rows ? row : rows - 1) * ld + (((lane & 3) ^ ((r >> 2) & 3)) << 3);
+      src[i] = W + (int64_t)(row < rows ? row : rows - 1) * ld + (((lane & 3) ^ chunk_xor(r >> 3)) << 3);
     }
   }
   __device__ __forceinline__ void start_at(int kt0) {
@@ -308,27 +282,18 @@ struct TileLoaderRows {          // [256 rows][32 k]: rows of the matrix, k its 
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[kIdx] + kt * kBK),
                                      (__attribute__((address_space(3))) void*)(lds_tile + (wave * kLoads + kIdx) * 1024), 16, 0, 0);
   }
-  __device__ __forceinline__ void issue(char* lds_tile, int kt, int wave) const {
-    static_assert(kLoads == 4, "written out for 4 wavefronts");
-    issue_one<0>(lds_tile, kt, wave);
-    issue_one<1>(lds_tile, kt, wave);
-    issue_one<2>(lds_tile, kt, wave);
-    issue_one<3>(lds_tile, kt, wave);
-  }
 };
 
-template <int NW>
 struct TileLoaderKMajorRows {    // [256 rows][32 k] with k the rows of the matrix: pieces of 32 k x 32 rows, as TileLoaderKMajor
-  static constexpr int kLoads = kTileBytes / 1024 / NW;
+  static constexpr int kLoads = kTileBytes / 1024 / 4;
   const uint16_t* src;           // this lane's chunk of row 0 of the wavefront's first piece
   int piece_step;                // elements from the wavefront's first piece to its second
   int k_rows, ld, k_lane, kt_first;
   __device__ __forceinline__ void init(const uint16_t* W, int tile, int rows, int cols, int wave, int lane) {
-    static_assert(kLoads == 4, "two pieces per wavefront");
     const int c0 = tile * kBM + 64 * wave, c1 = c0 + 32;         // columns past the end (a multiple of 64 is valid): any valid ones
     const int s0 = c0 < cols ? c0 : cols - 32, s1 = c1 < cols ? c1 : cols - 32;
     k_lane = lane >> 2;
-    src = W + s0 + (((lane & 3) ^ ((lane >> 4) & 3)) << 3);
+    src = W + s0 + (((lane & 3) ^ chunk_xor(lane >> 4)) << 3);
     piece_step = s1 - s0;
     k_rows = rows;
     ld = cols;
@@ -345,84 +310,8 @@ struct TileLoaderKMajorRows {    // [256 rows][32 k] with k the rows of the matr
   }
 };
 
-// Per-lane byte offsets, inside a [k = 32][32 rows] piece, of the two transposing reads (q = 0, 1)
-// that make one A fragment of k-substep 0.  The transposing read works on groups of 16 lanes: lane
-// i of a group supplies the address of 4 consecutive 16-bit elements and receives element i % 4 of
-// the lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12.  With lane i pointing at k = K0 + i / 4 and rows
-// 16 g + 4 (i % 4) .. + 3, lane i ends up with row 16 g + i and k = K0 .. K0 + 3: the MFMA's A layout
-// (row = lane % 32, 8 consecutive k from 8 * (lane / 32)) after two reads, K0 = 8 * (lane / 32) + 4 q.
-// The 16-byte chunks of a source row are stored XOR-ed with bits 2..3 of the row (see blk_off); for
-// these k values that is 2 * (lane / 32) + q.  The 32 lanes of a half-wavefront then cover all 64
-// LDS banks exactly once.
-struct KMajorFragOffsets {
-  int off[2];
-  __device__ __forceinline__ void init(int lane) {
-    const int i = lane & 15, g = (lane >> 4) & 1, lhi = lane >> 5, a = i & 3;
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      off[q] = (8 * lhi + 4 * q + (i >> 2)) * 64 + ((((2 * g + (a >> 1)) ^ (2 * lhi + q)) & 3) << 4) + (a & 1) * 8;
-  }
-};
-
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-// One k-substep of the row-major loop, instruction slot by slot (the compiler may not move anything
-// across a slot's end): slot m holds MFMA m on the fragments (au, bu); behind each of the first 4 + NB
-// MFMAs one fragment read of k-substep ks_load from (a_s, b_s) into (al, bl); the remaining MFMAs carry
-// the direct-to-LDS loads of this wavefront's share of slice k into lds_dst, evenly spaced (mixing them
-// with the fragment reads measured slower).
-template <int NW, int NB, int M = 0, class Loader>
-__device__ __forceinline__ void substep_slots(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
-                                              bf16x8 (&al)[4], bf16x8 (&bl)[NB], const char* a_s, const char* b_s,
-                                              int a_row0, int b_row0, int l32, int lhi, int ks_load,
-                                              const Loader& ld, char* lds_dst, int k, int wave) {
-  constexpr int kLoadFirst = 4 + NB, kLoadEvery = (4 * NB - kLoadFirst) / TileLoader<NW>::kLoads;
-  static_assert(kLoadEvery >= 1, "every load needs a slot");
-  if constexpr (M < 4 * NB) {
-    constexpr int i = M / NB, j = M % NB;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
-    if constexpr (M < 4) al[M] = *(const bf16x8*)(a_s + lds_chunk_off(a_row0 + M * 32 + l32, ks_load * 2 + lhi));
-    else if constexpr (M < 4 + NB) bl[M - 4] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + (M - 4) * 32 + l32, ks_load * 2 + lhi));
-    if constexpr (M >= kLoadFirst && (M - kLoadFirst) % kLoadEvery == 0 && (M - kLoadFirst) / kLoadEvery < TileLoader<NW>::kLoads)
-      ld.template issue_one<(M - kLoadFirst) / kLoadEvery>(lds_dst, k, wave);
-    __builtin_amdgcn_sched_barrier(0);
-    substep_slots<NW, NB, M + 1>(acc, au, bu, al, bl, a_s, b_s, a_row0, b_row0, l32, lhi, ks_load, ld, lds_dst, k, wave);
-  }
-}
-
-// The same for the loop that reads its A tiles from rows (TileLoaderRows), which refills two slices' A tiles at once:
-// kRefill 0: the loads of B, one every second MFMA as above; 1: eight loads of A, the two halves of each 128-byte
-// line one right after the other; 2: none.  NB = 2 (a tile of 128 columns): eight MFMAs, the loads behind the last two.
-template <int NB, int kRefill, int M = 0, class LoaderB>
-__device__ __forceinline__ void substep_slots_rows(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
-                                                   bf16x8 (&al)[4], bf16x8 (&bl)[NB], const char* a_s, const char* b_s,
-                                                   int a_row0, int b_row0, int l32, int lhi, int ks_load,
-                                                   const TileLoaderRows<4>& la, const LoaderB& lb, char* lds0, char* lds1,
-                                                   int k0, int k1, int wave) {
-  constexpr int kFirst = 4 + NB, kSlots = 4 * NB - kFirst;     // slots behind the fragment reads: 8, or 2
-  if constexpr (M < 4 * NB) {
-    constexpr int i = M / NB, j = M % NB, q = M - kFirst;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
-    if constexpr (M < 4) al[M] = *(const bf16x8*)(a_s + lds_chunk_off(a_row0 + M * 32 + l32, ks_load * 2 + lhi));
-    else if constexpr (M < kFirst) bl[M - 4] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + (M - 4) * 32 + l32, ks_load * 2 + lhi));
-    else if constexpr (kRefill == 0) {
-      if constexpr (q * LoaderB::kLoads % kSlots == 0) lb.template issue_one<q * LoaderB::kLoads / kSlots>(lds0, k0, wave);
-    } else if constexpr (kRefill == 1) {
-      if constexpr (NB == 4) {
-        if constexpr ((q & 1) == 0) la.template issue_one<q / 2>(lds0, k0, wave);
-        else la.template issue_one<q / 2>(lds1, k1, wave);
-      } else {
-        la.template issue_one<2 * q>(lds0, k0, wave);
-        la.template issue_one<2 * q>(lds1, k1, wave);
-        la.template issue_one<2 * q + 1>(lds0, k0, wave);
-        la.template issue_one<2 * q + 1>(lds1, k1, wave);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    substep_slots_rows<NB, kRefill, M + 1>(acc, au, bu, al, bl, a_s, b_s, a_row0, b_row0, l32, lhi, ks_load, la, lb, lds0, lds1, k0, k1, wave);
-  }
-}
 
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
@@ -437,106 +326,161 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int off) {
   return v;
 }
 
-// One k-substep of the k-major loop with 4 wavefronts of 128 x 128, slot by slot (see substep_slots): MFMA m on
-// (au, bu); behind the first 8 MFMAs one transposing read each (halves q = m % 2 of A block m / 2, from the
-// piece bases a_rd[q]) and behind the first 4 also one 16-byte read of B; behind MFMAs 8, 10, 12, 14 one
-// direct-to-LDS load of the refill (the A tile's when kRefillA, else the B tile's).  NB = 2 (a tile of 128 columns):
-// eight MFMAs, two transposing reads behind each of the first four, the two reads of B, then the loads.
-template <int NB, bool kRefillA, int M = 0, class LoaderA, class LoaderB>
-__device__ __forceinline__ void substep_slots_kmajor4(f32x16 (&acc)[4][NB], const bf16x8 (&au)[4], const bf16x8 (&bu)[NB],
-                                                      s16x4 (&al)[8], bf16x8 (&bl)[NB], const uint32_t (&a_rd)[2], const char* b_rd,
-                                                      const LoaderA& la, const LoaderB& lb, char* lds_dst,
-                                                      int k, int wave) {
-  if constexpr (M < 4 * NB) {
-    constexpr int i = M / NB, j = M % NB;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au[i], bu[j], acc[i][j], 0, 0, 0);
-    if constexpr (NB == 4) {
-      if constexpr (M < 4) bl[M] = *(const bf16x8*)(b_rd + M * 2048);
-      if constexpr (M < 8) al[M] = lds_read_tr16_b64(a_rd[M & 1], (M / 2) * 2048);
-      if constexpr (M >= 8 && (M & 1) == 0) {
-        if constexpr (kRefillA) la.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
-        else lb.template issue_one<(M - 8) / 2>(lds_dst, k, wave);
-      }
-    } else if constexpr (M < 4) {
-      al[2 * M] = lds_read_tr16_b64(a_rd[0], M * 2048);
-      al[2 * M + 1] = lds_read_tr16_b64(a_rd[1], M * 2048);
-    } else if constexpr (M < 6) {
-      bl[M - 4] = *(const bf16x8*)(b_rd + (M - 4) * 2048);
-    } else if constexpr (kRefillA) {
-      la.template issue_one<2 * (M - 6)>(lds_dst, k, wave);
-      la.template issue_one<2 * (M - 6) + 1>(lds_dst, k, wave);
-    } else {
-      lb.template issue_one<M - 6>(lds_dst, k, wave);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    substep_slots_kmajor4<NB, kRefillA, M + 1>(acc, au, bu, al, bl, a_rd, b_rd, la, lb, lds_dst, k, wave);
-  }
-}
-
-// fragments of k-substep ks: four 32-row blocks of A from row a_row0, NB 32-row blocks of B from b_row0
-template <int NB>
-__device__ __forceinline__ void load_frags(const char* a_s, const char* b_s, int a_row0, int b_row0, int l32, int lhi,
-                                           int ks, bf16x8 (&af)[4], bf16x8 (&bfr)[NB]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) af[i] = *(const bf16x8*)(a_s + lds_chunk_off(a_row0 + i * 32 + l32, ks * 2 + lhi));
-#pragma unroll
-  for (int j = 0; j < NB; ++j) bfr[j] = *(const bf16x8*)(b_s + lds_chunk_off(b_row0 + j * 32 + l32, ks * 2 + lhi));
-}
-
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 
-// NW wavefronts in a 2 x (NW/2) grid over the 256 x 256 tile: wavefront (wm, wn) owns rows
-// wm*128.. and columns wn*(NB*32).. with NB = 16/NW (4 wavefronts: 128 columns, 8: 64 columns).
-// acc[mb][nb] element r of lane l is C[row0 + mb*32 + 8*(r/4) + 4*(l/32) + r%4][col0 + nb*32 + l%32]
-// kA: how the A operand is stored.  k-major: along this contraction's k axis (g.kb_a_src is then the number of
-// k-slices of that source); rows: a row-major matrix of g.src_rows x g.src_cols, read as it is.
-enum class ASource { kBlocked, kKMajorBlocked, kRows, kKMajorRows };
 // one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
 // direct-to-LDS loads in flight): the ring, and behind it the words the epilogue parks across the k-loop
-template <int kStashWords>
 struct GemmShared {
   char ring[kStages][2][kTileBytes];
-  int stash[kStashWords > 0 ? kStashWords : 1];
+  int stash[4][256];             // per wavefront
 };
 
-// One tile.  NB: 32-column blocks per wavefront, 16 / NW; or 2 with 4 wavefronts: a tile of which only the first 128
-// columns are computed.
-template <class Epilogue, int NW, ASource kA, int NB, class Shared>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, const Epilogue& epi, Shared& sm, int tm, int tn, int range, int slab) {
-  constexpr bool AT = kA == ASource::kKMajorBlocked || kA == ASource::kKMajorRows;
-  constexpr bool kHalf = NB * NW < 16;
-  constexpr int kLoadsA = kTileBytes / 1024 / NW, kLoadsB = kHalf ? HalfTileLoader::kLoads : kLoadsA;   // per wavefront and slice
-  constexpr int kLoadsPerWave = kLoadsA + kLoadsB;
+// ---------------------------------------------------------------- GEMM core ----
+// One workgroup computes a 256 x 256 tile of C = P . Q^T (P: rows of the result, Q: its columns, both along the
+// contraction axis) with 4 wavefronts of 128 x 128 in 8 x 8 blocks of v_mfma_f32_16x16x32_bf16:
+// acc[i][j] element r of lane l is C[p0 + row(i, l, r)][q0 + 16 j + l % 16], row = 16 i + 4 (l / 16) + r for an operand whose
+// rows are in their order and 32 (i / 2) + 8 (l / 16) + 4 (i % 2) + r for one that is read with its rows interleaved
+// (is_interleaved), so that a lane holds eight consecutive rows: a 16-byte store of bf16.
+// Why 16 x 16 x 32: the three contractions run at the package's power limit, and this instruction needs less of it than
+// 32 x 32 x 16 at the same peak (an accumulator is read and written once per 32 k instead of once per 16): operands in
+// registers, nothing else going on, 1990 against 1755 TFLOP/s on normally distributed values, 1960 against 1710 with
+// exponentials on one side, equal (2450) on zeros.
+
+template <int kN, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (kN > 0) {
+    static_for<kN - 1>(f);
+    f(std::integral_constant<int, kN - 1>{});
+  }
+}
+
+// how many of `count` things spread evenly over slots 0 .. span - 1 come before slot m
+constexpr int spread(int m, int count, int span) { return m <= 0 ? 0 : m >= span ? count : (m * count + span - 1) / span; }
+
+// How an operand is stored: blocked layout (rows in order or interleaved), rows of a row-major matrix (interleaved, read as
+// it is), or either of them along the contraction's own axis (fragments through the transposing read).
+enum class Src { kBlocked, kBlockedInterleaved, kRows, kKMajorBlocked, kKMajorRows };
+
+constexpr bool is_kmajor(Src s) { return s == Src::kKMajorBlocked || s == Src::kKMajorRows; }
+constexpr bool is_interleaved(Src s) { return s == Src::kBlockedInterleaved || s == Src::kRows; }
+
+// Fragments of a wavefront's 16-row blocks out of an LDS tile: lane l gets row l % 16 of the block, k = 8 (l / 16) .. + 7.
+template <Src kS>
+struct FragReader {
+  static constexpr int kReads = is_kmajor(kS) ? 2 : 1;          // LDS reads per fragment
+  uint32_t off[is_kmajor(kS) ? 4 : 1];
+  __device__ __forceinline__ void init(int row0, int lane) {    // row0: the wavefront's first row, a multiple of 64
+    const int i = lane & 15, g = lane >> 4;
+    if constexpr (is_kmajor(kS)) {
+      // tile: [32-row piece][k = 32][32 rows], 16-byte chunks of a k-row XOR chunk_xor(k / 4).  Read q = 0, 1 of the block
+      // with rows 16 h .. of its piece: the transposing read works on groups of 16 lanes, lane i of a group supplies the address
+      // of 4 consecutive elements and receives element i % 4 of the lanes i / 4, i / 4 + 4, i / 4 + 8, i / 4 + 12.  With lane i pointing at
+      // k = 8 g + 4 q + i / 4 and rows 16 h + 4 (i % 4) .. + 3 it gets row 16 h + i, k = 8 g + 4 q .. + 3.  The 32 lanes of a
+      // half-wavefront cover all 64 banks once
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          off[2 * h + q] = row0 * 64 + (8 * g + 4 * q + (i >> 2)) * 64 + (((2 * h + ((i & 3) >> 1)) ^ chunk_xor(2 * g + q)) << 4) + (i & 1) * 8;
+    } else if constexpr (is_interleaved(kS)) {
+      off[0] = (row0 + 8 * (i >> 2) + (i & 3)) * 64 + ((g ^ chunk_xor(i >> 2)) << 4);
+    } else {
+      off[0] = (row0 + i) * 64 + ((g ^ chunk_xor(i >> 2)) << 4);
+    }
+  }
+};
+
+// c += a . b, the accumulator in the accumulation registers.  As inline assembly, because the allocator moves accumulators
+// about between the two register files in the loop when it is given 64 of them through the builtin (several hundred
+// moves per slice).  The compiler then does not know the instruction's wait states: a and b come from LDS reads that have
+// been waited for, c is next touched by another product of the same kind, and the epilogues read it through AccReader,
+// behind the wait states that a reader of the results needs.
+__device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+// Reads accumulators after the k-loop: the reads depend on `settled`, which the wait states produce, and take their operand
+// from the accumulation registers as it is (copied out by the compiler all 256 would be wanted at once: spills).
+struct AccReader {
+  int settled;
+  __device__ __forceinline__ AccReader() { asm volatile("s_nop 15\n\ts_nop 7\n\ts_mov_b32 %0, 0" : "=s"(settled)); }
+  __device__ __forceinline__ float operator()(const f32x4& c, int r) const {
+    float x;
+    asm("v_accvgpr_read_b32 %0, %1 ; %2" : "=v"(x) : "a"(c[r]), "s"(settled));
+    return x;
+  }
+  __device__ __forceinline__ f32x4 operator()(const f32x4& c) const {
+    return f32x4{(*this)(c, 0), (*this)(c, 1), (*this)(c, 2), (*this)(c, 3)};
+  }
+};
+
+// The fragments of kN 16-row blocks.  Read r of the set is r-th in block order (two reads make a fragment of a k-major tile).
+template <Src kS, int kN>
+struct FragSet {
+  static constexpr int kReads = kN * FragReader<kS>::kReads;
+  typename std::conditional<is_kmajor(kS), s16x4, bf16x8>::type v[kReads];
+  template <int kR>
+  __device__ __forceinline__ void read(const FragReader<kS>& rd, const char* tile) {
+    if constexpr (is_kmajor(kS)) v[kR] = lds_read_tr16_b64(lds_addr(tile) + rd.off[kR & 3], (kR >> 2) * 2048);
+    else if constexpr (is_interleaved(kS)) v[kR] = *(const bf16x8*)(tile + rd.off[0] + (kR >> 1) * 2048 + (kR & 1) * 256);
+    else v[kR] = *(const bf16x8*)(tile + rd.off[0] + kR * 1024);
+  }
+  template <int kB>
+  __device__ __forceinline__ bf16x8 get() const {
+    if constexpr (is_kmajor(kS)) {
+      const s16x4 a = v[2 * kB], b = v[2 * kB + 1];
+      const s16x8 both = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+      return __builtin_bit_cast(bf16x8, both);
+    } else {
+      return v[kB];
+    }
+  }
+};
+
+template <Src kS>
+using LoaderOf = typename std::conditional<kS == Src::kRows, TileLoaderRows,
+                 typename std::conditional<kS == Src::kKMajorBlocked, TileLoaderKMajor,
+                 typename std::conditional<kS == Src::kKMajorRows, TileLoaderKMajorRows, TileLoader>::type>::type>::type;
+
+// One tile: A (tile tm of the rows of the launch's tile grid) and B (tile tn of its columns).  kPIsB: the result's rows P
+// are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 for a tile of which only the first 128 rows of B are computed.
+//
+// Software pipeline over k-slices of 32.  Slice kt lives in ring buffer kt % 4; its fragments are read into registers while
+// slice kt - 1 is multiplied.  At the barrier in front of slice kt's products every wavefront has the fragments of slice
+// kt, so its buffer is refilled with slice kt + 4 under them, and slice kt + 1 has landed: loads complete in issue order,
+// hence a vmcnt that leaves slices kt + 2 and kt + 3 outstanding.  Slices past the end re-load the last one (into a buffer
+// nobody reads again), which keeps the body branch-free and the count fixed.  The number of slices is even (H is a multiple of
+// 64, the vocabulary and the tokens are padded, ranges start and end at even slices).  The 8 x NB products of a slice are written
+// slot by slot (the compiler may not move anything across a slot's end): fragment reads behind the products of the first
+// half, one every second of them, loads of the refill evenly spaced behind the second half.
+template <class Epilogue, Src kA, Src kB, bool kPIsB, int NB>
+__device__ __forceinline__ void mfma_tile(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int tm, int tn, int range, int slab) {
+  constexpr bool kHalf = NB == 4;
+  constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
+  using LoadA = LoaderOf<kA>;
+  using LoadB = typename std::conditional<kHalf, HalfTileLoader, LoaderOf<kB>>::type;
+  constexpr int kLoadsA = LoadA::kLoads, kLoadsB = LoadB::kLoads, kLoads = kLoadsA + kLoadsB;    // per wavefront and slice
   auto& lds = sm.ring;
-  int* pre_stash = sm.stash;
-  const int m0 = tm * kBM, n0 = tn * kBN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave / (NW / 2), wn = wave % (NW / 2);
-  const int a_row0 = wm * 128, b_row0 = wn * (NB * 32);
-  const int l32 = lane & 31, lhi = lane >> 5;
+  const int a_row0 = (wave >> 1) * 128, b_row0 = (wave & 1) * (NB * 16);
+  const int a0 = tm * kBM + a_row0, b0 = tn * kBN + b_row0;
 
-  f32x16 acc[4][NB];
+  f32x4 acc[NP][NQ];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < NP; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // per-column scalars the epilogue needs (token id, exponent shift): fetched into LDS now, read after the k-loop
-  typename Epilogue::template Pre<NB> pre;
-  epi.template prefetch<NB>(pre_stash, NW * 64, n0 + b_row0, lane, wave);
+  // what the epilogue needs per column (token id, exponent shift): fetched into LDS now, read after the k-loop
+  epi.template prefetch<NQ>(sm.stash[wave], kPIsB ? a0 : b0, lane);
 
-  using Blocked = typename std::conditional<AT, TileLoaderKMajor<NW>, TileLoader<NW>>::type;
-  using Rows = typename std::conditional<AT, TileLoaderKMajorRows<NW>, TileLoaderRows<NW>>::type;
-  constexpr bool kDirect = kA == ASource::kRows || kA == ASource::kKMajorRows;
-  typename std::conditional<kDirect, Rows, Blocked>::type la;
-  typename std::conditional<kHalf, HalfTileLoader, TileLoader<NW>>::type lb;
+  LoadA la;
+  LoadB lb;
   const int kt_all = g.K / kBK;
-  if constexpr (kDirect) la.init(g.A, tm, g.src_rows, g.src_cols, wave, lane);
-  else la.init(g.A, tm, AT ? g.kb_a_src : kt_all, wave, lane);
+  if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) la.init(g.A, tm, g.src_rows, g.src_cols, wave, lane);
+  else la.init(g.A, tm, kA == Src::kKMajorBlocked ? g.kb_a_src : kt_all, wave, lane);
   lb.init(g.B, tn, g.kb_b, wave, lane);
   int kt_n = kt_all;                                           // k-slices this workgroup contracts over
   if (range >= 0) {
@@ -545,188 +489,113 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const Epilogue& epi
     la.start_at(kt0);
     lb.start_at(kt0);
   }
+  auto clamp = [&](int k) { return k < kt_n ? k : kt_n - 1; };
+  auto load_a = [&](auto idx, int st, int k) { la.template issue_one<decltype(idx)::value>(lds[st][0], clamp(k), wave); };
+  auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(lds[st][1], clamp(k), wave); };
 
-  if constexpr (AT) {
-    // k-major A: the row-major pipeline below (refill in two halves), with 4 wavefronts of 128 x 128, every
-    // instruction of the loop placed by hand (substep_slots_kmajor4), and the A fragments through the transposing
-    // read issued as inline assembly.  (The compiler's builtin for that read carries no memory operand, so its
-    // wait-count pass puts a wait for ALL direct-to-LDS loads in flight in front of every such read: vmcnt(0)
-    // inside the k-loop, 20-30 % slower.  As inline assembly the read is invisible to that pass; the kernel
-    // waits for it itself, lgkmcnt(0) before the next substep uses what was read.  An earlier variant kept the
-    // builtin read and hid the loads instead, with 8 wavefronts and compiler-scheduled reads: 3.5 % slower.)
-    static_assert(NW == 4, "the k-major loop is written for 4 wavefronts");
-    KMajorFragOffsets fo;
-    fo.init(lane);
-    const int a_blk0 = a_row0 / 32;
-#pragma unroll
-    for (int st = 0; st < kStages; ++st) {
-      const int k = st < kt_n ? st : kt_n - 1;
-      la.template issue_one<0>(lds[st][0], k, wave);
-      la.template issue_one<1>(lds[st][0], k, wave);
-      la.template issue_one<2>(lds[st][0], k, wave);
-      la.template issue_one<3>(lds[st][0], k, wave);
-      if (st < kStages - 1) lb.issue(lds[st][1], k, wave);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 1) * kLoadsA + (kStages - 2) * kLoadsB));   // slice 0 has landed
-    __syncthreads();
-    s16x4 ah[2][8];
-    bf16x8 bfr[2][NB];
-    auto a_bases = [&](int stage, int ks, uint32_t (&out)[2]) {
-      const uint32_t piece0 = lds_addr(lds[stage][0] + a_blk0 * 2048 + ks * 1024);
-      out[0] = piece0 + fo.off[0];
-      out[1] = piece0 + fo.off[1];
-    };
-    auto join = [&](const s16x4 (&h)[8], bf16x8 (&out)[4]) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const s16x8 both = {h[2 * i][0], h[2 * i][1], h[2 * i][2], h[2 * i][3], h[2 * i + 1][0], h[2 * i + 1][1], h[2 * i + 1][2], h[2 * i + 1][3]};
-        out[i] = __builtin_bit_cast(bf16x8, both);
-      }
-    };
-    {
-      uint32_t ar[2];
-      a_bases(0, 0, ar);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) ah[0][m] = lds_read_tr16_b64(ar[m & 1], (m / 2) * 2048);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) bfr[0][j] = *(const bf16x8*)(lds[0][1] + lds_chunk_off(b_row0 + j * 32 + l32, lhi));
-    }
-    for (int kt = 0; kt < kt_n; ++kt) {
-      const int cur = kt % kStages, nxt = (kt + 1) % kStages, last = (kt + kStages - 1) % kStages;
-      int k1 = kt + kStages - 1;
-      k1 = k1 < kt_n ? k1 : kt_n - 1;
-      int k2 = kt + kStages;
-      k2 = k2 < kt_n ? k2 : kt_n - 1;
-      uint32_t ar[2];
-      bf16x8 au[4];
-      // first k-substep of slice kt: reads its second substep's fragments, refills the B tile of slice kt + 3
-      a_bases(cur, 1, ar);
-      __builtin_amdgcn_s_waitcnt(0xc07f);                      // lgkmcnt(0): the fragments read under the last substep
-      join(ah[0], au);
-      __builtin_amdgcn_sched_barrier(0);
-      substep_slots_kmajor4<NB, false>(acc, au, bfr[0], ah[1], bfr[1], ar, lds[cur][1] + lds_chunk_off(b_row0 + l32, 2 + lhi),
-                                   la, lb, lds[last][1], k1, wave);
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kLoadsPerWave) & 0xf0ff);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      // second k-substep: reads the first fragments of slice kt + 1, refills the A tile of lds[cur] with slice kt + 4
-      a_bases(nxt, 0, ar);
-      join(ah[1], au);
-      __builtin_amdgcn_sched_barrier(0);
-      substep_slots_kmajor4<NB, true>(acc, au, bfr[1], ah[0], bfr[0], ar, lds[nxt][1] + lds_chunk_off(b_row0 + l32, lhi),
-                                  la, lb, lds[cur][0], k2, wave);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
-    __syncthreads();
-    epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
-    return;
-  } else if constexpr (kA == ASource::kRows) {
-    // A from rows: the pipeline below, two slices per turn.  A slice is 64 bytes of a row, half a cache line; fetched
-    // a slice apart, the halves cost the line twice on the way from the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 as
-    // below, 11.48 from the repacked copy).  So both A tiles of slices
-    // kt + 3 and kt + 4 are refilled under the second k-substep of an odd slice kt, half after half; B as below.  Issue order:
-    // [even kt] B(kt + 3) [odd kt] B(kt + 3) A(kt + 3) A(kt + 4).  "Slice kt + 1 has landed" is then eight loads of A and two Bs
-    // at the barrier of an even slice (B A A of slice kt - 1, B of kt), two Bs at that of an odd one (of kt - 1 and kt).  H is a multiple of 64: the number of slices is even.
-    static_assert(NW == 4, "the loop is written for 4 wavefronts");
-    auto clamp = [&](int k) { return k < kt_n ? k : kt_n - 1; };
-    auto pair = [&](int st, int k) {
-      la.template issue_one<0>(lds[st][0], clamp(k), wave);
-      la.template issue_one<0>(lds[st + 1][0], clamp(k + 1), wave);
-      la.template issue_one<1>(lds[st][0], clamp(k), wave);
-      la.template issue_one<1>(lds[st + 1][0], clamp(k + 1), wave);
-      la.template issue_one<2>(lds[st][0], clamp(k), wave);
-      la.template issue_one<2>(lds[st + 1][0], clamp(k + 1), wave);
-      la.template issue_one<3>(lds[st][0], clamp(k), wave);
-      la.template issue_one<3>(lds[st + 1][0], clamp(k + 1), wave);
-    };
-    pair(0, 0);
-    lb.issue(lds[0][1], 0, wave);
-    lb.issue(lds[1][1], clamp(1), wave);
-    pair(2, 2);
-    lb.issue(lds[2][1], clamp(2), wave);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsA + 2 * kLoadsB));   // slice 0 has landed (younger: B1, A2, A3, B2)
-    __syncthreads();
-    bf16x8 af[2][4], bfr[2][NB];
-    load_frags<NB>(lds[0][0], lds[0][1], a_row0, b_row0, l32, lhi, 0, af[0], bfr[0]);
-    for (int kt = 0; kt < kt_n; kt += 2) {
-      const int c0 = kt % kStages, c1 = c0 + 1, c2 = (c0 + 2) % kStages, c3 = c2 + 1;    // buffers of slices kt .. kt + 3
-      __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<NB, 0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c0][0], lds[c0][1], a_row0, b_row0, l32, lhi, 1, la, lb,
-                            lds[c3][1], nullptr, clamp(kt + 3), 0, wave);
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsA + 2 * kLoadsB) & 0xf0ff);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<NB, 2>(acc, af[1], bfr[1], af[0], bfr[0], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 0, la, lb,
-                            nullptr, nullptr, 0, 0, wave);
-      substep_slots_rows<NB, 0>(acc, af[0], bfr[0], af[1], bfr[1], lds[c1][0], lds[c1][1], a_row0, b_row0, l32, lhi, 1, la, lb,
-                            lds[c0][1], nullptr, clamp(kt + 4), 0, wave);
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoadsB) & 0xf0ff);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      substep_slots_rows<NB, 1>(acc, af[1], bfr[1], af[0], bfr[0], lds[c2][0], lds[c2][1], a_row0, b_row0, l32, lhi, 0, la, lb,
-                            lds[c0][0], lds[c1][0], clamp(kt + 4), clamp(kt + 5), wave);
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
-    __syncthreads();
-    epi.unstash(pre, pre_stash, NW * 64);
-    epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
-  } else {
-  // Software pipeline over k-slices of 32.  Slice kt lives in lds[kt % 4]; three slices are
-  // in flight while one is consumed, so a load has two to three iterations to land.  The barrier
-  // sits between the two k-substeps of a slice; once it is passed, every wavefront has finished
-  // reading slice kt and its buffer may be refilled.  The refill is issued in two halves so that
-  // the loads of the NW wavefronts (which run in step) do not reach the CU's one address unit
-  // all within a few hundred cycles: the A tile under the second substep of slice kt, the B tile
-  // under the first substep of slice kt+1, each load one or two MFMAs after the previous one.
-  // Loads complete in issue order (A0 B0 A1 B1 ...), hence "slice kt+1 has landed" at the barrier of
-  // slice kt is vmcnt(2 * kLoadsPerWave): the halves of the two younger slices may be outstanding.
-  // Slices past the end re-load the last one (into a buffer nobody reads again) to keep the body
-  // branch-free and the count fixed.
-  static_assert(!kHalf, "half tiles are read from rows");
-  constexpr int kHalfLoads = kLoadsPerWave / 2;                // loads per wavefront and operand tile
-#pragma unroll
-  for (int st = 0; st < kStages; ++st) {
-    const int k = st < kt_n ? st : kt_n - 1;
-    la.issue(lds[st][0], k, wave);
-    if (st < kStages - 1) lb.issue(lds[st][1], k, wave);
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm((2 * kStages - 3) * kHalfLoads));   // slice 0 has landed
-  __syncthreads();
-  bf16x8 af[2][4], bfr[2][NB];
-  load_frags<NB>(lds[0][0], lds[0][1], a_row0, b_row0, l32, lhi, 0, af[0], bfr[0]);
+  FragReader<kA> ra;
+  FragReader<kB> rb;
+  ra.init(a_row0, lane);
+  rb.init(b_row0, lane);
+  FragSet<kA, 8> fa[2];
+  FragSet<kB, NB> fb[2];
+  constexpr int kReadsA = FragSet<kA, 8>::kReads, kReads = kReadsA + FragSet<kB, NB>::kReads;
 
-  for (int kt = 0; kt < kt_n; ++kt) {
-    const int cur = kt % kStages, nxt = (kt + 1) % kStages, last = (kt + kStages - 1) % kStages;
-    // first k-substep of slice kt; under its MFMAs: the second substep's fragments and the B half of
-    // the refill of the buffer released at the previous barrier (slice kt + 3)
-    int k1 = kt + kStages - 1;
-    k1 = k1 < kt_n ? k1 : kt_n - 1;
+  // products of the slice whose fragments are in set kCur; between them the fragments of the next one from ring buffer
+  // `next` into the other set and load(n), n = 0 .. kN - 1
+  auto products = [&](auto cur, int next, auto count, auto load) {
+    constexpr int kCur = decltype(cur)::value, kN = decltype(count)::value, kSlots = 8 * NB, kReadSpan = kSlots / 2;
+    const char *a_tile = lds[next][0], *b_tile = lds[next][1];
+    static_for<kSlots>([&](auto slot) {
+      constexpr int m = decltype(slot)::value, i = m / NB, j = (i & 1) ? NB - 1 - m % NB : m % NB;
+      if constexpr (kPIsB) mfma16(acc[j][i], fb[kCur].template get<j>(), fa[kCur].template get<i>());
+      else mfma16(acc[i][j], fa[kCur].template get<i>(), fb[kCur].template get<j>());
+      constexpr int r0 = spread(m, kReads, kReadSpan), r1 = spread(m + 1, kReads, kReadSpan);
+      static_for<r1 - r0>([&](auto read) {
+        constexpr int r = r0 + decltype(read)::value;
+        if constexpr (r < kReadsA) fa[1 - kCur].template read<r>(ra, a_tile);
+        else fb[1 - kCur].template read<r - kReadsA>(rb, b_tile);
+      });
+      constexpr int n0 = spread(m - kReadSpan, kN, kSlots - kReadSpan), n1 = spread(m + 1 - kReadSpan, kN, kSlots - kReadSpan);
+      static_for<n1 - n0>([&](auto n) { load(std::integral_constant<int, n0 + decltype(n)::value>{}); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // between two slices: this wavefront's fragments are in its registers and its share of all but the `young` youngest
+  // loads has landed; the barrier covers the others' shares
+  auto turn = [&](auto young) {
     __builtin_amdgcn_sched_barrier(0);
-    substep_slots<NW, NB>(acc, af[0], bfr[0], af[1], bfr[1], lds[cur][0], lds[cur][1], a_row0, b_row0, l32, lhi, 1,
-                          lb, lds[last][1], k1, wave);
-    // slice kt+1 has landed (this wavefront's share; the barrier covers the others) and this
-    // wavefront has finished reading slice kt, whose buffer is refilled from here on
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kStages - 2) * kLoadsPerWave) & 0xf0ff);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(decltype(young)::value) & 0xf0ff);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    // second k-substep; under it: first fragments of slice kt+1 and the A half of the refill of lds[cur]
-    int k2 = kt + kStages;
-    k2 = k2 < kt_n ? k2 : kt_n - 1;
-    substep_slots<NW, NB>(acc, af[1], bfr[1], af[0], bfr[0], lds[nxt][0], lds[nxt][1], a_row0, b_row0, l32, lhi, 0,
-                          la, lds[cur][0], k2, wave);
-  }
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
-  __syncthreads();
+  };
+  auto first_frags = [&] {
+    static_for<kReadsA>([&](auto r) { fa[0].template read<decltype(r)::value>(ra, lds[0][0]); });
+    static_for<kReads - kReadsA>([&](auto r) { fb[0].template read<decltype(r)::value>(rb, lds[0][1]); });
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 0> zero{};
+  constexpr integral_constant<int, 1> one{};
 
-  epi.unstash(pre, pre_stash, NW * 64);
-  epi(acc, pre, m0 + a_row0, n0 + b_row0, lane, wave, &lds[0][0][0], slab);
+  if constexpr (kA == Src::kRows) {
+    // A slice is 64 bytes of a row, half a cache line; fetched a slice apart, the halves cost the line twice on the way from
+    // the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 as below, 11.48 from the repacked copy).  So two slices' A tiles are
+    // refilled at once, half after half.  Issue order: [even kt] B(kt + 3) B(kt + 4) [odd kt] A(kt + 3) A(kt + 4).  "Slice
+    // kt + 1 has landed" leaves one B and two As outstanding in front of an even slice, two Bs in front of an odd one.
+    constexpr integral_constant<int, 2 * kLoadsA + kLoadsB> young_even{};
+    constexpr integral_constant<int, 2 * kLoadsB> young_odd{};
+    auto pair = [&](auto n, int st, int k) {                   // load n of two tiles: 0 .. 2 kLoadsA - 1
+      constexpr int i = decltype(n)::value;
+      load_a(integral_constant<int, i / 2>{}, st + (i & 1), k + (i & 1));
+    };
+    static_for<2 * kLoadsA>([&](auto n) { pair(n, 0, 0); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 0, 0); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 1, 1); });
+    static_for<2 * kLoadsA>([&](auto n) { pair(n, 2, 2); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 2, 2); });
+    turn(integral_constant<int, 2 * kLoadsA + 2 * kLoadsB>{});
+    first_frags();
+    turn(young_even);
+    for (int kt = 0; kt < kt_n; kt += 2) {
+      const int c0 = kt % kStages, c3 = (kt + 3) % kStages;    // buffers of slices kt and kt + 3
+      products(zero, c0 + 1, integral_constant<int, 2 * kLoadsB>{}, [&](auto n) {
+        constexpr int i = decltype(n)::value;
+        load_b(integral_constant<int, i % kLoadsB>{}, i < kLoadsB ? c3 : c0, i < kLoadsB ? kt + 3 : kt + 4);
+      });
+      turn(young_odd);
+      products(one, (c0 + 2) % kStages, integral_constant<int, 2 * kLoadsA>{}, [&](auto n) { pair(n, c0, kt + 4); });
+      turn(young_even);
+    }
+  } else {
+    auto load = [&](auto n, int st, int k) {
+      constexpr int i = decltype(n)::value;
+      if constexpr (i < kLoadsA) load_a(n, st, k);
+      else load_b(integral_constant<int, i - kLoadsA>{}, st, k);
+    };
+    constexpr integral_constant<int, (kStages - 2) * kLoads> young{};
+#pragma unroll
+    for (int st = 0; st < kStages; ++st) static_for<kLoads>([&](auto n) { load(n, st, st); });
+    turn(integral_constant<int, (kStages - 1) * kLoads>{});
+    first_frags();
+    turn(young);
+    auto slice = [&](auto cur, int kt) {
+      products(cur, (kt + 1) % kStages, integral_constant<int, kLoads>{}, [&](auto n) { load(n, kt % kStages, kt + kStages); });
+      turn(young);
+    };
+    for (int kt = 0; kt < kt_n; kt += 2) {
+      slice(zero, kt);
+      slice(one, kt + 1);
+    }
   }
+  const AccReader rd;
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
+  epi(acc, rd, kPIsB ? b0 : a0, kPIsB ? a0 : b0, lane, sm.stash[wave], slab);
 }
 
-template <class Epilogue, int NW, ASource kA = ASource::kBlocked>
-__global__ void __launch_bounds__(NW * 64, 1)
-gemm_nt_kernel(GemmArgs g, Epilogue epi) {
-  __shared__ __attribute__((aligned(1024))) GemmShared<Epilogue::template stash_words<16 / NW>() * NW * 64> sm;
+template <class Epilogue, Src kA, Src kB, bool kPIsB>
+__global__ void __launch_bounds__(256, 1)
+mfma_nt_kernel(GemmArgs g, Epilogue epi) {
+  __shared__ __attribute__((aligned(1024))) GemmShared sm;
   int tm, tn;
   const int n_tiles = g.tiles_m * g.tiles_n;
   int pid = (int)blockIdx.x, range = -1, slab = -1;           // range of the contraction axis / slab (-1: whole axis)
@@ -740,13 +609,13 @@ gemm_nt_kernel(GemmArgs g, Epilogue epi) {
   tile_of_block(g, pid, tm, tn);
   // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 of them
   // computes only those (301 log-probs at the 0.6B head: logits 153 -> 132 us; 59 tokens at the 8B head: call 1155 -> 1067 us).
-  if constexpr (kA == ASource::kRows || kA == ASource::kKMajorRows) {
+  if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
     if (epi.n_valid - tn * kBN <= kBN / 2) {
-      gemm_tile<Epilogue, NW, kA, 2>(g, epi, sm, tm, tn, range, slab);
+      mfma_tile<Epilogue, kA, kB, kPIsB, 4>(g, epi, sm, tm, tn, range, slab);
       return;
     }
   }
-  gemm_tile<Epilogue, NW, kA, 16 / NW>(g, epi, sm, tm, tn, range, slab);
+  mfma_tile<Epilogue, kA, kB, kPIsB, 8>(g, epi, sm, tm, tn, range, slab);
 }
 
 // ------------------------------------------------------------- epilogues ----
@@ -764,377 +633,217 @@ struct LogitsEpilogue {
   const int32_t* ids;              // target ids of the chunk's tokens
   const float* ref;                // [ld_part] exponent shift per token
 
-  static constexpr int kStageRow = 272;        // bytes per token row of the LDS staging tile (128 bf16 + pad)
-
   // The per-column scalars the epilogue needs (token id, exponent shift) are fetched before the k-loop
   // straight into LDS (direct-to-LDS loads of 4 bytes per lane, from a clamped index; n_valid >= 1 in
   // every launch) and read back after it: they wait for nothing, hold no registers across the loop, and
-  // are older than every operand load, so the loop's load counting is unchanged.  (Fetched into registers
-  // they either cost a wait before the first operand loads, or live across the loop, where the compiler
-  // spilled some of them and each reload in the epilogue waited for the stores in flight.)
-  template <int NB> struct Pre { int y[NB]; float shift[NB]; };
-  template <int NB> static constexpr int stash_words() { return 2 * NB; }
-  template <int NB>
-  __device__ __forceinline__ void prefetch(int* words, int n_threads, int k0, int lane, int wave) const {
+  // are older than every operand load, so the loop's load counting is unchanged.  words: this wavefront's, ids in the first
+  // 128, shifts in the others.
+  template <int NQ>
+  __device__ __forceinline__ void prefetch(int* words, int k0, int lane) const {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int kk = k0 + nb * 32 + (lane & 31);
+    for (int i = 0; i < NQ / 4; ++i) {
+      const int kk = k0 + i * 64 + lane;
       const int kc = kk < n_valid ? kk : n_valid - 1;
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ids + kc),
-                                       (__attribute__((address_space(3))) void*)(words + (2 * nb) * n_threads + wave * 64), 4, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(words + i * 64), 4, 0, 0);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ref + kc),
-                                       (__attribute__((address_space(3))) void*)(words + (2 * nb + 1) * n_threads + wave * 64), 4, 0, 0);
-    }
-  }
-  template <int NB>
-  __device__ __forceinline__ void unstash(Pre<NB>& pre, const int* words, int n_threads) const {
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      pre.y[nb] = words[(2 * nb) * n_threads + threadIdx.x];
-      pre.shift[nb] = __builtin_bit_cast(float, words[(2 * nb + 1) * n_threads + threadIdx.x]);
+                                       (__attribute__((address_space(3))) void*)(words + 128 + i * 64), 4, 0, 0);
     }
   }
 
-  template <int NB>
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][NB], const Pre<NB>& pre, int v0, int k0, int lane, int wave,
-                                             char* lds, int) const {
-    constexpr int kTok = NB * 32;                          // token columns of this wavefront
-    const int l32 = lane & 31, lhi = lane >> 5;
+  // acc: rows = vocabulary, interleaved: element r of acc[2 j + p][nb] in lane l is entry v0 + 32 j + 8 (l / 16) + 4 p + r of
+  // token k0 + 16 nb + l % 16
+  template <int NQ>
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[8][NQ], const AccReader& rd, int v0, int k0, int lane, const int* words, int) const {
+    const int l15 = lane & 15, g = lane >> 4;
     const int granule = v0 / kGranule;
     const bool all_rows_valid = v0 + kGranule <= V;
     constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
 
-    int y_of[NB];                  // target id of this lane's token per column block; -1: padding column, or
-    float shift_of[NB];            // an id outside the vocabulary (matches no row)
+    int y_of[NQ];                  // target id of this lane's token per column block; -1: padding column, or
+    float shift_of[NQ];            // an id outside the vocabulary (matches no row)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const bool tok_valid = k0 + nb * 32 + l32 < n_valid;
-      y_of[nb] = (tok_valid && pre.y[nb] >= 0 && pre.y[nb] < V) ? pre.y[nb] : -1;
-      shift_of[nb] = tok_valid ? pre.shift[nb] : 0.f;
+    for (int nb = 0; nb < NQ; ++nb) {
+      const bool tok_valid = k0 + nb * 16 + l15 < n_valid;
+      const int y = words[nb * 16 + l15];
+      y_of[nb] = (tok_valid && y >= 0 && y < V) ? y : -1;
+      shift_of[nb] = tok_valid ? __builtin_bit_cast(float, words[128 + nb * 16 + l15]) : 0.f;
     }
 
-    // exact target logit, if the target row lies in this granule and in this lane's half
+    // exact target logit, if the target row lies in this granule and in this lane's quarter
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+    for (int nb = 0; nb < NQ; ++nb) {
       const int yrel = y_of[nb] - v0;
       if (__any(yrel >= 0 && yrel < kGranule)) {
-        if (yrel >= 0 && yrel < kGranule && ((yrel >> 2) & 1) == lhi) {
+        if (yrel >= 0 && yrel < kGranule && ((yrel >> 3) & 3) == g) {
           float zt = 0.f;
 #pragma unroll
-          for (int mb = 0; mb < 4; ++mb)
+          for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (yrel == mb * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3)) zt = acc[mb][nb][r];
-          z_target[k0 + nb * 32 + l32] = zt;
+            for (int r = 0; r < 4; ++r) {
+              const float z = rd(acc[mb][nb], r);
+              zt = yrel == (mb >> 1) * 32 + 8 * g + 4 * (mb & 1) + r ? z : zt;
+            }
+          z_target[k0 + nb * 16 + l15] = zt;
         }
       }
     }
 
-    // One pass over the accumulators, 32 token columns (all 128 vocabulary rows of the wavefront) at a
+    // One pass over the accumulators, 16 token columns (all 128 vocabulary rows of the wavefront) at a
     // time: E = exp(min(z - shift, 70)) as 2^(min(z * log2(e) - shift * log2(e), 70 * log2(e))) (one fma,
-    // one min and the hardware exponential per logit, sixteen at a time with independent temporaries),
-    // its running sums, and at once the store of those columns, so that the stores of one group are in
-    // flight under the exponentials of the next.  E is stored once, rows = token, k = vocabulary (the
-    // dH contraction reads it as it is, the dW contraction through the transposing LDS read): a lane
-    // holds 4 consecutive vocabulary entries of its token; the 32 x 128 group is staged through this
-    // wavefront's own part of the LDS ring (free after the k-loop) and leaves as 16-byte stores, 1 KiB
-    // (16 token rows of one 32-wide vocabulary slice) contiguous per instruction.  The staging area is
-    // private to the wavefront and LDS operations of one wavefront execute in order, so no barrier is
-    // needed between its writes, its reads and the next group's writes.
-    char* stage = lds + wave * (32 * kStageRow);
+    // one min and the hardware exponential per logit, eight at a time with independent temporaries),
+    // its running sums, and at once the store.  E is stored once, rows = token, k = vocabulary (the
+    // dH contraction reads it as it is, the dW contraction through the transposing LDS read): the rows of W are read
+    // interleaved, so a lane holds 8 consecutive vocabulary entries of its token, one 16-byte chunk of the blocked layout,
+    // and an instruction stores 1 KiB (16 token rows of one 32-wide vocabulary slice) contiguous.
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
+    for (int nb = 0; nb < NQ; ++nb) {
       const float nshift2 = -shift_of[nb] * kLog2e;
+      uint16_t* e_row = kStoreE ? Eb + blk_off(k0 + nb * 16 + l15, v0 + 8 * g, kb_z) : nullptr;
       float s2[2] = {0.f, 0.f}, t2[2] = {0.f, 0.f};        // two independent chains per sum
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        float x2[16], e[16];
+      for (int j = 0; j < 4; ++j) {
+        float x2[8], e[8];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) x2[r] = fminf(fmaf(acc[mb][nb][r], kLog2e, nshift2), 70.f * kLog2e);
+        for (int r = 0; r < 8; ++r) x2[r] = fminf(fmaf(rd(acc[2 * j + (r >> 2)][nb], r & 3), kLog2e, nshift2), 70.f * kLog2e);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(x2[r]);
+        for (int r = 0; r < 8; ++r) e[r] = __builtin_amdgcn_exp2f(x2[r]);
         if (!all_rows_valid) {                             // only the last vocabulary tile pays for the row check
 #pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (v0 + mb * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3) >= V) e[r] = 0.f;
+          for (int r = 0; r < 8; ++r)
+            if (v0 + j * 32 + 8 * g + r >= V) e[r] = 0.f;
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < 8; ++r) {
           s2[r & 1] += e[r];
           if (kEntropy) t2[r & 1] = fmaf(e[r], x2[r], t2[r & 1]);
         }
         if (kStoreE) {
+          u32x4v w;
 #pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            uint2 w;
-            w.x = pack_bf16x2(e[4 * r4], e[4 * r4 + 1]);
-            w.y = pack_bf16x2(e[4 * r4 + 2], e[4 * r4 + 3]);
-            *(uint2*)(stage + l32 * kStageRow + (mb * 32 + 8 * r4 + 4 * lhi) * 2) = w;
-          }
+          for (int r = 0; r < 4; ++r) w[r] = pack_bf16x2(e[2 * r], e[2 * r + 1]);
+          NAT_E_STORE((u32x4v*)(e_row + j * kBlkElems), w);
         }
       }
-      if (kStoreE) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {                      // vocabulary slice i / 2, token rows (i % 2) * 16 .. + 15
-          const int sl = i >> 1, tok = (i & 1) * 16 + (lane >> 2), ch = lane & 3;
-          const uint4 val = *(const uint4*)(stage + tok * kStageRow + sl * 64 + ch * 16);
-          NAT_E_STORE((u32x4v*)(Eb + blk_off(k0 + nb * 32 + tok, v0 + sl * 32 + ch * 8, kb_z)), __builtin_bit_cast(u32x4v, val));
-        }
-      }
-      const int kk = k0 + nb * 32 + l32;                   // token column (always inside the padded chunk)
+      const int kk = k0 + nb * 16 + l15;                   // token column (always inside the padded chunk)
       float sum = s2[0] + s2[1];
+      sum += __shfl_xor(sum, 16);
       sum += __shfl_xor(sum, 32);
-      if (lhi == 0) s_part[(int64_t)granule * ld_part + kk] = sum;
+      if (g == 0) s_part[(int64_t)granule * ld_part + kk] = sum;
       if (kEntropy) {
         float t = (t2[0] + t2[1]) * kLn2;                  // back to natural-log units
+        t += __shfl_xor(t, 16);
         t += __shfl_xor(t, 32);
-        if (lhi == 0) t_part[(int64_t)granule * ld_part + kk] = t;
+        if (g == 0) t_part[(int64_t)granule * ld_part + kk] = t;
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 };
 
-// dH tile: rows = tokens of the chunk (A = E), columns = hidden units (B = W^T); rows scaled by beta.
+// dH tile: rows = hidden units (W^T, either interleaved or, when W is read as it is, k-major in order), columns = tokens of
+// the chunk (E); columns scaled by beta.  A lane holds its token's hidden units h0 + 32 j + 8 (l / 16) .. + 7 in acc[2 j], acc[2 j + 1]
+// (interleaved: one 16-byte store, 64 bytes of 16 token rows per instruction) or h0 + 16 i + 4 (l / 16) .. + 3 in acc[i].
+template <bool kInterleaved>
 struct DHiddenEpilogue {
-  int n_valid, H;
-  uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
-  const float* beta;               // [n_valid]
-  float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
-
-  template <int NB> struct Pre {};
-  template <int NB> static constexpr int stash_words() { return 0; }
-  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
-  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
-  template <int NB>
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][NB], const Pre<NB>&, int k0, int h0, int lane, int wave,
-                                             char* lds, int slab_id) const {
-    const int l32 = lane & 31, lhi = lane >> 5;
-    if (slab_id >= 0) {            // this workgroup's range of the vocabulary: the raw sums go to its slab
-      float* slab = partial + (int64_t)slab_id * (kBM * kBN);
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int k = k0 + mb * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-          if (k >= n_valid) continue;                          // padding rows of a short batch are not read back
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) slab[(k & (kBM - 1)) * kBN + (h0 & (kBN - 1)) + nb * 32 + l32] = acc[mb][nb][r];
-        }
-      return;
-    }
-    // 32 token rows at a time: beta_k * acc rounded to bf16 goes through this wavefront's own part of the LDS
-    // ring (free after the k-loop; rows of NB * 64 + 16 bytes) and leaves as 16-byte stores, whole rows of the
-    // wavefront's NB * 32 columns contiguous (2-byte stores straight from the accumulators took 80 k cycles
-    // per tile).  LDS operations of one wavefront execute in order: no barrier between its writes and reads.
-    constexpr int kRowBytes = NB * 64, kStageRow = kRowBytes + 16;
-    constexpr int kChunks = kRowBytes / 16, kRowsPerStore = 64 / kChunks;
-    char* stage = lds + wave * (32 * kStageRow);
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * lhi + (r & 3);
-        const int k = k0 + mb * 32 + row;
-        const float b = k < n_valid ? beta[k] : 0.f;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          *(uint16_t*)(stage + row * kStageRow + (nb * 32 + l32) * 2) = f32_to_bf16_bits(b * acc[mb][nb][r]);
-      }
-#pragma unroll
-      for (int i = 0; i < 32 / kRowsPerStore; ++i) {
-        const int row = i * kRowsPerStore + lane / kChunks, ch = lane % kChunks;
-        const uint4 val = *(const uint4*)(stage + row * kStageRow + ch * 16);
-        const int k = k0 + mb * 32 + row, h = h0 + ch * 8;
-        if (k < n_valid && h < H) *(uint4*)(dH + (int64_t)k * H + h) = val;     // H is a multiple of 8: whole chunks
-      }
-    }
-  }
-};
-
-// dH^T tile of the contraction that reads W as it is: rows = hidden units (A = W^T, k-major), columns = tokens (B = E).
-// A lane holds four consecutive hidden units of its token: 8-byte LDS writes, then the same 16-byte stores of whole rows.
-// (11 registers go to scratch, 9 in the epilogue of the repacked path: the accumulators fill the file.)
-struct DHiddenTEpilogue {
   int n_valid, H;
   uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
   const float* beta;               // [n_valid]
   float* partial;                  // tiles whose contraction is cut into ranges: [slab][256 tokens][256 hidden] fp32 raw sums
 
-  template <int NB> struct Pre {};
-  template <int NB> static constexpr int stash_words() { return 0; }
-  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
-  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
-  template <int NB>
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[4][NB], const Pre<NB>&, int h0, int k0, int lane, int wave,
-                                             char* lds, int slab_id) const {
-    const int l32 = lane & 31, lhi = lane >> 5;
-    if (slab_id >= 0) {
-      float* slab = partial + (int64_t)slab_id * (kBM * kBN);
+  template <int NQ> __device__ __forceinline__ void prefetch(int*, int, int) const {}
+  template <int NQ>
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[8][NQ], const AccReader& rd, int h0, int k0, int lane, const int*, int slab_id) const {
+    const int l15 = lane & 15, g = lane >> 4;
+    if (slab_id >= 0) {            // this workgroup's range of the vocabulary: the raw sums go to its slab
+      float* slab = partial + (int64_t)slab_id * (kBM * kBN) + (h0 & (kBM - 1));
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const int k = k0 + nb * 32 + l32;
-        if (k >= n_valid) continue;
+      for (int nb = 0; nb < NQ; ++nb) {
+        const int k = k0 + nb * 16 + l15;
+        if (k >= n_valid) continue;                            // padding rows of a short batch are not read back
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            *(float4*)(slab + (k & (kBN - 1)) * kBM + (h0 & (kBM - 1)) + mb * 32 + 8 * r4 + 4 * lhi) =
-                make_float4(acc[mb][nb][4 * r4], acc[mb][nb][4 * r4 + 1], acc[mb][nb][4 * r4 + 2], acc[mb][nb][4 * r4 + 3]);
+        for (int i = 0; i < 8; ++i)
+          *(f32x4*)(slab + (k & (kBN - 1)) * kBM + (kInterleaved ? (i >> 1) * 32 + 8 * g + 4 * (i & 1) : i * 16 + 4 * g)) = rd(acc[i][nb]);
       }
       return;
     }
-    constexpr int kStageRow = 128 * 2 + 16;                    // 128 hidden units of a token, and 16 bytes of padding
-    char* stage = lds + wave * (32 * kStageRow);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int kk = k0 + nb * 32 + l32;
-      const float b = kk < n_valid ? beta[kk] : 0.f;
+    for (int nb = 0; nb < NQ; ++nb) {
+      const int k = k0 + nb * 16 + l15;
+      const bool ok = k < n_valid;
+      const float b = ok ? beta[k] : 0.f;
+      uint16_t* row = dH + (int64_t)k * H + h0;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          uint2 w;
-          w.x = pack_bf16x2(b * acc[mb][nb][4 * r4], b * acc[mb][nb][4 * r4 + 1]);
-          w.y = pack_bf16x2(b * acc[mb][nb][4 * r4 + 2], b * acc[mb][nb][4 * r4 + 3]);
-          *(uint2*)(stage + l32 * kStageRow + (mb * 32 + 8 * r4 + 4 * lhi) * 2) = w;
+      for (int j = 0; j < 4; ++j) {
+        const f32x4 lo = rd(acc[2 * j][nb]), hi = rd(acc[2 * j + 1][nb]);
+        const uint2 wl = make_uint2(pack_bf16x2(b * lo[0], b * lo[1]), pack_bf16x2(b * lo[2], b * lo[3]));
+        const uint2 wh = make_uint2(pack_bf16x2(b * hi[0], b * hi[1]), pack_bf16x2(b * hi[2], b * hi[3]));
+        if (!ok || h0 + 32 * j >= H) continue;                 // H is a multiple of 64: 32 units are in or out
+        if (kInterleaved) {
+          *(uint4*)(row + 32 * j + 8 * g) = make_uint4(wl.x, wl.y, wh.x, wh.y);
+        } else {
+          *(uint2*)(row + 32 * j + 4 * g) = wl;
+          *(uint2*)(row + 32 * j + 16 + 4 * g) = wh;
         }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {                            // four token rows of 256 bytes per instruction
-        const int row = i * 4 + (lane >> 4), ch = lane & 15;
-        const uint4 val = *(const uint4*)(stage + row * kStageRow + ch * 16);
-        const int k = k0 + nb * 32 + row, h = h0 + ch * 8;
-        if (k < n_valid && h < H) *(uint4*)(dH + (int64_t)k * H + h) = val;
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 };
 
-// dW tile: rows = vocabulary (A = E^T), columns = hidden units (B = (diag(beta) H_chunk)^T).
+// dW tile: rows = hidden units ((diag(beta) H_chunk)^T), columns = vocabulary (E^T): a lane holds hidden units h0 + 16 i + 4 (l / 16)
+// .. + 3 of its vocabulary entry, 16 bytes of a row of dW.
 struct DWeightEpilogue {
   int V, H, accumulate;
   float* dW;                       // [V, H] fp32
   float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
 
-  template <int NB> struct Pre {};
-  template <int NB> static constexpr int stash_words() { return 0; }
-  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
-  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
-  // the wavefront's tile is MA x NB blocks of 32 x 32
-  template <int MA, int NB, class P>
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[MA][NB], const P&, int v0, int h0, int lane, int,
-                                             char*, int slab_id) const {
-    const int l32 = lane & 31, lhi = lane >> 5;
+  template <int NQ> __device__ __forceinline__ void prefetch(int*, int, int) const {}
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[8][8], const AccReader& rd, int h0, int v0, int lane, const int*, int slab_id) const {
+    const int l15 = lane & 15, g = lane >> 4;
     if (slab_id >= 0) {            // one range of this tile's tokens: raw sums to the slab, added up by dw_tail_reduce_kernel
-      float* slab = partial + (int64_t)slab_id * (kBM * kBN);
+      float* slab = partial + (int64_t)slab_id * (kBM * kBN) + ((v0 & (kBM - 1)) + l15) * kBN + (h0 & (kBN - 1)) + 4 * g;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+      for (int nb = 0; nb < 8; ++nb)
 #pragma unroll
-        for (int mb = 0; mb < MA; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            slab[((v0 & (kBM - 1)) + mb * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3)) * kBN + (h0 & (kBN - 1)) + nb * 32 + l32] = acc[mb][nb][r];
+        for (int i = 0; i < 8; ++i) *(f32x4*)(slab + nb * 16 * kBN + i * 16) = rd(acc[i][nb]);
       return;
     }
-    // One owner per element and launch, launches in stream order: the atomic sum is that of a
-    // read-modify-write, but the addition happens at the L2 and the workgroup does not wait for it.
-    // Addresses are a wave-uniform row pointer plus one per-lane offset (rows 4 * lhi further down, column
-    // l32), and the two launch-wide conditions (accumulate or overwrite, every row inside the vocabulary or
-    // the last tile's row check) are taken once, outside the loops: per element that leaves the store or
-    // atomic and a scalar add (per-element branches and 64-bit vector address arithmetic made this epilogue
-    // 31 k cycles per tile).
-    const uint32_t lane_off = (uint32_t)(4 * lhi) * (uint32_t)H + (uint32_t)l32;   // elements
-    const bool rows_ok = v0 + MA * 32 <= V;
-    auto sweep = [&](auto acc_mode, auto checked) {
+    const int rows = V - v0;                                   // valid rows from v0 on (may be <= 0)
+    float* dst = dW + (int64_t)(v0 + l15) * H + h0 + 4 * g;
+    // One owner per element and launch, launches in stream order: one fp32 addition old + sum per element.  Old values
+    // of 16 vocabulary rows are loaded while those before them are added and stored.
+    auto sweep = [&](auto acc_mode, auto all_valid) {
+      constexpr bool kAcc = decltype(acc_mode)::value, kAll = decltype(all_valid)::value;
+      auto ok = [&](int nb, int i) { return kAll || (nb * 16 + l15 < rows && h0 + i * 16 < H); };   // H is a multiple of 64
+      f32x4 old[2][8];
+      auto fetch = [&](int nb) {
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if (h0 + nb * 32 >= H) continue;                     // H is a multiple of 64: a 32-column block is in or out
-#pragma unroll
-        for (int mb = 0; mb < MA; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int v = v0 + mb * 32 + 8 * (r >> 2) + (r & 3);   // row of lanes 0..31 (wave-uniform)
-            if (decltype(checked)::value && v + 4 * lhi >= V) continue;
-            float* p = dW + (int64_t)v * H + (h0 + nb * 32) + lane_off;
-            if (decltype(acc_mode)::value) unsafeAtomicAdd(p, acc[mb][nb][r]);
-            else *p = acc[mb][nb][r];
-          }
-      }
-    };
-    if (accumulate) {
-      if (rows_ok) sweep(std::true_type{}, std::false_type{});
-      else sweep(std::true_type{}, std::true_type{});
-    } else {
-      if (rows_ok) sweep(std::false_type{}, std::false_type{});
-      else sweep(std::false_type{}, std::true_type{});
-    }
-  }
-};
-
-// The same tile added to dW by reading, adding and storing, for short contractions: the fp32 memory atomics above run at
-// 28 cycles an instruction, 1024 per tile, i.e. 1.9 ms for the whole of a 151936 x 4096 dW however few tokens are added to
-// it.  32 rows of the wavefront's tile at a time go through its own part of the LDS ring (free after the k-loop), so that
-// old values come and sums leave 16 bytes per lane, two whole rows of its columns per instruction; the old values are loaded
-// two blocks ahead of their use and before the stores of the block in hand (the load counter would wait for those
-// first).  One fp32 addition old + sum per element, as with the atomics.  See kReadAddSlices.  Two blocks of old values
-// (128 registers), the results and the accumulators do not fit: 65 registers go to scratch in this epilogue, none in the k-loop.
-struct DWeightAddEpilogue {
-  DWeightEpilogue whole;           // ranges of cut tiles still go to their slabs
-
-  template <int NB> struct Pre {};
-  template <int NB> static constexpr int stash_words() { return 0; }
-  template <int NB> __device__ __forceinline__ void prefetch(int*, int, int, int, int) const {}
-  template <int NB> __device__ __forceinline__ void unstash(Pre<NB>&, const int*, int) const {}
-  template <int MA, int NB, class P>
-  __device__ __forceinline__ void operator()(f32x16 (&acc)[MA][NB], const P& pre, int v0, int h0, int lane, int wave,
-                                             char* lds, int slab_id) const {
-    if (slab_id >= 0) {
-      whole(acc, pre, v0, h0, lane, wave, lds, slab_id);
-      return;
-    }
-    constexpr int kCols = NB * 32, kLanesPerRow = kCols / 4, kRowsPer = 64 / kLanesPerRow, kN = 32 / kRowsPer;
-    constexpr int kStageRow = kCols + 8;                       // floats: the two half-wavefronts' rows fall on different banks
-    const int l32 = lane & 31, lhi = lane >> 5, H = whole.H;
-    const int row = lane / kLanesPerRow, col = (lane % kLanesPerRow) * 4;
-    float* stage = (float*)lds + wave * (32 * kStageRow);
-    const int rows = whole.V - v0;                             // valid rows from v0 on (may be <= 0)
-    const bool col_ok = h0 + col < H;                          // H is a multiple of 64: a lane's four columns are in or out
-    float* dst = whole.dW + (int64_t)(v0 + row) * H + h0 + col;
-    auto sweep = [&](auto all_valid) {
-      constexpr bool kAll = decltype(all_valid)::value;        // no row or column to leave out
-      float4 old[2][kN];
-      auto fetch = [&](int mb) {
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          const int r = mb * 32 + i * kRowsPer;
-          if (kAll || (col_ok && r + row < rows)) old[mb & 1][i] = *(const float4*)(dst + (int64_t)r * H);
-          else old[mb & 1][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        for (int i = 0; i < 8; ++i)
+          if (ok(nb, i)) old[nb & 1][i] = *(const f32x4*)(dst + (int64_t)nb * 16 * H + i * 16);
+          else old[nb & 1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
       };
-      fetch(0);
-      fetch(1);
+      if (kAcc) fetch(0);
 #pragma unroll
-      for (int mb = 0; mb < MA; ++mb) {
+      for (int nb = 0; nb < 8; ++nb) {
+        if (kAcc && nb < 7) fetch(nb + 1);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            stage[(8 * (r >> 2) + 4 * lhi + (r & 3)) * kStageRow + nb * 32 + l32] = acc[mb][nb][r];
-        float4 out[kN];
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          const float4 o = old[mb & 1][i], x = *(const float4*)(stage + (i * kRowsPer + row) * kStageRow + col);
-          out[i] = make_float4(o.x + x.x, o.y + x.y, o.z + x.z, o.w + x.w);
+        for (int i = 0; i < 8; ++i) {
+          f32x4 x = rd(acc[i][nb]);
+          if (kAcc) x = old[nb & 1][i] + x;
+          if (ok(nb, i)) *(f32x4*)(dst + (int64_t)nb * 16 * H + i * 16) = x;
         }
-        if (mb + 2 < MA) fetch(mb + 2);
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          const int r = mb * 32 + i * kRowsPer;
-          if (kAll || (col_ok && r + row < rows)) *(float4*)(dst + (int64_t)r * H) = out[i];
-        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     };
-    if (rows >= MA * 32 && h0 + kCols <= H) sweep(std::true_type{});
-    else sweep(std::false_type{});
+    const bool all_valid = rows >= 128 && h0 + 128 <= H;
+    if (accumulate) {
+      if (all_valid) sweep(std::true_type{}, std::true_type{});
+      else sweep(std::true_type{}, std::false_type{});
+    } else {
+      if (all_valid) sweep(std::false_type{}, std::true_type{});
+      else sweep(std::false_type{}, std::false_type{});
+    }
   }
 };
 
@@ -1489,11 +1198,6 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }
 static int direct_tokens_forward(int H) { return H >= kBN ? 24576 : 8192; }
 
-// Up to how many k-slices (32 tokens) a chunk is added to dW by reading, adding and storing instead of by atomics.
-// Accumulating call, atomics against read-add-store, ms at V x H = 151936 x 4096: 59 tokens 2.47 / 1.66, 300: 2.88 / 2.23,
-// 1237: 4.76 / 4.58, 2500: 8.70 / 8.74, 4096: 12.04 / 12.18; at H = 1024: 59 tokens 0.68 / 0.50, 600: 1.03 / 0.90, 4096: equal.
-constexpr int kReadAddSlices = 64;
-
 // logits contraction: rows = vocabulary, columns = tokens (tiles_n tiles), contraction over the hidden size; W either
 // repacked (Wb) or read as it is (Wb NULL)
 template <class Epi>
@@ -1502,8 +1206,8 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H};
   const int grid = g.tiles_m * g.tiles_n;
-  if (Wb) gemm_nt_kernel<Epi, NAT_WAVES_LOGITS><<<grid, NAT_WAVES_LOGITS * 64, 0, s>>>(g, epi);
-  else gemm_nt_kernel<Epi, NAT_WAVES_LOGITS, ASource::kRows><<<grid, NAT_WAVES_LOGITS * 64, 0, s>>>(g, epi);
+  if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false><<<grid, 256, 0, s>>>(g, epi);
+  else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false><<<grid, 256, 0, s>>>(g, epi);
   NAT_LAUNCH_CHECK();
   return NAT_OK;
 }
@@ -1589,7 +1293,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
         // The tiles left over after the last full round of one tile per compute unit (all of them in a short batch)
         // are cut into ranges of the vocabulary: see range_cut.
         const int tiles = (snp / kBM) * (Hp / kBN);
-        const RangeCut cut = range_cut(tiles, Vp / kBK, 1);
+        const RangeCut cut = range_cut(tiles, Vp / kBK, 2);
         uint16_t* dH_s = (uint16_t*)a.dH + (int64_t)(c0 + s0) * H;
         ProfScope prof(PC_DHIDDEN, s);
         GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, Vp / kBK, cut.splits, cut.kt_per, cut.tail, V, H};
@@ -1598,11 +1302,11 @@ nat_status loss_bf16_run(const LossArgs& a) {
           g.B = Eb_s;
           g.tiles_m = Hp / kBM;
           g.tiles_n = snp / kBN;
-          DHiddenTEpilogue e{snv, H, dH_s, beta + s0, dh_part};
-          gemm_nt_kernel<DHiddenTEpilogue, NAT_WAVES_DHIDDEN, ASource::kKMajorRows><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+          DHiddenEpilogue<false> e{snv, H, dH_s, beta + s0, dh_part};
+          mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false><<<cut.grid, 256, 0, s>>>(g, e);
         } else {
-          DHiddenEpilogue e{snv, H, dH_s, beta + s0, dh_part};
-          gemm_nt_kernel<DHiddenEpilogue, NAT_WAVES_DHIDDEN><<<cut.grid, NAT_WAVES_DHIDDEN * 64, 0, s>>>(g, e);
+          DHiddenEpilogue<true> e{snv, H, dH_s, beta + s0, dh_part};
+          mfma_nt_kernel<DHiddenEpilogue<true>, Src::kBlocked, Src::kBlockedInterleaved, true><<<cut.grid, 256, 0, s>>>(g, e);
         }
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
@@ -1615,17 +1319,14 @@ nat_status loss_bf16_run(const LossArgs& a) {
       // A = E from its one copy (rows = token), i.e. stored along this contraction's k axis
       // The leftover tiles of the last round are cut into ranges of tokens (multiples of the 8 k-slices that the
       // k-major loader starts at): see range_cut.
-      const int kt = (nv + kBK - 1) / kBK;                       // only the slices that hold tokens
+      const int kt = (int)round_up((nv + kBK - 1) / kBK, 2);     // only the slices that hold tokens
       const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), kt, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
       GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail};
       DWeightEpilogue e{V, H, accumulate, a.dW, dh_part};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        if (accumulate && kt <= kReadAddSlices)
-          gemm_nt_kernel<DWeightAddEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, DWeightAddEpilogue{e});
-        else
-          gemm_nt_kernel<DWeightEpilogue, NAT_WAVES_DWEIGHT, ASource::kKMajorBlocked><<<cut.grid, NAT_WAVES_DWEIGHT * 64, 0, s>>>(g, e);
+        mfma_nt_kernel<DWeightEpilogue, Src::kKMajorBlocked, Src::kBlocked, true><<<cut.grid, 256, 0, s>>>(g, e);
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
           dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);

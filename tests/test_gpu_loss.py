@@ -230,6 +230,22 @@ def test_bf16_last_token_tile_half_full(stage, n_tok):
         check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok", [1, 33, 65, 289, 353])
+def test_bf16_workspace_contents_do_not_matter(stage, n_tok):
+    # the contractions walk k-slices two at a time: with an odd number of 32-token slices dW reads one more than holds
+    # tokens.  A workspace full of NaN bits gives the bits that a cleared one gives
+    H, V = 192, 700
+    case = make_loss_case(900 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+    outs = []
+    for byte in (0, 255):
+        hip_loss(stage, case, "bf16")
+        stage._ws["loss"].fill_(byte)
+        outs.append(hip_loss(stage, case, "bf16"))
+    for k in ("loss", "logp", "dH", "dW"):
+        assert torch.equal(outs[0][k], outs[1][k]), k
+    check(outs[1], oracle_loss(**case), n_tok, TOL_BF16, case)
+
+
 @pytest.mark.parametrize("V", [1025, 17153])
 @pytest.mark.parametrize("n_tok", [40, 2048, 2049])
 def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):
