@@ -21,51 +21,42 @@ struct TokenScalars { float L; float c; float kl; bool clipped; };   // clipped:
 // with d = ref_logp - logp:  KL = -d (log-ratio form) or exp(d) - d - 1 (non-negative form),
 // dKL/dlogp = 1 or 1 - exp(d);
 // token objective L = S - beta KL;  c = dLoss/dlogp = -grad_scale * w * (dS/dlogp - beta dKL/dlogp).
-// T: precision of the log-prob and of everything formed from it (float on the bf16 path, double on the fp32 path).
-// A behaviour log-prob equal to the log-prob as it is reported (rounded to fp32) gives r = 1 exactly in both.
-__device__ __forceinline__ float exp_of(float x) { return expf(x); }
-__device__ __forceinline__ double exp_of(double x) { return exp(x); }
-__device__ __forceinline__ float min_of(float a, float b) { return fminf(a, b); }
-__device__ __forceinline__ double min_of(double a, double b) { return fmin(a, b); }
-__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
-__device__ __forceinline__ double max_of(double a, double b) { return fmax(a, b); }
+// All of it in fp64.  A behaviour log-prob equal to the log-prob as it is reported (rounded to fp32) gives r = 1 exactly.
 // logp - other, 0 where they agree as fp32 numbers
-__device__ __forceinline__ float logp_minus(float logp, float other) { return logp - other; }
 __device__ __forceinline__ double logp_minus(double logp, float other) {
   const double d = logp - (double)other;
   return (float)logp == other && d - d == 0.0 ? 0.0 : d;
 }
-template <class T>
-__device__ __forceinline__ TokenScalars grpo_token_scalars(T logp, float old_logp, float A, float w,
+__device__ __forceinline__ TokenScalars grpo_token_scalars(double logp, float old_logp, float A, float w,
                                                            float eps_lo, float eps_hi, float grad_scale,
                                                            float beta_kl, int kl_kind, float ref_logp) {
-  const T lo = (T)(1.f - eps_lo), hi = (T)(1.f + eps_hi);
-  const T r = exp_of(logp_minus(logp, old_logp));
-  const T r_clip = min_of(max_of(r, lo), hi);
-  const T S = min_of(r * (T)A, r_clip * (T)A);
+  const double lo = (double)(1.f - eps_lo), hi = (double)(1.f + eps_hi);
+  const double r = exp(logp_minus(logp, old_logp));
+  const double r_clip = fmin(fmax(r, lo), hi);
+  const double S = fmin(r * (double)A, r_clip * (double)A);
   const bool active = (A > 0.f && r <= hi) || (A < 0.f && r >= lo);
-  T g = active ? r * (T)A : (T)0;
+  double g = active ? r * (double)A : (double)0;
   TokenScalars out;
   out.clipped = A != 0.f && !active;
-  T L = S;
+  double L = S;
   out.kl = 0.f;
   if (beta_kl != 0.f) {
-    const T d = -logp_minus(logp, ref_logp);
-    T kl, dkl;
+    const double d = -logp_minus(logp, ref_logp);
+    double kl, dkl;
     if (kl_kind == NAT_KL_NONNEG) {
-      const T ed = exp_of(d);
-      kl = ed - d - (T)1;
-      dkl = (T)1 - ed;
+      const double ed = exp(d);
+      kl = ed - d - (double)1;
+      dkl = (double)1 - ed;
     } else {
       kl = -d;
-      dkl = (T)1;
+      dkl = (double)1;
     }
     out.kl = (float)kl;
-    L = S - (T)beta_kl * kl;
-    g -= (T)beta_kl * dkl;
+    L = S - (double)beta_kl * kl;
+    g -= (double)beta_kl * dkl;
   }
   out.L = (float)L;
-  out.c = (float)(-(T)grad_scale * (T)w * g);
+  out.c = (float)(-(double)grad_scale * (double)w * g);
   return out;
 }
 

@@ -1013,15 +1013,17 @@ token_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t
     const int k = chunk_start + kk;
     const int y = ids[kk];
     bad_id = y < 0 || y >= V;
-    if (entropy_out) entropy_out[k] = logf(S) - sums.TZ / S;   // -sum_v p_v log p_v, p_v = E_v / S
+    // the scalar part of a token in fp64: a log-prob of 12 formed from fp32 numbers is rounded three times by up to 5e-7,
+    // and that is what a loss whose terms cancel was off by
+    const double log_S = log((double)S);
+    if (entropy_out) entropy_out[k] = (float)(log_S - (double)sums.TZ / (double)S);   // -sum_v p_v log p_v, p_v = E_v / S
     if (bad_id) {                                        // left out: no loss term, zero gradient
       beta_out[kk] = 0.f;
       if (logp_out) logp_out[k] = __builtin_nanf("");
       if (kl_out) kl_out[k] = __builtin_nanf("");
       term[k] = 0.f;
     } else {
-      const float lse = ref[kk] + logf(S);
-      const float logp = z_target[kk] - lse;
+      const double logp = (double)z_target[kk] - ((double)ref[kk] + log_S);
       const float w = kept_w[k];
       const float A = adv[kept_seq[k]];
       const TokenScalars ts = grpo_token_scalars(logp, old_logp[k], A, w, eps_lo, eps_hi, grad_scale,
@@ -1031,8 +1033,8 @@ token_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t
       beta_out[kk] = -ts.c / S;                          // dz_kv = beta_k E_kv off the target
       // the target entry of E is replaced by E' with beta_k E' = c_k (1 - p_target): the two backward
       // contractions then need no separate one-hot term
-      Eb[blk_off(kk, y, kb_z)] = f32_to_bf16_bits(-S * (1.f - __expf(logp)));
-      if (logp_out) logp_out[k] = logp;
+      Eb[blk_off(kk, y, kb_z)] = f32_to_bf16_bits(-S * (1.f - __expf((float)logp)));
+      if (logp_out) logp_out[k] = (float)logp;
       if (kl_out) kl_out[k] = ts.kl;
       term[k] = w * ts.L;
     }
@@ -1061,8 +1063,9 @@ logp_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t_
     const int k = chunk_start + kk;
     const int y = ids[kk];
     bad_id = y < 0 || y >= V;
-    logp_out[k] = bad_id ? __builtin_nanf("") : z_target[kk] - (ref[kk] + logf(sums.S));
-    if (entropy_out) entropy_out[k] = logf(sums.S) - sums.TZ / sums.S;
+    const double log_S = log((double)sums.S);          // in fp64, as in token_stats_kernel
+    logp_out[k] = bad_id ? __builtin_nanf("") : (float)((double)z_target[kk] - ((double)ref[kk] + log_S));
+    if (entropy_out) entropy_out[k] = (float)(log_S - (double)sums.TZ / (double)sums.S);
   }
   if (diag) {
     wave_count(bad_id, diag + NAT_DIAG_BAD_ID);
