@@ -396,8 +396,10 @@ struct FragReader {
 // moves per slice).  The compiler then does not know the instruction's wait states: a and b come from LDS reads that have
 // been waited for, c is next touched by another product of the same kind, and the epilogues read it through AccReader,
 // behind the wait states that a reader of the results needs.
+template <bool kFirst>             // kFirst: c = a . b
 __device__ __forceinline__ void mfma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  if constexpr (kFirst) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 // Reads accumulators after the k-loop: the reads depend on `settled`, which the wait states produce, and take their operand
@@ -412,6 +414,11 @@ struct AccReader {
   }
   __device__ __forceinline__ f32x4 operator()(const f32x4& c) const {
     return f32x4{(*this)(c, 0), (*this)(c, 1), (*this)(c, 2), (*this)(c, 3)};
+  }
+  // c to p[kOffset ..] as it is (s_nop: the registers of a 16-byte store may not be written by the very next instruction)
+  template <int kOffset>
+  __device__ __forceinline__ void store(float* p, const f32x4& c) const {
+    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 ; %3\n\ts_nop 0" : : "v"(p), "a"(c), "n"(kOffset * 4), "s"(settled) : "memory");
   }
 };
 
@@ -443,55 +450,108 @@ using LoaderOf = typename std::conditional<kS == Src::kRows, TileLoaderRows,
                  typename std::conditional<kS == Src::kKMajorBlocked, TileLoaderKMajor,
                  typename std::conditional<kS == Src::kKMajorRows, TileLoaderKMajorRows, TileLoader>::type>::type>::type;
 
-// One tile: A (tile tm of the rows of the launch's tile grid) and B (tile tn of its columns).  kPIsB: the result's rows P
-// are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 for a tile of which only the first 128 rows of B are computed.
+// What one workgroup computes at a time: a tile (tm, tn), over slices kt0 .. kt0 + kt_n - 1 of the contraction axis; slab: where
+// its raw sums go if that is one range of the axis (-1: the whole axis).
+struct Unit { int tm, tn, kt0, kt_n, slab; };
+__device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
+  Unit u{0, 0, 0, g.K / kBK, -1};
+  const int whole = g.tiles_m * g.tiles_n - g.tail_tiles;
+  if (g.k_splits > 1 && id >= whole) {
+    const int r = id - whole, range = r / g.tail_tiles, pos = r - range * g.tail_tiles;
+    u.kt0 = range * g.kt_per_split;                            // with a blocked k-major A a multiple of 8 (TileLoaderKMajor::start_at)
+    if (u.kt_n - u.kt0 > g.kt_per_split) u.kt_n = g.kt_per_split;
+    else u.kt_n -= u.kt0;
+    u.slab = pos * g.k_splits + range;
+    id = whole + pos;
+  }
+  tile_of_block(g, id, u.tm, u.tn);
+  return u;
+}
+
+// Units first, first + step, ... below end.  A is the operand of the tile grid's rows, B that of its columns.  kPIsB: the
+// result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 for tiles of which only the first 128 rows of B are computed.
 //
-// Software pipeline over k-slices of 32.  Slice kt lives in ring buffer kt % 4; its fragments are read into registers while
-// slice kt - 1 is multiplied.  At the barrier in front of slice kt's products every wavefront has the fragments of slice
-// kt, so its buffer is refilled with slice kt + 4 under them, and slice kt + 1 has landed: loads complete in issue order,
-// hence a vmcnt that leaves slices kt + 2 and kt + 3 outstanding.  Slices past the end re-load the last one (into a buffer
-// nobody reads again), which keeps the body branch-free and the count fixed.  The number of slices is even (H is a multiple of
-// 64, the vocabulary and the tokens are padded, ranges start and end at even slices).  The 8 x NB products of a slice are written
-// slot by slot (the compiler may not move anything across a slot's end): fragment reads behind the products of the first
-// half, one every second of them, loads of the refill evenly spaced behind the second half.
-template <class Epilogue, Src kA, Src kB, bool kPIsB, int NB>
-__device__ __forceinline__ void mfma_tile(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int tm, int tn, int range, int slab) {
+// Software pipeline over k-slices of 32.  The n-th slice lives in ring buffer n % 4; its fragments are read into registers while
+// slice n - 1 is multiplied.  At the barrier in front of slice n's products every wavefront has the fragments of slice
+// n, so its buffer is refilled with slice n + 4 under them, and slice n + 1 has landed: loads complete in issue order,
+// hence a vmcnt that leaves slices n + 2 and n + 3 outstanding (the epilogue's stores and loads count too: then it waits for
+// more than that, never for less).  The number of slices of a unit is even (H is a multiple of 64, the vocabulary and the
+// tokens are padded, ranges start and end at even slices): two per turn of the loop.  The slices of a workgroup's
+// units follow one another: while the last ones of a unit are multiplied and its epilogue runs, the first ones of the next are
+// loaded (kMany; without it there is one unit, and neither the bookkeeping nor a first pair of slices of its own that starts
+// from zero: 1 % on dH's thousands of slices).  Past the last unit the last two slices are loaded again (into buffers nobody reads), so that the body is free of
+// branches and the count fixed.  The 8 x NB products of a slice are written slot by slot (the compiler may not move anything
+// across a slot's end): fragment reads behind the products of the first half, one every second of them, loads of the refill
+// evenly spaced behind the second half.
+template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB>
+__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int first, int step, int end) {
   constexpr bool kHalf = NB == 4;
   constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
   using LoadA = LoaderOf<kA>;
   using LoadB = typename std::conditional<kHalf, HalfTileLoader, LoaderOf<kB>>::type;
   constexpr int kLoadsA = LoadA::kLoads, kLoadsB = LoadB::kLoads, kLoads = kLoadsA + kLoadsB;    // per wavefront and slice
+  using std::integral_constant;
+  constexpr integral_constant<int, 0> zero{};
+  constexpr integral_constant<int, 1> one{};
   auto& lds = sm.ring;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int a_row0 = (wave >> 1) * 128, b_row0 = (wave & 1) * (NB * 16);
-  const int a0 = tm * kBM + a_row0, b0 = tn * kBN + b_row0;
 
-  f32x4 acc[NP][NQ];
-#pragma unroll
-  for (int i = 0; i < NP; ++i)
-#pragma unroll
-    for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // what the epilogue needs per column (token id, exponent shift): fetched into LDS now, read after the k-loop
-  epi.template prefetch<NQ>(sm.stash[wave], kPIsB ? a0 : b0, lane);
-
+  // the loading side: slice `slice` and the one behind it of a unit of `slices` are loaded next
   LoadA la;
   LoadB lb;
-  const int kt_all = g.K / kBK;
-  if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) la.init(g.A, tm, g.src_rows, g.src_cols, wave, lane);
-  else la.init(g.A, tm, kA == Src::kKMajorBlocked ? g.kb_a_src : kt_all, wave, lane);
-  lb.init(g.B, tn, g.kb_b, wave, lane);
-  int kt_n = kt_all;                                           // k-slices this workgroup contracts over
-  if (range >= 0) {
-    const int kt0 = range * g.kt_per_split;                    // with a blocked k-major A a multiple of 8 (TileLoaderKMajor::start_at)
-    kt_n = kt_all - kt0 < g.kt_per_split ? kt_all - kt0 : g.kt_per_split;
-    la.start_at(kt0);
-    lb.start_at(kt0);
-  }
-  auto clamp = [&](int k) { return k < kt_n ? k : kt_n - 1; };
-  auto load_a = [&](auto idx, int st, int k) { la.template issue_one<decltype(idx)::value>(lds[st][0], clamp(k), wave); };
-  auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(lds[st][1], clamp(k), wave); };
+  int load_id = first, slice = 0, slices;
+  LoadB lb_last;                                               // kPaired: B of the slice loaded last comes with the next even one
+  int slice_last;
+  auto open = [&] {
+    const Unit u = unit_of(g, load_id);
+    if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) la.init(g.A, u.tm, g.src_rows, g.src_cols, wave, lane);
+    else la.init(g.A, u.tm, kA == Src::kKMajorBlocked ? g.kb_a_src : g.K / kBK, wave, lane);
+    lb.init(g.B, u.tn, g.kb_b, wave, lane);
+    la.start_at(u.kt0);
+    lb.start_at(u.kt0);
+    slice = 0;
+    slices = u.kt_n;
+  };
+  auto advance = [&] {
+    lb_last = lb;
+    slice_last = slice + 1;
+    slice += 2;
+    if constexpr (kMany) {
+      if (slice < slices) return;
+      slice = slices - 2;
+      if (load_id + step >= end) return;
+      load_id += step;
+      open();
+    } else {
+      slice = slice < slices ? slice : slices - 2;
+    }
+  };
+  auto load_a = [&](auto idx, int st, int k) { la.template issue_one<decltype(idx)::value>(lds[st][0], k, wave); };
+  auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(lds[st][1], k, wave); };
+  // Load n of the next two slices into buffers st and st + 1: first kEven with the even one, then kOdd.  A slice of an A read
+  // from rows is 64 bytes of a row, half a cache line; fetched a slice apart, the halves cost the line twice on the way from
+  // the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 together, 11.48 from the repacked copy): both slices' A tiles go
+  // with the odd one, half after half, and B's odd tile with the next even one (with the odd one too, 12 loads against 4: 15 %
+  // slower).
+  constexpr bool kPaired = kA == Src::kRows;
+  constexpr int kEven = kPaired ? 2 * kLoadsB : kLoads, kOdd = kPaired ? 2 * kLoadsA : kLoads;
+  auto load_even = [&](auto n, int st) {
+    constexpr int i = decltype(n)::value;
+    if constexpr (kPaired && i < kLoadsB) lb_last.template issue_one<i>(lds[(st ^ 2) + 1][1], slice_last, wave);
+    else if constexpr (kPaired) load_b(integral_constant<int, i - kLoadsB>{}, st, slice);
+    else if constexpr (i < kLoadsA) load_a(n, st, slice);
+    else load_b(integral_constant<int, i - kLoadsA>{}, st, slice);
+  };
+  auto load_odd = [&](auto n, int st) {
+    constexpr int i = decltype(n)::value;
+    if constexpr (kPaired) load_a(integral_constant<int, i / 2>{}, st + (i & 1), slice + (i & 1));
+    else if constexpr (i < kLoadsA) load_a(n, st + 1, slice + 1);
+    else load_b(integral_constant<int, i - kLoadsA>{}, st + 1, slice + 1);
+  };
+  // loads younger than the slice that has to have landed in front of an even and an odd slice's products
+  constexpr int kYoungEven = kPaired ? 2 * kLoadsA + kLoadsB : 2 * kLoads, kYoungOdd = kPaired ? 2 * kLoadsB : 2 * kLoads;
 
   FragReader<kA> ra;
   FragReader<kB> rb;
@@ -500,16 +560,18 @@ __device__ __forceinline__ void mfma_tile(const GemmArgs& g, const Epilogue& epi
   FragSet<kA, 8> fa[2];
   FragSet<kB, NB> fb[2];
   constexpr int kReadsA = FragSet<kA, 8>::kReads, kReads = kReadsA + FragSet<kB, NB>::kReads;
+  f32x4 acc[NP][NQ];
 
   // products of the slice whose fragments are in set kCur; between them the fragments of the next one from ring buffer
   // `next` into the other set and load(n), n = 0 .. kN - 1
-  auto products = [&](auto cur, int next, auto count, auto load) {
+  auto products = [&](auto is_first, auto cur, int next, auto count, auto load) {
+    constexpr bool kFirst = decltype(is_first)::value;
     constexpr int kCur = decltype(cur)::value, kN = decltype(count)::value, kSlots = 8 * NB, kReadSpan = kSlots / 2;
     const char *a_tile = lds[next][0], *b_tile = lds[next][1];
     static_for<kSlots>([&](auto slot) {
       constexpr int m = decltype(slot)::value, i = m / NB, j = (i & 1) ? NB - 1 - m % NB : m % NB;
-      if constexpr (kPIsB) mfma16(acc[j][i], fb[kCur].template get<j>(), fa[kCur].template get<i>());
-      else mfma16(acc[i][j], fa[kCur].template get<i>(), fb[kCur].template get<j>());
+      if constexpr (kPIsB) mfma16<kFirst>(acc[j][i], fb[kCur].template get<j>(), fa[kCur].template get<i>());
+      else mfma16<kFirst>(acc[i][j], fa[kCur].template get<i>(), fb[kCur].template get<j>());
       constexpr int r0 = spread(m, kReads, kReadSpan), r1 = spread(m + 1, kReads, kReadSpan);
       static_for<r1 - r0>([&](auto read) {
         constexpr int r = r0 + decltype(read)::value;
@@ -529,96 +591,104 @@ __device__ __forceinline__ void mfma_tile(const GemmArgs& g, const Epilogue& epi
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto first_frags = [&] {
-    static_for<kReadsA>([&](auto r) { fa[0].template read<decltype(r)::value>(ra, lds[0][0]); });
-    static_for<kReads - kReadsA>([&](auto r) { fb[0].template read<decltype(r)::value>(rb, lds[0][1]); });
-  };
-  using std::integral_constant;
-  constexpr integral_constant<int, 0> zero{};
-  constexpr integral_constant<int, 1> one{};
 
-  if constexpr (kA == Src::kRows) {
-    // A slice is 64 bytes of a row, half a cache line; fetched a slice apart, the halves cost the line twice on the way from
-    // the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 as below, 11.48 from the repacked copy).  So two slices' A tiles are
-    // refilled at once, half after half.  Issue order: [even kt] B(kt + 3) B(kt + 4) [odd kt] A(kt + 3) A(kt + 4).  "Slice
-    // kt + 1 has landed" leaves one B and two As outstanding in front of an even slice, two Bs in front of an odd one.
-    constexpr integral_constant<int, 2 * kLoadsA + kLoadsB> young_even{};
-    constexpr integral_constant<int, 2 * kLoadsB> young_odd{};
-    auto pair = [&](auto n, int st, int k) {                   // load n of two tiles: 0 .. 2 kLoadsA - 1
-      constexpr int i = decltype(n)::value;
-      load_a(integral_constant<int, i / 2>{}, st + (i & 1), k + (i & 1));
-    };
-    static_for<2 * kLoadsA>([&](auto n) { pair(n, 0, 0); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 0, 0); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 1, 1); });
-    static_for<2 * kLoadsA>([&](auto n) { pair(n, 2, 2); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 2, 2); });
-    turn(integral_constant<int, 2 * kLoadsA + 2 * kLoadsB>{});
-    first_frags();
-    turn(young_even);
-    for (int kt = 0; kt < kt_n; kt += 2) {
-      const int c0 = kt % kStages, c3 = (kt + 3) % kStages;    // buffers of slices kt and kt + 3
-      products(zero, c0 + 1, integral_constant<int, 2 * kLoadsB>{}, [&](auto n) {
-        constexpr int i = decltype(n)::value;
-        load_b(integral_constant<int, i % kLoadsB>{}, i < kLoadsB ? c3 : c0, i < kLoadsB ? kt + 3 : kt + 4);
-      });
-      turn(young_odd);
-      products(one, (c0 + 2) % kStages, integral_constant<int, 2 * kLoadsA>{}, [&](auto n) { pair(n, c0, kt + 4); });
-      turn(young_even);
-    }
+  // what the epilogue needs per column (token id, exponent shift): fetched into LDS ahead of the operands, read after the
+  // k-loop
+  Unit u = unit_of(g, first);
+  auto prefetch = [&] { epi.template prefetch<NQ>(sm.stash[wave], kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane); };
+  prefetch();
+  open();
+  if constexpr (kPaired) {
+    static_for<kOdd>([&](auto n) { load_odd(n, 0); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 0, slice); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 1, slice + 1); });
+    advance();
+    static_for<kOdd>([&](auto n) { load_odd(n, 2); });
+    static_for<kLoadsB>([&](auto n) { load_b(n, 2, slice); });
+    advance();
+    turn(integral_constant<int, 2 * kLoadsB + 2 * kLoadsA>{});
   } else {
-    auto load = [&](auto n, int st, int k) {
-      constexpr int i = decltype(n)::value;
-      if constexpr (i < kLoadsA) load_a(n, st, k);
-      else load_b(integral_constant<int, i - kLoadsA>{}, st, k);
-    };
-    constexpr integral_constant<int, (kStages - 2) * kLoads> young{};
 #pragma unroll
-    for (int st = 0; st < kStages; ++st) static_for<kLoads>([&](auto n) { load(n, st, st); });
-    turn(integral_constant<int, (kStages - 1) * kLoads>{});
-    first_frags();
-    turn(young);
-    auto slice = [&](auto cur, int kt) {
-      products(cur, (kt + 1) % kStages, integral_constant<int, kLoads>{}, [&](auto n) { load(n, kt % kStages, kt + kStages); });
-      turn(young);
-    };
-    for (int kt = 0; kt < kt_n; kt += 2) {
-      slice(zero, kt);
-      slice(one, kt + 1);
+    for (int st = 0; st < kStages; st += 2) {
+      static_for<kEven>([&](auto n) { load_even(n, st); });
+      static_for<kOdd>([&](auto n) { load_odd(n, st); });
+      advance();
     }
+    turn(integral_constant<int, 3 * kLoads>{});
   }
-  const AccReader rd;
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive the block
-  epi(acc, rd, kPIsB ? b0 : a0, kPIsB ? a0 : b0, lane, sm.stash[wave], slab);
+  static_for<kReadsA>([&](auto r) { fa[0].template read<decltype(r)::value>(ra, lds[0][0]); });
+  static_for<kReads - kReadsA>([&](auto r) { fb[0].template read<decltype(r)::value>(rb, lds[0][1]); });
+  turn(integral_constant<int, kYoungEven>{});
+  int st = 0;                                                  // ring buffer of the slice that is multiplied next
+  for (int id = first;;) {
+    __builtin_amdgcn_s_waitcnt(0xc07f);                        // lgkmcnt(0): else the compiler waits for scalar loads inside the loop
+    auto two_slices = [&](auto is_first) {
+      products(is_first, zero, st + 1, integral_constant<int, kEven>{}, [&](auto n) { load_even(n, st); });
+      turn(integral_constant<int, kYoungOdd>{});
+      products(std::false_type{}, one, st ^ 2, integral_constant<int, kOdd>{}, [&](auto n) { load_odd(n, st); });
+      turn(integral_constant<int, kYoungEven>{});
+      st ^= 2;
+      advance();
+    };
+    if constexpr (kMany) {
+      two_slices(std::true_type{});
+      for (int kt = 2; kt < u.kt_n; kt += 2) two_slices(std::false_type{});
+    } else {
+#pragma unroll
+      for (int i = 0; i < NP; ++i)
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < u.kt_n; kt += 2) two_slices(std::false_type{});
+    }
+    const AccReader rd;
+    epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane, sm.stash[wave], u.slab);
+    id += step;
+    if (!kMany || id >= end) break;
+    u = unit_of(g, id);
+    prefetch();
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive this
+  __syncthreads();
 }
 
-template <class Epilogue, Src kA, Src kB, bool kPIsB>
+__host__ __device__ __forceinline__ bool short_last(int n_valid, int tiles_n) { return n_valid - (tiles_n - 1) * kBN <= kBN / 2; }
+
+// Workgroups of a launch whose workgroups walk several units each: one per compute unit.  Over one unit per workgroup this
+// saves the ring's first fill and the clearing of the accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).
+// One unit each / walking, us: logits of 512 tokens at H = 1024 150 / 144, of 8192 2213 / 2094, of 700 at 4096 703 / 691, of 16384
+// 14197 / 14073; dW at H = 4096 with 300 tokens 713 / 640, 1237 1554 / 1461, 5000 4667 / 4589, 8192 7236 / 7180, but 16384 14323 / 14309 and at
+// H = 5120 18076 / 18136: up to kWalkSlices.  dH has two rounds of thousands of slices: one unit each.
+constexpr int kWalkSlices = 256;
+static int grid_of(int units) { return units < kNumCU ? units : kNumCU; }
+
+template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
 __global__ void __launch_bounds__(256, 1)
 mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   __shared__ __attribute__((aligned(1024))) GemmShared sm;
-  int tm, tn;
-  const int n_tiles = g.tiles_m * g.tiles_n;
-  int pid = (int)blockIdx.x, range = -1, slab = -1;           // range of the contraction axis / slab (-1: whole axis)
-  if (g.k_splits > 1 && pid >= n_tiles - g.tail_tiles) {
-    const int r = pid - (n_tiles - g.tail_tiles);
-    range = r / g.tail_tiles;
-    const int pos = r - range * g.tail_tiles;
-    pid = n_tiles - g.tail_tiles + pos;
-    slab = pos * g.k_splits + range;
-  }
-  tile_of_block(g, pid, tm, tn);
+  const int first = (int)blockIdx.x, step = (int)gridDim.x;
+  const int units = g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles;
   // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 of them
   // computes only those (301 log-probs at the 0.6B head: logits 153 -> 132 us; 59 tokens at the 8B head: call 1155 -> 1067 us).
+  // Such a launch has one unit per workgroup (short_last).
   if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
-    if (epi.n_valid - tn * kBN <= kBN / 2) {
-      mfma_tile<Epilogue, kA, kB, kPIsB, 4>(g, epi, sm, tm, tn, range, slab);
+    if (short_last(epi.n_valid, g.tiles_n) && unit_of(g, first).tn == g.tiles_n - 1) {
+      mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, first, step, first + 1);
       return;
     }
   }
-  mfma_tile<Epilogue, kA, kB, kPIsB, 8>(g, epi, sm, tm, tn, range, slab);
+  mfma_units<Epilogue, kA, kB, kPIsB, kMany, 8>(g, epi, sm, first, step, units);
 }
 
 // ------------------------------------------------------------- epilogues ----
+
+// sum of a value over the lanes l % 16 + 16 q, q = 0..3
+__device__ __forceinline__ float sum_quarters(float x) {
+  uint32_t a = __builtin_bit_cast(uint32_t, x);
+  const auto q = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+  a = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(a, a, false, false);
+  return __builtin_bit_cast(float, (uint32_t)h[0]) + __builtin_bit_cast(float, (uint32_t)h[1]);
+}
 
 // Logits tile: rows = vocabulary (A = W), columns = tokens of the chunk (B = H_chunk).
 template <bool kEntropy, bool kStoreE = true>
@@ -726,14 +796,10 @@ struct LogitsEpilogue {
         }
       }
       const int kk = k0 + nb * 16 + l15;                   // token column (always inside the padded chunk)
-      float sum = s2[0] + s2[1];
-      sum += __shfl_xor(sum, 16);
-      sum += __shfl_xor(sum, 32);
+      const float sum = sum_quarters(s2[0] + s2[1]);
       if (g == 0) s_part[(int64_t)granule * ld_part + kk] = sum;
       if (kEntropy) {
-        float t = (t2[0] + t2[1]) * kLn2;                  // back to natural-log units
-        t += __shfl_xor(t, 16);
-        t += __shfl_xor(t, 32);
+        const float t = sum_quarters((t2[0] + t2[1]) * kLn2);    // back to natural-log units
         if (g == 0) t_part[(int64_t)granule * ld_part + kk] = t;
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -793,8 +859,9 @@ struct DHiddenEpilogue {
 
 // dW tile: rows = hidden units ((diag(beta) H_chunk)^T), columns = vocabulary (E^T): a lane holds hidden units h0 + 16 i + 4 (l / 16)
 // .. + 3 of its vocabulary entry, 16 bytes of a row of dW.
+template <bool kAccumulate>
 struct DWeightEpilogue {
-  int V, H, accumulate;
+  int V, H;
   float* dW;                       // [V, H] fp32
   float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
 
@@ -804,17 +871,15 @@ struct DWeightEpilogue {
     if (slab_id >= 0) {            // one range of this tile's tokens: raw sums to the slab, added up by dw_tail_reduce_kernel
       float* slab = partial + (int64_t)slab_id * (kBM * kBN) + ((v0 & (kBM - 1)) + l15) * kBN + (h0 & (kBN - 1)) + 4 * g;
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) *(f32x4*)(slab + nb * 16 * kBN + i * 16) = rd(acc[i][nb]);
+      for (int nb = 0; nb < 8; ++nb) static_for<8>([&](auto i) { rd.template store<decltype(i)::value * 16>(slab + nb * 16 * kBN, acc[decltype(i)::value][nb]); });
       return;
     }
     const int rows = V - v0;                                   // valid rows from v0 on (may be <= 0)
     float* dst = dW + (int64_t)(v0 + l15) * H + h0 + 4 * g;
     // One owner per element and launch, launches in stream order: one fp32 addition old + sum per element.  Old values
     // of 16 vocabulary rows are loaded while those before them are added and stored.
-    auto sweep = [&](auto acc_mode, auto all_valid) {
-      constexpr bool kAcc = decltype(acc_mode)::value, kAll = decltype(all_valid)::value;
+    auto sweep = [&](auto all_valid) {
+      constexpr bool kAll = decltype(all_valid)::value;
       auto ok = [&](int nb, int i) { return kAll || (nb * 16 + l15 < rows && h0 + i * 16 < H); };   // H is a multiple of 64
       f32x4 old[2][8];
       auto fetch = [&](int nb) {
@@ -823,27 +888,25 @@ struct DWeightEpilogue {
           if (ok(nb, i)) old[nb & 1][i] = *(const f32x4*)(dst + (int64_t)nb * 16 * H + i * 16);
           else old[nb & 1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
       };
-      if (kAcc) fetch(0);
+      if (kAccumulate) fetch(0);
 #pragma unroll
       for (int nb = 0; nb < 8; ++nb) {
-        if (kAcc && nb < 7) fetch(nb + 1);
+        if (kAccumulate && nb < 7) fetch(nb + 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          f32x4 x = rd(acc[i][nb]);
-          if (kAcc) x = old[nb & 1][i] + x;
+          if (!kAccumulate) continue;
+          const f32x4 x = old[nb & 1][i] + rd(acc[i][nb]);
           if (ok(nb, i)) *(f32x4*)(dst + (int64_t)nb * 16 * H + i * 16) = x;
         }
+        if constexpr (!kAccumulate)
+          static_for<8>([&](auto i) {
+            if (ok(nb, i)) rd.template store<decltype(i)::value * 16>(dst + (int64_t)nb * 16 * H, acc[decltype(i)::value][nb]);
+          });
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    const bool all_valid = rows >= 128 && h0 + 128 <= H;
-    if (accumulate) {
-      if (all_valid) sweep(std::true_type{}, std::true_type{});
-      else sweep(std::true_type{}, std::false_type{});
-    } else {
-      if (all_valid) sweep(std::false_type{}, std::true_type{});
-      else sweep(std::false_type{}, std::false_type{});
-    }
+    if (rows >= 128 && h0 + 128 <= H) sweep(std::true_type{});
+    else sweep(std::false_type{});
   }
 };
 
@@ -1208,9 +1271,10 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
                                 const Epi& epi, hipStream_t s) {
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H};
-  const int grid = g.tiles_m * g.tiles_n;
-  if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false><<<grid, 256, 0, s>>>(g, epi);
-  else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false><<<grid, 256, 0, s>>>(g, epi);
+  const int units = g.tiles_m * g.tiles_n;
+  const int grid = !Wb && short_last(epi.n_valid, tiles_n) ? units : grid_of(units);
+  if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
+  else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
   NAT_LAUNCH_CHECK();
   return NAT_OK;
 }
@@ -1306,10 +1370,10 @@ nat_status loss_bf16_run(const LossArgs& a) {
           g.tiles_m = Hp / kBM;
           g.tiles_n = snp / kBN;
           DHiddenEpilogue<false> e{snv, H, dH_s, beta + s0, dh_part};
-          mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false><<<cut.grid, 256, 0, s>>>(g, e);
+          mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false, false><<<cut.grid, 256, 0, s>>>(g, e);
         } else {
           DHiddenEpilogue<true> e{snv, H, dH_s, beta + s0, dh_part};
-          mfma_nt_kernel<DHiddenEpilogue<true>, Src::kBlocked, Src::kBlockedInterleaved, true><<<cut.grid, 256, 0, s>>>(g, e);
+          mfma_nt_kernel<DHiddenEpilogue<true>, Src::kBlocked, Src::kBlockedInterleaved, true, false><<<cut.grid, 256, 0, s>>>(g, e);
         }
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
@@ -1326,10 +1390,13 @@ nat_status loss_bf16_run(const LossArgs& a) {
       const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), kt, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
       GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail};
-      DWeightEpilogue e{V, H, accumulate, a.dW, dh_part};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        mfma_nt_kernel<DWeightEpilogue, Src::kKMajorBlocked, Src::kBlocked, true><<<cut.grid, 256, 0, s>>>(g, e);
+        const int grid = kt <= kWalkSlices ? grid_of(cut.grid) : cut.grid;
+        if (accumulate)
+          mfma_nt_kernel<DWeightEpilogue<true>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<true>{V, H, a.dW, dh_part});
+        else
+          mfma_nt_kernel<DWeightEpilogue<false>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<false>{V, H, a.dW, dh_part});
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
           dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);

@@ -246,6 +246,16 @@ def test_bf16_workspace_contents_do_not_matter(stage, n_tok):
     check(outs[1], oracle_loss(**case), n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok,H,V", [(200, 64, 65700), (500, 192, 65700), (7200, 64, 3000), (6200, 320, 3000)])
+def test_bf16_workgroups_walk_several_tiles(stage, n_tok, H, V):
+    # more tiles than compute units: a workgroup's load ring runs on from one tile into the next.  257 vocabulary tiles and
+    # one or two token tiles with W read as it is, and 12 by 29 or 25 with W repacked; H = 64 has two k-slices per tile, so the
+    # loads run two tiles ahead.  dW: 257 tiles of 8 and 16 slices
+    case = make_loss_case(700 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+    ref = oracle_loss(**case)
+    check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
+
+
 @pytest.mark.parametrize("V", [1025, 17153])
 @pytest.mark.parametrize("n_tok", [40, 2048, 2049])
 def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):
