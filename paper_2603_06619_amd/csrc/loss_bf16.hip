@@ -217,18 +217,19 @@ struct TileLoader {
   }
 };
 
-// The first 128 rows of a [256][32] operand block: 8 KiB of each slice, two loads for each of 4 wavefronts.
-struct HalfTileLoader {
-  static constexpr int kLoads = 2;
+// The first kRows rows of a [256][32] operand block: 8 KiB of each slice, two loads for each of 4 wavefronts, or 4 KiB, one.
+template <int kRows>
+struct PartTileLoader {
+  static constexpr int kLoads = kRows / 64;
   const uint16_t* src;
   __device__ __forceinline__ void init(const uint16_t* base, int tile, int kb, int wave, int lane) {
-    src = base + (int64_t)tile * kb * kBlkElems + wave * 1024 + lane * 8;
+    src = base + (int64_t)tile * kb * kBlkElems + wave * (kLoads * 512) + lane * 8;
   }
   __device__ __forceinline__ void start_at(int kt0) { src += (int64_t)kt0 * kBlkElems; }
   template <int kIdx>
   __device__ __forceinline__ void issue_one(char* lds_tile, int kt, int wave) const {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)kt * kBlkElems),
-                                     (__attribute__((address_space(3))) void*)(lds_tile + wave * 2048), 16, kIdx * 1024, 0);
+                                     (__attribute__((address_space(3))) void*)(lds_tile + wave * (kLoads * 1024)), 16, kIdx * 1024, 0);
   }
 };
 
@@ -469,7 +470,7 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 }
 
 // Units first, first + step, ... below end.  A is the operand of the tile grid's rows, B that of its columns.  kPIsB: the
-// result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 for tiles of which only the first 128 rows of B are computed.
+// result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 or 2 for tiles of which only the first 128 or 64 rows of B are computed.
 //
 // Software pipeline over k-slices of 32.  The n-th slice lives in ring buffer n % 4; its fragments are read into registers while
 // slice n - 1 is multiplied.  At the barrier in front of slice n's products every wavefront has the fragments of slice
@@ -485,10 +486,9 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 // evenly spaced behind the second half.
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB>
 __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int first, int step, int end) {
-  constexpr bool kHalf = NB == 4;
   constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
   using LoadA = LoaderOf<kA>;
-  using LoadB = typename std::conditional<kHalf, HalfTileLoader, LoaderOf<kB>>::type;
+  using LoadB = typename std::conditional<NB < 8, PartTileLoader<NB * 32>, LoaderOf<kB>>::type;
   constexpr int kLoadsA = LoadA::kLoads, kLoadsB = LoadB::kLoads, kLoads = kLoadsA + kLoadsB;    // per wavefront and slice
   using std::integral_constant;
   constexpr integral_constant<int, 0> zero{};
@@ -651,7 +651,11 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   __syncthreads();
 }
 
-__host__ __device__ __forceinline__ bool short_last(int n_valid, int tiles_n) { return n_valid - (tiles_n - 1) * kBN <= kBN / 2; }
+// 16-row blocks of B per wavefront in the last of tiles_n tiles
+__host__ __device__ __forceinline__ int last_blocks(int n_valid, int tiles_n) {
+  const int n = n_valid - (tiles_n - 1) * kBN;
+  return n <= 64 ? 2 : n <= 128 ? 4 : 8;
+}
 
 // Workgroups of a launch whose workgroups walk several units each: one per compute unit.  Over one unit per workgroup this
 // saves the ring's first fill and the clearing of the accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).
@@ -667,12 +671,15 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   __shared__ __attribute__((aligned(1024))) GemmShared sm;
   const int first = (int)blockIdx.x, step = (int)gridDim.x;
   const int units = g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles;
-  // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 of them
-  // computes only those (301 log-probs at the 0.6B head: logits 153 -> 132 us; 59 tokens at the 8B head: call 1155 -> 1067 us).
-  // Such a launch has one unit per workgroup (short_last).
+  // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
+  // computes only those (128 of 256: 301 log-probs at the 0.6B head, logits 153 -> 132 us; 59 tokens at the 8B head, call 1155 -> 1067 us;
+  // 64 of 128: 301 log-probs at the 0.6B head 156 -> 148, 300 at the 8B head 454 -> 428, 60 tokens, call 1063 -> 1034).  Such a launch has one
+  // unit per workgroup.
   if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
-    if (short_last(epi.n_valid, g.tiles_n) && unit_of(g, first).tn == g.tiles_n - 1) {
-      mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, first, step, first + 1);
+    const int blocks = last_blocks(epi.n_valid, g.tiles_n);
+    if (blocks < 8 && unit_of(g, first).tn == g.tiles_n - 1) {
+      if (blocks == 2) mfma_units<Epilogue, kA, kB, kPIsB, kMany, 2>(g, epi, sm, first, step, first + 1);
+      else mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, first, step, first + 1);
       return;
     }
   }
@@ -711,7 +718,7 @@ struct LogitsEpilogue {
   template <int NQ>
   __device__ __forceinline__ void prefetch(int* words, int k0, int lane) const {
 #pragma unroll
-    for (int i = 0; i < NQ / 4; ++i) {
+    for (int i = 0; i < (NQ + 3) / 4; ++i) {
       const int kk = k0 + i * 64 + lane;
       const int kc = kk < n_valid ? kk : n_valid - 1;
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ids + kc),
@@ -1272,7 +1279,7 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H};
   const int units = g.tiles_m * g.tiles_n;
-  const int grid = !Wb && short_last(epi.n_valid, tiles_n) ? units : grid_of(units);
+  const int grid = !Wb && last_blocks(epi.n_valid, tiles_n) < 8 ? units : grid_of(units);
   if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
   else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
   NAT_LAUNCH_CHECK();

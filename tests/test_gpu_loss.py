@@ -230,6 +230,17 @@ def test_bf16_last_token_tile_half_full(stage, n_tok):
         check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok", [1, 64, 65, 320, 321])
+def test_bf16_last_token_tile_a_quarter_full(stage, n_tok):
+    # a last token tile with at most 64 tokens computes only its first 64 columns; log-probs alone and with the loss are equal
+    for H, V in ((192, 1000), (64, 9000)):
+        case = make_loss_case(530 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+        out = hip_loss(stage, case, "bf16")
+        check(out, oracle_loss(**case), n_tok, TOL_BF16, case)
+        fwd = stage.logp(to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"]), n_tok)
+        assert torch.equal(fwd["logp"][:n_tok], out["logp"][:n_tok])
+
+
 @pytest.mark.parametrize("n_tok", [1, 33, 65, 289, 353])
 def test_bf16_workspace_contents_do_not_matter(stage, n_tok):
     # the contractions walk k-slices two at a time: with an odd number of 32-token slices dW reads one more than holds
