@@ -35,6 +35,7 @@
 // k-major operand.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
+#include "walk.hip.h"
 
 #include <type_traits>
 
@@ -63,7 +64,6 @@ constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stag
 #define NAT_GROUP_DWEIGHT 4
 #endif
 constexpr int kMaxChunk = 32768;                  // most token rows per chunk (see recommended_cap)
-constexpr int kNumCU = 256;                       // compute units (one workgroup of these kernels each)
 constexpr int kMinSlicesPerRange = 32;            // least k-slices per range of a cut contraction axis, on average
 #ifndef NAT_SUBCHUNK
 #define NAT_SUBCHUNK 8192
@@ -172,6 +172,7 @@ struct GemmArgs {
   // epilogue is told which slab its raw sums go to (position among the cut tiles * k_splits + range)
   int k_splits, kt_per_split, tail_tiles;
   int src_rows, src_cols;     // A read from a row-major matrix (TileLoaderRows, TileLoaderKMajorRows): its extent
+  int walk;                   // most units per workgroup (walk_of)
 };
 
 // Block id -> output tile.  Blocks are dealt round-robin to the 8 XCDs, so ids
@@ -469,7 +470,7 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
   return u;
 }
 
-// Units first, first + step, ... below end.  A is the operand of the tile grid's rows, B that of its columns.  kPIsB: the
+// Units first, first + kNumCU, ... below end.  A is the operand of the tile grid's rows, B that of its columns.  kPIsB: the
 // result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 or 2 for tiles of which only the first 128 or 64 rows of B are computed.
 //
 // Software pipeline over k-slices of 32.  The n-th slice lives in ring buffer n % 4; its fragments are read into registers while
@@ -485,7 +486,7 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 // across a slot's end): fragment reads behind the products of the first half, one every second of them, loads of the refill
 // evenly spaced behind the second half.
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB>
-__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int first, int step, int end) {
+__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int first, int end) {
   constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
   using LoadA = LoaderOf<kA>;
   using LoadB = typename std::conditional<NB < 8, PartTileLoader<NB * 32>, LoaderOf<kB>>::type;
@@ -521,8 +522,8 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
     if constexpr (kMany) {
       if (slice < slices) return;
       slice = slices - 2;
-      if (load_id + step >= end) return;
-      load_id += step;
+      if (load_id + kNumCU >= end) return;
+      load_id += kNumCU;
       open();
     } else {
       slice = slice < slices ? slice : slices - 2;
@@ -642,7 +643,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
     }
     const AccReader rd;
     epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane, sm.stash[wave], u.slab);
-    id += step;
+    id += kNumCU;
     if (!kMany || id >= end) break;
     u = unit_of(g, id);
     prefetch();
@@ -657,33 +658,30 @@ __host__ __device__ __forceinline__ int last_blocks(int n_valid, int tiles_n) {
   return n <= 64 ? 2 : n <= 128 ? 4 : 8;
 }
 
-// Workgroups of a launch whose workgroups walk several units each: one per compute unit.  Over one unit per workgroup this
-// saves the ring's first fill and the clearing of the accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).
-// One unit each / walking, us: logits of 512 tokens at H = 1024 150 / 144, of 8192 2213 / 2094, of 700 at 4096 703 / 691, of 16384
-// 14197 / 14073; dW at H = 4096 with 300 tokens 713 / 640, 1237 1554 / 1461, 5000 4667 / 4589, 8192 7236 / 7180, but 16384 14323 / 14309 and at
-// H = 5120 18076 / 18136: up to kWalkSlices.  dH has two rounds of thousands of slices: one unit each.
+// Contractions of up to kWalkSlices k-slices are walked (walk_length), over one unit per workgroup this saves the ring's first fill and
+// the clearing of the accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).  One unit each / walking, us, in turn on
+// one box: logits at H = 1024 with 512 tokens 153 / 146, 1237 339 / 324, 8192 1963 / 1861; dW at H = 4096 with 300 tokens 703 / 636, 1237
+// (accumulating) 1816 / 1739, 8192 7308 / 7171, but 16384 14488 / 14496.  dH has two rounds of thousands of slices: one unit each.
 constexpr int kWalkSlices = 256;
-static int grid_of(int units) { return units < kNumCU ? units : kNumCU; }
 
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
 __global__ void __launch_bounds__(256, 1)
 mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   __shared__ __attribute__((aligned(1024))) GemmShared sm;
-  const int first = (int)blockIdx.x, step = (int)gridDim.x;
-  const int units = g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles;
+  const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
   // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
   // computes only those (128 of 256: 301 log-probs at the 0.6B head, logits 153 -> 132 us; 59 tokens at the 8B head, call 1155 -> 1067 us;
   // 64 of 128: 301 log-probs at the 0.6B head 156 -> 148, 300 at the 8B head 454 -> 428, 60 tokens, call 1063 -> 1034).  Such a launch has one
   // unit per workgroup.
   if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
     const int blocks = last_blocks(epi.n_valid, g.tiles_n);
-    if (blocks < 8 && unit_of(g, first).tn == g.tiles_n - 1) {
-      if (blocks == 2) mfma_units<Epilogue, kA, kB, kPIsB, kMany, 2>(g, epi, sm, first, step, first + 1);
-      else mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, first, step, first + 1);
+    if (blocks < 8 && unit_of(g, w.first).tn == g.tiles_n - 1) {
+      if (blocks == 2) mfma_units<Epilogue, kA, kB, kPIsB, kMany, 2>(g, epi, sm, w.first, w.first + 1);
+      else mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, w.first, w.first + 1);
       return;
     }
   }
-  mfma_units<Epilogue, kA, kB, kPIsB, kMany, 8>(g, epi, sm, first, step, units);
+  mfma_units<Epilogue, kA, kB, kPIsB, kMany, 8>(g, epi, sm, w.first, w.end);
 }
 
 // ------------------------------------------------------------- epilogues ----
@@ -1277,9 +1275,10 @@ template <class Epi>
 static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uint16_t* Hb, int V, int H, int Vp, int tiles_n,
                                 const Epi& epi, hipStream_t s) {
   ProfScope prof(PC_LOGITS, s);
-  GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H};
+  GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
-  const int grid = !Wb && last_blocks(epi.n_valid, tiles_n) < 8 ? units : grid_of(units);
+  if (Wb || last_blocks(epi.n_valid, tiles_n) == 8) g.walk = walk_length(units, H / kBK);
+  const int grid = walk_grid(units, g.walk);
   if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
   else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
   NAT_LAUNCH_CHECK();
@@ -1370,7 +1369,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
         const RangeCut cut = range_cut(tiles, Vp / kBK, 2);
         uint16_t* dH_s = (uint16_t*)a.dH + (int64_t)(c0 + s0) * H;
         ProfScope prof(PC_DHIDDEN, s);
-        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, Vp / kBK, cut.splits, cut.kt_per, cut.tail, V, H};
+        GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, Vp / kBK, cut.splits, cut.kt_per, cut.tail, V, H, 1};
         if (direct) {            // dH^T = W^T E^T from W as it is
           g.A = W;
           g.B = Eb_s;
@@ -1396,10 +1395,11 @@ nat_status loss_bf16_run(const LossArgs& a) {
       const int kt = (int)round_up((nv + kBK - 1) / kBK, 2);     // only the slices that hold tokens
       const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), kt, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
-      GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail};
+      GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail, 0, 0,
+                 kt <= kWalkSlices ? walk_length(cut.grid, kt) : 1};
       {
         ProfScope prof(PC_DWEIGHT, s);
-        const int grid = kt <= kWalkSlices ? grid_of(cut.grid) : cut.grid;
+        const int grid = walk_grid(cut.grid, g.walk);
         if (accumulate)
           mfma_nt_kernel<DWeightEpilogue<true>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<true>{V, H, a.dW, dh_part});
         else

@@ -1,0 +1,37 @@
+// How the units (tiles, or ranges of the contraction axis of a tile) of a launch are dealt to workgroups that take several.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace nat {
+
+constexpr int kNumCU = 256;        // compute units (one workgroup of the matrix kernels each)
+
+// Groups of kNumCU workgroups take walk * kNumCU consecutive units each, workgroup b of a group its units b, b + kNumCU, ...: the units
+// start in the order in which one workgroup per unit would start them, and on the same XCD.
+struct Walk { int first, end; };   // units first, first + kNumCU, ... below end
+__host__ __device__ inline Walk walk_of(int block, int walk, int units) {
+  const int start = block / kNumCU * walk * kNumCU;
+  return Walk{start + block % kNumCU, units - start < walk * kNumCU ? units : start + walk * kNumCU};
+}
+
+// workgroups of such a launch
+inline int walk_grid(int units, int walk) {
+  const int per_group = walk * kNumCU, rest = units % per_group;
+  return units / per_group * kNumCU + (rest < kNumCU ? rest : kNumCU);
+}
+
+// Units per workgroup of a launch of units of kt k-slices each.  A compute unit that another stream's kernel holds takes nothing until that
+// ends, and what its workgroup was dealt waits: so a walk is at most a third of the launch's rounds of one unit per compute unit (but
+// two units), and at most kWalkBudget slices, by which the ring's first fill is a few per cent.  Log-probs beside a kernel on
+// another stream that holds 16 / 32 compute units, time against the same call alone; one unit each, every unit dealt in advance, as
+// here: 8192 tokens at H = 1024 1.19 / 1.23, 1.86 / 1.98, 1.24 / 1.26; 2048 at H = 4096 1.11 / 1.15, 1.81 / 1.83, 1.13 / 1.20; 512 at H = 1024
+// 1.18 / 1.20, 1.44 / 1.49, 1.13 / 1.26.  What it costs alone, us, in the same order: 1963, 1852, 1861; 512 tokens 153, 142, 146; dW of 300 tokens at
+// H = 4096 703, 622, 636.  A budget of 1024 slices is no faster and 1.29 / 1.35 beside the other kernel.
+constexpr int kWalkBudget = 512;
+inline int walk_length(int units, int kt) {
+  const int rounds = units / kNumCU, most = kWalkBudget / kt;
+  const int walk = rounds / 3 > 2 ? rounds / 3 : 2;
+  return walk < most ? walk : most > 1 ? most : 1;
+}
+
+}  // namespace nat

@@ -1,0 +1,50 @@
+"""How the units of a launch are dealt to workgroups (csrc/walk.hip.h), without a GPU: its host code in a small program."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2603_06619_amd as nat
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(nat.__file__)), "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <vector>
+#include "walk.hip.h"
+int main() {
+  using namespace nat;
+  const int units_of[] = {1, 2, 255, 256, 257, 511, 512, 513, 594, 1024, 1188, 1189, 2047, 2970, 9504, 19008, 58212};
+  const int slices[] = {2, 8, 10, 32, 38, 80, 112, 128, 160, 256, 480, 512, 513, 8192};
+  for (int units : units_of)
+    for (int kt : slices) {
+      const int walk = walk_length(units, kt), grid = walk_grid(units, walk), rounds = units / kNumCU;
+      // no workgroup is dealt more than a third of the launch (two units of a short one), nor more slices than the budget
+      if (walk < 1 || (walk > 2 && walk * 3 > rounds) || (walk > 1 && walk * kt > kWalkBudget)) return std::printf("length %d of %d x %d\n", walk, units, kt), 1;
+      std::vector<int> taken(units, 0);
+      for (int b = 0; b < grid; ++b) {
+        const Walk w = walk_of(b, walk, units);
+        int n = 0;
+        for (int id = w.first; id < w.end; id += kNumCU, ++n) {
+          if (id < 0 || id >= units || taken[id]++) return std::printf("unit %d of %d\n", id, units), 1;
+          if (id % kNumCU != b % kNumCU || id / (walk * kNumCU) != b / kNumCU) return std::printf("order: unit %d, workgroup %d\n", id, b), 1;
+        }
+        if (n < 1 || n > walk) return std::printf("workgroup %d takes %d of %d\n", b, n, units), 1;
+      }
+      for (int id = 0; id < units; ++id)
+        if (!taken[id]) return std::printf("unit %d of %d left out\n", id, units), 1;
+    }
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
+def test_units_are_dealt_once_in_order_and_in_short_walks(tmp_path):
+    src, exe = tmp_path / "walk.hip", tmp_path / "walk"
+    src.write_text(PROGRAM)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert run.returncode == 0, run.stdout
