@@ -172,7 +172,7 @@ struct GemmArgs {
   // epilogue is told which slab its raw sums go to (position among the cut tiles * k_splits + range)
   int k_splits, kt_per_split, tail_tiles;
   int src_rows, src_cols;     // A read from a row-major matrix (TileLoaderRows, TileLoaderKMajorRows): its extent
-  int walk;                   // most units per workgroup (walk_of)
+  int walk;                   // kMany: most units per workgroup (walk_of)
 };
 
 // Block id -> output tile.  Blocks are dealt round-robin to the 8 XCDs, so ids
@@ -658,30 +658,28 @@ __host__ __device__ __forceinline__ int last_blocks(int n_valid, int tiles_n) {
   return n <= 64 ? 2 : n <= 128 ? 4 : 8;
 }
 
-// Contractions of up to kWalkSlices k-slices are walked (walk_length), over one unit per workgroup this saves the ring's first fill and
-// the clearing of the accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).  One unit each / walking, us, in turn on
-// one box: logits at H = 1024 with 512 tokens 153 / 146, 1237 339 / 324, 8192 1963 / 1861; dW at H = 4096 with 300 tokens 703 / 636, 1237
-// (accumulating) 1816 / 1739, 8192 7308 / 7171, but 16384 14488 / 14496.  dH has two rounds of thousands of slices: one unit each.
-constexpr int kWalkSlices = 256;
-
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
 __global__ void __launch_bounds__(256, 1)
 mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   __shared__ __attribute__((aligned(1024))) GemmShared sm;
-  const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
-  // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
-  // computes only those (128 of 256: 301 log-probs at the 0.6B head, logits 153 -> 132 us; 59 tokens at the 8B head, call 1155 -> 1067 us;
-  // 64 of 128: 301 log-probs at the 0.6B head 156 -> 148, 300 at the 8B head 454 -> 428, 60 tokens, call 1063 -> 1034).  Such a launch has one
-  // unit per workgroup.
-  if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
-    const int blocks = last_blocks(epi.n_valid, g.tiles_n);
-    if (blocks < 8 && unit_of(g, w.first).tn == g.tiles_n - 1) {
-      if (blocks == 2) mfma_units<Epilogue, kA, kB, kPIsB, kMany, 2>(g, epi, sm, w.first, w.first + 1);
-      else mfma_units<Epilogue, kA, kB, kPIsB, kMany, 4>(g, epi, sm, w.first, w.first + 1);
-      return;
+  if constexpr (kMany) {
+    const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
+    mfma_units<Epilogue, kA, kB, kPIsB, true, 8>(g, epi, sm, w.first, w.end);
+  } else {
+    const int id = (int)blockIdx.x;
+    // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
+    // computes only those (128 of 256: 301 log-probs at the 0.6B head, logits 153 -> 132 us; 59 tokens at the 8B head, call 1155 -> 1067 us;
+    // 64 of 128: 301 log-probs at the 0.6B head 156 -> 148, 300 at the 8B head 454 -> 428, 60 tokens, call 1063 -> 1034).
+    if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
+      const int blocks = last_blocks(epi.n_valid, g.tiles_n);
+      if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {
+        if (blocks == 2) mfma_units<Epilogue, kA, kB, kPIsB, false, 2>(g, epi, sm, id, id + 1);
+        else mfma_units<Epilogue, kA, kB, kPIsB, false, 4>(g, epi, sm, id, id + 1);
+        return;
+      }
     }
+    mfma_units<Epilogue, kA, kB, kPIsB, false, 8>(g, epi, sm, id, id + 1);
   }
-  mfma_units<Epilogue, kA, kB, kPIsB, kMany, 8>(g, epi, sm, w.first, w.end);
 }
 
 // ------------------------------------------------------------- epilogues ----
@@ -1277,10 +1275,14 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
-  if (Wb || last_blocks(epi.n_valid, tiles_n) == 8) g.walk = walk_length(units, H / kBK);
-  const int grid = walk_grid(units, g.walk);
-  if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
-  else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<grid, 256, 0, s>>>(g, epi);
+  if (Wb || last_blocks(epi.n_valid, tiles_n) == 8) g.walk = logits_walk(units, H / kBK);
+  if (g.walk > 1) {
+    if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
+    else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
+  } else {
+    if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, false><<<units, 256, 0, s>>>(g, epi);
+    else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, false><<<units, 256, 0, s>>>(g, epi);
+  }
   NAT_LAUNCH_CHECK();
   return NAT_OK;
 }
@@ -1396,7 +1398,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
       const RangeCut cut = range_cut((Vp / kBM) * (Hp / kBN), kt, 8);
       const int accumulate = (c0 > 0 || a.accumulate_dw) ? 1 : 0;
       GemmArgs g{Eb, Hktb, kt * kBK, Vp / kBM, Hp / kBN, NAT_GROUP_DWEIGHT, Vp / 32, np / kBK, cut.splits, cut.kt_per, cut.tail, 0, 0,
-                 kt <= kWalkSlices ? walk_length(cut.grid, kt) : 1};
+                 dw_walk(cut.grid, kt)};
       {
         ProfScope prof(PC_DWEIGHT, s);
         const int grid = walk_grid(cut.grid, g.walk);

@@ -34,4 +34,14 @@ inline int walk_length(int units, int kt) {
   return walk < most ? walk : most > 1 ? most : 1;
 }
 
+// Contractions of up to so many k-slices are walked: over one unit per workgroup that saves the ring's first fill and the clearing of the
+// accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).  One unit each / walking, us, in turn on one box:
+// logits at H = 1024 with 512 tokens 153 / 146, 1237 339 / 324, 8192 1963 / 1861; 8192 tokens at 3584 6220 / 6177, at 4096 6977 / 6976, but at 5120
+// 8904 / 8961 and 25000 tokens there 27000 / 28162 (equal on another box): the longer the tiles, the further the workgroups of an XCD drift apart.
+// dW at H = 4096 with 300 tokens 703 / 636, 1237 (accumulating) 1816 / 1739, 8192 7308 / 7171, but 16384 14488 / 14496.  dH has two rounds
+// of thousands of slices: one unit each.
+constexpr int kLogitsWalkSlices = 128, kDWeightWalkSlices = 256;
+inline int logits_walk(int units, int kt) { return kt <= kLogitsWalkSlices ? walk_length(units, kt) : 1; }
+inline int dw_walk(int units, int kt) { return kt <= kDWeightWalkSlices ? walk_length(units, kt) : 1; }
+
 }  // namespace nat

@@ -36,6 +36,9 @@ int main() {
       for (int id = 0; id < units; ++id)
         if (!taken[id]) return std::printf("unit %d of %d left out\n", id, units), 1;
     }
+  // long contractions: one unit per workgroup (a hidden size of 5120 is 160 slices; 8192 tokens of dW are 256)
+  if (logits_walk(44550, 128) < 2 || logits_walk(44550, 130) != 1 || logits_walk(19008, 160) != 1) return std::printf("logits\n"), 1;
+  if (dw_walk(9504, 256) < 2 || dw_walk(9504, 258) != 1) return std::printf("dW\n"), 1;
   return 0;
 }
 """
