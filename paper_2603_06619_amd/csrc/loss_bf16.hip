@@ -48,7 +48,7 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 // long after they have left the L2: non-temporal stores (1 % on the logits kernel).
 #define NAT_E_STORE(ptr, val) __builtin_nontemporal_store((val), (ptr))
 
-constexpr int kBM = 256, kBN = 256, kBK = 32;     // block tile: 4 wavefronts of 128 x 128, one per SIMD
+constexpr int kBM = 256, kBK = 32;                // block tile kBM x kBN: 4 wavefronts of 128 x 128, one per SIMD
 constexpr int kStages = 4;                        // LDS ring of k-slices (4 x 32 KiB)
 constexpr int kGranule = 128;                     // vocabulary rows per soft-max partial
 constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stage
@@ -650,12 +650,6 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // no direct-to-LDS load may outlive this
   __syncthreads();
-}
-
-// 16-row blocks of B per wavefront in the last of tiles_n tiles
-__host__ __device__ __forceinline__ int last_blocks(int n_valid, int tiles_n) {
-  const int n = n_valid - (tiles_n - 1) * kBN;
-  return n <= 64 ? 2 : n <= 128 ? 4 : 8;
 }
 
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
@@ -1275,7 +1269,7 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
-  if (Wb || last_blocks(epi.n_valid, tiles_n) == 8) g.walk = logits_walk(units, H / kBK);
+  g.walk = logits_walk(units, H / kBK, Wb ? 8 : last_blocks(epi.n_valid, tiles_n), tiles_n);
   if (g.walk > 1) {
     if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
     else mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);

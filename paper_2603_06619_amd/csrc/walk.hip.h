@@ -5,6 +5,13 @@
 namespace nat {
 
 constexpr int kNumCU = 256;        // compute units (one workgroup of the matrix kernels each)
+constexpr int kBN = 256;           // columns of a tile
+
+// 16-column blocks per wavefront (two wavefronts side by side) that the last of tiles_n tiles needs for n_valid columns
+__host__ __device__ inline int last_blocks(int n_valid, int tiles_n) {
+  const int n = n_valid - (tiles_n - 1) * kBN;
+  return n <= 64 ? 2 : n <= 128 ? 4 : 8;
+}
 
 // Groups of kNumCU workgroups take walk * kNumCU consecutive units each, workgroup b of a group its units b, b + kNumCU, ...: the units
 // start in the order in which one workgroup per unit would start them, and on the same XCD.
@@ -41,7 +48,16 @@ inline int walk_length(int units, int kt) {
 // dW at H = 4096 with 300 tokens 703 / 636, 1237 (accumulating) 1816 / 1739, 8192 7308 / 7171, but 16384 14488 / 14496.  dH has two rounds
 // of thousands of slices: one unit each.
 constexpr int kLogitsWalkSlices = 128, kDWeightWalkSlices = 256;
-inline int logits_walk(int units, int kt) { return kt <= kLogitsWalkSlices ? walk_length(units, kt) : 1; }
+// A short last tile (last < 8 blocks) is computed by workgroups of one unit, so the whole launch is: what the short tile saves falls with
+// the number of tile columns, what walking saves does not.  Short last tile / walked whole, log-probs of 256 (columns - 1) + 45 tokens at
+// V = 151936, us: H = 64 2 columns 45.7 / 48.9, 3 63.3 / 63.0, 5 100 / 96; 256 5 133 / 137, 6 157 / 156, 8 208 / 201; 512 7 256 / 269, 8 295 / 297,
+// 9 330 / 327; 1024 7 419 / 434, 8 496 / 499, 9 540 / 542, 17 1031 / 1008, 33 1986 / 1904; 2048 8 903 / 915, 9 1019 / 1014; 4096 8 1717 / 1749,
+// 9 1905 / 1908, 17 3630 / 3608, 49 10795 / 10422; with 100 tokens in the last tile H = 1024 8 507 / 504, 4096 8 1747 / 1763, 9 1933 / 1916.
+inline int short_tile_columns(int kt) { return kt < 12 ? 2 + kt / 2 : 8; }
+inline int logits_walk(int units, int kt, int last, int tiles_n) {
+  if (kt > kLogitsWalkSlices || (last < 8 && tiles_n <= short_tile_columns(kt))) return 1;
+  return walk_length(units, kt);
+}
 inline int dw_walk(int units, int kt) { return kt <= kDWeightWalkSlices ? walk_length(units, kt) : 1; }
 
 }  // namespace nat

@@ -267,6 +267,22 @@ def test_bf16_workgroups_walk_several_tiles(stage, n_tok, H, V):
     check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
 
 
+@pytest.mark.parametrize("n_tok", [513, 769, 1025, 1124])
+def test_bf16_nearly_empty_last_token_tile_of_several(stage, n_tok):
+    # H = 64: with three tile columns the short last tile has workgroups of its own, with more the workgroups walk it as a whole one;
+    # entropies too, and the log-probs of the tokens in front of it have the bits that they have without it
+    H, V = 64, 40000
+    case = make_loss_case(560 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+    ref = oracle_loss(**case)
+    check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case)
+    hidden, W, ids = to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"])
+    whole = stage.logp(hidden, W, ids, n_tok, want_entropy=True)
+    full = n_tok // 256 * 256
+    front = stage.logp(hidden[:full], W, ids[:full], full, want_entropy=True)
+    for k in ("logp", "entropy"):
+        assert torch.equal(whole[k][:full], front[k][:full]), k
+
+
 @pytest.mark.parametrize("V", [1025, 17153])
 @pytest.mark.parametrize("n_tok", [40, 2048, 2049])
 def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):

@@ -37,8 +37,14 @@ int main() {
         if (!taken[id]) return std::printf("unit %d of %d left out\n", id, units), 1;
     }
   // long contractions: one unit per workgroup (a hidden size of 5120 is 160 slices; 8192 tokens of dW are 256)
-  if (logits_walk(44550, 128) < 2 || logits_walk(44550, 130) != 1 || logits_walk(19008, 160) != 1) return std::printf("logits\n"), 1;
+  if (logits_walk(44550, 128, 8, 75) < 2 || logits_walk(44550, 130, 8, 75) != 1 || logits_walk(19008, 160, 8, 32) != 1) return std::printf("logits\n"), 1;
   if (dw_walk(9504, 256) < 2 || dw_walk(9504, 258) != 1) return std::printf("dW\n"), 1;
+  // one token more than 64 full tile columns does not take the walk from them; 45 more than one does, whose short tile saves more
+  if (last_blocks(16385, 65) != 2 || logits_walk(594 * 65, 32, 2, 65) < 2) return std::printf("16385 tokens\n"), 1;
+  if (last_blocks(301, 2) != 2 || logits_walk(594 * 2, 32, 2, 2) != 1) return std::printf("301 tokens\n"), 1;
+  for (int kt = 2; kt <= 128; kt += 2)
+    for (int last = 2; last < 8; last += 2)
+      if (logits_walk(594 * 2, kt, last, 2) != 1 || logits_walk(594 * 9, kt, last, 9) < 2) return std::printf("short tile, %d slices\n", kt), 1;
   return 0;
 }
 """
