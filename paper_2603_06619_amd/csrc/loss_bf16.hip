@@ -417,10 +417,11 @@ struct AccReader {
   __device__ __forceinline__ f32x4 operator()(const f32x4& c) const {
     return f32x4{(*this)(c, 0), (*this)(c, 1), (*this)(c, 2), (*this)(c, 3)};
   }
-  // c to p[kOffset ..] as it is (s_nop: the registers of a 16-byte store may not be written by the very next instruction)
+  // c to p[kOffset ..] as it is (s_nop: the registers of a 16-byte store may not be written by a vector instruction within the next two
+  // wait states, and the compiler does not know that this is one)
   template <int kOffset>
   __device__ __forceinline__ void store(float* p, const f32x4& c) const {
-    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 ; %3\n\ts_nop 0" : : "v"(p), "a"(c), "n"(kOffset * 4), "s"(settled) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 ; %3\n\ts_nop 1" : : "v"(p), "a"(c), "n"(kOffset * 4), "s"(settled) : "memory");
   }
 };
 

@@ -1,6 +1,9 @@
-"""Checks of the machine code built from loss_bf16.hip, without a GPU.  Its matrix products are inline assembly, so the
-compiler does not keep their wait states: nothing may move accumulators or fragments about between them, and the
-accumulators may be read only behind the wait states at the head of the epilogue."""
+"""Checks of the machine code built from loss_bf16.hip, without a GPU.  Its matrix products, transposing LDS reads and some
+of its 16-byte stores are inline assembly, so the compiler does not keep their wait states: nothing may move accumulators or
+fragments about between the products or write their operands just before one, the accumulators may be read only behind the
+wait states at the head of the epilogue, what a transposing read fetches only behind a wait for it, and the registers of a
+store may not be written right behind it."""
+import glob
 import os
 import re
 import subprocess
@@ -15,12 +18,15 @@ def kernels(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("llvm-objdump is not installed")
     import paper_2603_06619_amd as nat
-    if not os.path.exists(nat.library_path()):
-        from paper_2603_06619_amd import build
-        build.build()
+    from paper_2603_06619_amd import build
     d = tmp_path_factory.mktemp("isa")
     lib = os.path.join(str(d), "lib.so")
-    os.symlink(nat.library_path(), lib)
+    sources = glob.glob(os.path.join(build.CSRC, "*")) + [os.path.join(build.ROOT, "include", "nat.h"), build.__file__]
+    built = nat.library_path()
+    if os.path.exists(built) and os.path.getmtime(built) >= max(os.path.getmtime(f) for f in sources):
+        os.symlink(built, lib)
+    else:                                                 # not the code that is there: one of its own
+        build.build(lib_path=lib, obj_dir=str(tmp_path_factory.mktemp("obj")))
     subprocess.run([OBJDUMP, "--offloading", lib], cwd=d, check=True, stdout=subprocess.DEVNULL)
     found = {}
     for f in sorted(os.listdir(d)):
@@ -49,7 +55,7 @@ def test_products_are_not_mixed_with_register_moves(kernels):
                 loops += 1
                 body = block[products[0]:products[-1] + 1]
                 assert all(y.startswith("v_mfma_f32_16x16x32_bf16 ") for y in body if y.startswith("v_mfma")), name
-                moves = [y for y in body if re.match(r"v_accvgpr|v_mov_b32|scratch_|buffer_", y)]
+                moves = [y for y in body if re.match(r"v_accvgpr|v_(pk_)?mov_b|scratch_|buffer_", y)]
                 assert not moves, (name, moves[:4])
             block = []
         assert loops, name
@@ -61,26 +67,99 @@ def registers(x):
             for n in range(int(lo or one), int(hi or one) + 1)}
 
 
+def every_path(code, step, start):
+    """Follows every path of the control flow: step(state, instruction, the one before) gives the state behind an instruction."""
+    index = {at: i for i, (_, at, _) in enumerate(code)}
+    seen, todo = set(), [(0, start)]
+    while todo:
+        i, state = todo.pop()
+        while (i, state) not in seen:
+            seen.add((i, state))
+            x, _, to = code[i]
+            assert not re.match(r"s_(setpc|swappc|call)", x), x
+            state = step(state, x, code[i - 1][0])
+            if x.startswith("s_endpgm"):
+                break
+            if x.startswith("s_cbranch"):
+                todo.append((index[to], state))
+            i = index[to] if x.startswith("s_branch") else i + 1
+    assert len(seen) > 500
+
+
 def test_accumulators_are_read_behind_the_wait_states(kernels):
-    # along every path of the control flow: after a product, nothing but products names its result before the wait states
+    # after a product, nothing but products names its result before the wait states
+    def step(results, x, before):
+        if x.startswith("v_mfma"):
+            return results | registers(x.split(",")[0])
+        if x == "s_nop 7" and before == "s_nop 15":
+            return frozenset()
+        assert not results & registers(x), (name, x)
+        return results
+
     for name, code in kernels.items():
-        index = {at: i for i, (_, at, _) in enumerate(code)}
-        seen, todo = set(), [(0, frozenset())]
-        while todo:
-            i, results = todo.pop()
-            while (i, results) not in seen:
-                seen.add((i, results))
-                x, _, to = code[i]
-                if x.startswith("v_mfma"):
-                    results = results | registers(x.split(",")[0])
-                elif x == "s_nop 7" and code[i - 1][0] == "s_nop 15":
-                    results = frozenset()
-                else:
-                    assert not results & registers(x), (name, x)
-                assert not re.match(r"s_(setpc|swappc|call)", x), (name, x)
-                if x.startswith("s_endpgm"):
-                    break
-                if x.startswith("s_cbranch"):
-                    todo.append((index[to], results))
-                i = index[to] if x.startswith("s_branch") else i + 1
-        assert len(seen) > 500, name
+        every_path(code, step, frozenset())
+
+
+def written_by_vector_alu(x):
+    if not x.startswith("v_"):
+        return set()
+    operands = x.split(",")
+    return registers(operands[0]) | (registers(operands[1]) if "_swap" in x else set())
+
+
+def aged(state, x, keep):
+    """(register, wait states since) behind x, as long as they are fewer than `keep`."""
+    n = int(x.split()[1]) + 1 if x.startswith("s_nop") else 1
+    return {(r, age + n) for r, age in state if age + n < keep}
+
+
+def test_product_operands_are_not_written_right_before(kernels):
+    # two wait states between a vector instruction that writes a register and a product that reads it: what the compiler keeps
+    # in front of a product that it knows
+    def step(recent, x, _):
+        if x.startswith("v_mfma"):
+            sources = registers(",".join(x.split(",")[1:]))
+            assert not sources & {r for r, _ in recent}, (name, x)
+            return frozenset(aged(recent, x, 2))
+        return frozenset(aged(recent, x, 2) | {(r, 0) for r in written_by_vector_alu(x)})
+
+    for name, code in kernels.items():
+        every_path(code, step, frozenset())
+
+
+def test_transposing_reads_are_waited_for(kernels):
+    def step(pending, x, _):
+        if x.startswith("s_waitcnt") and "lgkmcnt(0)" in x:
+            return frozenset()
+        if x.startswith("ds_read_b64_tr_b16"):
+            result, address = x.split(",")[0], x.split(",")[1]
+            assert not pending & registers(address), (name, x)
+            reads.append(x)
+            return pending | registers(result)
+        assert not pending & registers(x), (name, x)
+        return pending
+
+    reads = []
+    for name, code in kernels.items():
+        every_path(code, step, frozenset())
+    assert reads
+
+
+def test_store_data_is_not_written_right_behind(kernels):
+    # two wait states between a store of 16 bytes and a vector instruction that writes what it stores.  Those in inline
+    # assembly keep them by themselves: the compiler may put anything behind them
+    def step(recent, x, _):
+        assert not written_by_vector_alu(x) & {r for r, _ in recent}, (name, x)
+        state = aged(recent, x, 2)
+        if re.match(r"(global|flat)_store_dwordx4", x):
+            state |= {(r, 0) for r in registers(x.split(",")[1])}
+        return frozenset(state)
+
+    own = 0
+    for name, code in kernels.items():
+        every_path(code, step, frozenset())
+        for (x, _, _), (y, _, _) in zip(code, code[1:]):
+            if re.match(r"global_store_dwordx4 v\[\d+:\d+\], a\[", x):
+                own += 1
+                assert y == "s_nop 1", (name, x, y)
+    assert own
