@@ -75,6 +75,15 @@ def test_bf16_path_with_kl_and_entropy(stage, kind, n_tok, H, V):
     assert n_tok < 10 or max_rel_err(base["dW"], ref["dW"]) > 0.05
 
 
+@pytest.mark.parametrize("n_tok,H,V", [(500, 192, 65700), (6200, 320, 3000)])
+def test_bf16_entropy_where_workgroups_walk(stage, n_tok, H, V):
+    # more logits tiles than compute units, W read as it is and repacked
+    case = add_ref(make_loss_case(150 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1), 2)
+    out, ref = run_both(stage, case, "bf16", 0.25, KINDS[0])
+    check(out, ref, n_tok, TOL_BF16, case)
+    check_diag(out, ref, n_tok, 1e-4)
+
+
 def test_bf16_entropy_of_peaked_and_flat_policies(stage):
     # half the tokens have a dominant logit (entropy near 0), the others a spread of +-20
     n_tok, H, V = 400, 128, 2000

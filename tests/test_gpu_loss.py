@@ -283,15 +283,7 @@ def test_bf16_nearly_empty_last_token_tile_of_several(stage, n_tok):
         assert torch.equal(whole[k][:full], front[k][:full]), k
 
 
-@pytest.mark.parametrize("V", [1025, 17153])
-@pytest.mark.parametrize("n_tok", [40, 2048, 2049])
-def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):
-    # up to 2048 tokens a chunk is added to dW by reading, adding and storing, beyond that by fp32 atomics; tiles whose token
-    # axis is cut are added by the kernel that sums their ranges.  V = 17153: 136 tiles, more than half a round of compute units,
-    # so none is cut; V = 1025: 10 tiles, all cut from 2048 tokens on.  One addition of the same sum per element either way, so
-    # accumulating equals old + the overwritten result bit for bit.  Columns and rows past the end of the last tiles (H = 320, one
-    # row in the last tile) keep what they held
-    H = 320
+def accumulated_and_plain(stage, n_tok, H, V):
     case = make_loss_case(600 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
     plain = hip_loss(stage, case, "bf16")["dW"]
     big = torch.randn((V + 1, H), generator=torch.Generator(device=DEV).manual_seed(1), device=DEV) * plain.abs().mean()
@@ -299,6 +291,39 @@ def test_bf16_accumulation_by_read_add_store_and_by_atomics(stage, n_tok, V):
     acc = hip_loss(stage, case, "bf16", dW=big[:V], accumulate_dw=True)["dW"]
     assert torch.equal(acc, old[:V] + plain)
     assert torch.equal(big[V], old[V])
+    return case, plain
+
+
+@pytest.mark.parametrize("V", [1025, 17153])
+@pytest.mark.parametrize("n_tok", [40, 2048, 2049])
+def test_bf16_accumulating_equals_old_plus_overwritten(stage, n_tok, V):
+    # a chunk is added to dW by reading, adding and storing, in the contraction or, for tiles whose token axis is cut, in the kernel that
+    # sums their ranges.  V = 17153: 136 tiles, more than half a round of compute units, so none is cut; V = 1025: 10 tiles, all cut
+    # from 2048 tokens on.  One addition of the same sum per element either way, so accumulating equals old + the overwritten result
+    # bit for bit.  Columns and rows past the end of the last tiles (H = 320, one row in the last tile) keep what they held
+    accumulated_and_plain(stage, n_tok, 320, V)
+
+
+@pytest.mark.parametrize("n_tok", [200, 2100])
+def test_bf16_accumulating_where_workgroups_walk(stage, n_tok):
+    # 257 dW tiles, so that a workgroup's old values and stores come between the next tile's loads: 8 slices each, and 66, where the
+    # 257th is cut into two ranges and a walk goes from a whole tile to a range
+    case, plain = accumulated_and_plain(stage, n_tok, 64, 65700)
+    if n_tok == 200:
+        assert max_rel_err(plain.cpu().numpy(), oracle_loss(**case)["dW"]) <= TOL_BF16
+
+
+@pytest.mark.parametrize("n_tok", [8192, 8193])
+def test_bf16_dw_where_walks_end(stage, n_tok):
+    # 258 dW tiles of 256 k-slices are walked, of 258 not.  Against the sum of calls over half the tokens, whose products are the same
+    # and whose fp32 sums run in another order: 512 additions of relative 2^-24 each, with random signs 1.4e-6
+    H, V = 320, 33000
+    case, plain = accumulated_and_plain(stage, n_tok, H, V)
+    dW = torch.zeros((V, H), device=DEV)
+    for half in (slice(0, 4096), slice(4096, n_tok)):
+        part = {k: (v[half] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
+        hip_loss(stage, part, "bf16", dW=dW, accumulate_dw=True)
+    assert float((plain - dW).norm() / dW.norm()) <= 1e-5
 
 
 @pytest.mark.parametrize("H,V,n", [(64, 7, 6144), (320, 700, 6144), (192, 1025, 6144), (256, 700, 7168)])
@@ -328,7 +353,7 @@ def test_bf16_forward_pass_w_repacked_and_read_as_it_is_agree(stage, H, V, n):
 
 @pytest.mark.parametrize("n_tok,H,V,label", [
     (4700, 3584, 2100, "dH: a full round of tiles and ten more in two vocabulary ranges"),
-    (100, 128, 40000, "dH: one tile in 39 vocabulary ranges"),
+    (100, 128, 40000, "dH: one tile in 37 vocabulary ranges"),
     (257, 320, 9000, "dH: four tiles, two of them with one valid row, in nine ranges"),
 ])
 def test_bf16_dh_leftover_tiles_cut_into_vocabulary_ranges(stage, n_tok, H, V, label):
