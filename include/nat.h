@@ -400,8 +400,8 @@ nat_status nat_profile_collect(double* h_ms, int64_t* h_launches, int32_t n_clas
 /*
  * Practical ceilings of the machine (measurement aids, not on the path).  The caller times them
  * with events on `stream`.
- *   nat_probe_mfma_bf16: 2048 workgroups of 4 wavefronts, each issuing `iters` x 16 independent
- *     32x32x16 bf16 matrix products on operands held in registers (random_operands = 0: constant
+ *   nat_probe_mfma_bf16: 2048 workgroups of 4 wavefronts, each issuing `iters` x 32 independent
+ *     16x16x32 bf16 matrix products on operands held in registers (random_operands = 0: constant
  *     operands; 1: pseudo-random sign and mantissa bits, which is what the power limit sees on
  *     real data).  d_scratch: nat_probe_mfma_scratch_bytes() of device memory (written, contents
  *     meaningless); *h_flops (HOST, may be NULL) receives the flops of the launch.

@@ -12,23 +12,35 @@ namespace nat {
 
 typedef __bf16 probe_bf16x8 __attribute__((ext_vector_type(8)));
 typedef short probe_s16x8 __attribute__((ext_vector_type(8)));
-typedef float probe_f32x16 __attribute__((ext_vector_type(16)));
+typedef float probe_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kProbeBlocks = 256 * 8;             // eight workgroups per compute unit in sequence
-constexpr int kProbeThreads = 256;                // one wavefront per SIMD, 256 accumulator registers each
+constexpr int kProbeThreads = 256;                // one wavefront per SIMD
 
-// 16 independent 32x32x16 products per iteration and wavefront: the accumulator tile of the GEMM core.
+// As in the core the product is inline assembly: given the builtin, the compiler moves accumulators between the products.
+__device__ __forceinline__ void probe_product(probe_f32x4& c, const probe_bf16x8& a, const probe_bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+// 32 independent 16x16x32 products per iteration and wavefront: half a k-slice of the GEMM core.  On one card in turn, TFLOP/s: random operand
+// bits 2171, the same flops as 32x32x16 products 1895; constant operands 2471 and 2477.  The power limit, by which the core chose the instruction.
 __global__ void __launch_bounds__(kProbeThreads, 1)
 probe_mfma_kernel(float* __restrict__ out, int iters, int random_operands) {
-  probe_f32x16 acc[16];
+  probe_f32x4 acc[8][4];
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-  probe_bf16x8 a[4], b[4];
+    for (int j = 0; j < 4; ++j) acc[i][j] = probe_f32x4{0.f, 0.f, 0.f, 0.f};
+  probe_bf16x8 a[8], b[4];
+  auto settle = [&] {                              // what is done to the accumulators before it comes before what follows
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
+  };
   unsigned x = threadIdx.x * 2654435761u + blockIdx.x * 40503u + 17u;
 #pragma unroll
-  for (int f = 0; f < 4; ++f) {
+  for (int f = 0; f < 8; ++f) {
     probe_s16x8 ra, rb;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {                 // values in +-[1, 2): sign and mantissa bits random
@@ -38,20 +50,27 @@ probe_mfma_kernel(float* __restrict__ out, int iters, int random_operands) {
       rb[i] = random_operands ? (short)(((x >> 16) & 0x807f) | 0x3f80) : (short)0x3f80;
     }
     a[f] = __builtin_bit_cast(probe_bf16x8, ra);
-    b[f] = __builtin_bit_cast(probe_bf16x8, rb);
+    if (f < 4) b[f] = __builtin_bit_cast(probe_bf16x8, rb);
   }
+  settle();
+#pragma unroll
+  for (int f = 0; f < 8; ++f) asm volatile("" : "+v"(a[f]), "+v"(b[f & 3]));
+  asm volatile("s_nop 1");                         // a product may read what a vector instruction wrote two wait states later
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i * 4 + j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i * 4 + j], 0, 0, 0);
+      for (int j = 0; j < 4; ++j) probe_product(acc[i][j], a[i], b[j]);
   }
+  asm volatile("s_nop 15\n\ts_nop 7");         // a product's result may be read that many wait states later
+  settle();
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
+  for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s += acc[i][r];
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s += acc[i][j][r];
   out[(size_t)blockIdx.x * kProbeThreads + threadIdx.x] = s;
 }
 
@@ -72,8 +91,8 @@ extern "C" nat_status nat_probe_mfma_bf16(int32_t random_operands, int32_t iters
   if (!d_scratch || iters <= 0) return NAT_INVALID_ARG;
   probe_mfma_kernel<<<kProbeBlocks, kProbeThreads, 0, (hipStream_t)stream>>>(d_scratch, iters, random_operands);
   NAT_LAUNCH_CHECK();
-  // blocks x 4 wavefronts x iterations x 16 products of 2 * 32 * 32 * 16 flops
-  if (h_flops) *h_flops = (double)kProbeBlocks * 4.0 * (double)iters * 16.0 * 32768.0;
+  // blocks x 4 wavefronts x iterations x 32 products of 2 * 16 * 16 * 32 flops
+  if (h_flops) *h_flops = (double)kProbeBlocks * 4.0 * (double)iters * 32.0 * 16384.0;
   return NAT_OK;
 }
 

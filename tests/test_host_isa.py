@@ -1,4 +1,4 @@
-"""Checks of the machine code built from loss_bf16.hip, without a GPU.  Its matrix products, transposing LDS reads and some
+"""Checks of the machine code built from loss_bf16.hip and ceilings.hip, without a GPU.  Their matrix products, transposing LDS reads and some
 of its 16-byte stores are inline assembly, so the compiler does not keep their wait states: nothing may move accumulators or
 fragments about between the products or write their operands just before one, the accumulators may be read only behind the
 wait states at the head of the epilogue, what a transposing read fetches only behind a wait for it, and the registers of a
@@ -35,7 +35,7 @@ def kernels(tmp_path_factory):
         text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", os.path.join(str(d), f)], check=True,
                               stdout=subprocess.PIPE, text=True).stdout
         for name, body in re.findall(r"^[0-9a-f]+ <(\S+)>:\n((?:[ \t].*\n)+)", text, flags=re.M):
-            if "mfma_nt_kernel" in name:
+            if "mfma_nt_kernel" in name or "probe_mfma_kernel" in name:
                 # (instruction, its offset in the kernel, offset of its branch target)
                 code = [re.match(r"\s*(.*?)\s*// ([0-9A-F]+):[^<]*(?:<[^+>]*(?:\+0x([0-9a-f]+))?>)?", line).groups() for line in body.splitlines() if "//" in line]
                 found[name] = [(x, int(at, 16) - int(code[0][1], 16), int(to or "0", 16)) for x, at, to in code]
