@@ -45,15 +45,16 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 // The soft-max numerators are written once and read back only by the two backward contractions,
-// long after they have left the L2: non-temporal stores (1 % on the logits kernel).
+// long after they have left the L2: non-temporal stores (logits of 8192 tokens
+// at H = 4096 6990 -> 6929 us, of 16384 at H = 1024 4200 -> 4084).
 #define NAT_E_STORE(ptr, val) __builtin_nontemporal_store((val), (ptr))
 
 constexpr int kBM = 256, kBK = 32;                // block tile kBM x kBN: 4 wavefronts of 128 x 128, one per SIMD
 constexpr int kStages = 4;                        // LDS ring of k-slices (4 x 32 KiB)
 constexpr int kGranule = 128;                     // vocabulary rows per soft-max partial
 constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stage
-// Tile rows per group of the block -> tile map, per contraction (measured: 4 is 1-2 % faster than 8
-// for the two backward contractions, 2 and 6 are slower, 16 is 8 % slower).
+// Tile rows per group of the block -> tile map, per contraction (whole step at the 8B head: logits in groups of 4 equal,
+// of 16 3.4 % slower; dH and dW in groups of 8 1.5 % slower).
 #ifndef NAT_GROUP_LOGITS
 #define NAT_GROUP_LOGITS 8
 #endif
@@ -482,7 +483,8 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 // tokens are padded, ranges start and end at even slices): two per turn of the loop.  The slices of a workgroup's
 // units follow one another: while the last ones of a unit are multiplied and its epilogue runs, the first ones of the next are
 // loaded (kMany; without it there is one unit, and neither the bookkeeping nor a first pair of slices of its own that starts
-// from zero: 1 % on dH's thousands of slices).  Past the last unit the last two slices are loaded again (into buffers nobody reads), so that the body is free of
+// from zero: 1 % on dH's thousands of slices, 0.7 % on logits of 112 to 160; dW of 512 slices took 14523 us without and 14489 with
+// it).  Past the last unit the last two slices are loaded again (into buffers nobody reads), so that the body is free of
 // branches and the count fixed.  The 8 x NB products of a slice are written slot by slot (the compiler may not move anything
 // across a slot's end): fragment reads behind the products of the first half, one every second of them, loads of the refill
 // evenly spaced behind the second half.
@@ -534,9 +536,8 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(lds[st][1], k, wave); };
   // Load n of the next two slices into buffers st and st + 1: first kEven with the even one, then kOdd.  A slice of an A read
   // from rows is 64 bytes of a row, half a cache line; fetched a slice apart, the halves cost the line twice on the way from
-  // the L2 (12289 tokens at H = 4096: 11.92 ms, 11.55 together, 11.48 from the repacked copy): both slices' A tiles go
-  // with the odd one, half after half, and B's odd tile with the next even one (with the odd one too, 12 loads against 4: 15 %
-  // slower).
+  // the L2 (log-probs of 12288 tokens at H = 4096 10454 us, 10163 together; 2048 1824 / 1766, at H = 1024 519 / 504): both slices'
+  // A tiles go with the odd one, half after half, and B's odd tile with the next even one, 8 loads each.
   constexpr bool kPaired = kA == Src::kRows;
   constexpr int kEven = kPaired ? 2 * kLoadsB : kLoads, kOdd = kPaired ? 2 * kLoadsA : kLoads;
   auto load_even = [&](auto n, int st) {
@@ -663,8 +664,8 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   } else {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
-    // computes only those (128 of 256: 301 log-probs at the 0.6B head, logits 153 -> 132 us; 59 tokens at the 8B head, call 1155 -> 1067 us;
-    // 64 of 128: 301 log-probs at the 0.6B head 156 -> 148, 300 at the 8B head 454 -> 428, 60 tokens, call 1063 -> 1034).
+    // computes only those (whole call with 256 / 128 / 64 columns, us: 301 log-probs at the 0.6B head 138 / 127 / 120, 300 at the 8B head
+    // 474 / 427 / 408; loss at the 8B head 60 tokens 1085 / 1010 / 982, 100 1141 / 1062, 1100 3616 / 3547).
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
       const int blocks = last_blocks(epi.n_valid, g.tiles_n);
       if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {
@@ -1183,8 +1184,9 @@ static int sub_chunk_rows(int cap, int Hp) {
 
 // Chunk capacity of the recommended workspace.  Forward pass alone: kMaxChunk.  With the backward pass the
 // chunk also sizes the stored soft-max numerators (cap x Vp x 2 bytes), and the dW contraction, whose
-// contraction axis is the chunk, is within 0.2 % of its 32768-token speed at 16384 (measured): the
-// smallest of 16384 / 24576 / 32768 rows whose dH launch fills whole rounds of workgroups to 97 %.
+// contraction axis is the chunk, gains little beyond 16384 (whole step at the 8B head 351.9 ms, 351.2 at 24576 and
+// 351.0 at 32768 with 34 and 68 % more workspace; 8192: 1.5 % slower): the smallest of 16384 / 24576 / 32768 rows
+// whose dH launch fills whole rounds of workgroups to 97 %.
 static int recommended_cap(int32_t N_k, int32_t H, bool backward) {
   const int64_t all = round_up(N_k > 0 ? N_k : 1, kBN);
   if (!backward) return (int)(all > kMaxChunk ? kMaxChunk : all);
@@ -1230,8 +1232,9 @@ size_t logp_bf16_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal
 // compute unit run whole; the tiles left over (at most half a round: with more, two ranges each would not fit one
 // round) are cut into as many ranges of the contraction axis as fill the chip once, of at least kMinSlicesPerRange
 // on average (a workgroup's load ring and epilogue cost about ten slices), starts multiples of `align`; the last range takes
-// what that rounding leaves (1256 slices in 39 ranges: 38 of 33 and one of 2).
-// 5003 tokens at the 7B head: 280 dH tiles took a second round for 24 of them, 6.26 ms; cut into ten ranges, 3.96 ms.
+// what that rounding leaves (1256 slices: 36 ranges of 34 and one of 32).
+// 5003 tokens at the 7B head: 280 dH tiles took a second round for 24 of them, 6.52 ms; cut into ten ranges, 3.87 ms.  1237 at the 8B
+// head 2.82 / 1.13; dW of 16384 tokens there 14.28 / 14.07.
 struct RangeCut { int splits, kt_per, tail, grid; };
 static RangeCut range_cut(int tiles, int kt_all, int align) {
   RangeCut c{1, kt_all, 0, tiles};
@@ -1250,15 +1253,14 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 
 // Up to how many tokens a call reads W as it is instead of repacking it first.  The repack moves W three times with the
 // backward pass (0.77 ms at V x H = 151936 x 4096, 0.21 ms at H = 1024), twice without (0.50 / 0.12 ms), whatever the
-// batch; reading rows costs the logits contraction 1 to 2 % and the dH contraction, with its transposing reads, 3 to
-// 5 %, so the gain shrinks with the batch.  The lines are where it ends for the last of the hidden sizes; repacked against
+// batch; what reading rows costs the logits contraction and the dH contraction, with its transposing reads, grows with it.  Repacked /
 // direct in alternating runs, whole call, ms at V = 151936 unless stated.  H a multiple of the 256-wide dH tile: 1500 tokens
-// 5.56 / 4.99 (H = 4096), 1.55 / 1.41 (1024); 5000: 15.1 / 14.6, 4.17 / 4.07; 7168: 21.7 / 21.2 (4096), 5.75 / 5.66 (1024), 27.08 / 26.96
-// (5120); 8192: 23.5 / 23.2 (4096) but 29.4 / 29.7 (5120).  Other H, whose dH tiles are padded (the work grows with the
-// tiles, the repack with H): 1500: 1.08 / 0.97 (576), 0.80 / 0.72 (320); 5000: 2.88 / 2.87, 2.03 / 2.00; 6144: 3.46 / 3.48, 2.39 / 2.39; 7168: 3.97 / 4.01, 2.77 / 2.81;
-// 8192 at V = 50000: 1.08 / 1.10 (320).  Forward pass alone: 2000 tokens 2.42 / 1.98 (4096), 0.68 / 0.59 (1024); 12289 with the
-// entropy: 12.02 / 11.79, 3.52 / 3.38; 24576: 24.4 / 24.1, 6.42 / 6.37, 29.9 / 29.7 (5120); 49152: 45.7 / 45.7, 12.9 / 12.9, 57.0 / 57.8; with
-// contractions of a few slices 5000: 0.386 / 0.386 (H = 64, V = 160000), 16384: 1.19 / 1.20.
+// 5.14 / 4.50 (H = 4096), 1.49 / 1.34 (1024); 5000: 13.55 / 13.01, 3.76 / 3.66; 7168: 18.87 / 18.54 (4096), 5.16 / 5.09 (1024), 23.74 / 23.61
+// (5120), but 17.44 / 17.66 (3584, V = 152064); 8192: 20.94 / 20.59 (4096), 26.42 / 26.87 (5120).  Other H, whose dH tiles are padded (the work
+// grows with the tiles, the repack with H): 1500: 1.02 / 0.92 (576), 0.72 / 0.64 (320); 5000: 2.61 / 2.59, 1.85 / 1.81; 6144: 3.13 / 3.12, 2.16 / 2.17; 7168:
+// 3.54 / 3.56, 2.50 / 2.55; 8192 at V = 50000: 0.97 / 1.00 (320).  Forward pass alone: 2000 tokens 2.16 / 1.76 (4096), 0.59 / 0.50 (1024); 12288: 10.62 / 10.13,
+// 2.92 / 2.83; 24576: 21.2 / 20.4, 5.75 / 5.71, 26.4 / 26.3 (5120); 49152: 41.8 / 40.8, 11.3 / 11.4, 52.0 / 52.3; with contractions of a few
+// slices 5000: 0.328 / 0.322 (H = 64, V = 160000), 8192: 0.510 / 0.506, 16384: 0.992 / 0.991.
 static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }
 static int direct_tokens_forward(int H) { return H >= kBN ? 24576 : 8192; }
 
@@ -1326,7 +1328,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
     }
     // The forward sweep and the dH contraction go over the chunk in sub-chunks: shorter launches of
     // the three contractions alternate, which this power-limited part rewards with a higher clock
-    // (measured: both run faster on 8192 tokens than on 32768), while the dW contraction below keeps
+    // (whole step at the 8B head: sub-chunks of 16384 instead of 8192 tokens 0.4 % slower), while the dW contraction below keeps
     // the whole chunk as its contraction axis (it is the one that loses on short axes).
     for (int s0 = 0; s0 < nv; s0 += sub) {
       const int snv = nv - s0 < sub ? nv - s0 : sub;
