@@ -163,3 +163,19 @@ def test_store_data_is_not_written_right_behind(kernels):
                 own += 1
                 assert y == "s_nop 1", (name, x, y)
     assert own
+
+
+def test_dh_scales_are_loaded_together(kernels):
+    # the per-token scales of dH, a 4-byte load each, stand in front of the first result: loaded block by block of tokens each would wait
+    # for memory in turn.  Behind a store of results (bf16, 8 or 16 bytes per lane) there is no such load
+    found = 0
+    for name, code in kernels.items():
+        if "DHiddenEpilogue" not in name:
+            continue
+        loads = [i for i, (x, _, _) in enumerate(code) if re.match(r"global_load_dword ", x)]
+        packs = [i for i, (x, _, _) in enumerate(code) if x.startswith("v_cvt_pk_bf16_f32")]
+        found += len(loads)
+        assert loads and packs, name
+        for first, last in zip(loads, loads[1:]):
+            assert not any(first < i < last for i in packs) or any(code[i][0].startswith("v_mfma") for i in range(first, last)), name
+    assert found >= 16
