@@ -35,6 +35,7 @@
 // k-major operand.
 #include "nat_internal.h"
 #include "grpo_scalar.hip.h"
+#include "row_stage.hip.h"
 #include "walk.hip.h"
 
 #include <type_traits>
@@ -329,14 +330,21 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int off) {
   return v;
 }
 
+// Four 16-byte reads, waited for: as inline assembly for the same reason.  (Accesses of one wavefront to LDS are in order: what it wrote before is read.)
+__device__ __forceinline__ void lds_read_rows(const uint32_t (&addr)[4], f32x4 (&x)[4]) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]) : "v"(addr[0]), "v"(addr[1]), "v"(addr[2]), "v"(addr[3]) : "memory");
+}
+
 // s_waitcnt immediates (gfx9 encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8)
 constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 
 // one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
-// direct-to-LDS loads in flight): the ring, and behind it the words the epilogue parks across the k-loop
+// direct-to-LDS loads in flight): the ring, and behind it the words of the epilogue (parked across the k-loop, or staged)
+template <int kWords>
 struct GemmShared {
   char ring[kStages][2][kTileBytes];
-  int stash[4][256];             // per wavefront
+  int words[4][kWords];          // per wavefront
 };
 
 // ---------------------------------------------------------------- GEMM core ----
@@ -418,11 +426,9 @@ struct AccReader {
   __device__ __forceinline__ f32x4 operator()(const f32x4& c) const {
     return f32x4{(*this)(c, 0), (*this)(c, 1), (*this)(c, 2), (*this)(c, 3)};
   }
-  // c to p[kOffset ..] as it is (s_nop: the registers of a 16-byte store may not be written by a vector instruction within the next two
-  // wait states, and the compiler does not know that this is one)
-  template <int kOffset>
-  __device__ __forceinline__ void store(float* p, const f32x4& c) const {
-    asm volatile("global_store_dwordx4 %0, %1, off offset:%2 ; %3\n\ts_nop 1" : : "v"(p), "a"(c), "n"(kOffset * 4), "s"(settled) : "memory");
+  // c to LDS as it is
+  __device__ __forceinline__ void stage(uint32_t addr, const f32x4& c) const {
+    asm volatile("ds_write_b128 %0, %1 ; %2" : : "v"(addr), "a"(c), "s"(settled) : "memory");
   }
 };
 
@@ -489,7 +495,7 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 // across a slot's end): fragment reads behind the products of the first half, one every second of them, loads of the refill
 // evenly spaced behind the second half.
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB>
-__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared& sm, int first, int end) {
+__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared<Epilogue::kWords>& sm, int first, int end) {
   constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
   using LoadA = LoaderOf<kA>;
   using LoadB = typename std::conditional<NB < 8, PartTileLoader<NB * 32>, LoaderOf<kB>>::type;
@@ -598,7 +604,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   // what the epilogue needs per column (token id, exponent shift): fetched into LDS ahead of the operands, read after the
   // k-loop
   Unit u = unit_of(g, first);
-  auto prefetch = [&] { epi.template prefetch<NQ>(sm.stash[wave], kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane); };
+  auto prefetch = [&] { epi.template prefetch<NQ>(sm.words[wave], kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane); };
   prefetch();
   open();
   if constexpr (kPaired) {
@@ -644,7 +650,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
       for (int kt = 0; kt < u.kt_n; kt += 2) two_slices(std::false_type{});
     }
     const AccReader rd;
-    epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane, sm.stash[wave], u.slab);
+    epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane, sm.words[wave], u.slab);
     id += kNumCU;
     if (!kMany || id >= end) break;
     u = unit_of(g, id);
@@ -657,7 +663,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
 template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
 __global__ void __launch_bounds__(256, 1)
 mfma_nt_kernel(GemmArgs g, Epilogue epi) {
-  __shared__ __attribute__((aligned(1024))) GemmShared sm;
+  __shared__ __attribute__((aligned(1024))) GemmShared<Epilogue::kWords> sm;
   if constexpr (kMany) {
     const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
     mfma_units<Epilogue, kA, kB, kPIsB, true, 8>(g, epi, sm, w.first, w.end);
@@ -696,6 +702,7 @@ struct LogitsEpilogue {
   int64_t ld_part;                 // leading dimension (tokens) of the partial sums
   int kb_z;                        // k-slices of Eb (Vp / 32)
   uint16_t* Eb;                    // blocked, rows = token, k = vocabulary: E = exp(z - ref), stored once
+  static constexpr int kWords = 256;
   float* s_part;                   // [Vp/128, ld_part] partial sums of E
   float* t_part;                   // [Vp/128, ld_part] partial sums of E (z - ref) (entropy), kEntropy only
   float* z_target;                 // [ld_part] exact target logits
@@ -811,6 +818,7 @@ struct LogitsEpilogue {
 // (interleaved: one 16-byte store, 64 bytes of 16 token rows per instruction) or h0 + 16 i + 4 (l / 16) .. + 3 in acc[i].
 template <bool kInterleaved>
 struct DHiddenEpilogue {
+  static constexpr int kWords = 1;
   int n_valid, H;
   uint16_t* dH;                    // rows of this chunk, [n_valid, H] bf16
   const float* beta;               // [n_valid]
@@ -860,55 +868,67 @@ struct DHiddenEpilogue {
 };
 
 // dW tile: rows = hidden units ((diag(beta) H_chunk)^T), columns = vocabulary (E^T): a lane holds hidden units h0 + 16 i + 4 (l / 16)
-// .. + 3 of its vocabulary entry, 16 bytes of a row of dW.
+// .. + 3 of its vocabulary entry.  Stored from there an instruction writes half a cache line of 16 rows, and a tile's 256 KiB leave its compute unit at
+// 16 bytes a cycle (16 k cycles, 27 k when accumulating, beside 1090 per k-slice): a wavefront's results go through LDS, 16 vocabulary entries x 64 hidden
+// units at a time, and leave as 256 bytes of four rows per instruction.  From registers / so, us: 8 tiles of 8 slices 14.7 / 11.0; 200 tokens at H = 1024, V =
+// 160000 184 / 159; H = 4096, V = 151936: 300 632 / 608, 1237 accumulating 1773 / 1611, 16384 accumulating 14931 / 14966.
 template <bool kAccumulate>
 struct DWeightEpilogue {
+  static constexpr int kWords = kStageFloats;
   int V, H;
   float* dW;                       // [V, H] fp32
   float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
 
   template <int NQ> __device__ __forceinline__ void prefetch(int*, int, int) const {}
-  __device__ __forceinline__ void operator()(const f32x4 (&acc)[8][8], const AccReader& rd, int h0, int v0, int lane, const int*, int slab_id) const {
-    const int l15 = lane & 15, g = lane >> 4;
-    if (slab_id >= 0) {            // one range of this tile's tokens: raw sums to the slab, added up by dw_tail_reduce_kernel
-      float* slab = partial + (int64_t)slab_id * (kBM * kBN) + ((v0 & (kBM - 1)) + l15) * kBN + (h0 & (kBN - 1)) + 4 * g;
+  __device__ __forceinline__ void operator()(const f32x4 (&acc)[8][8], const AccReader& rd, int h0, int v0, int lane, const int* words, int slab_id) const {
+    asm volatile("" : "+v"(lane)); // else all that is formed from it is kept across the walk, and spilled
+    uint32_t write[4], read[4];
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) static_for<8>([&](auto i) { rd.template store<decltype(i)::value * 16>(slab + nb * 16 * kBN, acc[decltype(i)::value][nb]); });
-      return;
+    for (int i = 0; i < 4; ++i) {
+      write[i] = lds_addr(words) + 4 * stage_write_at(lane, i);
+      read[i] = lds_addr(words) + 4 * stage_read_at(lane, i);
     }
-    const int rows = V - v0;                                   // valid rows from v0 on (may be <= 0)
-    float* dst = dW + (int64_t)(v0 + l15) * H + h0 + 4 * g;
-    // One owner per element and launch, launches in stream order: one fp32 addition old + sum per element.  Old values
-    // of 16 vocabulary rows are loaded while those before them are added and stored.
-    auto sweep = [&](auto all_valid) {
-      constexpr bool kAll = decltype(all_valid)::value;
-      auto ok = [&](int nb, int i) { return kAll || (nb * 16 + l15 < rows && h0 + i * 16 < H); };   // H is a multiple of 64
-      f32x4 old[2][8];
-      auto fetch = [&](int nb) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (ok(nb, i)) old[nb & 1][i] = *(const f32x4*)(dst + (int64_t)nb * 16 * H + i * 16);
-          else old[nb & 1][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // to dst: this wavefront's [128 vocabulary entries][128 hidden units], a row `ld` elements, rows x cols of them valid (cols a multiple of 64).  One owner
+    // per element and launch, launches in stream order: one fp32 addition old + sum per element.  Old values are loaded a step ahead.
+    auto sweep = [&](auto all_valid, auto add, float* dst, int ld, int rows, int cols) {
+      constexpr bool kAll = decltype(all_valid)::value, kAdd = decltype(add)::value;
+      auto ok = [&](int step, int j) { return kAll || ((step & 7) * 16 + stage_read_row(lane, j) < rows && (step >> 3) * 64 < cols); };
+      const uint32_t lane_bytes = 4u * (uint32_t)(stage_read_row(lane, 0) * ld + stage_read_column(lane));     // the rest of an address is the wavefront's
+      auto at = [&](int step, int j) {
+        return (f32x4*)((char*)(dst + (int64_t)((step & 7) * 16 + stage_read_row(0, j)) * ld + (step >> 3) * 64) + lane_bytes);
       };
-      if (kAccumulate) fetch(0);
+      f32x4 old[2][4];
+      auto fetch = [&](int step) {
 #pragma unroll
-      for (int nb = 0; nb < 8; ++nb) {
-        if (kAccumulate && nb < 7) fetch(nb + 1);
+        for (int j = 0; j < 4; ++j)
+          if (ok(step, j)) old[step & 1][j] = *at(step, j);
+          else old[step & 1][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      };
+      if (kAdd) fetch(0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          if (!kAccumulate) continue;
-          const f32x4 x = old[nb & 1][i] + rd(acc[i][nb]);
-          if (ok(nb, i)) *(f32x4*)(dst + (int64_t)nb * 16 * H + i * 16) = x;
+      for (int step = 0; step < 16; ++step) {
+        if (!kAll && (step >> 3) * 64 >= cols) break;
+        if (kAdd && step < 15) fetch(step + 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rd.stage(write[i], acc[(step >> 3) * 4 + i][step & 7]);
+        f32x4 x[4];
+        lds_read_rows(read, x);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (kAdd) x[j] = old[step & 1][j] + x[j];
+          if (ok(step, j)) *at(step, j) = x[j];
         }
-        if constexpr (!kAccumulate)
-          static_for<8>([&](auto i) {
-            if (ok(nb, i)) rd.template store<decltype(i)::value * 16>(dst + (int64_t)nb * 16 * H, acc[decltype(i)::value][nb]);
-          });
         __builtin_amdgcn_sched_barrier(0);
       }
     };
-    if (rows >= 128 && h0 + 128 <= H) sweep(std::true_type{});
-    else sweep(std::false_type{});
+    if (slab_id >= 0) {            // one range of this tile's tokens: raw sums to the slab, added up by dw_tail_reduce_kernel
+      sweep(std::true_type{}, std::false_type{}, partial + (int64_t)slab_id * (kBM * kBN) + (v0 & (kBM - 1)) * kBN + (h0 & (kBN - 1)), kBN, 128, 128);
+      return;
+    }
+    if (v0 >= V) return;
+    float* dst = dW + (int64_t)v0 * H + h0;
+    if (V - v0 >= 128 && h0 + 128 <= H) sweep(std::true_type{}, std::bool_constant<kAccumulate>{}, dst, H, 128, 128);
+    else sweep(std::false_type{}, std::bool_constant<kAccumulate>{}, dst, H, V - v0, H - h0);
   }
 };
 
