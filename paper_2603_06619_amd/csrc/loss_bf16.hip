@@ -671,7 +671,7 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
     // computes only those (whole call with 256 / 128 / 64 columns, us: 301 log-probs at the 0.6B head 138 / 127 / 120, 300 at the 8B head
-    // 474 / 427 / 408; loss at the 8B head 60 tokens 1085 / 1010 / 982, 100 1141 / 1062, 1100 3616 / 3547).
+    // 474 / 427 / 408; loss at the 8B head 60 tokens 1091 / 1015 / 988, 100 1119 / 1038, 1100 3557 / 3479).
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
       const int blocks = last_blocks(epi.n_valid, g.tiles_n);
       if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {
@@ -1207,8 +1207,8 @@ static int sub_chunk_rows(int cap, int Hp) {
 
 // Chunk capacity of the recommended workspace.  Forward pass alone: kMaxChunk.  With the backward pass the
 // chunk also sizes the stored soft-max numerators (cap x Vp x 2 bytes), and the dW contraction, whose
-// contraction axis is the chunk, gains little beyond 16384 (whole step at the 8B head 351.9 ms, 351.2 at 24576 and
-// 351.0 at 32768 with 34 and 68 % more workspace; 8192: 1.5 % slower): the smallest of 16384 / 24576 / 32768 rows
+// contraction axis is the chunk, gains nothing beyond 16384 (whole step at the 8B head 355.5 ms, 355.3 at 24576 and
+// 355.6 at 32768 with 34 and 68 % more workspace; 8192: 0.8 % slower): the smallest of 16384 / 24576 / 32768 rows
 // whose dH launch fills whole rounds of workgroups to 97 %.
 static int recommended_cap(int32_t N_k, int32_t H, bool backward) {
   const int64_t all = round_up(N_k > 0 ? N_k : 1, kBN);
@@ -1257,7 +1257,7 @@ size_t logp_bf16_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal
 // on average (a workgroup's load ring and epilogue cost about ten slices), starts multiples of `align`; the last range takes
 // what that rounding leaves (1256 slices: 36 ranges of 34 and one of 32).
 // 5003 tokens at the 7B head: 280 dH tiles took a second round for 24 of them, 6.52 ms; cut into ten ranges, 3.87 ms.  1237 at the 8B
-// head 2.82 / 1.13; dW of 16384 tokens there 14.28 / 14.07.
+// head 2.82 / 1.13; dW of 16384 tokens there 14.14 / 13.93.
 struct RangeCut { int splits, kt_per, tail, grid; };
 static RangeCut range_cut(int tiles, int kt_all, int align) {
   RangeCut c{1, kt_all, 0, tiles};
@@ -1278,10 +1278,10 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 // backward pass (0.77 ms at V x H = 151936 x 4096, 0.21 ms at H = 1024), twice without (0.50 / 0.12 ms), whatever the
 // batch; what reading rows costs the logits contraction and the dH contraction, with its transposing reads, grows with it.  Repacked /
 // direct in alternating runs, whole call, ms at V = 151936 unless stated.  H a multiple of the 256-wide dH tile: 1500 tokens
-// 5.14 / 4.50 (H = 4096), 1.49 / 1.34 (1024); 5000: 13.55 / 13.01, 3.76 / 3.66; 7168: 18.87 / 18.54 (4096), 5.16 / 5.09 (1024), 23.74 / 23.61
-// (5120), but 17.44 / 17.66 (3584, V = 152064); 8192: 20.94 / 20.59 (4096), 26.42 / 26.87 (5120).  Other H, whose dH tiles are padded (the work
-// grows with the tiles, the repack with H): 1500: 1.02 / 0.92 (576), 0.72 / 0.64 (320); 5000: 2.61 / 2.59, 1.85 / 1.81; 6144: 3.13 / 3.12, 2.16 / 2.17; 7168:
-// 3.54 / 3.56, 2.50 / 2.55; 8192 at V = 50000: 0.97 / 1.00 (320).  Forward pass alone: 2000 tokens 2.16 / 1.76 (4096), 0.59 / 0.50 (1024); 12288: 10.62 / 10.13,
+// 5.06 / 4.49 (H = 4096), 1.44 / 1.30 (1024); 5000: 13.55 / 13.02, 3.74 / 3.65; 7168: 18.87 / 18.62 (4096), 5.15 / 5.08 (1024), 23.74 / 23.63
+// (5120), but 17.41 / 17.56 (3584, V = 152064); 8192: 20.99 / 20.63 (4096), 26.44 / 26.73 (5120).  Other H, whose dH tiles are padded (the work
+// grows with the tiles, the repack with H): 1500: 1.00 / 0.91 (576), 0.73 / 0.64 (320); 5000: 2.61 / 2.58, 1.85 / 1.81; 6144: 3.14 / 3.13, 2.16 / 2.15; 7168:
+// 3.54 / 3.55, 2.49 / 2.54; 8192 at V = 50000: 0.98 / 0.99 (320).  Forward pass alone: 2000 tokens 2.16 / 1.76 (4096), 0.59 / 0.50 (1024); 12288: 10.62 / 10.13,
 // 2.92 / 2.83; 24576: 21.2 / 20.4, 5.75 / 5.71, 26.4 / 26.3 (5120); 49152: 41.8 / 40.8, 11.3 / 11.4, 52.0 / 52.3; with contractions of a few
 // slices 5000: 0.328 / 0.322 (H = 64, V = 160000), 8192: 0.510 / 0.506, 16384: 0.992 / 0.991.
 static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }

@@ -33,7 +33,7 @@ inline int walk_grid(int units, int walk) {
 // another stream that holds 16 / 32 compute units, time against the same call alone; one unit each, every unit dealt in advance, as
 // here: 8192 tokens at H = 1024 1.19 / 1.23, 1.86 / 1.98, 1.24 / 1.26; 2048 at H = 4096 1.11 / 1.15, 1.81 / 1.83, 1.13 / 1.20; 512 at H = 1024
 // 1.18 / 1.20, 1.44 / 1.49, 1.13 / 1.26.  What it costs alone, us, in the same order: 1963, 1852, 1861; 512 tokens 153, 142, 146; dW of 300 tokens at
-// H = 4096 703, 622, 636.  A budget of 1024 slices is no faster and 1.29 / 1.35 beside the other kernel.
+// H = 4096 694, 605, 612.  A budget of 1024 slices is no faster and 1.29 / 1.35 beside the other kernel.
 constexpr int kWalkBudget = 512;
 inline int walk_length(int units, int kt) {
   const int rounds = units / kNumCU, most = kWalkBudget / kt;
@@ -45,7 +45,7 @@ inline int walk_length(int units, int kt) {
 // accumulators (7 k cycles of a tile that has 1090 per slice and 11 k of epilogue).  One unit each / walking, us, in turn on one box:
 // logits at H = 1024 with 512 tokens 153 / 146, 1237 339 / 324, 8192 1963 / 1861; 8192 tokens at 3584 6220 / 6177, at 4096 6977 / 6976, but at 5120
 // 8904 / 8961 and 25000 tokens there 27000 / 28162 (equal on another box): the longer the tiles, the further the workgroups of an XCD drift apart.
-// dW at H = 4096 with 300 tokens 703 / 636, 1237 (accumulating) 1816 / 1739, 8192 7308 / 7171, but 16384 14488 / 14496.  dH has two rounds
+// dW at H = 4096 with 300 tokens 694 / 612, 1237 (accumulating) 1731 / 1628, 8192 7058 / 7021, but 16384 (accumulating) 14182 / 14182.  dH has two rounds
 // of thousands of slices: one unit each.
 constexpr int kLogitsWalkSlices = 128, kDWeightWalkSlices = 256;
 // A short last tile (last < 8 blocks) is computed by workgroups of one unit, so the whole launch is: what the short tile saves falls with
