@@ -872,10 +872,15 @@ struct DHiddenEpilogue {
 // 16 bytes a cycle (16 k cycles, 27 k when accumulating, beside 1090 per k-slice): a wavefront's results go through LDS, 16 vocabulary entries x 64 hidden
 // units at a time, and leave as 256 bytes of four rows per instruction.  From registers / so, us: 8 tiles of 8 slices 14.7 / 11.0; 200 tokens at H = 1024, V =
 // 160000 184 / 159; H = 4096, V = 151936: 300 632 / 608, 1237 accumulating 1773 / 1611, 16384 accumulating 14931 / 14966.
+// A dW beyond the Infinity Cache (kDWeightStreamBytes) is read and written past the caches: nothing of it is there when it is next wanted, and
+// what it would push out is W, and the numerators of this launch.  Cached / past, whole call at H = 4096, V = 151936, us: 300 tokens 1537 / 1466, 1237 3663 /
+// 3636, twice 1237 (the second accumulating) 7580 / 7502, twice 60 2452 / 2303, 32768 82170 / 82054.  One that fits: H = 1024, V = 30000, twice 200 tokens 231 / 241.
+constexpr int64_t kDWeightStreamBytes = int64_t(256) << 20;
 template <bool kAccumulate>
 struct DWeightEpilogue {
   static constexpr int kWords = kStageFloats;
   int V, H;
+  bool stream;                     // dW past the caches
   float* dW;                       // [V, H] fp32
   float* partial;                  // tiles whose contraction is cut into ranges: [slab][256][256] fp32 raw sums
 
@@ -890,8 +895,8 @@ struct DWeightEpilogue {
     }
     // to dst: this wavefront's [128 vocabulary entries][128 hidden units], a row `ld` elements, rows x cols of them valid (cols a multiple of 64).  One owner
     // per element and launch, launches in stream order: one fp32 addition old + sum per element.  Old values are loaded a step ahead.
-    auto sweep = [&](auto all_valid, auto add, float* dst, int ld, int rows, int cols) {
-      constexpr bool kAll = decltype(all_valid)::value, kAdd = decltype(add)::value;
+    auto sweep = [&](auto all_valid, auto add, auto past_caches, float* dst, int ld, int rows, int cols) {
+      constexpr bool kAll = decltype(all_valid)::value, kAdd = decltype(add)::value, kStream = decltype(past_caches)::value;
       auto ok = [&](int step, int j) { return kAll || ((step & 7) * 16 + stage_read_row(lane, j) < rows && (step >> 3) * 64 < cols); };
       const uint32_t lane_bytes = 4u * (uint32_t)(stage_read_row(lane, 0) * ld + stage_read_column(lane));     // the rest of an address is the wavefront's
       auto at = [&](int step, int j) {
@@ -901,7 +906,7 @@ struct DWeightEpilogue {
       auto fetch = [&](int step) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          if (ok(step, j)) old[step & 1][j] = *at(step, j);
+          if (ok(step, j)) old[step & 1][j] = kStream ? __builtin_nontemporal_load(at(step, j)) : *at(step, j);
           else old[step & 1][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       };
       if (kAdd) fetch(0);
@@ -916,19 +921,23 @@ struct DWeightEpilogue {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (kAdd) x[j] = old[step & 1][j] + x[j];
-          if (ok(step, j)) *at(step, j) = x[j];
+          if (!ok(step, j)) continue;
+          if (kStream) __builtin_nontemporal_store(x[j], at(step, j));
+          else *at(step, j) = x[j];
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     };
     if (slab_id >= 0) {            // one range of this tile's tokens: raw sums to the slab, added up by dw_tail_reduce_kernel
-      sweep(std::true_type{}, std::false_type{}, partial + (int64_t)slab_id * (kBM * kBN) + (v0 & (kBM - 1)) * kBN + (h0 & (kBN - 1)), kBN, 128, 128);
+      sweep(std::true_type{}, std::false_type{}, std::false_type{}, partial + (int64_t)slab_id * (kBM * kBN) + (v0 & (kBM - 1)) * kBN + (h0 & (kBN - 1)), kBN, 128, 128);
       return;
     }
     if (v0 >= V) return;
     float* dst = dW + (int64_t)v0 * H + h0;
-    if (V - v0 >= 128 && h0 + 128 <= H) sweep(std::true_type{}, std::bool_constant<kAccumulate>{}, dst, H, 128, 128);
-    else sweep(std::false_type{}, std::bool_constant<kAccumulate>{}, dst, H, V - v0, H - h0);
+    constexpr std::bool_constant<kAccumulate> add{};
+    if (V - v0 < 128 || h0 + 128 > H) sweep(std::false_type{}, add, std::false_type{}, dst, H, V - v0, H - h0);
+    else if (stream) sweep(std::true_type{}, add, std::true_type{}, dst, H, 128, 128);
+    else sweep(std::true_type{}, add, std::false_type{}, dst, H, 128, 128);
   }
 };
 
@@ -1422,10 +1431,11 @@ nat_status loss_bf16_run(const LossArgs& a) {
       {
         ProfScope prof(PC_DWEIGHT, s);
         const int grid = walk_grid(cut.grid, g.walk);
+        const bool stream = (int64_t)V * H * 4 > kDWeightStreamBytes;
         if (accumulate)
-          mfma_nt_kernel<DWeightEpilogue<true>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<true>{V, H, a.dW, dh_part});
+          mfma_nt_kernel<DWeightEpilogue<true>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<true>{V, H, stream, a.dW, dh_part});
         else
-          mfma_nt_kernel<DWeightEpilogue<false>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<false>{V, H, a.dW, dh_part});
+          mfma_nt_kernel<DWeightEpilogue<false>, Src::kKMajorBlocked, Src::kBlocked, true, true><<<grid, 256, 0, s>>>(g, DWeightEpilogue<false>{V, H, stream, a.dW, dh_part});
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
           dw_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, V, H, accumulate, a.dW);

@@ -326,6 +326,13 @@ def test_bf16_dw_where_walks_end(stage, n_tok):
     assert float((plain - dW).norm() / dW.norm()) <= 1e-5
 
 
+@pytest.mark.parametrize("V", [61680, 61681])
+def test_bf16_dw_at_the_line_where_it_passes_the_caches(stage, V):
+    # 1088 x 61680 x 4 bytes are the last below 256 MiB; whole tiles and, in both directions, cut ones
+    case, plain = accumulated_and_plain(stage, 40, 1088, V)
+    assert max_rel_err(plain.cpu().numpy(), oracle_loss(**case)["dW"]) <= TOL_BF16
+
+
 @pytest.mark.parametrize("H,V,n", [(64, 7, 6144), (320, 700, 6144), (192, 1025, 6144), (256, 700, 7168)])
 def test_bf16_w_repacked_and_read_as_it_is_agree(stage, H, V, n):
     # up to n tokens the contractions read W in place, beyond that a repacked copy: the same products in the same
