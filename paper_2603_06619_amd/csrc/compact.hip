@@ -4,8 +4,8 @@
 // closed form, or read from a per-token array), plus an optional gather of the
 // kept rows.
 //
-// Passes over the bit mask: per-tile population counts, (for large batches) an exclusive scan
-// of the tile counts, and a scatter in which each wavefront ranks its 64 tokens with a
+// Passes over the bit mask: (for large batches) population counts of tiles and of groups of tiles,
+// and a scatter in which each wavefront ranks its 64 tokens with a
 // bit-prefix so that consecutive lanes write consecutive outputs.  The scatter also gathers the
 // per-token words (ids, behaviour log-probs) and writes the per-rollout offsets; the gather of
 // hidden rows is a kernel of its own.
@@ -17,12 +17,13 @@ namespace nat {
 
 constexpr int kTileTokens = 4096;                 // tokens per scatter block
 constexpr int kTileWords = kTileTokens / 32;      // 128 mask words
-// Up to this many tiles (4.2 million tokens) a scatter block adds up the counts of the tiles before
-// its own instead of a scan launch between the two passes; up to kInlineCountTiles (half a million
-// tokens, 64 KiB of mask) it counts the mask words themselves and there is no count launch either.
-// Up to kInlineScanTiles the block also has sixteen wavefronts of 256 tokens, not four of 1024: with fewer
-// blocks than the chip holds, the chain of loads of one wavefront is the kernel's time.
-constexpr int kInlineScanTiles = 1024, kInlineCountTiles = 128;
+constexpr int kGroupTiles = 16;                   // tiles whose counts are also added up, one block of the count pass
+// Up to kInlineTiles (two million tokens, 256 KiB of mask) a scatter block counts the mask words before its own tile and
+// there is no count launch; beyond, it adds up the counts of the groups before its own and of the tiles before it in its group.
+// Up to there the block also has sixteen wavefronts of 256 tokens, not four of 1024: with few
+// blocks the chain of loads of one wavefront is the kernel's time.  Whole selection with the line at 256 / 512 / 1024 tiles, us: 320 tiles 24.7 /
+// 19.0 / 19.1; 450 tiles of 550-token rollouts 32.5 / 29.3 / 29.3; 980 tiles 35.4 / 35.6 / 43.9, Poisson 45.9 / 45.9 / 52.3.
+constexpr int kInlineTiles = 512;
 
 __device__ __forceinline__ int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -38,46 +39,24 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return v;
 }
 
-// tile_count[b] = number of kept tokens among packed positions [b*4096, (b+1)*4096); one wavefront per tile
-__global__ void __launch_bounds__(256)
+// tile_count[b] = number of kept tokens among packed positions [b*4096, (b+1)*4096), one wavefront per tile; group_count[g] = the sum of
+// 16 of them, one block per group.  (A scan of the tile counts by one block, a launch of its own that every tile waited for, took 17 us
+// at 2^26 tokens.)
+__global__ void __launch_bounds__(kGroupTiles * 64)
 compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, int n_tiles,
-                     int32_t* __restrict__ tile_count) {
-  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (tile >= n_tiles) return;
+                     int32_t* __restrict__ tile_count, int32_t* __restrict__ group_count) {
+  __shared__ int count[kGroupTiles];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tile = blockIdx.x * kGroupTiles + wave;
   const int64_t w = (int64_t)tile * kTileWords + 2 * lane;      // n_words is even
   const int c = wave_sum(w < n_words ? __popc(mask_bits[w]) + __popc(mask_bits[w + 1]) : 0);
-  if (lane == 0) tile_count[tile] = c;
-}
-
-// tile_offset[0..n_tiles) = exclusive scan of tile_count.  One block, kScanPer consecutive tiles per thread.
-constexpr int kScanPer = 8;
-__global__ void __launch_bounds__(1024)
-compact_scan_kernel(const int32_t* __restrict__ tile_count, int n_tiles, int32_t* __restrict__ tile_offset) {
-  __shared__ int wave_tot[16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int carry = 0;
-  for (int base = 0; base < n_tiles; base += 1024 * kScanPer) {
-    const int j0 = base + (int)threadIdx.x * kScanPer;
-    int v[kScanPer], mine = 0;
-#pragma unroll
-    for (int e = 0; e < kScanPer; ++e) {
-      v[e] = j0 + e < n_tiles ? tile_count[j0 + e] : 0;
-      mine += v[e];
-    }
-    const int incl = wave_inclusive_scan(mine);
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    int run = carry + incl - mine;
-    for (int w = 0; w < 16; ++w) {
-      if (w < wave) run += wave_tot[w];
-      carry += wave_tot[w];
-    }
-#pragma unroll
-    for (int e = 0; e < kScanPer; ++e) {
-      if (j0 + e < n_tiles) tile_offset[j0 + e] = run;
-      run += v[e];
-    }
-    __syncthreads();
+  if (lane == 0) {
+    count[wave] = c;
+    if (tile < n_tiles) tile_count[tile] = c;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int sum = wave_sum(lane < kGroupTiles ? count[lane] : 0);
+    if (lane == 0) group_count[blockIdx.x] = sum;
   }
 }
 
@@ -102,63 +81,104 @@ struct ScatterArgs {
   double n_rollouts; const double* pi;
   const uint32_t* mask_bits; int64_t n_words; int64_t n_tokens; int64_t kept_cap;
   const int64_t* cu; int B;
-  const int32_t* tile_count; const int32_t* tile_offset;        // offsets; or NULL: the block adds up the counts; or both NULL:
-                                                                // it counts the mask words
+  const int32_t* tile_count; const int32_t* group_count;        // of the count pass; or NULL: the block counts the mask words
+  int mask_wide;                                                // mask_bits is 16-byte aligned
   int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept;
   const int32_t* ids; int32_t* ids_k; const float* old_logp; float* old_logp_k;
 };
 
-// One block per tile of 4096 positions, kWaves wavefronts, 64 positions at a time, four such groups in flight:
-// the loads of a batch (ids, log-probs, probabilities) are issued before its first weight is computed.
-// Bound by the bytes it moves and, for weights that differ from token to token, by their fp64 divisions; by latency
-// at the size of a real batch.  The per-token words ride along here because the token is already in hand: a
-// row-gather block per kept token for them took 8.66 ms of a 2^26-token batch (compaction as a whole 9.06 ->
-// 0.39 ms), 190 us of a 1.3-million-token one (whole selection 225 -> 25 us; scatter 17 us with four wavefronts per
-// block, 14.5 with sixteen).
-template <int kWaves>
+// One block per tile of 4096 positions, kWaves wavefronts, 64 positions at a time.
+// Bound by the bytes it moves; by the chain of dependent loads at the size of a real batch.  A wavefront reads its own mask words and has all its
+// per-token loads (probabilities, ids, log-probs) out before the tokens in front of the tile are counted and its rollouts are looked up: loads
+// in flight are worth more than wavefronts (sixteen groups at once take 99 registers; 2^26 Poisson tokens, four groups at a time 362 us,
+// eight 350, sixteen 337: 1.65 GB at 4.9 TB/s; 387 with the loads behind the search and a scan launch).  Tiles go from the last to the first: what
+// the selection read and wrote last is still in the Infinity Cache (from the first: 20 us more).  1.3 million tokens in 128 rollouts: 20 -> 15 us.
+// The per-token words ride along here because the token is already in hand: a row-gather block per kept token for them took
+// 8.66 ms of a 2^26-token batch, 190 us of a 1.3-million-token one.
+template <int kWaves, bool kPi>
 __global__ void __launch_bounds__(kWaves * 64)
 compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
-  constexpr int kBatch = 4, kThreads = kWaves * 64, kGroups = 64 / kWaves;      // groups of 64 positions per wavefront
+  constexpr int kThreads = kWaves * 64, kGroups = 64 / kWaves, kSpanWords = kGroups * 2;      // groups of 64 positions per wavefront
   __shared__ uint32_t words[kTileWords];
-  __shared__ int prefix[kTileWords + 1];                        // kept tokens of the tile before word w
-  __shared__ int wave_tot[2], wave_before[kWaves];
+  __shared__ int prefix[kTileWords];                            // kept tokens of the wavefront's span before word w
+  __shared__ int wave_tot[kWaves], wave_before[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tile = blockIdx.x, n_tiles = gridDim.x;
+  const int n_tiles = gridDim.x, tile = n_tiles - 1 - (int)blockIdx.x;
   const int64_t tile_first = (int64_t)tile * kTileTokens;
+  const int64_t span_first = tile_first + wave * (kGroups * 64), span_end = span_first + kGroups * 64;
 
-  uint32_t word = 0;
-  if (tid < kTileWords) {
-    const int64_t wi = (int64_t)tile * kTileWords + tid;
-    word = wi < c.n_words ? c.mask_bits[wi] : 0u;
-    words[tid] = word;
+  const int64_t wi = (int64_t)tile * kTileWords + wave * kSpanWords + lane;
+  const uint32_t word = lane < kSpanWords && wi < c.n_words ? c.mask_bits[wi] : 0u;
+
+  uint64_t group[kGroups];
+  int id[kGroups];
+  float lp[kGroups];
+  double p[kGroups];
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    group[g] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * g) |
+               ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)word, 2 * g + 1) << 32);
+    const int64_t n = span_first + g * 64 + lane;
+    // a set bit at a position the per-token arrays do not have (a foreign mask) is ranked but reads and writes nothing
+    const bool here = ((group[g] >> lane) & 1ull) && n < c.n_tokens;
+    if (kPi) p[g] = here ? c.pi[n] : 1.0;                       // what the weight waits for first
+    id[g] = here && c.ids ? c.ids[n] : 0;
+    lp[g] = here && c.old_logp ? c.old_logp[n] : 0.f;
   }
+
   int before = 0;
-  if (!c.tile_offset) {
-    if (c.tile_count) for (int j = tid; j < tile; j += kThreads) before += c.tile_count[j];
-    else for (int j = tid; j < tile * kTileWords; j += kThreads) before += __popc(c.mask_bits[j]);
+  if (c.group_count) {
+    const int group = tile / kGroupTiles, first = group * kGroupTiles;
+    for (int j = tid; j < group; j += kThreads) before += c.group_count[j];
+    if (tid < tile - first) before += c.tile_count[first + tid];
+  } else if (c.mask_wide) {
+    const uint4* q = reinterpret_cast<const uint4*>(c.mask_bits);
+#pragma unroll 4
+    for (int j = tid; j < tile * (kTileWords / 4); j += kThreads) {
+      const uint4 x = q[j];
+      before += __popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w);
+    }
+  } else {
+#pragma unroll 4
+    for (int j = tid; j < tile * kTileWords; j += kThreads) before += __popc(c.mask_bits[j]);
   }
   // how many rollouts start before the tile, before its end; at or before this wavefront's first position, its last one
-  const int64_t N = c.cu[c.B], span_first = tile_first + wave * (kGroups * 64), span_end = span_first + kGroups * 64;
+  const int64_t N = c.cu[c.B];
   const int64_t span_last = span_end - 1 < N ? span_end - 1 : N - 1;
   const int64_t key[4] = {tile_first, tile_first + kTileTokens, span_first + 1, span_last + 1};
   int at[4];
   wave_lower_bounds<4>(c.cu, c.B + 1, key, at);
-  const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
-  if (tid < kTileWords && lane == 63) wave_tot[wave] = incl;
-  before = wave_sum(before);
-  if (lane == 0) wave_before[wave] = before;
-  __syncthreads();
-  if (tid < kTileWords) {
-    const int excl = incl - cnt + (wave == 1 ? wave_tot[0] : 0);
-    prefix[tid] = excl;
-    if (tid == kTileWords - 1) prefix[kTileWords] = excl + cnt;
+  int i_lo = 0, i_hi = c.B;                                     // positions at or beyond N: any rollout (foreign mask)
+  if (span_first < N) {                                         // the last rollout that starts at or before the first position
+    i_lo = at[2] > 0 ? at[2] - 1 : 0;
+    i_lo = i_lo < c.B ? i_lo : c.B - 1;                         // offsets that do not ascend must not lead past the array
+    i_hi = at[3] < c.B ? at[3] : c.B;
+    i_hi = i_hi <= i_lo ? i_lo + 1 : i_hi;
   }
-  int tile_base = 0;
-  if (c.tile_offset) tile_base = c.tile_offset[tile];
-  else
-    for (int w = 0; w < kWaves; ++w) tile_base += wave_before[w];
+  const bool one_rollout = i_hi - i_lo == 1;
+  const int64_t one_start = c.cu[i_lo], one_T = c.cu[i_lo + 1] - one_start;
+  const int one_scheme = !kPi && a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
+
+  const int cnt = __popc(word), incl = wave_inclusive_scan(cnt);
+  const int span_kept = __builtin_amdgcn_readlane(incl, 63);
+  if (lane < kSpanWords) {
+    words[wave * kSpanWords + lane] = word;
+    prefix[wave * kSpanWords + lane] = incl - cnt;
+  }
+  before = wave_sum(before);
+  if (lane == 0) {
+    wave_tot[wave] = span_kept;
+    wave_before[wave] = before;
+  }
   __syncthreads();
-  if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + prefix[kTileWords];
+  int tile_base = 0, span_base = 0, tile_kept = 0;              // kept tokens before the tile, in it before the span, in it
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    tile_base += wave_before[w];
+    tile_kept += wave_tot[w];
+    if (w < wave) span_base += wave_tot[w];
+  }
+  if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + tile_kept;
   // Offsets of the rollouts that start in this tile (offsets outside [0, n_tokens] count as its ends), by the whole block
   // and four loads at a time: empty rollouts can put any number of them at one position.  Compaction of 100 rollouts of 1000
   // tokens and 4000 / 65000 / a million empty ones: 17.8 / 210 / 5300 us by the wavefront of their span, 8.7 / 22 / 311 by the block.
@@ -173,62 +193,40 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
       const int64_t pos = start[e] < 0 ? 0 : start[e] > c.n_tokens ? c.n_tokens : start[e];
       const int64_t off = pos - tile_first;
       const int rel = off < 0 ? 0 : off > kTileTokens ? kTileTokens : (int)off, w = rel >> 5, rem = rel & 31;
-      c.cu_kept[i0 + e * kThreads] = tile_base + prefix[w] + (rem ? __popc(words[w] & ((1u << rem) - 1u)) : 0);
-    }
-  }
-
-  constexpr int kSpanWords = kGroups * 2;
-  if (prefix[wave * kSpanWords] == prefix[(wave + 1) * kSpanWords]) return;      // nothing kept
-  int i_lo = 0, i_hi = c.B;                                     // positions at or beyond N: any rollout (foreign mask)
-  if (span_first < N) {                                         // the last rollout that starts at or before the first position
-    i_lo = at[2] > 0 ? at[2] - 1 : 0;
-    i_lo = i_lo < c.B ? i_lo : c.B - 1;                         // offsets that do not ascend must not lead past the array
-    i_hi = at[3] < c.B ? at[3] : c.B;
-    i_hi = i_hi <= i_lo ? i_lo + 1 : i_hi;
-  }
-  const bool one_rollout = i_hi - i_lo == 1;
-  const int64_t one_start = c.cu[i_lo], one_T = c.cu[i_lo + 1] - one_start;
-  const int one_scheme = a.scheme_per_rollout ? a.scheme_per_rollout[i_lo] : a.scheme;
-
-  for (int g0 = 0; g0 < kGroups; g0 += kBatch) {
-    bool keep[kBatch];
-    int out[kBatch], id[kBatch], seq[kBatch];
-    float lp[kBatch];
-    double p[kBatch];
-    int64_t n[kBatch];
-#pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
-      const int w = wave * kSpanWords + 2 * (g0 + b);
-      const uint64_t group = (uint64_t)words[w] | ((uint64_t)words[w + 1] << 32);
-      n[b] = span_first + (g0 + b) * 64 + lane;
-      out[b] = tile_base + prefix[w] + __popcll(group & ((1ull << lane) - 1ull));
-      // entries beyond the outputs' capacity are counted but not written; a set bit at a position the
-      // per-token arrays do not have (a foreign mask) is ranked but reads and writes nothing
-      keep[b] = ((group >> lane) & 1ull) && out[b] < c.kept_cap && n[b] < c.n_tokens;
-      id[b] = keep[b] && c.ids ? c.ids[n[b]] : 0;
-      lp[b] = keep[b] && c.old_logp ? c.old_logp[n[b]] : 0.f;
-      p[b] = keep[b] && c.pi ? c.pi[n[b]] : 1.0;
-      seq[b] = i_lo;
-    }
-#pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
-      if (!keep[b]) continue;
-      int64_t start = one_start, T = one_T;
-      int scheme = one_scheme;
-      if (!one_rollout) {
-        seq[b] = rollout_of_pos(c.cu, i_lo, i_hi, n[b]);
-        start = c.cu[seq[b]];
-        T = c.cu[seq[b] + 1] - start;
-        if (a.scheme_per_rollout) scheme = a.scheme_per_rollout[seq[b]];
+      int kept = tile_kept;
+      if (w < kTileWords) {
+        kept = prefix[w] + __popc(words[w] & ((1u << rem) - 1u));
+        for (int v = 0; v < w / kSpanWords; ++v) kept += wave_tot[v];
       }
-      const int o = out[b];
-      c.kept_idx[o] = (int32_t)n[b];
-      c.kept_seq[o] = seq[b];
-      c.kept_w[o] = c.pi ? (float)(1.0 / ((c.n_rollouts * (double)T) * p[b]))
-                         : ht_weight(scheme, T, n[b] - start + 1, c.n_rollouts, a.p, a.min_cut);
-      if (c.ids) c.ids_k[o] = id[b];
-      if (c.old_logp) c.old_logp_k[o] = lp[b];
+      c.cu_kept[i0 + e * kThreads] = tile_base + kept;
     }
+  }
+  if (span_kept == 0) return;
+
+  int at_lane = lane;                                           // else all that was formed from it for the loads is kept: 131 and more registers
+  asm volatile("" : "+v"(at_lane));
+  int out0 = tile_base + span_base;                             // first output of the current group
+#pragma unroll
+  for (int g = 0; g < kGroups; ++g) {
+    const int64_t n = span_first + g * 64 + at_lane;
+    const int o = out0 + __popcll(group[g] & ((1ull << at_lane) - 1ull));
+    out0 += __popcll(group[g]);
+    // entries beyond the outputs' capacity are counted but not written
+    if (!((group[g] >> at_lane) & 1ull) || o >= c.kept_cap || n >= c.n_tokens) continue;
+    int64_t start = one_start, T = one_T;
+    int scheme = one_scheme, seq = i_lo;
+    if (!one_rollout) {
+      seq = rollout_of_pos(c.cu, i_lo, i_hi, n);
+      start = c.cu[seq];
+      T = c.cu[seq + 1] - start;
+      if (!kPi && a.scheme_per_rollout) scheme = a.scheme_per_rollout[seq];
+    }
+    c.kept_idx[o] = (int32_t)n;
+    c.kept_seq[o] = seq;
+    c.kept_w[o] = kPi ? (float)(1.0 / ((c.n_rollouts * (double)T) * p[g]))
+                      : ht_weight(scheme, T, n - start + 1, c.n_rollouts, a.p, a.min_cut);
+    if (c.ids) c.ids_k[o] = id[g];
+    if (c.old_logp) c.old_logp_k[o] = lp[g];
   }
 }
 
@@ -255,7 +253,7 @@ gather_rows_kernel(const int32_t* __restrict__ kept_idx, const int32_t* __restri
 
 constexpr int64_t n_tiles_of(int64_t N) { return (N + kTileTokens - 1) / kTileTokens; }
 
-// tile_count[n_tiles] + tile_offset[n_tiles + 1], int32, rounded up to 256 bytes
+// tile_count[n_tiles] + group_count (at most n_tiles + 1), int32, rounded up to 256 bytes
 constexpr size_t compact_ws_bytes(int64_t N) {
   return (((size_t)(2 * n_tiles_of(N) + 1) * sizeof(int32_t) + 255) / 256) * 256 + 256;
 }
@@ -319,24 +317,22 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
   const int64_t n_tiles = n_tiles_of(c.N);
   const int64_t n_words = nat_mask_words(c.N);
   int32_t* tile_count = (int32_t*)c.ws;
-  int32_t* tile_offset = tile_count + n_tiles;
+  int32_t* group_count = tile_count + n_tiles;
   {
     ProfScope prof(PC_COMPACT, s, !c.no_timing);
     if (n_tiles > 0) {
-      const bool count = n_tiles > kInlineCountTiles, scan = n_tiles > kInlineScanTiles;
+      const bool count = n_tiles > kInlineTiles;
       if (count) {
-        compact_count_kernel<<<(unsigned)((n_tiles + 3) / 4), 256, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count);
-        NAT_LAUNCH_CHECK();
-      }
-      if (scan) {
-        compact_scan_kernel<<<1, 1024, 0, s>>>(tile_count, (int)n_tiles, tile_offset);
+        compact_count_kernel<<<(unsigned)((n_tiles + kGroupTiles - 1) / kGroupTiles), 1024, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count, group_count);
         NAT_LAUNCH_CHECK();
       }
       const ScatterArgs sc{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B,
-                           count ? tile_count : nullptr, scan ? tile_offset : nullptr, c.kept_idx, c.kept_seq, c.kept_w,
-                           c.cu_kept, c.n_kept, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
-      if (scan) compact_scatter_kernel<4><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
-      else compact_scatter_kernel<16><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
+                           count ? tile_count : nullptr, count ? group_count : nullptr, ((uintptr_t)c.mask_bits & 15) == 0,
+                           c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
+      if (count && c.pi) compact_scatter_kernel<4, true><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
+      else if (count) compact_scatter_kernel<4, false><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
+      else if (c.pi) compact_scatter_kernel<16, true><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
+      else compact_scatter_kernel<16, false><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
       NAT_LAUNCH_CHECK();
     } else {
       compact_empty_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.B, c.cu_kept, c.n_kept);
@@ -407,8 +403,8 @@ extern "C" nat_status nat_compact_static(const nat_select_params* params, int32_
   void* ws = nullptr;
   st = static_scratch(&ws);
   if (st != NAT_OK) return st;
-  // every word of the scratch that the kernels read is written earlier in the same call (the tile
-  // counts by the count pass, the offsets by the scan), so nothing has to be cleared between calls
+  // every word of the scratch that the kernels read is written earlier in the same call (the counts of tiles and
+  // groups by the count pass), so nothing has to be cleared between calls
   return compact_run(a, CompactArgs{n_rollouts_global, d_mask_bits, nullptr, d_cu_seqlens, B, N, kept_cap, d_kept_idx,
                                     d_kept_seq, d_kept_w, d_cu_kept, d_n_kept, h_n_kept, d_hidden, d_hidden_k, H,
                                     dtype, d_ids, d_ids_k, d_old_logp, d_old_logp_k, ws, kStaticScratchBytes,

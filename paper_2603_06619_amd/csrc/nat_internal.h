@@ -46,10 +46,23 @@ __device__ __forceinline__ int rollout_of_pos(const OffsetT* __restrict__ cu, in
 }
 
 // out[q] = number of entries of the non-decreasing cu[0 .. n_cu) that are < n[q], wavefront-uniform.  The whole
-// wavefront searches, 64 probes per round and K values at once: 4096 rollouts take two dependent loads, not twelve.
+// wavefront searches, 64 probes per round and K values at once: 4096 rollouts take two dependent loads, not twelve, and up to
+// 256 one.
 template <int K>
 __device__ __forceinline__ void wave_lower_bounds(const int64_t* __restrict__ cu, int n_cu, const int64_t (&n)[K], int (&out)[K]) {
   const int lane = threadIdx.x & 63;
+  if (n_cu <= 256) {
+    int64_t v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = 64 * e + lane < n_cu ? cu[64 * e + lane] : INT64_MAX;
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      out[q] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[q] += __popcll(__ballot(v[e] < n[q]));
+    }
+    return;
+  }
   int lo[K], hi[K];
 #pragma unroll
   for (int q = 0; q < K; ++q) { lo[q] = 0; hi[q] = n_cu; }

@@ -128,8 +128,8 @@ def test_zero_advantage_rollouts_are_dropped(stage, scheme, kw):
 
 @pytest.mark.parametrize("n_tiles,extra", [(1, -1), (1, 0), (1, 1), (2, 1023), (128, 0), (128, 1), (1024, 0), (1024, 1)])
 def test_compaction_at_tile_and_scan_boundaries(stage, n_tiles, extra):
-    # tiles of 4096 positions; up to 128 of them a scatter block counts the earlier mask words itself, up to 1024 it adds up
-    # their counts, beyond that a scan runs first.  Rollouts: runs of empty and one-token ones at edges of tiles and spans
+    # tiles of 4096 positions; up to 512 of them a scatter block counts the earlier mask words itself, beyond that it adds up
+    # the counts of tiles and groups of tiles.  Rollouts: runs of empty and one-token ones at edges of tiles and spans
     N = 4096 * n_tiles + extra
     rng = np.random.default_rng(N)
     edges = np.concatenate([[0, 0, 1, 1023, 1024, 1025, 4095, 4095, 4096, 4096, 4097], rng.integers(0, N, 70)])
@@ -147,7 +147,7 @@ def test_compaction_at_tile_and_scan_boundaries(stage, n_tiles, extra):
 
 @pytest.mark.parametrize("N", [1, 4096, 9000, 4096 * 129 + 5, 4096 * 1025 + 3])
 def test_compaction_offsets_of_long_runs_of_empty_rollouts(stage, N):
-    # a tile's block writes the offsets of all rollouts that start in it, 1024 (256 above 1024 tiles) x 4 at a time: runs of
+    # a tile's block writes the offsets of all rollouts that start in it, 1024 (256 above 512 tiles) x 4 at a time: runs of
     # empty rollouts around multiples of that, at the start, at a tile's edge, inside and at N
     rng = np.random.default_rng(N)
     inside = rng.integers(0, N + 1, 40)
@@ -155,3 +155,33 @@ def test_compaction_offsets_of_long_runs_of_empty_rollouts(stage, N):
     cu = np.sort(np.concatenate([[0, N], inside] + [np.full(n, pos) for pos, n in runs])).astype(np.int64)
     o = oracle_select_compact(cu, osel.DET, beta=0.5)
     assert_select_compact_equal(hip_select_compact(stage, cu, osel.DET, beta=0.5), o, N)
+
+
+@pytest.mark.parametrize("n_tiles,extra,B", [(512, 0, 254), (512, 1, 255), (528, 0, 256), (529, -4095, 300), (90, 77, 255)])
+def test_compaction_where_counting_changes(stage, n_tiles, extra, B):
+    # up to and beyond the tiles whose blocks count the mask words themselves, whole and begun groups of 16 tiles, and as many rollouts
+    # as one round of the search takes; a mask that is not 16-byte aligned gives the same
+    import paper_2603_06619_amd as nat
+    N = 4096 * n_tiles + extra
+    rng = np.random.default_rng(N)
+    cu = np.concatenate([[0], np.sort(rng.integers(0, N + 1, B - 1)), [N]]).astype(np.int64)
+    o = oracle_select_compact(cu, osel.URS, p=0.4, seed=5, step=1)
+    h = hip_select_compact(stage, cu, osel.URS, p=0.4, seed=5, step=1)
+    assert_select_compact_equal(h, o, N)
+    shifted = torch.zeros(h["mask_bits"].numel() + 1, dtype=torch.int32, device=DEV)[1:]
+    shifted.copy_(h["mask_bits"])
+    assert shifted.data_ptr() % 16 == 4
+    again = {k: torch.full_like(h[k], -1) for k in ("kept_idx", "kept_seq", "kept_w", "cu_kept", "n_kept_dev")}
+    nat.nat_compact(nat.SelectParams(nat.URS, p=0.4, seed=5, step=1), B, shifted, to_dev(cu), B, N, *again.values(), None,
+                    torch.empty(nat.compact_workspace_bytes(N), dtype=torch.uint8, device=DEV))
+    nk = o["n_kept"]
+    for k, v in again.items():
+        assert torch.equal(v[:nk], h[k][:nk]), k
+        if k.startswith("kept"):
+            assert bool((v[nk:] == -1).all()), k
+    # the same tokens weighted by given probabilities
+    pi = torch.full((N,), 0.4, dtype=torch.float64, device=DEV)
+    nat.nat_compact_pi(B, h["mask_bits"], pi, to_dev(cu), B, N, *again.values(), None,
+                       torch.empty(nat.compact_workspace_bytes(N), dtype=torch.uint8, device=DEV))
+    for k, v in again.items():
+        assert torch.equal(v[:nk], h[k][:nk]) or (k == "kept_w" and float((v[:nk] / h[k][:nk] - 1).abs().max()) <= 2.0 ** -23), k
