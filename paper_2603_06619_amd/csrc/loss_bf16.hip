@@ -766,50 +766,63 @@ struct LogitsEpilogue {
     }
 
     // One pass over the accumulators, 16 token columns (all 128 vocabulary rows of the wavefront) at a
-    // time: E = exp(min(z - shift, 70)) as 2^(min(z * log2(e) - shift * log2(e), 70 * log2(e))) (one fma,
-    // one min and the hardware exponential per logit, eight at a time with independent temporaries),
-    // its running sums, and at once the store.  E is stored once, rows = token, k = vocabulary (the
+    // time: E = exp(min(z - shift, 70)) as 2^(z * log2(e) - shift * log2(e)) (one fma and the hardware exponential per
+    // logit, eight at a time with independent temporaries), its running sums, and at once the store.  The bound of 70 acts
+    // on hardly any tile: where the sums show that it would (an exponential at or above e^70, an infinity or NaN among them
+    // makes them that large), the wavefront makes the pass again with it.  (One minimum less per logit: logits of 16384 tokens at H = 1024 4040
+    // -> 3966 us, log-probs of 8192 there 1886 -> 1845, of 4000 at H = 256 389 -> 369.)  E is stored once, rows = token, k = vocabulary (the
     // dH contraction reads it as it is, the dW contraction through the transposing LDS read): the rows of W are read
     // interleaved, so a lane holds 8 consecutive vocabulary entries of its token, one 16-byte chunk of the blocked layout,
     // and an instruction stores 1 KiB (16 token rows of one 32-wide vocabulary slice) contiguous.
+    float total = 0.f;
+    auto sweep = [&](auto clamped) {
+      constexpr bool kClamp = decltype(clamped)::value;
 #pragma unroll
-    for (int nb = 0; nb < NQ; ++nb) {
-      const float nshift2 = -shift_of[nb] * kLog2e;
-      uint16_t* e_row = kStoreE ? Eb + blk_off(k0 + nb * 16 + l15, v0 + 8 * g, kb_z) : nullptr;
-      float s2[2] = {0.f, 0.f}, t2[2] = {0.f, 0.f};        // two independent chains per sum
+      for (int nb = 0; nb < NQ; ++nb) {
+        const float nshift2 = -shift_of[nb] * kLog2e;
+        uint16_t* e_row = kStoreE ? Eb + blk_off(k0 + nb * 16 + l15, v0 + 8 * g, kb_z) : nullptr;
+        float s2[2] = {0.f, 0.f}, t2[2] = {0.f, 0.f};      // two independent chains per sum
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float x2[8], e[8];
+        for (int j = 0; j < 4; ++j) {
+          float x2[8], e[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) x2[r] = fminf(fmaf(rd(acc[2 * j + (r >> 2)][nb], r & 3), kLog2e, nshift2), 70.f * kLog2e);
+          for (int r = 0; r < 8; ++r) {
+            x2[r] = fmaf(rd(acc[2 * j + (r >> 2)][nb], r & 3), kLog2e, nshift2);
+            if (kClamp) x2[r] = fminf(x2[r], 70.f * kLog2e);
+          }
 #pragma unroll
-        for (int r = 0; r < 8; ++r) e[r] = __builtin_amdgcn_exp2f(x2[r]);
-        if (!all_rows_valid) {                             // only the last vocabulary tile pays for the row check
+          for (int r = 0; r < 8; ++r) e[r] = __builtin_amdgcn_exp2f(x2[r]);
+          if (!all_rows_valid) {                           // only the last vocabulary tile pays for the row check
 #pragma unroll
-          for (int r = 0; r < 8; ++r)
-            if (v0 + j * 32 + 8 * g + r >= V) e[r] = 0.f;
+            for (int r = 0; r < 8; ++r)
+              if (v0 + j * 32 + 8 * g + r >= V) e[r] = 0.f;
+          }
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            s2[r & 1] += e[r];
+            if (kEntropy) t2[r & 1] = fmaf(e[r], x2[r], t2[r & 1]);
+          }
+          if (kStoreE) {
+            u32x4v w;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[r] = pack_bf16x2(e[2 * r], e[2 * r + 1]);
+            NAT_E_STORE((u32x4v*)(e_row + j * kBlkElems), w);
+          }
         }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          s2[r & 1] += e[r];
-          if (kEntropy) t2[r & 1] = fmaf(e[r], x2[r], t2[r & 1]);
+        const int kk = k0 + nb * 16 + l15;                 // token column (always inside the padded chunk)
+        if (!kClamp) total += s2[0] + s2[1];
+        const float sum = sum_quarters(s2[0] + s2[1]);
+        if (g == 0) s_part[(int64_t)granule * ld_part + kk] = sum;
+        if (kEntropy) {
+          const float t = sum_quarters((t2[0] + t2[1]) * kLn2);  // back to natural-log units
+          if (g == 0) t_part[(int64_t)granule * ld_part + kk] = t;
         }
-        if (kStoreE) {
-          u32x4v w;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) w[r] = pack_bf16x2(e[2 * r], e[2 * r + 1]);
-          NAT_E_STORE((u32x4v*)(e_row + j * kBlkElems), w);
-        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      const int kk = k0 + nb * 16 + l15;                   // token column (always inside the padded chunk)
-      const float sum = sum_quarters(s2[0] + s2[1]);
-      if (g == 0) s_part[(int64_t)granule * ld_part + kk] = sum;
-      if (kEntropy) {
-        const float t = sum_quarters((t2[0] + t2[1]) * kLn2);    // back to natural-log units
-        if (g == 0) t_part[(int64_t)granule * ld_part + kk] = t;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    };
+    sweep(std::false_type{});
+    constexpr float kBelowClamp = 1e30f;                   // < e^70: no exponential of a smaller sum was above the bound
+    if (__builtin_expect(__any(!(total < kBelowClamp)), 0)) sweep(std::true_type{});
   }
 };
 

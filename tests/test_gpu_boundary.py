@@ -224,3 +224,44 @@ def test_shift_range_counter_flags_tokens_beyond_the_bound(stage):
     ref = ogrpo.forward_logp(case["hidden"], case["W"], case["ids"])
     ok = gap < 60.0
     assert np.abs(out["logp"].cpu().numpy()[:n_tok][ok] - ref["logp"][ok]).max() <= 2e-3
+
+
+@pytest.mark.parametrize("n_tok,V", [(40, 1000), (300, 1500)])
+def test_bound_of_the_shift_where_it_acts(stage, n_tok, V):
+    # every third token's target lies up to e^90 below its mode: its numerators are clamped at e^70, in the log-prob and the entropy alike
+    # (fp64 sums of the clamped numerators; fp32 logits of 128 products and exponents up to 70: 1e-4), and the tokens
+    # beside it, in the same tile, get what they get beside ordinary ones, bit for bit
+    H = 128
+    rng = np.random.default_rng(n_tok)
+    case = make_loss_case(41, n_tok, H, V, "bf16", noise=0.1, w_std=0.7)
+    Z = case["hidden"].astype(np.float64) @ case["W"].astype(np.float64).T
+    far = np.arange(n_tok) % 3 == 1
+    tame = case["ids"].copy()
+    tame[far] = Z[far].argmax(axis=1)
+    case["ids"][~far] = tame[~far] = Z[~far].argmax(axis=1)
+    case["hidden"][far] *= 2.0                            # exact in bf16
+    Z[far] *= 2.0
+    case["ids"][far] = np.argsort(Z[far], axis=1)[:, V // 50]
+    gap = Z.max(axis=1) - Z[np.arange(n_tok), case["ids"]]
+    assert (gap[far] > 70.5).sum() > n_tok // 10 and gap.max() < 125.0
+    h, W = to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16)
+    got = stage.logp(h, W, to_dev(case["ids"]), n_tok, want_entropy=True)
+    beside = stage.logp(h, W, to_dev(tame), n_tok, want_entropy=True)
+    for k in ("logp", "entropy"):
+        assert torch.equal(got[k][~torch.from_numpy(far)], beside[k][~torch.from_numpy(far)]), k
+    x = np.minimum(Z - Z[np.arange(n_tok), case["ids"]][:, None], 70.0)
+    E = np.exp(x)
+    S = E.sum(axis=1)
+    assert np.abs(got["logp"].cpu().numpy() + np.log(S)).max() <= 1e-4
+    assert np.abs(got["entropy"].cpu().numpy() - (np.log(S) - (E * x).sum(axis=1) / S))[~far | (gap < 69.0)].max() <= 1e-4
+    # logits that are no numbers reach the same bound: nothing but their tokens is lost
+    h2 = h.clone()
+    h2[1] = float("nan")
+    odd = stage.logp(h2, W, to_dev(tame), n_tok)["logp"]
+    keep = torch.arange(n_tok) != 1
+    assert bool(torch.isnan(odd[1])) and torch.equal(odd[keep], beside["logp"][keep])
+    # the loss stores the numerators: clamped ones in the place of any that overflowed, ordinary ones untouched
+    out, tame_out = hip_loss(stage, case, "bf16"), hip_loss(stage, dict(case, ids=tame), "bf16")
+    assert torch.equal(out["logp"][:n_tok], got["logp"][:n_tok])
+    assert bool(torch.isfinite(out["dH"].float()).all()) and bool(torch.isfinite(out["dW"]).all())
+    assert torch.equal(out["dH"][:n_tok][~torch.from_numpy(far)], tame_out["dH"][:n_tok][~torch.from_numpy(far)])
