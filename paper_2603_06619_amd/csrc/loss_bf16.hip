@@ -51,9 +51,11 @@ typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 #define NAT_E_STORE(ptr, val) __builtin_nontemporal_store((val), (ptr))
 
 constexpr int kBM = 256, kBK = 32;                // block tile kBM x kBN: 4 wavefronts of 128 x 128, one per SIMD
-constexpr int kStages = 4;                        // LDS ring of k-slices (4 x 32 KiB)
 constexpr int kGranule = 128;                     // vocabulary rows per soft-max partial
 constexpr int kTileBytes = kBM * kBK * 2;         // 16 KiB per operand per stage
+// LDS ring of k-slices: both operands' tiles, nb 32-row blocks of the second one; four of 32 KiB, or six where the second one's are narrow
+constexpr int stage_bytes(int nb) { return kTileBytes + nb * 32 * kBK * 2; }
+constexpr int ring_stages(int nb) { return nb <= 5 ? 6 : 4; }
 // Tile rows per group of the block -> tile map, per contraction (whole step at the 8B head: logits in groups of 4 equal,
 // of 16 3.4 % slower; dH and dW in groups of 8 1.5 % slower).
 #ifndef NAT_GROUP_LOGITS
@@ -220,19 +222,29 @@ struct TileLoader {
   }
 };
 
-// The first kRows rows of a [256][32] operand block: 8 KiB of each slice, two loads for each of 4 wavefronts, or 4 KiB, one.
-template <int kRows>
+// kBlocks * 32 rows of a blocked operand from row `row0` on, a multiple of 16 (16 rows are one KiB of a block, and their chunk
+// order repeats from one to the next): 2 * kBlocks KiB per slice, dealt to the 4 wavefronts; where that does not come out even the last
+// one loads its last KiB again.
+template <int kBlocks>
 struct PartTileLoader {
-  static constexpr int kLoads = kRows / 64;
-  const uint16_t* src;
-  __device__ __forceinline__ void init(const uint16_t* base, int tile, int kb, int wave, int lane) {
-    src = base + (int64_t)tile * kb * kBlkElems + wave * (kLoads * 512) + lane * 8;
+  static constexpr int kPieces = 2 * kBlocks, kLoads = (kPieces + 3) / 4;
+  const uint16_t* src[kLoads];
+  static __device__ __forceinline__ int piece(int wave, int i) { const int q = wave * kLoads + i; return q < kPieces ? q : kPieces - 1; }
+  __device__ __forceinline__ void init(const uint16_t* base, int row0, int kb, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int q = row0 / 16 + piece(wave, i);
+      src[i] = base + (int64_t)(q >> 4) * kb * kBlkElems + (q & 15) * 512 + lane * 8;
+    }
   }
-  __device__ __forceinline__ void start_at(int kt0) { src += (int64_t)kt0 * kBlkElems; }
+  __device__ __forceinline__ void start_at(int kt0) {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) src[i] += (int64_t)kt0 * kBlkElems;
+  }
   template <int kIdx>
   __device__ __forceinline__ void issue_one(char* lds_tile, int kt, int wave) const {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (int64_t)kt * kBlkElems),
-                                     (__attribute__((address_space(3))) void*)(lds_tile + wave * (kLoads * 1024)), 16, kIdx * 1024, 0);
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[kIdx] + (int64_t)kt * kBlkElems),
+                                     (__attribute__((address_space(3))) void*)(lds_tile + piece(wave, kIdx) * 1024), 16, 0, 0);
   }
 };
 
@@ -341,9 +353,9 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 
 // one LDS object (with a second one the compiler's wait-count pass orders every fragment read behind all
 // direct-to-LDS loads in flight): the ring, and behind it the words of the epilogue (parked across the k-loop, or staged)
-template <int kWords>
+template <int kWords, int kNB = 8>
 struct GemmShared {
-  char ring[kStages][2][kTileBytes];
+  char ring[ring_stages(kNB)][stage_bytes(kNB)];
   int words[4][kWords];          // per wavefront
 };
 
@@ -479,12 +491,13 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 }
 
 // Units first, first + kNumCU, ... below end.  A is the operand of the tile grid's rows, B that of its columns.  kPIsB: the
-// result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or 4 or 2 for tiles of which only the first 128 or 64 rows of B are computed.
+// result's rows P are B's.  NB: 16-row blocks of B per wavefront, 8, or fewer for tiles with fewer columns: of a grid of columns that
+// are kColumns wide, all of them or the first NB * 32 of 256.  kRing: the NB that the ring in LDS is laid out for.
 //
-// Software pipeline over k-slices of 32.  The n-th slice lives in ring buffer n % 4; its fragments are read into registers while
+// Software pipeline over k-slices of 32.  The n-th slice lives in ring buffer n % kS, kS = 4 or 6; its fragments are read into registers while
 // slice n - 1 is multiplied.  At the barrier in front of slice n's products every wavefront has the fragments of slice
-// n, so its buffer is refilled with slice n + 4 under them, and slice n + 1 has landed: loads complete in issue order,
-// hence a vmcnt that leaves slices n + 2 and n + 3 outstanding (the epilogue's stores and loads count too: then it waits for
+// n, so its buffer is refilled with slice n + kS under them, and slice n + 1 has landed: loads complete in issue order,
+// hence a vmcnt that leaves slices n + 2 to n + kS - 1 outstanding (the epilogue's stores and loads count too: then it waits for
 // more than that, never for less).  The number of slices of a unit is even (H is a multiple of 64, the vocabulary and the
 // tokens are padded, ranges start and end at even slices): two per turn of the loop.  The slices of a workgroup's
 // units follow one another: while the last ones of a unit are multiplied and its epilogue runs, the first ones of the next are
@@ -494,16 +507,21 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
 // branches and the count fixed.  The 8 x NB products of a slice are written slot by slot (the compiler may not move anything
 // across a slot's end): fragment reads behind the products of the first half, one every second of them, loads of the refill
 // evenly spaced behind the second half.
-template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB>
-__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared<Epilogue::kWords>& sm, int first, int end) {
+template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB, int kColumns = kBN, int kRing = 8>
+__device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& epi, GemmShared<Epilogue::kWords, kRing>& sm, int first, int end) {
   constexpr int NP = kPIsB ? NB : 8, NQ = kPIsB ? 8 : NB;
+  static_assert(kColumns == kBN || !kPIsB, "narrow columns of the tile grid are the result's");
   using LoadA = LoaderOf<kA>;
-  using LoadB = typename std::conditional<NB < 8, PartTileLoader<NB * 32>, LoaderOf<kB>>::type;
+  using LoadB = typename std::conditional<NB < 8, PartTileLoader<NB>, LoaderOf<kB>>::type;
   constexpr int kLoadsA = LoadA::kLoads, kLoadsB = LoadB::kLoads, kLoads = kLoadsA + kLoadsB;    // per wavefront and slice
   using std::integral_constant;
   constexpr integral_constant<int, 0> zero{};
   constexpr integral_constant<int, 1> one{};
-  auto& lds = sm.ring;
+  constexpr int kS = ring_stages(kRing), kAhead = kS / 2 - 1;  // ring buffers; pairs of slices that stay in flight
+  auto a_buf = [&](int st) { return &sm.ring[st][0]; };
+  auto b_buf = [&](int st) { return &sm.ring[st][kTileBytes]; };
+  auto pair_after = [](int st) { return kS == 4 ? st ^ 2 : st + 2 == kS ? 0 : st + 2; };
+  auto pair_before = [](int st) { return kS == 4 ? st ^ 2 : st == 0 ? kS - 2 : st - 2; };
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int a_row0 = (wave >> 1) * 128, b_row0 = (wave & 1) * (NB * 16);
@@ -518,7 +536,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
     const Unit u = unit_of(g, load_id);
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) la.init(g.A, u.tm, g.src_rows, g.src_cols, wave, lane);
     else la.init(g.A, u.tm, kA == Src::kKMajorBlocked ? g.kb_a_src : g.K / kBK, wave, lane);
-    lb.init(g.B, u.tn, g.kb_b, wave, lane);
+    lb.init(g.B, NB < 8 ? u.tn * kColumns : u.tn, g.kb_b, wave, lane);
     la.start_at(u.kt0);
     lb.start_at(u.kt0);
     slice = 0;
@@ -538,8 +556,8 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
       slice = slice < slices ? slice : slices - 2;
     }
   };
-  auto load_a = [&](auto idx, int st, int k) { la.template issue_one<decltype(idx)::value>(lds[st][0], k, wave); };
-  auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(lds[st][1], k, wave); };
+  auto load_a = [&](auto idx, int st, int k) { la.template issue_one<decltype(idx)::value>(a_buf(st), k, wave); };
+  auto load_b = [&](auto idx, int st, int k) { lb.template issue_one<decltype(idx)::value>(b_buf(st), k, wave); };
   // Load n of the next two slices into buffers st and st + 1: first kEven with the even one, then kOdd.  A slice of an A read
   // from rows is 64 bytes of a row, half a cache line; fetched a slice apart, the halves cost the line twice on the way from
   // the L2 (log-probs of 12288 tokens at H = 4096 10454 us, 10163 together; 2048 1824 / 1766, at H = 1024 519 / 504): both slices'
@@ -548,7 +566,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   constexpr int kEven = kPaired ? 2 * kLoadsB : kLoads, kOdd = kPaired ? 2 * kLoadsA : kLoads;
   auto load_even = [&](auto n, int st) {
     constexpr int i = decltype(n)::value;
-    if constexpr (kPaired && i < kLoadsB) lb_last.template issue_one<i>(lds[(st ^ 2) + 1][1], slice_last, wave);
+    if constexpr (kPaired && i < kLoadsB) lb_last.template issue_one<i>(b_buf(pair_before(st) + 1), slice_last, wave);
     else if constexpr (kPaired) load_b(integral_constant<int, i - kLoadsB>{}, st, slice);
     else if constexpr (i < kLoadsA) load_a(n, st, slice);
     else load_b(integral_constant<int, i - kLoadsA>{}, st, slice);
@@ -560,7 +578,8 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
     else load_b(integral_constant<int, i - kLoadsA>{}, st + 1, slice + 1);
   };
   // loads younger than the slice that has to have landed in front of an even and an odd slice's products
-  constexpr int kYoungEven = kPaired ? 2 * kLoadsA + kLoadsB : 2 * kLoads, kYoungOdd = kPaired ? 2 * kLoadsB : 2 * kLoads;
+  constexpr int kYoungEven = kPaired ? 2 * kAhead * kLoadsA + (2 * kAhead - 1) * kLoadsB : 2 * kAhead * kLoads;
+  constexpr int kYoungOdd = kPaired ? 2 * (kAhead - 1) * kLoadsA + 2 * kAhead * kLoadsB : 2 * kAhead * kLoads;
 
   FragReader<kA> ra;
   FragReader<kB> rb;
@@ -576,7 +595,7 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   auto products = [&](auto is_first, auto cur, int next, auto count, auto load) {
     constexpr bool kFirst = decltype(is_first)::value;
     constexpr int kCur = decltype(cur)::value, kN = decltype(count)::value, kSlots = 8 * NB, kReadSpan = kSlots / 2;
-    const char *a_tile = lds[next][0], *b_tile = lds[next][1];
+    const char *a_tile = a_buf(next), *b_tile = b_buf(next);
     static_for<kSlots>([&](auto slot) {
       constexpr int m = decltype(slot)::value, i = m / NB, j = (i & 1) ? NB - 1 - m % NB : m % NB;
       if constexpr (kPIsB) mfma16<kFirst>(acc[j][i], fb[kCur].template get<j>(), fa[kCur].template get<i>());
@@ -604,29 +623,29 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   // what the epilogue needs per column (token id, exponent shift): fetched into LDS ahead of the operands, read after the
   // k-loop
   Unit u = unit_of(g, first);
-  auto prefetch = [&] { epi.template prefetch<NQ>(sm.words[wave], kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane); };
+  auto prefetch = [&] { epi.template prefetch<NQ>(sm.words[wave], kPIsB ? u.tm * kBM + a_row0 : u.tn * kColumns + b_row0, lane); };
   prefetch();
   open();
   if constexpr (kPaired) {
-    static_for<kOdd>([&](auto n) { load_odd(n, 0); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 0, slice); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 1, slice + 1); });
-    advance();
-    static_for<kOdd>([&](auto n) { load_odd(n, 2); });
-    static_for<kLoadsB>([&](auto n) { load_b(n, 2, slice); });
-    advance();
-    turn(integral_constant<int, 2 * kLoadsB + 2 * kLoadsA>{});
+#pragma unroll
+    for (int st = 0; st < kS; st += 2) {
+      static_for<kOdd>([&](auto n) { load_odd(n, st); });
+      static_for<kLoadsB>([&](auto n) { load_b(n, st, slice); });
+      if (st + 2 < kS) static_for<kLoadsB>([&](auto n) { load_b(n, st + 1, slice + 1); });
+      advance();
+    }
+    turn(integral_constant<int, 2 * kAhead * (kLoadsA + kLoadsB)>{});
   } else {
 #pragma unroll
-    for (int st = 0; st < kStages; st += 2) {
+    for (int st = 0; st < kS; st += 2) {
       static_for<kEven>([&](auto n) { load_even(n, st); });
       static_for<kOdd>([&](auto n) { load_odd(n, st); });
       advance();
     }
-    turn(integral_constant<int, 3 * kLoads>{});
+    turn(integral_constant<int, (kS - 1) * kLoads>{});
   }
-  static_for<kReadsA>([&](auto r) { fa[0].template read<decltype(r)::value>(ra, lds[0][0]); });
-  static_for<kReads - kReadsA>([&](auto r) { fb[0].template read<decltype(r)::value>(rb, lds[0][1]); });
+  static_for<kReadsA>([&](auto r) { fa[0].template read<decltype(r)::value>(ra, a_buf(0)); });
+  static_for<kReads - kReadsA>([&](auto r) { fb[0].template read<decltype(r)::value>(rb, b_buf(0)); });
   turn(integral_constant<int, kYoungEven>{});
   int st = 0;                                                  // ring buffer of the slice that is multiplied next
   for (int id = first;;) {
@@ -634,9 +653,9 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
     auto two_slices = [&](auto is_first) {
       products(is_first, zero, st + 1, integral_constant<int, kEven>{}, [&](auto n) { load_even(n, st); });
       turn(integral_constant<int, kYoungOdd>{});
-      products(std::false_type{}, one, st ^ 2, integral_constant<int, kOdd>{}, [&](auto n) { load_odd(n, st); });
+      products(std::false_type{}, one, pair_after(st), integral_constant<int, kOdd>{}, [&](auto n) { load_odd(n, st); });
       turn(integral_constant<int, kYoungEven>{});
-      st ^= 2;
+      st = pair_after(st);
       advance();
     };
     if constexpr (kMany) {
@@ -649,8 +668,11 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
         for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       for (int kt = 0; kt < u.kt_n; kt += 2) two_slices(std::false_type{});
     }
+    // with more slices in flight than a unit of two has, what its prefetch() fetched may be among them
+    if constexpr (kMany && kAhead > 1)
+      if (u.kt_n == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoads));
     const AccReader rd;
-    epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kBN + b_row0, lane, sm.words[wave], u.slab);
+    epi(acc, rd, kPIsB ? u.tn * kBN + b_row0 : u.tm * kBM + a_row0, kPIsB ? u.tm * kBM + a_row0 : u.tn * kColumns + b_row0, lane, sm.words[wave], u.slab);
     id += kNumCU;
     if (!kMany || id >= end) break;
     u = unit_of(g, id);
@@ -660,18 +682,18 @@ __device__ __forceinline__ void mfma_units(const GemmArgs& g, const Epilogue& ep
   __syncthreads();
 }
 
-template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany>
+template <class Epilogue, Src kA, Src kB, bool kPIsB, bool kMany, int NB = 8>
 __global__ void __launch_bounds__(256, 1)
 mfma_nt_kernel(GemmArgs g, Epilogue epi) {
-  __shared__ __attribute__((aligned(1024))) GemmShared<Epilogue::kWords> sm;
+  __shared__ __attribute__((aligned(1024))) GemmShared<Epilogue::kWords, NB> sm;
   if constexpr (kMany) {
     const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
-    mfma_units<Epilogue, kA, kB, kPIsB, true, 8>(g, epi, sm, w.first, w.end);
+    mfma_units<Epilogue, kA, kB, kPIsB, true, NB, NB * 32, NB>(g, epi, sm, w.first, w.end);
   } else {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
-    // computes only those (whole call with 256 / 128 / 64 columns, us: 301 log-probs at the 0.6B head 138 / 127 / 120, 300 at the 8B head
-    // 474 / 427 / 408; loss at the 8B head 60 tokens 1091 / 1015 / 988, 100 1119 / 1038, 1100 3557 / 3479).
+    // computes only those (whole call with 256 / 128 / 64 columns, us: loss at the 8B head 60 tokens 1091 / 1015 / 988, 100 1119 / 1038, 1100
+    // 3557 / 3479).
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
       const int blocks = last_blocks(epi.n_valid, g.tiles_n);
       if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {
@@ -1317,6 +1339,25 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
+  // W read as it is: up to seven tile columns are as wide as their tokens need, 32 * blocks each (dW reads whole pairs of 32-token slices), so that
+  // no tile is a nearly empty one, and where that leaves room in LDS the ring holds six slices: such a launch waits for W, and what is in flight
+  // of it decides.  Columns of 256 with a short last one / equal ones / the same with six slices, whole log-prob call, us: H = 1024 40 tokens 76.5 / 74.1 /
+  // 70.4, 150 93.5 / 85.6 / 85.6, 301 117.3 / 117.4 / 110.8, 600 192.8 / 186.3, 1300 368 / 349; H = 4096 150 314.7 / 289.4 / 289.3, 301 403.7 / 415.7 / 393.3, 560
+  // 655 / 628, 1070 1098 / 1084; H = 2048, V = 20000 300 46.6 / 37.7 / 38.0; H = 64, V = 3000 150 16.6 / 15.2 / 15.4.
+  const int per_block = 32 * tiles_n, blocks = Wb ? 8 : (int)((round_up(epi.n_valid, 64) + per_block - 1) / per_block);
+  if (blocks < 8) {
+    g.walk = walk_length(units, H / kBK);                     // also beyond kLogitsWalkSlices (H = 5120: 40 tokens 324.8 one tile each, 323.2; 301 557.5 / 552.7)
+    auto go = [&](auto nb) {
+      mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true, decltype(nb)::value><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
+    };
+    if (blocks <= 2) go(std::integral_constant<int, 2>{});
+    else if (blocks <= 4) go(std::integral_constant<int, 4>{});
+    else if (blocks == 5) go(std::integral_constant<int, 5>{});
+    else if (blocks == 6) go(std::integral_constant<int, 6>{});
+    else go(std::integral_constant<int, 7>{});
+    NAT_LAUNCH_CHECK();
+    return NAT_OK;
+  }
   g.walk = logits_walk(units, H / kBK, Wb ? 8 : last_blocks(epi.n_valid, tiles_n), tiles_n);
   if (g.walk > 1) {
     if (Wb) mfma_nt_kernel<Epi, Src::kBlockedInterleaved, Src::kBlocked, false, true><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);

@@ -283,6 +283,24 @@ def test_bf16_nearly_empty_last_token_tile_of_several(stage, n_tok):
         assert torch.equal(whole[k][:full], front[k][:full]), k
 
 
+@pytest.mark.parametrize("H,V", [(64, 66000), (128, 700), (448, 66000)])
+def test_bf16_tile_columns_of_every_width(stage, H, V):
+    # up to seven equal tile columns of 64, 128, 160, 192, 224 or 256 tokens, four or six slices in flight, with 2, 4 and 14 slices per tile
+    # and walks of one or two: log-probs and entropies of the first n tokens have the bits that they have among 1800 (columns of 256)
+    case = make_loss_case(800 + H, 1800, H, V, "bf16", noise=0.15, w_std=0.1)
+    hidden, W, ids = to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"])
+    all_of_it = stage.logp(hidden, W, ids, 1800, want_entropy=True)
+    for n in (1, 64, 65, 128, 129, 160, 161, 192, 193, 224, 225, 256, 257, 320, 321, 384, 385, 449, 513, 577, 641, 672, 769, 896, 897, 1025, 1088,
+              1089, 1281, 1344, 1537, 1568):
+        for stored in stage._ws.values():
+            stored.fill_(255)
+        some = stage.logp(hidden[:n], W, ids[:n], n, want_entropy=True)
+        for k in ("logp", "entropy"):
+            assert torch.equal(some[k][:n], all_of_it[k][:n]), (n, k)
+    part = {k: (v[:161] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
+    check(hip_loss(stage, part, "bf16"), oracle_loss(**part), 161, TOL_BF16, part)
+
+
 def accumulated_and_plain(stage, n_tok, H, V):
     case = make_loss_case(600 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
     plain = hip_loss(stage, case, "bf16")["dW"]
