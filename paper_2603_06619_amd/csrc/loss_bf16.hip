@@ -1081,9 +1081,10 @@ constexpr float kShiftRangeLimit = 2.5154386709191669e30f;     // e^70
 // Per-token sums of the per-granule partials: kStatTokens tokens per workgroup; the granules of a
 // token are split over kStatParts groups of threads (granule gi goes to group gi % kStatParts), each
 // of which walks its granules in order, and the groups' sums are added in a fixed tree, so the result
-// does not depend on timing.  Bound by the latency of the walk (149 granules per group at V = 151936): with 32
-// loads in flight instead of 8 a launch over 3000 tokens takes 14 us instead of 19.  Returns to the first kStatTokens threads only.
-constexpr int kStatTokens = 32, kStatParts = 8, kStatBatch = 32;
+// does not depend on timing.  Bound by the latency of the walk (75 granules per group at V = 151936) in a short batch: 32
+// loads in flight, 14 us over 3000 tokens (19 with 8), and 16 groups (8 / 16 / 32: 40 tokens with the entropy at V = 160000 18.1 / 12.6 /
+// 12.5 us, 1237 tokens 13.9 / 12.1 / 12.1, 16384 21.6 / 21.8 / 24.8).  Returns to the first kStatTokens threads only.
+constexpr int kStatTokens = 32, kStatParts = 16, kStatBatch = 32;
 struct TokenSums { float S, TZ; bool in_shift_range; };
 struct StatShared { float s[kStatParts][kStatTokens], t[kStatParts][kStatTokens], m[kStatParts][kStatTokens]; };
 
@@ -1113,15 +1114,25 @@ __device__ __forceinline__ TokenSums token_sums(const float* __restrict__ s_part
   sh.m[part][t] = mx;
   __syncthreads();
   TokenSums out;
-  out.S = ((sh.s[0][t] + sh.s[1][t]) + (sh.s[2][t] + sh.s[3][t])) + ((sh.s[4][t] + sh.s[5][t]) + (sh.s[6][t] + sh.s[7][t]));
-  out.TZ = ((sh.t[0][t] + sh.t[1][t]) + (sh.t[2][t] + sh.t[3][t])) + ((sh.t[4][t] + sh.t[5][t]) + (sh.t[6][t] + sh.t[7][t]));
+  auto tree = [&](const float (&x)[kStatParts][kStatTokens]) {
+    float v[kStatParts];
+#pragma unroll
+    for (int q = 0; q < kStatParts; ++q) v[q] = x[q][t];
+#pragma unroll
+    for (int n = kStatParts / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int q = 0; q < n; ++q) v[q] = v[2 * q] + v[2 * q + 1];
+    return v[0];
+  };
+  out.S = tree(sh.s);
+  out.TZ = tree(sh.t);
   float m = sh.m[0][t];
   for (int q = 1; q < kStatParts; ++q) m = fmaxf(m, sh.m[q][t]);
   out.in_shift_range = m >= kShiftRangeLimit;
   return out;
 }
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kStatTokens * kStatParts)
 token_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t_part, int n_granules, int64_t ld,
                    const float* __restrict__ ref, const float* __restrict__ z_target, int n_valid, int chunk_start,
                    const int32_t* __restrict__ ids, int V,
@@ -1177,7 +1188,7 @@ token_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t
 }
 
 // Forward pass alone: log-prob of the target (and the entropy) from the per-granule sums.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kStatTokens * kStatParts)
 logp_stats_kernel(const float* __restrict__ s_part, const float* __restrict__ t_part, int n_granules, int64_t ld,
                   const float* __restrict__ ref, const float* __restrict__ z_target, int n_valid, int chunk_start,
                   const int32_t* __restrict__ ids, int V,
