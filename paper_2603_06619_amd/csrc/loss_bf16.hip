@@ -689,6 +689,8 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   if constexpr (kMany) {
     const Walk w = walk_of((int)blockIdx.x, g.walk, g.tiles_m * g.tiles_n + (g.k_splits - 1) * g.tail_tiles);
     mfma_units<Epilogue, kA, kB, kPIsB, true, NB, NB * 32, NB>(g, epi, sm, w.first, w.end);
+  } else if constexpr (NB < 8) {
+    mfma_units<Epilogue, kA, kB, kPIsB, false, NB, NB * 32, NB>(g, epi, sm, (int)blockIdx.x, (int)blockIdx.x + 1);
   } else {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
@@ -979,16 +981,16 @@ struct DWeightEpilogue {
 // dH tiles of a launch whose last tail_tiles tiles (in launch order) were cut into k_splits ranges of the vocabulary:
 // dH[k][h] = beta_k * (slab 0 + slab 1 + ...) of the tile, in range order.  One block per 1024 elements of a tile.
 __global__ void __launch_bounds__(256)
-dh_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, bool transposed, const float* __restrict__ beta,
+dh_tail_reduce_kernel(const float* __restrict__ partial, GemmArgs g, bool transposed, int columns /*tokens of a tile*/, const float* __restrict__ beta,
                       int n_valid, int H, uint16_t* __restrict__ dH) {
   const int pos = blockIdx.y;
   int tm, tn;                                                          // tile of tokens, of hidden units
   if (transposed) tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tn, tm);
   else tile_of_block(g, g.tiles_m * g.tiles_n - g.tail_tiles + pos, tm, tn);
   const int e = (blockIdx.x * 256 + threadIdx.x) * 4;                  // four hidden units of a token
-  const int k = tm * kBM + e / kBN, h = tn * kBN + e % kBN;
-  if (k >= n_valid || h >= H) return;                                  // H is a multiple of 64
-  const float* slab = partial + (int64_t)pos * g.k_splits * (kBM * kBN) + e;
+  const int row = e / kBN, k = tm * columns + row, h = tn * kBN + e % kBN;
+  if (row >= columns || k >= n_valid || h >= H) return;                // H is a multiple of 64
+  const float* slab = partial + (int64_t)pos * g.k_splits * (kBM * kBN) + (k & (kBM - 1)) * kBN + e % kBN;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
   for (int r = 0; r < g.k_splits; ++r) {
@@ -1342,6 +1344,28 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }
 static int direct_tokens_forward(int H) { return H >= kBN ? 24576 : 8192; }
 
+// Width of the token columns, 32 * blocks each, of a call that reads W as it is: up to seven columns are as wide as their tokens need (dW
+// reads whole pairs of 32-token slices), so that no tile is a nearly empty one, and where that leaves room in LDS the ring holds six slices:
+// such a launch waits for W, and what is in flight of it decides, the less so as the columns that share its rows ask for the same.  Columns of 256
+// with a short last one / equal ones / the same with six slices, whole log-prob call, us: H = 1024 40 tokens 76.5 / 74.1 / 70.4, 150 93.5 / 85.6 /
+// 85.6, 301 117.3 / 117.4 / 110.8, 600 192.8 / 186.3, 1300 368 / 349; H = 4096 150 314.7 / 289.4 / 289.3, 301 403.7 / 415.7 / 393.3, 560 655 / 628, 1070
+// 1098 / 1084; H = 2048, V = 20000 300 46.6 / 37.7 / 38.0; H = 64, V = 3000 150 16.6 / 15.2 / 15.4.  dH, a short last column / equal ones: H = 1024 150
+// tokens 109 / 100, 300 188 / 155, 600 240 / 221; H = 4096 300 459 / 456, 1070 1070 / 1057.
+static int column_blocks(int n_valid, int tiles_n) {
+  const int per_block = 32 * tiles_n;
+  return (int)((round_up(n_valid, 64) + per_block - 1) / per_block);
+}
+
+// launch(integral_constant) with the number of blocks that is built for so many: 2, 4, 5, 6 or 7
+template <class F>
+static void with_blocks(int blocks, F&& launch) {
+  if (blocks <= 2) launch(std::integral_constant<int, 2>{});
+  else if (blocks <= 4) launch(std::integral_constant<int, 4>{});
+  else if (blocks == 5) launch(std::integral_constant<int, 5>{});
+  else if (blocks == 6) launch(std::integral_constant<int, 6>{});
+  else launch(std::integral_constant<int, 7>{});
+}
+
 // logits contraction: rows = vocabulary, columns = tokens (tiles_n tiles), contraction over the hidden size; W either
 // repacked (Wb) or read as it is (Wb NULL)
 template <class Epi>
@@ -1350,22 +1374,12 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   ProfScope prof(PC_LOGITS, s);
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
-  // W read as it is: up to seven tile columns are as wide as their tokens need, 32 * blocks each (dW reads whole pairs of 32-token slices), so that
-  // no tile is a nearly empty one, and where that leaves room in LDS the ring holds six slices: such a launch waits for W, and what is in flight
-  // of it decides.  Columns of 256 with a short last one / equal ones / the same with six slices, whole log-prob call, us: H = 1024 40 tokens 76.5 / 74.1 /
-  // 70.4, 150 93.5 / 85.6 / 85.6, 301 117.3 / 117.4 / 110.8, 600 192.8 / 186.3, 1300 368 / 349; H = 4096 150 314.7 / 289.4 / 289.3, 301 403.7 / 415.7 / 393.3, 560
-  // 655 / 628, 1070 1098 / 1084; H = 2048, V = 20000 300 46.6 / 37.7 / 38.0; H = 64, V = 3000 150 16.6 / 15.2 / 15.4.
-  const int per_block = 32 * tiles_n, blocks = Wb ? 8 : (int)((round_up(epi.n_valid, 64) + per_block - 1) / per_block);
+  const int blocks = Wb ? 8 : column_blocks(epi.n_valid, tiles_n);
   if (blocks < 8) {
     g.walk = walk_length(units, H / kBK);                     // also beyond kLogitsWalkSlices (H = 5120: 40 tokens 324.8 one tile each, 323.2; 301 557.5 / 552.7)
-    auto go = [&](auto nb) {
+    with_blocks(blocks, [&](auto nb) {
       mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true, decltype(nb)::value><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
-    };
-    if (blocks <= 2) go(std::integral_constant<int, 2>{});
-    else if (blocks <= 4) go(std::integral_constant<int, 4>{});
-    else if (blocks == 5) go(std::integral_constant<int, 5>{});
-    else if (blocks == 6) go(std::integral_constant<int, 6>{});
-    else go(std::integral_constant<int, 7>{});
+    });
     NAT_LAUNCH_CHECK();
     return NAT_OK;
   }
@@ -1466,20 +1480,30 @@ nat_status loss_bf16_run(const LossArgs& a) {
         uint16_t* dH_s = (uint16_t*)a.dH + (int64_t)(c0 + s0) * H;
         ProfScope prof(PC_DHIDDEN, s);
         GemmArgs g{Eb_s, Wtb, Vp, snp / kBM, Hp / kBN, NAT_GROUP_DHIDDEN, 0, Vp / kBK, cut.splits, cut.kt_per, cut.tail, V, H, 1};
+        int columns = kBN;
         if (direct) {            // dH^T = W^T E^T from W as it is
           g.A = W;
           g.B = Eb_s;
           g.tiles_m = Hp / kBM;
           g.tiles_n = snp / kBN;
           DHiddenEpilogue<false> e{snv, H, dH_s, beta + s0, dh_part};
-          mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false, false><<<cut.grid, 256, 0, s>>>(g, e);
+          const int blocks = column_blocks(snv, g.tiles_n);
+          if (blocks < 8) {
+            with_blocks(blocks, [&](auto nb) {
+              constexpr int kNB = decltype(nb)::value;
+              mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false, false, kNB><<<cut.grid, 256, 0, s>>>(g, e);
+              columns = kNB * 32;
+            });
+          } else {
+            mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false, false><<<cut.grid, 256, 0, s>>>(g, e);
+          }
         } else {
           DHiddenEpilogue<true> e{snv, H, dH_s, beta + s0, dh_part};
           mfma_nt_kernel<DHiddenEpilogue<true>, Src::kBlocked, Src::kBlockedInterleaved, true, false><<<cut.grid, 256, 0, s>>>(g, e);
         }
         NAT_LAUNCH_CHECK();
         if (cut.splits > 1) {
-          dh_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, direct, beta + s0, snv, H, dH_s);
+          dh_tail_reduce_kernel<<<dim3(kBM * kBN / 1024, cut.tail), 256, 0, s>>>(dh_part, g, direct, columns, beta + s0, snv, H, dH_s);
           NAT_LAUNCH_CHECK();
         }
       }

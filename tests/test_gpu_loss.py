@@ -387,6 +387,19 @@ def test_bf16_dh_leftover_tiles_cut_into_vocabulary_ranges(stage, n_tok, H, V, l
     check(hip_loss(stage, case, "bf16"), ref, n_tok, TOL_BF16, case, label=label)
 
 
+@pytest.mark.parametrize("n_tok,H,V", [(150, 64, 30000), (190, 320, 9000), (300, 1024, 9000), (420, 256, 9000), (530, 576, 5000), (1070, 128, 4200),
+                                       (330, 4160, 3000)])
+def test_bf16_dh_of_narrow_columns_in_ranges(stage, n_tok, H, V):
+    # dH of one to five equal tile columns of 160 to 224 tokens, its vocabulary cut into ranges: numbers of tiles and of units that
+    # do and do not divide by the 8 XCDs (1, 2, 8, 2, 9, 5, 34 tiles).  Two runs agree bit for bit
+    case = make_loss_case(320 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.02)
+    out = hip_loss(stage, case, "bf16")
+    check(out, oracle_loss(**case), n_tok, TOL_BF16, case)
+    first = out["dH"].clone()
+    stage._ws["loss"].fill_(255)
+    assert torch.equal(first, hip_loss(stage, case, "bf16")["dH"])
+
+
 def test_bf16_dw_leftover_tiles_cut_into_token_ranges(stage):
     # 8 dW tiles on 256 compute units: all of them are "left over" after the last full round, so the library
     # cuts their token axis (8173 tokens = 256 k-slices) into 8 ranges and adds the partial tiles in range
