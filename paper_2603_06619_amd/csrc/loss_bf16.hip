@@ -479,7 +479,13 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
   Unit u{0, 0, 0, g.K / kBK, -1};
   const int whole = g.tiles_m * g.tiles_n - g.tail_tiles;
   if (g.k_splits > 1 && id >= whole) {
-    const int r = id - whole, range = r / g.tail_tiles, pos = r - range * g.tail_tiles;
+    // ids congruent mod 8 share an L2, as in tile_of_block (whole is a multiple of 256): an XCD gets consecutive ranges, and of a range consecutive tiles,
+    // so that the tiles of one range, which read the same slices of both operands, fetch them once.  dH, us, tile by tile over the XCDs / so: H =
+    // 4096 150 tokens 290 / 233, 300 455 / 390, 560 663 / 627, H = 1024 300 155 / 115, 600 222 / 177
+    const int n = g.tail_tiles * g.k_splits, per = n / 8, r = id - whole;
+    const int v = r < per * 8 ? (r & 7) * per + (r >> 3) : r, range = v / g.tail_tiles;
+    int pos = v - range * g.tail_tiles;
+    if (g.tail_tiles % 8 == 0) pos = pos % (g.tail_tiles / 8) * 8 + pos / (g.tail_tiles / 8);
     u.kt0 = range * g.kt_per_split;                            // with a blocked k-major A a multiple of 8 (TileLoaderKMajor::start_at)
     if (u.kt_n - u.kt0 > g.kt_per_split) u.kt_n = g.kt_per_split;
     else u.kt_n -= u.kt0;
