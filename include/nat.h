@@ -143,7 +143,8 @@ size_t nat_compact_workspace_bytes(int64_t N);
  *   d_kept_w   [kept_cap] float out;
  *   d_cu_kept  [B+1] int32 out: kept-token offsets per rollout;
  *   d_n_kept   [1] int32 out;  h_n_kept: optional PINNED host int32 that receives the
- *              same value by an asynchronous copy on `stream` (NULL = skip);
+ *              same value on `stream`, written by a kernel or copied (NULL = skip): read it
+ *              once the call has completed there;
  *   optional gather (any of the three pairs may be NULL):
  *     d_hidden [N, H] -> d_hidden_k [kept_cap, H] rows of kept tokens, dtype NAT_DTYPE_*,
  *     d_ids [N] -> d_ids_k [kept_cap],  d_old_logp [N] -> d_old_logp_k [kept_cap];
@@ -258,7 +259,7 @@ nat_status nat_compact_pi(int32_t n_rollouts_global, const uint32_t* d_mask_bits
  *                token k (ascending (i, t), the order of nat_compact); kept_cap >= sum L_i
  *                (N always suffices);
  *   d_totals     [2] int32 out: number of truncated rows, longest truncated sequence;
- *   h_totals     optional PINNED host int32[2] receiving the same by an asynchronous copy;
+ *   h_totals     optional PINNED host int32[2] receiving the same, written by a kernel or copied;
  *   d_input_ids -> d_input_ids_packed: optional gather of the full input's token ids
  *                ([sum_i (P_i + T_i)] -> [rows_cap]); both NULL to skip.
  * Rows beyond rows_cap / kept_cap are not written.

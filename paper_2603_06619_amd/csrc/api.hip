@@ -46,6 +46,18 @@ __global__ void fill_zero_kernel(float4* __restrict__ p4, size_t n4, float* __re
   if (blockIdx.x == 0 && (int)threadIdx.x < n_tail) tail[threadIdx.x] = 0.f;
 }
 
+int32_t* pinned_words(int32_t* h) {
+  if (!h) return nullptr;
+  hipPointerAttribute_t at{};
+  int dev = -1;
+  if (hipPointerGetAttributes(&at, h) != hipSuccess) {
+    (void)hipGetLastError();               // not memory that HIP knows: copied to, as any other
+    return nullptr;
+  }
+  if (at.type != hipMemoryTypeHost || at.devicePointer != (void*)h || hipGetDevice(&dev) != hipSuccess || at.device != dev) return nullptr;
+  return h;
+}
+
 nat_status fill_zero_f32(float* p, size_t n, hipStream_t s) {
   if (n == 0) return NAT_OK;
   ProfScope prof(PC_FILL, s);

@@ -83,7 +83,7 @@ struct ScatterArgs {
   const int64_t* cu; int B;
   const int32_t* tile_count; const int32_t* group_count;        // of the count pass; or NULL: the block counts the mask words
   int mask_wide;                                                // mask_bits is 16-byte aligned
-  int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept;
+  int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept; int32_t* h_n_kept /*pinned, or NULL*/;
   const int32_t* ids; int32_t* ids_k; const float* old_logp; float* old_logp_k;
 };
 
@@ -178,7 +178,10 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
     tile_kept += wave_tot[w];
     if (w < wave) span_base += wave_tot[w];
   }
-  if (tile == n_tiles - 1 && tid == 0) *c.n_kept = tile_base + tile_kept;
+  if (tile == n_tiles - 1 && tid == 0) {
+    *c.n_kept = tile_base + tile_kept;
+    if (c.h_n_kept) host_store(c.h_n_kept, tile_base + tile_kept);
+  }
   // Offsets of the rollouts that start in this tile (offsets outside [0, n_tokens] count as its ends), by the whole block
   // and four loads at a time: empty rollouts can put any number of them at one position.  Compaction of 100 rollouts of 1000
   // tokens and 4000 / 65000 / a million empty ones: 17.8 / 210 / 5300 us by the wavefront of their span, 8.7 / 22 / 311 by the block.
@@ -232,10 +235,13 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
 
 // N = 0: nothing is kept, every rollout starts at 0.
 __global__ void __launch_bounds__(256)
-compact_empty_kernel(int B, int32_t* __restrict__ cu_kept, int32_t* __restrict__ n_kept) {
+compact_empty_kernel(int B, int32_t* __restrict__ cu_kept, int32_t* __restrict__ n_kept, int32_t* __restrict__ h_n_kept) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i <= B) cu_kept[i] = 0;
-  if (i == 0) *n_kept = 0;
+  if (i == 0) {
+    *n_kept = 0;
+    if (h_n_kept) host_store(h_n_kept, 0);
+  }
 }
 
 // One block per kept row: copy row kept_idx[k] of `src` (row_bytes, multiple of 16) to row k.
@@ -318,6 +324,7 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
   const int64_t n_words = nat_mask_words(c.N);
   int32_t* tile_count = (int32_t*)c.ws;
   int32_t* group_count = tile_count + n_tiles;
+  int32_t* pinned = pinned_words(c.h_n_kept);
   {
     ProfScope prof(PC_COMPACT, s, !c.no_timing);
     if (n_tiles > 0) {
@@ -328,18 +335,18 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
       }
       const ScatterArgs sc{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B,
                            count ? tile_count : nullptr, count ? group_count : nullptr, ((uintptr_t)c.mask_bits & 15) == 0,
-                           c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
+                           c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept, pinned, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
       if (count && c.pi) compact_scatter_kernel<4, true><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
       else if (count) compact_scatter_kernel<4, false><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
       else if (c.pi) compact_scatter_kernel<16, true><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
       else compact_scatter_kernel<16, false><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
       NAT_LAUNCH_CHECK();
     } else {
-      compact_empty_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.B, c.cu_kept, c.n_kept);
+      compact_empty_kernel<<<(c.B + 1 + 255) / 256, 256, 0, s>>>(c.B, c.cu_kept, c.n_kept, pinned);
       NAT_LAUNCH_CHECK();
     }
   }
-  if (c.h_n_kept) NAT_HIP_TRY(hipMemcpyAsync(c.h_n_kept, c.n_kept, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if (c.h_n_kept && !pinned) NAT_HIP_TRY(hipMemcpyAsync(c.h_n_kept, c.n_kept, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   const int64_t gather_rows = c.N < c.kept_cap ? c.N : c.kept_cap;
   if (gather_rows > 0 && c.hidden) {
     ProfScope prof(PC_GATHER, s, !c.no_timing);

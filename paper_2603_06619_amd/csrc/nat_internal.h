@@ -136,6 +136,12 @@ nat_status logp_bf16_run(const LogpArgs& a);
 size_t logp_f32_workspace_bytes(int32_t N_k, int32_t H, int32_t V, bool minimal);
 nat_status logp_f32_run(const LogpArgs& a);
 
+// `h`, the pinned words that a call reports counts in, if kernels on the current device can write there, else NULL (memory of another device, or
+// not pinned: copied to).  A kernel that writes them takes a copy and its gap out of the stream and 2 us of host time out of
+// the call: selection of 1.3 million tokens 19.4 -> 17.5 us, with a truncated batch of 0.29 million 29.9 -> 26.4, of 2000 14.7 -> 12.7.
+int32_t* pinned_words(int32_t* h);
+__device__ __forceinline__ void host_store(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+
 // shared small kernels (api.hip)
 nat_status fill_zero_f32(float* p, size_t n, hipStream_t s);
 

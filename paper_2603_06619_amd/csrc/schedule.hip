@@ -116,7 +116,7 @@ schedule_cut_kernel(uint32_t key0, uint32_t key1, uint32_t step, int32_t rollout
 __global__ void __launch_bounds__(1024)
 prefix_scan_kernel(const int32_t* __restrict__ prompt_len, const int64_t* __restrict__ cu,
                    const int32_t* __restrict__ cut_len, int B, int32_t* __restrict__ cu_packed,
-                   int32_t* __restrict__ cu_loss, int32_t* __restrict__ totals) {
+                   int32_t* __restrict__ cu_loss, int32_t* __restrict__ totals, int32_t* __restrict__ h_totals) {
   __shared__ int wave_rows[16], wave_loss[16], wave_max[16];
   __shared__ int carry_rows, carry_loss;
   if (threadIdx.x == 0) { carry_rows = 0; carry_loss = 0; }
@@ -157,6 +157,10 @@ prefix_scan_kernel(const int32_t* __restrict__ prompt_len, const int64_t* __rest
     cu_loss[B] = carry_loss;
     totals[0] = carry_rows;
     totals[1] = m;
+    if (h_totals) {
+      host_store(h_totals, carry_rows);
+      host_store(h_totals + 1, m);
+    }
   }
 }
 
@@ -249,9 +253,10 @@ extern "C" nat_status nat_prefix_pack(const int32_t* d_prompt_len, const int64_t
   if (rows_cap > 0 && kept_cap > 0 && !d_loss_row) return NAT_INVALID_ARG;
   if ((d_input_ids != nullptr) != (d_input_ids_packed != nullptr)) return NAT_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
+  int32_t* pinned = pinned_words(h_totals);
   {
     ProfScope prof(PC_PREFIX_PACK, s);
-    prefix_scan_kernel<<<1, 1024, 0, s>>>(d_prompt_len, d_cu_seqlens, d_cut_len, B, d_cu_packed, d_cu_loss, d_totals);
+    prefix_scan_kernel<<<1, 1024, 0, s>>>(d_prompt_len, d_cu_seqlens, d_cut_len, B, d_cu_packed, d_cu_loss, d_totals, pinned);
     NAT_LAUNCH_CHECK();
     if (rows_cap > 0) {
       prefix_rows_kernel<<<(unsigned)((rows_cap + 255) / 256), 256, 0, s>>>(
@@ -260,6 +265,6 @@ extern "C" nat_status nat_prefix_pack(const int32_t* d_prompt_len, const int64_t
       NAT_LAUNCH_CHECK();
     }
   }
-  if (h_totals) NAT_HIP_TRY(hipMemcpyAsync(h_totals, d_totals, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  if (h_totals && !pinned) NAT_HIP_TRY(hipMemcpyAsync(h_totals, d_totals, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   return NAT_OK;
 }

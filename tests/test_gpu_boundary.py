@@ -265,3 +265,31 @@ def test_bound_of_the_shift_where_it_acts(stage, n_tok, V):
     assert torch.equal(out["logp"][:n_tok], got["logp"][:n_tok])
     assert bool(torch.isfinite(out["dH"].float()).all()) and bool(torch.isfinite(out["dW"]).all())
     assert torch.equal(out["dH"][:n_tok][~torch.from_numpy(far)], tame_out["dH"][:n_tok][~torch.from_numpy(far)])
+
+
+@pytest.mark.parametrize("memory", ["pinned", "inside pinned", "pageable"])
+def test_counts_reach_host_memory_of_any_kind(stage, memory):
+    # a kernel writes them where it can, and they are copied elsewhere; nothing beside them is touched
+    import paper_2603_06619_amd as nat
+    host = torch.full((6,), -5, dtype=torch.int32)
+    host = host if memory == "pageable" else host.pin_memory()
+    first = 1 if memory == "inside pinned" else 0
+    for lengths in ([700, 0, 41], [0, 0]):
+        cu = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+        B, N = len(lengths), int(cu[-1])
+        b = _select_buffers(nat, B, N)
+        params = nat.SelectParams(nat.RPC, min_cut=3, seed=4, step=1)
+        o = oracle_select_compact(cu, osel.RPC, C=3, seed=4, step=1)
+        nat.nat_select(params, to_dev(cu), B, N, b["cut"], b["mask"])
+        nat.nat_compact(params, B, b["mask"], to_dev(cu), B, N, b["idx"], b["seq"], b["w"], b["cuk"], b["nk"], host[first:], b["ws"])
+        torch.cuda.synchronize()
+        assert int(host[first]) == o["n_kept"] == int(b["nk"].item())
+        plen = to_dev(np.array([5, 9, 2][:B], dtype=np.int32))
+        i32 = lambda n: torch.zeros(max(int(n), 1), dtype=torch.int32, device=DEV)
+        cap = N + int(plen.sum())
+        totals = i32(2)
+        nat.nat_prefix_pack(plen, to_dev(cu), b["cut"], B, 1, cap, N, i32(B + 1), i32(B + 1), i32(cap), i32(cap), i32(N), totals, host[first + 2:])
+        torch.cuda.synchronize()
+        assert host[first + 2:first + 4].tolist() == totals.tolist() and totals.tolist()[0] == int(plen.sum()) + o["n_kept"]
+    untouched = [k for k in range(6) if k not in (first, first + 2, first + 3)]
+    assert (host[untouched] == -5).all()
