@@ -282,6 +282,24 @@ def test_prefix_pack_many_rollouts_spans_scan_chunks(stage):
     _pack_both(stage, P, cu, cut, 1)
 
 
+@pytest.mark.parametrize("B,hi", [(1, 3), (3, 0), (255, 40), (256, 40), (257, 9), (1024, 1200), (1025, 30)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_prefix_pack_of_rollouts_scanned_by_every_block(stage, B, hi, shift):
+    # up to 1024 rollouts, four to a thread, and beyond; with empty ones, and more rows than the 524288 that all blocks take at once
+    rng = np.random.default_rng(B)
+    T = rng.integers(0, hi + 1, B)
+    T[rng.random(B) < 0.2] = 0
+    P = rng.integers(1, 5, B)
+    cu = np.concatenate([[0], np.cumsum(T)]).astype(np.int64)
+    cut = np.array([rng.integers(0, t + 1) for t in T], np.int32)
+    cut[::3] = T[::3]
+    ids = rng.integers(0, 1 << 30, int(cu[-1]) + int(P.sum())).astype(np.int32)
+    _pack_both(stage, P, cu, cut, shift, ids)
+    if B == 1024:
+        assert int(P.sum()) + int(cut.sum()) < 524288
+        _pack_both(stage, P, cu * 3, (cut * 3).astype(np.int32), shift)
+
+
 def test_prefix_pack_full_size_after_rpc_select(stage):
     import paper_2603_06619_amd as nat
     lay = si.batch_layout("qwen3_8b_head_rpc", 2000)
