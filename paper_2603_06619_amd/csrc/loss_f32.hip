@@ -227,23 +227,44 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
+// A row of at most kF32RowRegs * 256 logits stays in registers between the passes over it (kCached: `row`), a longer one is read again: with the loads ahead
+// (f32_token_kernel), whole loss call at V = 4096, H = 256, us: 100 tokens 58.1 -> 55.5, 601 94.5 -> 92.3.
+constexpr int kF32RowRegs = 16;
 struct F32RowSums { float m; double s, t; };
 struct F32RowShared { float m[4]; double s[4], t[4]; };
-__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, F32RowShared& sh) {
+template <bool kCached>
+__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, F32RowShared& sh, float (&row)[kF32RowRegs]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float m = -INFINITY;
+  if (kCached) {
+#pragma unroll
+    for (int i = 0; i < kF32RowRegs; ++i) {
+      const int v = threadIdx.x + i * kF32Threads;
+      row[i] = v < V ? z[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int i = 0; i < kF32RowRegs; ++i) m = fmaxf(m, row[i]);
+  } else {
 #pragma unroll 4
-  for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
+    for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
+  }
   m = wave_max_f(m);
   if (lane == 0) sh.m[wave] = m;
   __syncthreads();
   m = fmaxf(fmaxf(sh.m[0], sh.m[1]), fmaxf(sh.m[2], sh.m[3]));
   double s = 0.0, t = 0.0;
-#pragma unroll 4
-  for (int v = threadIdx.x; v < V; v += kF32Threads) {
-    const float zc = z[v] - m, e = expf(zc);
+  auto add = [&](float x) {
+    const float zc = x - m, e = expf(zc);
     s += (double)e;
     t = fma((double)e, (double)zc, t);
+  };
+  if (kCached) {
+#pragma unroll
+    for (int i = 0; i < kF32RowRegs; ++i)
+      if ((int)threadIdx.x + i * kF32Threads < V) add(row[i]);
+  } else {
+#pragma unroll 4
+    for (int v = threadIdx.x; v < V; v += kF32Threads) add(z[v]);
   }
   s = wave_sum_d(s);
   t = wave_sum_d(t);
@@ -252,6 +273,8 @@ __device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, 
   return F32RowSums{m, (sh.s[0] + sh.s[1]) + (sh.s[2] + sh.s[3]), (sh.t[0] + sh.t[1]) + (sh.t[2] + sh.t[3])};
 }
 
+// One block per token.  Bound by latency: what only the first thread needs (ids, weights, the target's logit) is loaded ahead of the reductions.
+template <bool kCached>
 __global__ void __launch_bounds__(kF32Threads)
 f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_logp, const float* __restrict__ adv,
                  const int32_t* __restrict__ kept_seq, const float* __restrict__ kept_w,
@@ -264,25 +287,32 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
   const int kc = blockIdx.x;                 // token within the chunk
   const int k = chunk_start + kc;
   float* z = dz + (size_t)kc * V;
-  const F32RowSums sums = f32_row_sums(z, V, sh);
+  const int y = ids[k];
+  const bool bad_id = y < 0 || y >= V;
+  float z_y = 0.f, w = 0.f, A = 0.f, old = 0.f, ref = 0.f;
+  if (!bad_id) {
+    z_y = z[y];
+    w = kept_w[k];
+    A = adv[kept_seq[k]];
+    old = old_logp[k];
+    if (klp.beta != 0.f) ref = klp.ref_logp[k];
+  }
+  float row[kF32RowRegs];
+  const F32RowSums sums = f32_row_sums<kCached>(z, V, sh, row);
   if (threadIdx.x == 0) {
-    const double lse = (double)sums.m + log(sums.s);
+    const double log_s = log(sums.s), lse = (double)sums.m + log_s;
     // -sum p log p = log(sum) - (sum of e (z - m)) / sum
-    if (entropy_out) entropy_out[k] = (float)(log(sums.s) - sums.t / sums.s);
-    const int yk = ids[k];
+    if (entropy_out) entropy_out[k] = (float)(log_s - sums.t / sums.s);
     bcast[0] = (float)lse;
-    if (yk < 0 || yk >= V) {                 // no such token: left out (no loss term, zero gradient)
+    if (bad_id) {                            // no such token: left out (no loss term, zero gradient)
       if (logp_out) logp_out[k] = __builtin_nanf("");
       if (kl_out) kl_out[k] = __builtin_nanf("");
       term[k] = 0.f;
       bcast[1] = 0.f;
       if (diag) atomicAdd(diag + NAT_DIAG_BAD_ID, 1);
     } else {
-      const double logp = (double)z[yk] - lse;
-      const float w = kept_w[k];
-      const float A = adv[kept_seq[k]];
-      const TokenScalars ts = grpo_token_scalars(logp, old_logp[k], A, w, eps_lo, eps_hi, grad_scale,
-                                                 klp.beta, klp.kind, klp.beta != 0.f ? klp.ref_logp[k] : 0.f);
+      const double logp = (double)z_y - lse;
+      const TokenScalars ts = grpo_token_scalars(logp, old, A, w, eps_lo, eps_hi, grad_scale, klp.beta, klp.kind, ref);
       if (logp_out) logp_out[k] = (float)logp;
       if (kl_out) kl_out[k] = ts.kl;
       term[k] = w * ts.L;
@@ -295,10 +325,15 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
   }
   __syncthreads();
   const float lse = bcast[0], c = bcast[1];
-  const int y = ids[k];
-  for (int v = threadIdx.x; v < V; v += kF32Threads) {
-    const float sm = expf(z[v] - lse);
-    z[v] = c * ((v == y ? 1.f : 0.f) - sm);
+  auto put = [&](int v, float x) { z[v] = c * ((v == y ? 1.f : 0.f) - expf(x - lse)); };
+  if (kCached) {
+#pragma unroll
+    for (int i = 0; i < kF32RowRegs; ++i) {
+      const int v = threadIdx.x + i * kF32Threads;
+      if (v < V) put(v, row[i]);
+    }
+  } else {
+    for (int v = threadIdx.x; v < V; v += kF32Threads) put(v, z[v]);
   }
 }
 
@@ -332,9 +367,12 @@ nat_status loss_f32_run(const LossArgs& a) {
       const float* hid = (const float*)a.hidden + (size_t)c0 * a.H;
       nat_status st = f32_gemm<false, false>(hid, a.H, (const float*)a.W, a.H, n, a.V, a.H, dz, a.V, 0, s);
       if (st != NAT_OK) return st;
-      f32_token_kernel<<<n, kF32Threads, 0, s>>>(
-          a.ids, a.old_logp, a.adv, a.kept_seq, a.kept_w, c0, a.V, a.eps_lo, a.eps_hi, a.grad_scale,
-          KlArgs{a.ref_logp, a.beta_kl, a.kl_kind}, dz, a.logp, term, a.kl_out, a.entropy_out, a.diag);
+      auto token = [&](auto kernel) {
+        kernel<<<n, kF32Threads, 0, s>>>(a.ids, a.old_logp, a.adv, a.kept_seq, a.kept_w, c0, a.V, a.eps_lo, a.eps_hi, a.grad_scale,
+                                         KlArgs{a.ref_logp, a.beta_kl, a.kl_kind}, dz, a.logp, term, a.kl_out, a.entropy_out, a.diag);
+      };
+      if (a.V <= kF32RowRegs * kF32Threads) token(f32_token_kernel<true>);
+      else token(f32_token_kernel<false>);
       NAT_LAUNCH_CHECK();
       st = f32_gemm<false, true>(dz, a.V, (const float*)a.W, a.H, n, a.H, a.V, (float*)a.dH + (size_t)c0 * a.H, a.H, 0, s);
       if (st != NAT_OK) return st;
@@ -350,13 +388,15 @@ nat_status loss_f32_run(const LossArgs& a) {
 
 
 // Forward pass alone: log-prob of the target and entropy of one token per block.
+template <bool kCached>
 __global__ void __launch_bounds__(kF32Threads)
 f32_logp_kernel(const float* __restrict__ z_scratch /*[chunk, V]*/, const int32_t* __restrict__ ids, int chunk_start, int V,
                 float* __restrict__ logp_out, float* __restrict__ entropy_out, int32_t* __restrict__ diag) {
   __shared__ F32RowShared sh;
   const int kc = blockIdx.x, k = chunk_start + kc;
   const float* z = z_scratch + (size_t)kc * V;
-  const F32RowSums sums = f32_row_sums(z, V, sh);
+  float row[kF32RowRegs];
+  const F32RowSums sums = f32_row_sums<kCached>(z, V, sh, row);
   if (threadIdx.x == 0) {
     const int yk = ids[k];
     if (yk < 0 || yk >= V) {
@@ -389,7 +429,8 @@ nat_status logp_f32_run(const LogpArgs& a) {
     const nat_status st = f32_gemm<false, false>((const float*)a.hidden + (size_t)c0 * a.H, a.H, (const float*)a.W, a.H, n,
                                                  a.V, a.H, (float*)a.ws, a.V, 0, s);
     if (st != NAT_OK) return st;
-    f32_logp_kernel<<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
+    if (a.V <= kF32RowRegs * kF32Threads) f32_logp_kernel<true><<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
+    else f32_logp_kernel<false><<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
     NAT_LAUNCH_CHECK();
   }
   return NAT_OK;

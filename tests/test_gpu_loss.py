@@ -85,6 +85,23 @@ def test_fp32_contraction_remainders(stage, n_tok, H, V):
     check(hip_loss(stage, case, "f32"), ref, n_tok, TOL_F32, case)
 
 
+@pytest.mark.parametrize("V", [255, 4095, 4096, 4097])
+def test_fp32_rows_kept_in_registers_and_read_again(stage, V):
+    # up to 4096 logits of a token stay in registers, 16 to a thread; an id outside the vocabulary among the tokens
+    case = make_loss_case(1000 + V, 19, 48, V, "f32")
+    check(hip_loss(stage, case, "f32"), oracle_loss(**case), 19, TOL_F32, case)
+    ids = case["ids"].copy()
+    ids[[0, 7]] = [V, -1]
+    keep = np.delete(np.arange(19), [0, 7])
+    out = hip_loss(stage, dict(case, ids=ids), "f32", want_entropy=True)
+    part = {k: (v[keep] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
+    ref = oracle_loss(**part)
+    assert max_rel_err(out["dW"].cpu().numpy(), ref["dW"]) <= TOL_F32
+    assert bool(torch.isnan(out["logp"][[0, 7]]).all()) and bool((out["dH"][[0, 7]] == 0).all())
+    fwd = stage.logp(to_dev(case["hidden"]), to_dev(case["W"]), to_dev(ids), 19, want_entropy=True)
+    assert torch.equal(fwd["logp"][keep], out["logp"][keep]) and torch.equal(fwd["entropy"][:19], out["entropy"][:19])
+
+
 def test_fp32_vocabulary_beyond_the_columns_of_one_launch(stage):
     # the contractions take 2^20 columns of the logits to a launch.  (Whole tensors only: a wavefront's chain of 2^17 terms of dH
     # rounds by up to 2^17 x 2^-24 of the sum of their magnitudes, 8e-3 of the small part that check() takes alone)
