@@ -264,7 +264,7 @@ constexpr size_t compact_ws_bytes(int64_t N) {
   return (((size_t)(2 * n_tiles_of(N) + 1) * sizeof(int32_t) + 255) / 256) * 256 + 256;
 }
 
-// Scratch of nat_compact_static: the tile counts and offsets of up to NAT_COMPACT_STATIC_MAX_TOKENS
+// Scratch of nat_compact_static: the counts of tiles and groups of up to NAT_COMPACT_STATIC_MAX_TOKENS
 // tokens (about 513 KiB), resident on every GPU the library runs on until the process ends.  In host
 // code this name stands for the symbol, not for a device address: the address on each device comes
 // from hipGetSymbolAddress (static_scratch below) and only that pointer is handed to kernels.

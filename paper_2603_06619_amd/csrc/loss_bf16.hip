@@ -700,8 +700,8 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   } else {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
-    // computes only those (whole call with 256 / 128 / 64 columns, us: loss at the 8B head 60 tokens 1091 / 1015 / 988, 100 1119 / 1038, 1100
-    // 3557 / 3479).
+    // computes only those (of five columns or more: fewer are as wide as they need, column_blocks.  Loss at the 8B head, 1100 tokens, with 256 / 128
+    // columns 3557 / 3479 us).
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
       const int blocks = last_blocks(epi.n_valid, g.tiles_n);
       if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {

@@ -48,7 +48,8 @@ inline int walk_length(int units, int kt) {
 // dW at H = 4096 with 300 tokens 694 / 612, 1237 (accumulating) 1731 / 1628, 8192 7058 / 7021, but 16384 (accumulating) 14182 / 14182.  dH has two rounds
 // of thousands of slices: one unit each.
 constexpr int kLogitsWalkSlices = 128, kDWeightWalkSlices = 256;
-// A short last tile (last < 8 blocks) is computed by workgroups of one unit, so the whole launch is: what the short tile saves falls with
+// A short last tile (last < 8 blocks; of columns of 256, which calls of few tokens that read W as it is do not have) is computed by workgroups of one
+// unit, so the whole launch is: what the short tile saves falls with
 // the number of tile columns, what walking saves does not.  Short last tile / walked whole, log-probs of 256 (columns - 1) + 45 tokens at
 // V = 151936, us: H = 64 2 columns 45.7 / 48.9, 3 63.3 / 63.0, 5 100 / 96; 256 5 133 / 137, 6 157 / 156, 8 208 / 201; 512 7 256 / 269, 8 295 / 297,
 // 9 330 / 327; 1024 7 419 / 434, 8 496 / 499, 9 540 / 542, 17 1031 / 1008, 33 1986 / 1904; 2048 8 903 / 915, 9 1019 / 1014; 4096 8 1717 / 1749,
