@@ -825,7 +825,7 @@ struct LogitsEpilogue {
           if (!all_rows_valid) {                           // only the last vocabulary tile pays for the row check
 #pragma unroll
             for (int r = 0; r < 8; ++r)
-              if (v0 + j * 32 + 8 * g + r >= V) e[r] = 0.f;
+              if (v0 + j * 32 + 8 * g + r >= V) e[r] = x2[r] = 0.f;    // x2 too: it may be infinite or NaN, and no sum would tell
           }
 #pragma unroll
           for (int r = 0; r < 8; ++r) {

@@ -267,6 +267,34 @@ def test_bound_of_the_shift_where_it_acts(stage, n_tok, V):
     assert torch.equal(out["dH"][:n_tok][~torch.from_numpy(far)], tame_out["dH"][:n_tok][~torch.from_numpy(far)])
 
 
+@pytest.mark.parametrize("n_tok,H,V", [(40, 64, 257), (300, 128, 1100), (150, 192, 1408), (8300, 64, 1025)])
+def test_entropy_where_the_last_row_or_a_token_is_no_number(stage, n_tok, H, V):
+    # rows past the vocabulary in the last tile (copies of its last row where W is read in place, zeros in a repacked W) add nothing to the entropy,
+    # whatever the logits: V % 256 is 1 to 128, so that a whole granule of 128 rows is such.  An infinite or NaN logit counts as one at the bound, 70
+    # above the target's, and a token that is NaN has V of them: its entropy is log V.  Expected in fp64; fp32 sums near 70 e^70: 1e-4
+    case = make_loss_case(43, n_tok, H, V, "bf16", noise=0.1, w_std=0.1)
+    h, ids = case["hidden"].copy(), np.minimum(case["ids"], V - 2).astype(np.int32)
+    h[:, 0] = np.abs(h[:, 0]) + 0.25
+    Z = h.astype(np.float64) @ case["W"].astype(np.float64).T
+    x = Z - Z[np.arange(n_tok), ids][:, None]
+    x[:, V - 1] = 70.0
+    E = np.exp(x)
+    expect = np.log(E.sum(axis=1)) - (E * x).sum(axis=1) / E.sum(axis=1)
+    hd, W = to_dev(h, torch.bfloat16), to_dev(case["W"], torch.bfloat16)
+    for value in (float("inf"), float("nan")):
+        broken = W.clone()
+        broken[V - 1, 0] = value
+        if n_tok < 8192:                                  # repacked, the rows past it are zeros
+            got = stage.logp(hd, broken, to_dev(ids), n_tok, want_entropy=True)["entropy"].cpu().numpy()[:n_tok]
+            assert np.abs(got - expect).max() <= 1e-4, value
+    hd[::3] = float("nan")
+    tame = stage.logp(to_dev(h, torch.bfloat16), W, to_dev(ids), n_tok, want_entropy=True)["entropy"].clone()
+    got = stage.logp(hd, W, to_dev(ids), n_tok, want_entropy=True)["entropy"]
+    assert np.abs(got[:n_tok:3].cpu().numpy() - np.log(V)).max() <= 1e-4
+    others = torch.arange(n_tok) % 3 != 0
+    assert torch.equal(got[:n_tok][others], tame[:n_tok][others])
+
+
 @pytest.mark.parametrize("memory", ["pinned", "inside pinned", "pageable"])
 def test_counts_reach_host_memory_of_any_kind(stage, memory):
     # a kernel writes them where it can, and they are copied elsewhere; nothing beside them is touched
