@@ -700,8 +700,8 @@ mfma_nt_kernel(GemmArgs g, Epilogue epi) {
   } else {
     const int id = (int)blockIdx.x;
     // Where W is read as it is the batch is short and the columns are its tokens: a last tile with at most 128 or 64 of them
-    // computes only those (of five columns or more: fewer are as wide as they need, column_blocks.  Loss at the 8B head, 1100 tokens, with 256 / 128
-    // columns 3557 / 3479 us).
+    // computes only those (where the columns are not all narrower, logits_columns_pay and dh_columns_pay.  Loss at the 8B head, 1100 tokens, with 256 /
+    // 128 columns 3557 / 3479 us).
     if constexpr (kA == Src::kRows || kA == Src::kKMajorRows) {
       const int blocks = last_blocks(epi.n_valid, g.tiles_n);
       if (blocks < 8 && unit_of(g, id).tn == g.tiles_n - 1) {
@@ -1350,18 +1350,6 @@ static RangeCut range_cut(int tiles, int kt_all, int align) {
 static int direct_tokens(int H) { return H % kBN == 0 ? 7168 : 6144; }
 static int direct_tokens_forward(int H) { return H >= kBN ? 24576 : 8192; }
 
-// Width of the token columns, 32 * blocks each, of a call that reads W as it is: up to seven columns are as wide as their tokens need (dW
-// reads whole pairs of 32-token slices), so that no tile is a nearly empty one, and where that leaves room in LDS the ring holds six slices:
-// such a launch waits for W, and what is in flight of it decides, the less so as the columns that share its rows ask for the same.  Columns of 256
-// with a short last one / equal ones / the same with six slices, whole log-prob call, us: H = 1024 40 tokens 76.5 / 74.1 / 70.4, 150 93.5 / 85.6 /
-// 85.6, 301 117.3 / 117.4 / 110.8, 600 192.8 / 186.3, 1300 368 / 349; H = 4096 150 314.7 / 289.4 / 289.3, 301 403.7 / 415.7 / 393.3, 560 655 / 628, 1070
-// 1098 / 1084; H = 2048, V = 20000 300 46.6 / 37.7 / 38.0; H = 64, V = 3000 150 16.6 / 15.2 / 15.4.  dH, a short last column / equal ones: H = 1024 150
-// tokens 109 / 100, 300 188 / 155, 600 240 / 221; H = 4096 300 459 / 456, 1070 1070 / 1057.
-static int column_blocks(int n_valid, int tiles_n) {
-  const int per_block = 32 * tiles_n;
-  return (int)((round_up(n_valid, 64) + per_block - 1) / per_block);
-}
-
 // launch(integral_constant) with the number of blocks that is built for so many: 2, 4, 5, 6 or 7
 template <class F>
 static void with_blocks(int blocks, F&& launch) {
@@ -1381,8 +1369,8 @@ static nat_status launch_logits(const uint16_t* W, const uint16_t* Wb, const uin
   GemmArgs g{Wb ? Wb : W, Hb, H, Vp / kBM, tiles_n, NAT_GROUP_LOGITS, 0, H / kBK, 1, 0, 0, V, H, 1};
   const int units = g.tiles_m * g.tiles_n;
   const int blocks = Wb ? 8 : column_blocks(epi.n_valid, tiles_n);
-  if (blocks < 8) {
-    g.walk = walk_length(units, H / kBK);                     // also beyond kLogitsWalkSlices (H = 5120: 40 tokens 324.8 one tile each, 323.2; 301 557.5 / 552.7)
+  if (logits_columns_pay(blocks, tiles_n, g.tiles_m, H / kBK)) {
+    g.walk = walk_length(units, H / kBK);                     // also beyond kLogitsWalkSlices (one or two columns there: within 1 % of one tile each)
     with_blocks(blocks, [&](auto nb) {
       mfma_nt_kernel<Epi, Src::kRows, Src::kBlocked, false, true, decltype(nb)::value><<<walk_grid(units, g.walk), 256, 0, s>>>(g, epi);
     });
@@ -1494,7 +1482,7 @@ nat_status loss_bf16_run(const LossArgs& a) {
           g.tiles_n = snp / kBN;
           DHiddenEpilogue<false> e{snv, H, dH_s, beta + s0, dh_part};
           const int blocks = column_blocks(snv, g.tiles_n);
-          if (blocks < 8) {
+          if (dh_columns_pay(blocks, g.tiles_n, g.tiles_m, Vp / kBK)) {
             with_blocks(blocks, [&](auto nb) {
               constexpr int kNB = decltype(nb)::value;
               mfma_nt_kernel<DHiddenEpilogue<false>, Src::kKMajorRows, Src::kBlocked, false, false, kNB><<<cut.grid, 256, 0, s>>>(g, e);

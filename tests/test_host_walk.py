@@ -45,6 +45,27 @@ int main() {
   for (int kt = 2; kt <= 128; kt += 2)
     for (int last = 2; last < 8; last += 2)
       if (logits_walk(594 * 2, kt, last, 2) != 1 || logits_walk(594 * 9, kt, last, 9) < 2) return std::printf("short tile, %d slices\n", kt), 1;
+  // equal token columns: as many blocks as the tokens need, never more than the columns of 256 hold, and none for ordinary widths
+  for (int n = 1; n <= 7168; ++n) {
+    const int tiles = (n + kBN - 1) / kBN, blocks = column_blocks(n, tiles);
+    const bool narrow = n <= 192 || (n > 256 && n <= 448) || (n > 512 && n <= 640) || (n > 768 && n <= 896) || (n > 1024 && n <= 1088) || (n > 1280 && n <= 1344);
+    if (blocks > 8 || blocks * 32 * tiles < (n + 63) / 64 * 64 || (blocks < 8) != narrow) return std::printf("%d tokens: %d blocks\n", n, blocks), 1;
+    if (blocks == 8 && (logits_columns_pay(8, tiles, 36, 32) || dh_columns_pay(8, tiles, 4, 288))) return std::printf("%d tokens, width of 256\n", n), 1;
+  }
+  // where both sides were timed: {tokens, H, V, equal columns of the logits, of dH}
+  const struct { int n, H, V; bool logits, dh; } timed[] = {
+      {100, 2048, 1000, false, true}, {128, 1024, 3000, false, true}, {1, 1024, 700, false, true}, {65, 1024, 32000, true, true}, {40, 64, 151936, true, true},
+      {150, 192, 1000, true, true}, {150, 4096, 151936, true, true}, {300, 5120, 151936, true, true}, {301, 1024, 151936, true, true}, {330, 2048, 151936, true, true},
+      {330, 4096, 151936, false, true}, {330, 5120, 32000, false, true}, {330, 5120, 20000, true, true}, {330, 4096, 64000, true, true}, {448, 5120, 151936, true, true}, {513, 4096, 151936, true, true}, {640, 1024, 32000, true, true},
+      {513, 5120, 151936, false, false}, {600, 5120, 9000, true, true}, {769, 1024, 151936, false, true}, {832, 2048, 151936, false, true}, {832, 5120, 151936, false, false},
+      {800, 64, 151936, true, true}, {800, 1024, 20000, false, true}, {800, 320, 20000, false, true}, {800, 1024, 32000, true, true}, {800, 4096, 100000, false, true},
+      {1025, 2048, 32000, false, true}, {1025, 1024, 16000, false, true}, {1088, 5120, 151936, false, false}, {1088, 1024, 151936, true, true}, {1025, 4096, 9000, true, true},
+      {1300, 4096, 151936, true, true}, {1300, 5120, 151936, false, false}};
+  for (auto t : timed) {
+    const int tiles = (t.n + kBN - 1) / kBN, blocks = column_blocks(t.n, tiles), rows = (t.V + 255) / 256;
+    if (logits_columns_pay(blocks, tiles, rows, t.H / 32) != t.logits || dh_columns_pay(blocks, tiles, (t.H + 255) / 256, rows * 8) != t.dh)
+      return std::printf("columns of %d tokens, H = %d, V = %d\n", t.n, t.H, t.V), 1;
+  }
   return 0;
 }
 """
