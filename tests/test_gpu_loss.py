@@ -32,9 +32,10 @@ def stage():
     return LossStage(DEV)
 
 
-def check(out, ref, n, tol, case=None, logp_atol=None, label=None):
-    """Whole-tensor bounds, and (given the case's inputs) the contraction-only bounds."""
+def check(out, ref, n, tol, case=None, logp_atol=None, label=None, all_zero=False):
+    """Whole-tensor bounds, and (given the case's inputs) the contraction-only bounds.  all_zero: every advantage is 0."""
     bf16 = tol == TOL_BF16
+    assert all_zero != bool(np.abs(ref["dH"]).max() > 0 and np.abs(ref["dW"]).max() > 0), "gradients of zero check nothing"
     tol_loss = TOL_LOSS_BF16 if bf16 else tol
     e_loss = abs(out["loss"].item() - ref["loss"]) / max(abs(ref["loss"]), 1e-300)
     assert e_loss <= tol_loss + 1e-12, ("loss", e_loss)
@@ -133,7 +134,7 @@ def test_bf16_path_small_shapes(stage, n_tok, H, V):
     case = make_loss_case(100 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
     ref = oracle_loss(**case)
     out = hip_loss(stage, case, "bf16")
-    check(out, ref, n_tok, TOL_BF16, case)
+    check(out, ref, n_tok, TOL_BF16, case, all_zero=n_tok == 1)
 
 
 def test_bf16_grad_scale_and_eps(stage):
@@ -240,7 +241,8 @@ def test_bf16_hidden_size_not_a_multiple_of_the_tile(stage):
 
 @pytest.mark.parametrize("n_tok", [31, 128, 129, 384, 385, 640])
 def test_bf16_last_token_tile_half_full(stage, n_tok):
-    # a last token tile with at most 128 tokens computes only its first 128 columns (logits, and dH whole and in ranges)
+    # one token tile, half full or full, of a W that stays in the caches computes its first 64 or 128 columns of 256; tiles of several
+    # columns are equal ones, 192 and 224 wide (logits, and dH whole and in ranges)
     for H, V in ((192, 1000), (64, 9000)):
         case = make_loss_case(500 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
         ref = oracle_loss(**case)
@@ -249,7 +251,7 @@ def test_bf16_last_token_tile_half_full(stage, n_tok):
 
 @pytest.mark.parametrize("n_tok", [1, 64, 65, 320, 321])
 def test_bf16_last_token_tile_a_quarter_full(stage, n_tok):
-    # a last token tile with at most 64 tokens computes only its first 64 columns; log-probs alone and with the loss are equal
+    # one token tile of at most 64 or 128 tokens, and two equal ones 160 and 192 wide; log-probs alone and with the loss are equal
     for H, V in ((192, 1000), (64, 9000)):
         case = make_loss_case(530 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
         out = hip_loss(stage, case, "bf16")
@@ -286,7 +288,7 @@ def test_bf16_workgroups_walk_several_tiles(stage, n_tok, H, V):
 
 @pytest.mark.parametrize("n_tok", [513, 769, 1025, 1124])
 def test_bf16_nearly_empty_last_token_tile_of_several(stage, n_tok):
-    # H = 64: with three tile columns the short last tile has workgroups of its own, with more the workgroups walk it as a whole one;
+    # H = 64: three to five equal columns, and (1124) five of 256, whose short last tile the workgroups walk as a whole one;
     # entropies too, and the log-probs of the tokens in front of it have the bits that they have without it
     H, V = 64, 40000
     case = make_loss_case(560 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
@@ -302,7 +304,7 @@ def test_bf16_nearly_empty_last_token_tile_of_several(stage, n_tok):
 
 @pytest.mark.parametrize("H,V", [(64, 66000), (128, 700), (448, 66000)])
 def test_bf16_tile_columns_of_every_width(stage, H, V):
-    # up to seven equal tile columns of 64, 128, 160, 192, 224 or 256 tokens, four or six slices in flight, with 2, 4 and 14 slices per tile
+    # up to six equal tile columns of 64, 128, 160, 192 or 224 tokens, four or six slices in flight, or columns of 256, with 2, 4 and 14 slices per tile
     # and walks of one or two: log-probs and entropies of the first n tokens have the bits that they have among 1800 (columns of 256)
     case = make_loss_case(800 + H, 1800, H, V, "bf16", noise=0.15, w_std=0.1)
     hidden, W, ids = to_dev(case["hidden"], torch.bfloat16), to_dev(case["W"], torch.bfloat16), to_dev(case["ids"])
@@ -314,8 +316,40 @@ def test_bf16_tile_columns_of_every_width(stage, H, V):
         some = stage.logp(hidden[:n], W, ids[:n], n, want_entropy=True)
         for k in ("logp", "entropy"):
             assert torch.equal(some[k][:n], all_of_it[k][:n]), (n, k)
-    part = {k: (v[:161] if k in ("hidden", "ids", "old_logp", "kept_seq", "kept_w") else v) for k, v in case.items()}
-    check(hip_loss(stage, part, "bf16"), oracle_loss(**part), 161, TOL_BF16, part)
+
+
+@pytest.mark.parametrize("n_tok", [40, 100, 161, 260, 321, 448, 513, 640, 800, 1025, 1300])
+@pytest.mark.parametrize("H,V", [(64, 4000), (320, 1500)])
+def test_bf16_gradients_of_every_column_width(stage, n_tok, H, V):
+    # dH and dW where the token columns are 64, 128 (dH alone; the logits of so small a W are not), 192, 160, 192, 224, 192, 224, 224, 224 and 224 wide,
+    # one to six of them
+    case = make_loss_case(840 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1)
+    hip_loss(stage, case, "bf16")
+    stage._ws["loss"].fill_(255)
+    check(hip_loss(stage, case, "bf16"), oracle_loss(**case), n_tok, TOL_BF16, case)
+
+
+@pytest.mark.parametrize("n_tok,H,V", [
+    (1124, 192, 3000),       # five columns, 100 tokens in the last: its first 128 columns
+    (1100, 320, 17000),      # more tiles than compute units
+    (1800, 448, 3000),       # eight columns, 8 tokens in the last: its first 64
+    (1580, 4160, 1000),      # seven columns, 44 in the last, 130 slices per tile
+    (600, 4160, 22100),      # three columns that are no equal ones: more tiles than compute units and more than 128 slices
+])
+def test_bf16_short_last_token_tile_beside_whole_ones(stage, n_tok, H, V):
+    # a last token tile with at most 128 or 64 tokens has workgroups of its own that compute only its first 128 or 64 columns.  Loss and
+    # gradients of all tokens against the oracle, and the entropies of those in the last tile
+    case = make_loss_case(870 + n_tok, n_tok, H, V, "bf16", noise=0.15, w_std=0.1 if H < 4096 else 0.02)
+    hip_loss(stage, case, "bf16")
+    stage._ws["loss"].fill_(255)
+    out = hip_loss(stage, case, "bf16", want_entropy=True)
+    ref = oracle_loss(**case)
+    check(out, ref, n_tok, TOL_BF16, case)
+    last = slice((n_tok - 1) // 256 * 256, n_tok)
+    assert max_rel_err(out["dH"][last].float().cpu().numpy(), ref["dH"][last]) <= TOL_BF16
+    from oracle import grpo as ogrpo
+    ent = ogrpo.forward_logp(case["hidden"][last], case["W"], case["ids"][last])["entropy"]
+    assert max_rel_err(out["entropy"][last].cpu().numpy(), ent) <= 1e-4
 
 
 def accumulated_and_plain(stage, n_tok, H, V):
