@@ -180,8 +180,12 @@ def test_compaction_where_counting_changes(stage, n_tiles, extra, B):
         if k.startswith("kept"):
             assert bool((v[nk:] == -1).all()), k
     # the same tokens weighted by given probabilities
+    for v in again.values():
+        v.fill_(-1)
     pi = torch.full((N,), 0.4, dtype=torch.float64, device=DEV)
     nat.nat_compact_pi(B, h["mask_bits"], pi, to_dev(cu), B, N, *again.values(), None,
                        torch.empty(nat.compact_workspace_bytes(N), dtype=torch.uint8, device=DEV))
     for k, v in again.items():
         assert torch.equal(v[:nk], h[k][:nk]) or (k == "kept_w" and float((v[:nk] / h[k][:nk] - 1).abs().max()) <= 2.0 ** -23), k
+        if k.startswith("kept"):
+            assert bool((v[nk:] == -1).all()), k
