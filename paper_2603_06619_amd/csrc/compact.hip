@@ -17,7 +17,11 @@ namespace nat {
 
 constexpr int kTileTokens = 4096;                 // tokens per scatter block
 constexpr int kTileWords = kTileTokens / 32;      // 128 mask words
-constexpr int kGroupTiles = 16;                   // tiles whose counts are also added up, one block of the count pass
+// Tiles whose counts are also added up, one block of the count pass: every tile adds up all groups before its own, so beyond kLongTiles (2^28 tokens)
+// the groups are longer.  Compaction, us, a scan launch / groups of 16 / of 256: 2^29 tokens 1490 / 1488 / 1382, with ids and log-probs 2798 / 2433 / 2521; 2^30
+// 3036 / 3278 / 2832, 6187 / 5335 / 5373; 2^31 6280 / 8335 / 6039, 11253 / 12509 / 10148, one token in a hundred kept 4262 / 6271 / 4012.
+constexpr int kGroupTiles = 16, kLongGroupTiles = 256, kLongTiles = 65536;
+constexpr int group_tiles_of(int64_t n_tiles) { return n_tiles > kLongTiles ? kLongGroupTiles : kGroupTiles; }
 // Up to kInlineTiles (two million tokens, 256 KiB of mask) a scatter block counts the mask words before its own tile and
 // there is no count launch; beyond, it adds up the counts of the groups before its own and of the tiles before it in its group.
 // Up to there the block also has sixteen wavefronts of 256 tokens, not four of 1024: with few
@@ -40,19 +44,23 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 }
 
 // tile_count[b] = number of kept tokens among packed positions [b*4096, (b+1)*4096), one wavefront per tile; group_count[g] = the sum of
-// 16 of them, one block per group.  (A scan of the tile counts by one block, a launch of its own that every tile waited for, took 17 us
-// at 2^26 tokens.)
+// group_tiles of them, one block per group, 16 tiles at a time.  (A scan of the tile counts by one block, a launch of its own that every tile waited
+// for, took 17 us at 2^26 tokens.)
 __global__ void __launch_bounds__(kGroupTiles * 64)
-compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, int n_tiles,
+compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, int n_tiles, int group_tiles,
                      int32_t* __restrict__ tile_count, int32_t* __restrict__ group_count) {
   __shared__ int count[kGroupTiles];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tile = blockIdx.x * kGroupTiles + wave;
-  const int64_t w = (int64_t)tile * kTileWords + 2 * lane;      // n_words is even
-  const int c = wave_sum(w < n_words ? __popc(mask_bits[w]) + __popc(mask_bits[w + 1]) : 0);
-  if (lane == 0) {
-    count[wave] = c;
-    if (tile < n_tiles) tile_count[tile] = c;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int mine = 0;
+#pragma unroll 4
+  for (int t = wave; t < group_tiles; t += kGroupTiles) {
+    const int tile = blockIdx.x * group_tiles + t;
+    const int64_t w = (int64_t)tile * kTileWords + 2 * lane;    // n_words is even
+    const int c = wave_sum(w < n_words ? __popc(mask_bits[w]) + __popc(mask_bits[w + 1]) : 0);
+    if (lane == 0 && tile < n_tiles) tile_count[tile] = c;
+    mine += c;
   }
+  if (lane == 0) count[wave] = mine;
   __syncthreads();
   if (wave == 0) {
     const int sum = wave_sum(lane < kGroupTiles ? count[lane] : 0);
@@ -82,6 +90,7 @@ struct ScatterArgs {
   const uint32_t* mask_bits; int64_t n_words; int64_t n_tokens; int64_t kept_cap;
   const int64_t* cu; int B;
   const int32_t* tile_count; const int32_t* group_count;        // of the count pass; or NULL: the block counts the mask words
+  int group_tiles;
   int mask_wide;                                                // mask_bits is 16-byte aligned
   int32_t* kept_idx; int32_t* kept_seq; float* kept_w; int32_t* cu_kept; int32_t* n_kept; int32_t* h_n_kept /*pinned, or NULL*/;
   const int32_t* ids; int32_t* ids_k; const float* old_logp; float* old_logp_k;
@@ -128,9 +137,9 @@ compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
 
   int before = 0;
   if (c.group_count) {
-    const int group = tile / kGroupTiles, first = group * kGroupTiles;
+    const int group = tile / c.group_tiles, first = group * c.group_tiles;
     for (int j = tid; j < group; j += kThreads) before += c.group_count[j];
-    if (tid < tile - first) before += c.tile_count[first + tid];
+    for (int j = first + tid; j < tile; j += kThreads) before += c.tile_count[j];
   } else if (c.mask_wide) {
     const uint4* q = reinterpret_cast<const uint4*>(c.mask_bits);
 #pragma unroll 4
@@ -329,12 +338,14 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
     ProfScope prof(PC_COMPACT, s, !c.no_timing);
     if (n_tiles > 0) {
       const bool count = n_tiles > kInlineTiles;
+      const int group_tiles = group_tiles_of(n_tiles);
       if (count) {
-        compact_count_kernel<<<(unsigned)((n_tiles + kGroupTiles - 1) / kGroupTiles), 1024, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, tile_count, group_count);
+        compact_count_kernel<<<(unsigned)((n_tiles + group_tiles - 1) / group_tiles), kGroupTiles * 64, 0, s>>>(c.mask_bits, n_words, (int)n_tiles, group_tiles,
+                                                                                                           tile_count, group_count);
         NAT_LAUNCH_CHECK();
       }
       const ScatterArgs sc{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B,
-                           count ? tile_count : nullptr, count ? group_count : nullptr, ((uintptr_t)c.mask_bits & 15) == 0,
+                           count ? tile_count : nullptr, count ? group_count : nullptr, group_tiles, ((uintptr_t)c.mask_bits & 15) == 0,
                            c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept, pinned, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
       if (count && c.pi) compact_scatter_kernel<4, true><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
       else if (count) compact_scatter_kernel<4, false><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);

@@ -69,3 +69,29 @@ def test_large_batch_properties_and_samples(big, scheme, kw):
         w_dev = sc["kept_w"][int(cuk[i]):int(cuk[i]) + len(kept_t)].cpu().numpy()
         w_ref = osel.ht_weights_rollout(scheme, T, kept_t, B, p=kw.get("p", 1.0), C=kw.get("C", 1))
         assert np.array_equal(w_dev.view(np.uint32), w_ref.view(np.uint32)), int(i)
+
+
+@pytest.mark.parametrize("extra", [0, 1, 4096 * 300 + 77])
+def test_compaction_where_groups_of_tiles_grow_longer(extra):
+    # beyond 2^28 tokens (65536 tiles) the counts are added up in groups of 256 tiles, not 16; 300 tiles more end inside a group.  Kept positions,
+    # rollouts and offsets against the mask itself
+    import paper_2603_06619_amd as nat
+    B, N = 300, (1 << 28) + extra
+    rng = np.random.default_rng(5)
+    cu = torch.from_numpy(np.concatenate([[0], np.sort(rng.integers(0, N + 1, B - 1)), [N]]).astype(np.int64)).to(DEV)
+    i32 = lambda n: torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    cap = N // 32
+    mask, cut, idx, seq, cuk, nk = i32(nat.mask_words(N)), i32(B), i32(cap), i32(cap), i32(B + 1), i32(1)
+    w = torch.empty(cap, device=DEV)
+    params = nat.SelectParams(nat.URS, p=1.0 / 64, seed=3, step=1)
+    nat.nat_select(params, cu, B, N, cut, mask)
+    nat.nat_compact(params, B, mask, cu, B, N, idx, seq, w, cuk, nk, None,
+                    torch.full((nat.compact_workspace_bytes(N),), 255, dtype=torch.uint8, device=DEV))
+    shift = torch.arange(32, dtype=torch.int32, device=DEV)
+    pos = torch.cat([torch.nonzero(((mask[a:a + (1 << 20)].unsqueeze(1) >> shift) & 1).reshape(-1)).reshape(-1) + 32 * a
+                     for a in range(0, mask.numel(), 1 << 20)])
+    n = pos.numel()
+    assert int(nk.item()) == n and N // 80 < n < cap
+    assert torch.equal(idx[:n].to(torch.int64), pos) and bool((idx[n:] == -1).all())
+    assert torch.equal(cuk.to(torch.int64), torch.searchsorted(pos, cu))
+    assert torch.equal(seq[:n].to(torch.int64), torch.searchsorted(cu, pos, right=True) - 1)
