@@ -47,7 +47,7 @@ __global__ void fill_zero_kernel(float4* __restrict__ p4, size_t n4, float* __re
 }
 
 int32_t* pinned_words(int32_t* h) {
-  if (!h) return nullptr;
+  if (!h || hipPeekAtLastError() != hipSuccess) return nullptr;      // an error of the caller's: the launch that follows reports it
   hipPointerAttribute_t at{};
   int dev = -1;
   if (hipPointerGetAttributes(&at, h) != hipSuccess) {

@@ -3,6 +3,8 @@ include/nat.h declares, and rejects bad arguments before launching anything."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -198,3 +200,35 @@ def test_profile_interface(lib):
     cnt = (ctypes.c_int64 * n)()
     assert lib.nat_profile_collect(ms, cnt, n) == 0 and sum(cnt) == 0
     assert lib.nat_profile_collect(ms, cnt, 1) == 1
+
+
+STUBBED_RUNTIME = r"""
+#include <stdint.h>
+#include <stdio.h>
+// the library's calls bind to these: a runtime that knows no host memory, and whose last error is a variable
+static int last;
+extern "C" int hipPointerGetAttributes(void*, const void*) { return last = 1; }
+extern "C" int hipGetLastError() { const int e = last; last = 0; return e; }
+extern "C" int hipPeekAtLastError() { return last; }
+extern "C" int hipGetDevice(int* d) { *d = 0; return 0; }
+namespace nat { int32_t* pinned_words(int32_t* h); }
+int main() {
+  int32_t word = 0;
+  if (nat::pinned_words(&word) || last) return printf("no error pending: %d left\n", last), 1;
+  last = 101;
+  if (nat::pinned_words(&word) || last != 101) return printf("the caller's error: %d left\n", last), 1;
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_a_pending_error_of_the_caller_outlives_the_look_at_its_host_words(lib, tmp_path):
+    # the launch behind it is what reports the error; the look at the memory neither hides nor replaces it
+    import paper_2603_06619_amd as nat
+    src, exe = tmp_path / "pending.cpp", tmp_path / "pending"
+    src.write_text(STUBBED_RUNTIME)
+    path = os.path.abspath(nat.library_path())
+    subprocess.run(["g++", "-rdynamic", str(src), path, "-Wl,-rpath," + os.path.dirname(path), "-Wl,--allow-shlib-undefined", "-o", str(exe)], check=True)
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
+    assert run.returncode == 0, run.stdout
