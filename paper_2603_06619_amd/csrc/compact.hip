@@ -28,6 +28,16 @@ constexpr int group_tiles_of(int64_t n_tiles) { return n_tiles > kLongTiles ? kL
 // blocks the chain of loads of one wavefront is the kernel's time.  Whole selection with the line at 256 / 512 / 1024 tiles, us: 320 tiles 24.7 /
 // 19.0 / 19.1; 450 tiles of 550-token rollouts 32.5 / 29.3 / 29.3; 980 tiles 35.4 / 35.6 / 43.9, Poisson 45.9 / 45.9 / 52.3.
 constexpr int kInlineTiles = 512;
+// With given probabilities, which take the registers, 1280 blocks of four wavefronts are resident at a time (waves_per_simd), and a launch of a few more
+// takes twice as long: up to kEightTiles eight wavefronts of 512 tokens a block.  Compaction of rollouts of 20 / 400 / 16384 tokens with ids and log-probs,
+// us, four / eight: 1300 tiles 63.6 / 53.0, 43.9 / 42.6, 33.8 / 33.5; 1536 71.3 / 57.0, 47.9 / 44.0, 36.7 / 37.1; 1792 76.1 / 63.2, 51.3 / 48.8, 40.9 / 41.6; 3500 144 / 136, 107 / 108, 91 /
+// 93; 16384 608 / 581, 435 / 449, 382 / 391.
+constexpr int kEightTilesFrom = 1280, kEightTiles = 1792;
+// Wavefronts per SIMD that the registers of a kernel have to leave room for: a launch that is just over one round of the blocks that the chip holds takes
+// twice as long.  Four wavefronts a block, rollouts of 20 / 400 / 16384 tokens, us, as the compiler likes it / so: 1700 tiles 70.5 / 57.7, 44.7 / 38.7, 33.6 / 31.2, with
+// probabilities 1025 tiles 56.9 / 47.2, 39.6 / 33.0, 28.3 / 27.3; no slower anywhere from 700 to 16384 tiles.  (All eight: 16384 tiles of 1500 tokens 326 / 349; with
+// probabilities seven, which spills: +15 %.)
+constexpr int waves_per_simd(int waves, bool pi) { return waves == 4 ? pi ? 5 : 7 : waves == 8 ? 8 : 1; }
 
 __device__ __forceinline__ int wave_sum(int v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -52,7 +62,6 @@ compact_count_kernel(const uint32_t* __restrict__ mask_bits, int64_t n_words, in
   __shared__ int count[kGroupTiles];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int mine = 0;
-#pragma unroll 4
   for (int t = wave; t < group_tiles; t += kGroupTiles) {
     const int tile = blockIdx.x * group_tiles + t;
     const int64_t w = (int64_t)tile * kTileWords + 2 * lane;    // n_words is even
@@ -99,13 +108,13 @@ struct ScatterArgs {
 // One block per tile of 4096 positions, kWaves wavefronts, 64 positions at a time.
 // Bound by the bytes it moves; by the chain of dependent loads at the size of a real batch.  A wavefront reads its own mask words and has all its
 // per-token loads (probabilities, ids, log-probs) out before the tokens in front of the tile are counted and its rollouts are looked up: loads
-// in flight are worth more than wavefronts (sixteen groups at once take 99 registers; 2^26 Poisson tokens, four groups at a time 362 us,
+// in flight are worth more than wavefronts (sixteen groups at once take 96 registers; 2^26 Poisson tokens, four groups at a time 362 us,
 // eight 350, sixteen 337: 1.65 GB at 4.9 TB/s; 387 with the loads behind the search and a scan launch).  Tiles go from the last to the first: what
 // the selection read and wrote last is still in the Infinity Cache (from the first: 20 us more).  1.3 million tokens in 128 rollouts: 20 -> 15 us.
 // The per-token words ride along here because the token is already in hand: a row-gather block per kept token for them took
 // 8.66 ms of a 2^26-token batch, 190 us of a 1.3-million-token one.
 template <int kWaves, bool kPi>
-__global__ void __launch_bounds__(kWaves * 64)
+__global__ void __launch_bounds__(kWaves * 64, waves_per_simd(kWaves, kPi))
 compact_scatter_kernel(SelectArgs a, ScatterArgs c) {
   constexpr int kThreads = kWaves * 64, kGroups = 64 / kWaves, kSpanWords = kGroups * 2;      // groups of 64 positions per wavefront
   __shared__ uint32_t words[kTileWords];
@@ -347,7 +356,8 @@ nat_status compact_run(const SelectArgs& a, const CompactArgs& c) {
       const ScatterArgs sc{(double)c.n_rollouts_global, c.pi, c.mask_bits, n_words, c.N, c.kept_cap, c.cu, c.B,
                            count ? tile_count : nullptr, count ? group_count : nullptr, group_tiles, ((uintptr_t)c.mask_bits & 15) == 0,
                            c.kept_idx, c.kept_seq, c.kept_w, c.cu_kept, c.n_kept, pinned, c.ids, c.ids_k, c.old_logp, c.old_logp_k};
-      if (count && c.pi) compact_scatter_kernel<4, true><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
+      if (count && c.pi && n_tiles > kEightTilesFrom && n_tiles <= kEightTiles) compact_scatter_kernel<8, true><<<(unsigned)n_tiles, 512, 0, s>>>(a, sc);
+      else if (count && c.pi) compact_scatter_kernel<4, true><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
       else if (count) compact_scatter_kernel<4, false><<<(unsigned)n_tiles, 256, 0, s>>>(a, sc);
       else if (c.pi) compact_scatter_kernel<16, true><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);
       else compact_scatter_kernel<16, false><<<(unsigned)n_tiles, 1024, 0, s>>>(a, sc);

@@ -157,10 +157,11 @@ def test_compaction_offsets_of_long_runs_of_empty_rollouts(stage, N):
     assert_select_compact_equal(hip_select_compact(stage, cu, osel.DET, beta=0.5), o, N)
 
 
-@pytest.mark.parametrize("n_tiles,extra,B", [(512, 0, 254), (512, 1, 255), (528, 0, 256), (529, -4095, 300), (90, 77, 255)])
+@pytest.mark.parametrize("n_tiles,extra,B", [(512, 0, 254), (512, 1, 255), (528, 0, 256), (529, -4095, 300), (90, 77, 255),
+                                               (1281, -4095, 4000), (1537, 77, 9000), (1792, 0, 300), (1793, -4095, 300)])
 def test_compaction_where_counting_changes(stage, n_tiles, extra, B):
-    # up to and beyond the tiles whose blocks count the mask words themselves, whole and begun groups of 16 tiles, and as many rollouts
-    # as one round of the search takes; a mask that is not 16-byte aligned gives the same
+    # up to and beyond the tiles whose blocks count the mask words themselves, whole and begun groups of 16 tiles, as many rollouts
+    # as one round of the search takes, and blocks of four and eight wavefronts; a mask that is not 16-byte aligned gives the same
     import paper_2603_06619_amd as nat
     N = 4096 * n_tiles + extra
     rng = np.random.default_rng(N)
