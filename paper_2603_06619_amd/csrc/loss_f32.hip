@@ -227,23 +227,35 @@ __device__ __forceinline__ double wave_sum_d(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
-// A row of at most kF32RowRegs * 256 logits stays in registers between the passes over it (kCached: `row`), a longer one is read again: with the loads ahead
-// (f32_token_kernel), whole loss call at V = 4096, H = 256, us: 100 tokens 58.1 -> 55.5, 601 94.5 -> 92.3.
+// A row of at most kF32RowRegs * 256 logits stays in registers between the passes over it (kRegs of them: `row`), a longer one is read again (0): with the
+// loads ahead (f32_token_kernel), whole loss call at V = 4096, H = 256, us: 100 tokens 58.1 -> 55.5, 601 94.5 -> 92.3.  The passes go over all kRegs, so a
+// short row has fewer.  1024 tokens, read again / sixteen always / so, us: log-probs V = 2048, H = 4 18.6 / 19.7 / 18.5, V = 700, H = 64 14.1 / 15.0 / 13.8, V = 300, H =
+// 1024 20.1 / 21.2 / 19.7; loss V = 31, H = 1024 38.4 / 40.6 / 38.6, V = 1000, H = 64 43.9 / 44.0 / 42.7.
 constexpr int kF32RowRegs = 16;
+// launch(integral_constant) with the registers for a row of V logits: 1, 2, 4, 8 or 16, or 0
+template <class F>
+static void with_row_regs(int V, F&& launch) {
+  if (V <= kF32Threads) launch(std::integral_constant<int, 1>{});
+  else if (V <= 2 * kF32Threads) launch(std::integral_constant<int, 2>{});
+  else if (V <= 4 * kF32Threads) launch(std::integral_constant<int, 4>{});
+  else if (V <= 8 * kF32Threads) launch(std::integral_constant<int, 8>{});
+  else if (V <= kF32RowRegs * kF32Threads) launch(std::integral_constant<int, kF32RowRegs>{});
+  else launch(std::integral_constant<int, 0>{});
+}
 struct F32RowSums { float m; double s, t; };
 struct F32RowShared { float m[4]; double s[4], t[4]; };
-template <bool kCached>
-__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, F32RowShared& sh, float (&row)[kF32RowRegs]) {
+template <int kRegs>
+__device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, int V, F32RowShared& sh, float (&row)[kRegs + 1]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float m = -INFINITY;
-  if (kCached) {
+  if (kRegs > 0) {
 #pragma unroll
-    for (int i = 0; i < kF32RowRegs; ++i) {
+    for (int i = 0; i < kRegs; ++i) {
       const int v = threadIdx.x + i * kF32Threads;
       row[i] = v < V ? z[v] : -INFINITY;
     }
 #pragma unroll
-    for (int i = 0; i < kF32RowRegs; ++i) m = fmaxf(m, row[i]);
+    for (int i = 0; i < kRegs; ++i) m = fmaxf(m, row[i]);
   } else {
 #pragma unroll 4
     for (int v = threadIdx.x; v < V; v += kF32Threads) m = fmaxf(m, z[v]);
@@ -258,9 +270,9 @@ __device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, 
     s += (double)e;
     t = fma((double)e, (double)zc, t);
   };
-  if (kCached) {
+  if (kRegs > 0) {
 #pragma unroll
-    for (int i = 0; i < kF32RowRegs; ++i)
+    for (int i = 0; i < kRegs; ++i)
       if ((int)threadIdx.x + i * kF32Threads < V) add(row[i]);
   } else {
 #pragma unroll 4
@@ -274,7 +286,7 @@ __device__ __forceinline__ F32RowSums f32_row_sums(const float* __restrict__ z, 
 }
 
 // One block per token.  Bound by latency: what only the first thread needs (ids, weights, the target's logit) is loaded ahead of the reductions.
-template <bool kCached>
+template <int kRegs>
 __global__ void __launch_bounds__(kF32Threads)
 f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_logp, const float* __restrict__ adv,
                  const int32_t* __restrict__ kept_seq, const float* __restrict__ kept_w,
@@ -297,8 +309,8 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
     old = old_logp[k];
     if (klp.beta != 0.f) ref = klp.ref_logp[k];
   }
-  float row[kF32RowRegs];
-  const F32RowSums sums = f32_row_sums<kCached>(z, V, sh, row);
+  float row[kRegs + 1];
+  const F32RowSums sums = f32_row_sums<kRegs>(z, V, sh, row);
   if (threadIdx.x == 0) {
     const double log_s = log(sums.s), lse = (double)sums.m + log_s;
     // -sum p log p = log(sum) - (sum of e (z - m)) / sum
@@ -326,9 +338,9 @@ f32_token_kernel(const int32_t* __restrict__ ids, const float* __restrict__ old_
   __syncthreads();
   const float lse = bcast[0], c = bcast[1];
   auto put = [&](int v, float x) { z[v] = c * ((v == y ? 1.f : 0.f) - expf(x - lse)); };
-  if (kCached) {
+  if (kRegs > 0) {
 #pragma unroll
-    for (int i = 0; i < kF32RowRegs; ++i) {
+    for (int i = 0; i < kRegs; ++i) {
       const int v = threadIdx.x + i * kF32Threads;
       if (v < V) put(v, row[i]);
     }
@@ -371,8 +383,7 @@ nat_status loss_f32_run(const LossArgs& a) {
         kernel<<<n, kF32Threads, 0, s>>>(a.ids, a.old_logp, a.adv, a.kept_seq, a.kept_w, c0, a.V, a.eps_lo, a.eps_hi, a.grad_scale,
                                          KlArgs{a.ref_logp, a.beta_kl, a.kl_kind}, dz, a.logp, term, a.kl_out, a.entropy_out, a.diag);
       };
-      if (a.V <= kF32RowRegs * kF32Threads) token(f32_token_kernel<true>);
-      else token(f32_token_kernel<false>);
+      with_row_regs(a.V, [&](auto regs) { token(f32_token_kernel<decltype(regs)::value>); });
       NAT_LAUNCH_CHECK();
       st = f32_gemm<false, true>(dz, a.V, (const float*)a.W, a.H, n, a.H, a.V, (float*)a.dH + (size_t)c0 * a.H, a.H, 0, s);
       if (st != NAT_OK) return st;
@@ -388,15 +399,15 @@ nat_status loss_f32_run(const LossArgs& a) {
 
 
 // Forward pass alone: log-prob of the target and entropy of one token per block.
-template <bool kCached>
+template <int kRegs>
 __global__ void __launch_bounds__(kF32Threads)
 f32_logp_kernel(const float* __restrict__ z_scratch /*[chunk, V]*/, const int32_t* __restrict__ ids, int chunk_start, int V,
                 float* __restrict__ logp_out, float* __restrict__ entropy_out, int32_t* __restrict__ diag) {
   __shared__ F32RowShared sh;
   const int kc = blockIdx.x, k = chunk_start + kc;
   const float* z = z_scratch + (size_t)kc * V;
-  float row[kF32RowRegs];
-  const F32RowSums sums = f32_row_sums<kCached>(z, V, sh, row);
+  float row[kRegs + 1];
+  const F32RowSums sums = f32_row_sums<kRegs>(z, V, sh, row);
   if (threadIdx.x == 0) {
     const int yk = ids[k];
     if (yk < 0 || yk >= V) {
@@ -429,8 +440,9 @@ nat_status logp_f32_run(const LogpArgs& a) {
     const nat_status st = f32_gemm<false, false>((const float*)a.hidden + (size_t)c0 * a.H, a.H, (const float*)a.W, a.H, n,
                                                  a.V, a.H, (float*)a.ws, a.V, 0, s);
     if (st != NAT_OK) return st;
-    if (a.V <= kF32RowRegs * kF32Threads) f32_logp_kernel<true><<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
-    else f32_logp_kernel<false><<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
+    with_row_regs(a.V, [&](auto regs) {
+      f32_logp_kernel<decltype(regs)::value><<<n, kF32Threads, 0, s>>>((const float*)a.ws, a.ids, c0, a.V, a.logp, a.entropy, a.diag);
+    });
     NAT_LAUNCH_CHECK();
   }
   return NAT_OK;
