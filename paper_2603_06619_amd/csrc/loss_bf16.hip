@@ -393,7 +393,7 @@ template <Src kS>
 struct FragReader {
   static constexpr int kReads = is_kmajor(kS) ? 2 : 1;          // LDS reads per fragment
   uint32_t off[is_kmajor(kS) ? 4 : 1];
-  __device__ __forceinline__ void init(int row0, int lane) {    // row0: the wavefront's first row, a multiple of 64
+  __device__ __forceinline__ void init(int row0, int lane) {    // row0: the wavefront's first row, a multiple of 16 (k-major: of 64)
     const int i = lane & 15, g = lane >> 4;
     if constexpr (is_kmajor(kS)) {
       // tile: [32-row piece][k = 32][32 rows], 16-byte chunks of a k-row XOR chunk_xor(k / 4).  Read q = 0, 1 of the block
@@ -481,7 +481,8 @@ __device__ __forceinline__ Unit unit_of(const GemmArgs& g, int id) {
   if (g.k_splits > 1 && id >= whole) {
     // ids congruent mod 8 share an L2, as in tile_of_block (whole is a multiple of 256): an XCD gets consecutive ranges, and of a range consecutive tiles,
     // so that the tiles of one range, which read the same slices of both operands, fetch them once.  dH, us, tile by tile over the XCDs / so: H =
-    // 4096 150 tokens 290 / 233, 300 455 / 390, 560 663 / 627, H = 1024 300 155 / 115, 600 222 / 177
+    // 4096 150 tokens 290 / 233, 300 455 / 390, 560 663 / 627, H = 1024 300 155 / 115, 600 222 / 177.  dW, whose ranges read less in common, takes the same
+    // time either way (H = 1024 to 5120, V = 9000 to 151936, 600 to 8192 tokens: 0 +/- 1.5 %)
     const int n = g.tail_tiles * g.k_splits, per = n / 8, r = id - whole;
     const int v = r < per * 8 ? (r & 7) * per + (r >> 3) : r, range = v / g.tail_tiles;
     int pos = v - range * g.tail_tiles;
@@ -800,7 +801,8 @@ struct LogitsEpilogue {
     // logit, eight at a time with independent temporaries), its running sums, and at once the store.  The bound of 70 acts
     // on hardly any tile: where the sums show that it would (an exponential at or above e^70, an infinity or NaN among them
     // makes them that large), the wavefront makes the pass again with it.  (One minimum less per logit: logits of 16384 tokens at H = 1024 4040
-    // -> 3966 us, log-probs of 8192 there 1886 -> 1845, of 4000 at H = 256 389 -> 369.)  E is stored once, rows = token, k = vocabulary (the
+    // -> 3966 us, log-probs of 8192 there 1886 -> 1845, of 4000 at H = 256 389 -> 369.  Where one token in 128 or all are beyond the bound, every
+    // pass is made twice: 4000 tokens at H = 256 485, 8192 at H = 1024 2067, at H = 4096 6956 against 6775 with the minimum.)  E is stored once, rows = token, k = vocabulary (the
     // dH contraction reads it as it is, the dW contraction through the transposing LDS read): the rows of W are read
     // interleaved, so a lane holds 8 consecutive vocabulary entries of its token, one 16-byte chunk of the blocked layout,
     // and an instruction stores 1 KiB (16 token rows of one 32-wide vocabulary slice) contiguous.
@@ -917,7 +919,10 @@ struct DHiddenEpilogue {
 // 160000 184 / 159; H = 4096, V = 151936: 300 632 / 608, 1237 accumulating 1773 / 1611, 16384 accumulating 14931 / 14966.
 // A dW beyond the Infinity Cache (kDWeightStreamBytes) is read and written past the caches: nothing of it is there when it is next wanted, and
 // what it would push out is W, and the numerators of this launch.  Cached / past, whole call at H = 4096, V = 151936, us: 300 tokens 1537 / 1466, 1237 3663 /
-// 3636, twice 1237 (the second accumulating) 7580 / 7502, twice 60 2452 / 2303, 32768 82170 / 82054.  One that fits: H = 1024, V = 30000, twice 200 tokens 231 / 241.
+// 3636, twice 1237 (the second accumulating) 7580 / 7502, twice 60 2452 / 2303, 32768 82170 / 82054.  Where the line lies: whole calls of 40 / 600 tokens past the
+// caches against cached, per cent, overwriting and accumulating: H = 1024, 41 MB -5 / -1, +6 / +5; 82 MB +3 / +2, +12 / +7; 131 MB +4 / 0, +7 / -3; 184 MB 0 / -6, -2 / -5; 246 MB
+// -7 / -9, -13 / -5; 307 MB -15 / -6, -15 / -3; H = 4096, 164 MB -2 / -7, -10 / -6; 246 MB -17 / -10, -16 / -8; 328 MB -21 / -7, -10 / -5.  Above 256 MiB past the caches was never
+// slower; between 180 MB and the line it would be faster too.
 constexpr int64_t kDWeightStreamBytes = int64_t(256) << 20;
 template <bool kAccumulate>
 struct DWeightEpilogue {
@@ -1090,7 +1095,7 @@ constexpr float kShiftRangeLimit = 2.5154386709191669e30f;     // e^70
 // token are split over kStatParts groups of threads (granule gi goes to group gi % kStatParts), each
 // of which walks its granules in order, and the groups' sums are added in a fixed tree, so the result
 // does not depend on timing.  Bound by the latency of the walk (75 granules per group at V = 151936) in a short batch: 32
-// loads in flight, 14 us over 3000 tokens (19 with 8), and 16 groups (8 / 16 / 32: 40 tokens with the entropy at V = 160000 18.1 / 12.6 /
+// loads in flight (3000 tokens in 8 groups 14 us, 19 with 8 loads), and 16 groups (8 / 16 / 32: 40 tokens with the entropy at V = 160000 18.1 / 12.6 /
 // 12.5 us, 1237 tokens 13.9 / 12.1 / 12.1, 16384 21.6 / 21.8 / 24.8).  Returns to the first kStatTokens threads only.
 constexpr int kStatTokens = 32, kStatParts = 16, kStatBatch = 32;
 struct TokenSums { float S, TZ; bool in_shift_range; };

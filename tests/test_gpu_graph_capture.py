@@ -1,4 +1,4 @@
-"""The library calls only enqueue kernels (and one small pinned copy) on the caller's stream, allocate
+"""The library calls only enqueue kernels (and a small copy of a count to host memory that kernels cannot write) on the caller's stream, allocate
 nothing and clear memory with a fill kernel, so a caller can record them into a HIP graph.  The loss call
 and the selection calls are captured, replayed several times with eager work in between, and every replay
 is compared bit for bit with the eager result."""
